@@ -48,7 +48,7 @@ KERNEL_SOURCE = {
     "score_mean_colsum": "encoder_score.hip", "encoder_select": "select.hip",
     "llm_select": "select.hip", "sim_argmax": "sim_merge.hip",
     "merge": "sim_merge.hip", "llm_score": "llm.hip",
-    "compact": "llm.hip",
+    "compact": "llm.hip", "select_compact": "select.hip",
     "fused_q": "fused.hip", "fused_split_q": "fused.hip", "fused_qt": "fused.hip",
     "fused_logits": "fused.hip", "fused_softmax": "fused.hip",
     "fused_colsum": "fused.hip",
@@ -109,20 +109,23 @@ def algorithmic_work(w: wl.Workload, inputs: str = "qk"):
     if l is not None:
         es = 2 if l.dtype == wl.BF16 else 4
         row = (l.hidden + 2 * l.kv_heads * l.head_dim) * es
-        out["llm_select"] = ("hbm", l.batch * l.vis_len * 4 + l.batch * l.keep * 4)
+        select = l.batch * l.vis_len * 4 + l.batch * l.keep * 4
         # rows the method has to move: the kept visual rows and the rows after the span; an
         # out-of-place call also copies the prefix rows, counted apart
         moved = l.keep + l.text
         prefix = 0 if l.in_place else l.prefix
         if inputs == "qk":
             out["llm_score"] = ("hbm", l.batch * l.kv_heads * l.vis_len * l.head_dim * es)
-            out["compact"] = ("hbm", l.batch * moved * row * 2)
-            extra["compact"] = {"prefix_rows_bytes": l.batch * prefix * row * 2}
         else:
             _score_chain_work(out, l.batch, l.hidden, l.q_heads, l.kv_heads, l.head_dim,
                               l.n_query, l.vis_len)
-            out["compact"] = ("hbm", l.batch * moved * l.hidden * es * 2)
-            extra["compact"] = {"prefix_rows_bytes": l.batch * prefix * l.hidden * es * 2}
+            row = l.hidden * es
+        if l.in_place:
+            out["llm_select"] = ("hbm", select)
+            out["compact"] = ("hbm", l.batch * moved * row * 2)
+        else:  # one launch selects and copies
+            out["select_compact"] = ("hbm", select + l.batch * moved * row * 2)
+            extra["select_compact"] = {"prefix_rows_bytes": l.batch * prefix * row * 2}
     return out, extra
 
 
@@ -374,6 +377,8 @@ def kernel_source_digest(kernel: str) -> str:
     names = [KERNEL_SOURCE[kernel], "common.hpp", "launch.hpp"]
     if KERNEL_SOURCE[kernel] == "fused.hip":
         names.append("fused.hpp")
+    if kernel in ("compact", "select_compact", "llm_select"):
+        names.append("compact.hpp")
     for name in names:
         with open(os.path.join(ROOT, "paper_2505_22654_amd", "csrc", name), "rb") as f:
             h.update(f.read())

@@ -249,6 +249,22 @@ int vscan_llm_prune_fused_ragged(const vscan_llm_desc *desc, const vscan_seq_met
                                  float *scores_out, void *workspace, size_t workspace_bytes,
                                  void *stream);
 
+/* The two ragged calls for a caller whose table is on the host only and who wants every output
+ * value defined: the call itself puts the table at the start of the workspace ([batch] entries,
+ * there until the workspace is used again) without making the host wait; out of place,
+ * destination rows past a sequence's result are zero, and so are scores past its span.
+ * Everything else as above.  Workspace: vscan_llm_ragged_workspace_size bytes (`from_hidden` != 0
+ * for the second form), 16-byte aligned. */
+int vscan_llm_ragged_workspace_size(const vscan_llm_desc *desc, int from_hidden, size_t *bytes);
+int vscan_llm_prune_ragged_padded(const vscan_llm_desc *desc, const vscan_seq_meta *meta_host,
+                                  const void *q, void *k, void *v, void *hidden, int32_t *kept_idx,
+                                  void *k_out, void *v_out, void *hidden_out, float *scores_out,
+                                  void *workspace, size_t workspace_bytes, void *stream);
+int vscan_llm_prune_fused_ragged_padded(const vscan_llm_desc *desc, const vscan_seq_meta *meta_host,
+                                        void *hidden, const void *w_q, const void *w_k_t,
+                                        int32_t *kept_idx, void *hidden_out, float *scores_out,
+                                        void *workspace, size_t workspace_bytes, void *stream);
+
 /* ---------------------------------------------------------------------------
  * Stage 2 for a caller that does not hold the layer's queries and keys: the
  * scores of Eq. 5 computed as the equation is written, from the hidden states

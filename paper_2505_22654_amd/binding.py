@@ -26,7 +26,8 @@ EXPORTS = ("vscan_encoder_workspace_size", "vscan_encoder_reduce", "vscan_llm_wo
            "vscan_version", "vscan_budget", "vscan_budget_solve_r1", "vscan_flops",
            "vscan_llm_prune_ragged", "vscan_llm_fused_workspace_size", "vscan_llm_prune_fused",
            "vscan_encoder_fused_workspace_size", "vscan_encoder_reduce_fused",
-           "vscan_llm_prune_fused_ragged", "vscan_llm_prune_static")
+           "vscan_llm_prune_fused_ragged", "vscan_llm_prune_static", "vscan_llm_ragged_workspace_size",
+           "vscan_llm_prune_ragged_padded", "vscan_llm_prune_fused_ragged_padded")
 STATIC_SCRATCH_BYTES = 16 << 20
 
 
@@ -112,6 +113,15 @@ def lib():
         L.vscan_llm_prune_fused_ragged.argtypes = [ctypes.POINTER(LlmDesc), vp, vp, vp, vp, vp, i32p,
                                                    vp, f32p, vp, ctypes.c_size_t, vp]
         L.vscan_llm_prune_fused_ragged.restype = ctypes.c_int
+        L.vscan_llm_ragged_workspace_size.argtypes = [ctypes.POINTER(LlmDesc), ctypes.c_int,
+                                                      ctypes.POINTER(ctypes.c_size_t)]
+        L.vscan_llm_ragged_workspace_size.restype = ctypes.c_int
+        L.vscan_llm_prune_ragged_padded.argtypes = [ctypes.POINTER(LlmDesc), vp, vp, vp, vp, vp,
+                                                    i32p, vp, vp, vp, f32p, vp, ctypes.c_size_t, vp]
+        L.vscan_llm_prune_ragged_padded.restype = ctypes.c_int
+        L.vscan_llm_prune_fused_ragged_padded.argtypes = [ctypes.POINTER(LlmDesc), vp, vp, vp, vp,
+                                                          i32p, vp, f32p, vp, ctypes.c_size_t, vp]
+        L.vscan_llm_prune_fused_ragged_padded.restype = ctypes.c_int
         L.vscan_profile_enable.argtypes = [ctypes.c_int]
         L.vscan_profile_enable.restype = ctypes.c_int
         L.vscan_profile_read.argtypes = [ctypes.POINTER(KernelTime), ctypes.c_int,
@@ -186,38 +196,45 @@ def flops(n_per_layer, d: int, m: int) -> float:
     return float(out.value)
 
 
+def _ragged_setup(desc, meta, batch: int, from_hidden: bool, device):
+    """The host table of a ragged call and a workspace whose first bytes become the device table."""
+    import torch
+    assert len(meta) == batch
+    host = (ctypes.c_int32 * (4 * max(batch, 1)))(*[int(x) for m in meta for x in m])
+    n = ctypes.c_size_t(0)
+    rc = lib().vscan_llm_ragged_workspace_size(ctypes.byref(desc), int(from_hidden), ctypes.byref(n))
+    if rc != VSCAN_OK:
+        raise VscanError(rc, "vscan_llm_ragged_workspace_size")
+    workspace = torch.empty(n.value, dtype=torch.uint8, device=device)
+    table = workspace[:16 * batch].view(torch.int32).view(batch, 4)
+    return host, workspace, table
+
+
 def llm_prune_ragged(shape, meta, q, k, v, hidden, want_scores: bool = False) -> Dict[str, object]:
-    """vscan_llm_prune_ragged.  `shape` carries the shared fields and the capacities (seq_len,
-    vis_len, keep); `meta` is a list of (seq_len, vis_start, vis_len, keep) per sequence.
+    """vscan_llm_prune_ragged_padded.  `shape` carries the shared fields and the capacities
+    (seq_len, vis_len, keep); `meta` is a list of (seq_len, vis_start, vis_len, keep) per sequence.
     Out-of-place results are tensors shaped like the inputs (rows past a sequence's result are
-    zero-filled here so that they are defined); `out_len` lists the result lengths."""
+    zero); `out_len` lists the result lengths."""
     import torch
     desc = llm_desc(shape)
-    need = llm_workspace_size(desc)
     dev = q.device
-    B = shape.batch
-    assert len(meta) == B
-    host = (ctypes.c_int32 * (4 * max(B, 1)))(*[int(x) for m in meta for x in m])
-    meta_dev = torch.tensor([list(map(int, m)) for m in meta], dtype=torch.int32,
-                            device=dev).reshape(B, 4).contiguous()
-    workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    out = {"kept_idx": torch.empty((B, shape.keep), dtype=torch.int32, device=dev)}
+    host, workspace, table = _ragged_setup(desc, meta, shape.batch, False, dev)
+    out = {"kept_idx": torch.empty((shape.batch, shape.keep), dtype=torch.int32, device=dev)}
     if want_scores:
-        out["scores"] = torch.zeros((B, shape.vis_len), dtype=torch.float32, device=dev)
+        out["scores"] = torch.empty((shape.batch, shape.vis_len), dtype=torch.float32, device=dev)
     if shape.in_place:
         ko = vo = ho = None
     else:
-        ko, vo, ho = torch.zeros_like(k), torch.zeros_like(v), torch.zeros_like(hidden)
-    rc = lib().vscan_llm_prune_ragged(ctypes.byref(desc), ctypes.cast(host, ctypes.c_void_p),
-                                      _ptr(meta_dev), _ptr(q), _ptr(k), _ptr(v), _ptr(hidden),
-                                      _ptr(out["kept_idx"]), _ptr(ko), _ptr(vo), _ptr(ho),
-                                      _ptr(out.get("scores")), _ptr(workspace),
-                                      workspace.numel(), _stream_handle())
+        ko, vo, ho = torch.empty_like(k), torch.empty_like(v), torch.empty_like(hidden)
+    rc = lib().vscan_llm_prune_ragged_padded(ctypes.byref(desc), ctypes.addressof(host), _ptr(q),
+                                             _ptr(k), _ptr(v), _ptr(hidden), _ptr(out["kept_idx"]),
+                                             _ptr(ko), _ptr(vo), _ptr(ho), _ptr(out.get("scores")),
+                                             _ptr(workspace), workspace.numel(), _stream_handle())
     if rc != VSCAN_OK:
-        raise VscanError(rc, "vscan_llm_prune_ragged")
+        raise VscanError(rc, "vscan_llm_prune_ragged_padded")
     out["k"], out["v"], out["hidden"] = (k, v, hidden) if shape.in_place else (ko, vo, ho)
     out["out_len"] = [m[0] - m[2] + m[3] for m in meta]
-    out["meta_device"], out["workspace"] = meta_dev, workspace  # alive until the work has run
+    out["meta_device"], out["workspace"] = table, workspace  # alive until the work has run
     return out
 
 
@@ -461,31 +478,26 @@ def encoder_reduce_fused(shape, hidden, w_q, w_k_t, x, local=None, want_assign: 
 
 
 def llm_prune_fused_ragged(shape, meta, hidden, w_q, w_k_t, want_scores: bool = False) -> Dict[str, object]:
-    """vscan_llm_prune_fused_ragged.  `shape` carries the shared fields and the capacities;
+    """vscan_llm_prune_fused_ragged_padded.  `shape` carries the shared fields and the capacities;
     `meta` lists (seq_len, vis_start, vis_len, keep) per sequence.  The out-of-place result is
-    shaped like `hidden` (zero-filled here past a sequence's result); `out_len` lists the
-    result lengths."""
+    shaped like `hidden` (rows past a sequence's result are zero); `out_len` lists the result
+    lengths."""
     import torch
     desc = llm_desc(shape)
-    need = llm_fused_workspace_size(desc)
     dev = hidden.device
-    B = shape.batch
-    assert len(meta) == B
-    host = (ctypes.c_int32 * (4 * max(B, 1)))(*[int(x) for m in meta for x in m])
-    meta_dev = torch.tensor([list(map(int, m)) for m in meta], dtype=torch.int32,
-                            device=dev).reshape(B, 4).contiguous()
-    workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    out = {"kept_idx": torch.empty((B, shape.keep), dtype=torch.int32, device=dev)}
+    host, workspace, table = _ragged_setup(desc, meta, shape.batch, True, dev)
+    out = {"kept_idx": torch.empty((shape.batch, shape.keep), dtype=torch.int32, device=dev)}
     if want_scores:
-        out["scores"] = torch.zeros((B, shape.vis_len), dtype=torch.float32, device=dev)
-    ho = None if shape.in_place else torch.zeros_like(hidden)
-    rc = lib().vscan_llm_prune_fused_ragged(ctypes.byref(desc), ctypes.cast(host, ctypes.c_void_p),
-                                            _ptr(meta_dev), _ptr(hidden), _ptr(w_q), _ptr(w_k_t),
-                                            _ptr(out["kept_idx"]), _ptr(ho), _ptr(out.get("scores")),
-                                            _ptr(workspace), workspace.numel(), _stream_handle())
+        out["scores"] = torch.empty((shape.batch, shape.vis_len), dtype=torch.float32, device=dev)
+    ho = None if shape.in_place else torch.empty_like(hidden)
+    rc = lib().vscan_llm_prune_fused_ragged_padded(ctypes.byref(desc), ctypes.addressof(host),
+                                                   _ptr(hidden), _ptr(w_q), _ptr(w_k_t),
+                                                   _ptr(out["kept_idx"]), _ptr(ho),
+                                                   _ptr(out.get("scores")), _ptr(workspace),
+                                                   workspace.numel(), _stream_handle())
     if rc != VSCAN_OK:
-        raise VscanError(rc, "vscan_llm_prune_fused_ragged")
+        raise VscanError(rc, "vscan_llm_prune_fused_ragged_padded")
     out["hidden"] = hidden if shape.in_place else ho
     out["out_len"] = [m[0] - m[2] + m[3] for m in meta]
-    out["meta_device"], out["workspace"] = meta_dev, workspace  # alive until the work has run
+    out["meta_device"], out["workspace"] = table, workspace  # alive until the work has run
     return out

@@ -12,8 +12,8 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libvscan.so")
 
 SOURCES = ["api.cpp", "budget.cpp", "encoder_score.hip", "select.hip", "sim_merge.hip", "llm.hip", "fused.hip",
-           "static_entry.hip"]
-HEADERS = ["common.hpp", "launch.hpp", "fused.hpp", os.path.join("..", "..", "include", "vscan.h")]
+           "static_entry.hip", "ragged_entry.hip"]
+HEADERS = ["common.hpp", "launch.hpp", "compact.hpp", "fused.hpp", os.path.join("..", "..", "include", "vscan.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

@@ -100,7 +100,7 @@ int plan_encoder(const vscan_encoder_desc *d, int with_local, EncoderPlan *p) {
 
 struct LlmPlan {
     int rows, k0, nk, S_out;
-    size_t off_part, off_split_e, off_split_stats, bytes;
+    size_t off_part, off_split_e, off_split_stats, off_claim, bytes;
 };
 
 int plan_llm(const vscan_llm_desc *d, LlmPlan *p) {
@@ -135,6 +135,8 @@ int plan_llm(const vscan_llm_desc *d, LlmPlan *p) {
     if (chunks > 0) off += align_up((size_t)d->batch * d->kv_heads * p->rows * d->vis_len * sizeof(float));
     p->off_split_stats = off;
     if (chunks > 0) off += align_up((size_t)d->batch * d->kv_heads * chunks * p->rows * 2 * sizeof(float));
+    p->off_claim = off;
+    if (!d->in_place) off += align_up((size_t)d->batch * sizeof(uint32_t));
     p->bytes = off ? off : kAlign;
     return VSCAN_OK;
 }
@@ -177,7 +179,7 @@ int plan_fused_scratch(int64_t seqs, int S, int hidden, int q_heads, int kv_head
 struct FusedPlan {
     int k0, nk, S_out, R;
     FusedScratch f;
-    size_t off_part, bytes;
+    size_t off_part, off_claim, bytes;
 };
 
 int plan_fused(const vscan_llm_desc *d, FusedPlan *p) {
@@ -204,7 +206,8 @@ int plan_fused(const vscan_llm_desc *d, FusedPlan *p) {
                                       d->head_dim, d->n_query, p->nk, elem_bytes(d->dtype), 0, &p->f);
     if (rc != VSCAN_OK) return rc;
     p->off_part = p->f.end;
-    p->bytes = p->off_part + align_up((size_t)d->batch * d->vis_len * sizeof(float));
+    p->off_claim = p->off_part + align_up((size_t)d->batch * d->vis_len * sizeof(float));
+    p->bytes = p->off_claim + (d->in_place ? 0 : align_up((size_t)d->batch * sizeof(uint32_t)));
     return VSCAN_OK;
 }
 
@@ -599,10 +602,29 @@ int vscan_llm_workspace_size(const vscan_llm_desc *desc, size_t *bytes) {
     return VSCAN_OK;
 }
 
-// Shared by the uniform and the ragged entry point.  `meta` (device) is NULL for a uniform
-// batch; `max_out_rows` is the longest result, `out_rows` the row stride of the destinations.
-static int run_llm(const vscan_llm_desc *d, const LlmPlan &p, const SeqMeta *meta, int max_out_rows,
-                   int out_rows, const void *q, void *k, void *v, void *hidden, int32_t *kept_idx,
+// Initial state of the words an out-of-place selection launch hands over through.
+static SelectSeed select_seed(const vscan_llm_desc *d, int32_t *kept_idx, uint32_t *claim) {
+    SelectSeed seed;
+    if (!claim) return seed;
+    seed.kept = kept_idx;
+    seed.n_kept = (int64_t)d->batch * d->keep;
+    seed.claim = claim;
+    seed.n_claim = d->batch;
+    return seed;
+}
+
+// What a ragged call adds to a uniform one.
+struct RaggedCall {
+    const SeqMeta *meta = nullptr;       // device table (NULL: a uniform batch)
+    const SeqMeta *upload_from = nullptr;  // host table the call itself puts into `meta` first
+    TableUpload upload = nullptr;
+    int zero_tail = 0;                   // outputs past a sequence's results are zeroed
+};
+
+// Shared by the uniform and the ragged entry points.  `max_static_rows`: see CompactArgs;
+// `out_rows` is the row stride of the destinations.
+static int run_llm(const vscan_llm_desc *d, const LlmPlan &p, const RaggedCall &ragged,
+                   int max_static_rows, int out_rows, const void *q, void *k, void *v, void *hidden, int32_t *kept_idx,
                    void *k_out, void *v_out, void *hidden_out, float *scores_out, void *workspace,
                    size_t workspace_bytes, void *stream) {
     const int rc_args = check_llm_tensors(d, q, k, v, hidden, kept_idx, k_out, v_out, hidden_out,
@@ -614,6 +636,8 @@ static int run_llm(const vscan_llm_desc *d, const LlmPlan &p, const SeqMeta *met
 
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     unsigned char *ws = reinterpret_cast<unsigned char *>(workspace);
+    if (ragged.upload)
+        VSCAN_LAUNCH("table_upload", ragged.upload(const_cast<SeqMeta *>(ragged.meta), ragged.upload_from, d->batch, s));
 
     LlmScoreArgs sa;
     sa.q = q;
@@ -630,22 +654,12 @@ static int run_llm(const vscan_llm_desc *d, const LlmPlan &p, const SeqMeta *met
     sa.domain_all = d->softmax_domain == VSCAN_KEYS_ALL;
     sa.is_bf16 = d->dtype == VSCAN_BF16;
     sa.scale = resolve_scale(d->scale, d->head_dim);
-    sa.meta = meta;
+    sa.meta = ragged.meta;
     sa.split_e = reinterpret_cast<float *>(ws + p.off_split_e);
     sa.split_stats = reinterpret_cast<float *>(ws + p.off_split_stats);
+    uint32_t *claim = d->in_place ? nullptr : reinterpret_cast<uint32_t *>(ws + p.off_claim);
+    sa.seed = select_seed(d, kept_idx, claim);
     VSCAN_LAUNCH("llm_score", launch_llm_score(sa, s));
-
-    LlmSelectArgs se;
-    se.part = sa.part;
-    se.B = d->batch;
-    se.Hkv = d->kv_heads;
-    se.V = d->vis_len;
-    se.keep = d->keep;
-    se.norm = 1.0f / ((float)d->n_query * (float)d->q_heads);
-    se.kept_idx = kept_idx;
-    se.scores_out = scores_out;
-    se.meta = meta;
-    VSCAN_LAUNCH("llm_select", launch_llm_select(se, s));
 
     CompactArgs ca;
     ca.k = k;
@@ -669,8 +683,28 @@ static int run_llm(const vscan_llm_desc *d, const LlmPlan &p, const SeqMeta *met
     ca.elem_bytes = elem_bytes(d->dtype);
     ca.in_place = d->in_place;
     ca.out_rows = out_rows;
-    ca.max_out_rows = max_out_rows;
-    ca.meta = meta;
+    ca.max_static_rows = max_static_rows;
+    ca.zero_tail = ragged.zero_tail;
+    ca.meta = ragged.meta;
+
+    LlmSelectArgs se;
+    se.part = sa.part;
+    se.B = d->batch;
+    se.Hkv = d->kv_heads;
+    se.V = d->vis_len;
+    se.keep = d->keep;
+    se.norm = 1.0f / ((float)d->n_query * (float)d->q_heads);
+    se.kept_idx = kept_idx;
+    se.scores_out = scores_out;
+    se.meta = ragged.meta;
+    se.zero_tail = ragged.zero_tail;
+    if (!d->in_place) {
+        se.copy = &ca;
+        se.claim = claim;
+        VSCAN_LAUNCH("select_compact", launch_llm_select(se, s));
+        return VSCAN_OK;
+    }
+    VSCAN_LAUNCH("llm_select", launch_llm_select(se, s));
     VSCAN_LAUNCH("compact", launch_compact(ca, s));
     return VSCAN_OK;
 }
@@ -681,8 +715,8 @@ static int llm_prune_impl(const vscan_llm_desc *d, const void *q, void *k, void 
     LlmPlan p;
     const int rc = plan_llm(d, &p);
     if (rc != VSCAN_OK) return rc;
-    return run_llm(d, p, nullptr, p.S_out, d->in_place ? d->seq_len : p.S_out, q, k, v, hidden,
-                   kept_idx, k_out, v_out, hidden_out, scores_out, workspace, workspace_bytes,
+    return run_llm(d, p, {}, d->seq_len - d->vis_len, d->in_place ? d->seq_len : p.S_out, q, k, v,
+                   hidden, kept_idx, k_out, v_out, hidden_out, scores_out, workspace, workspace_bytes,
                    stream);
 }
 
@@ -693,11 +727,15 @@ int vscan_llm_prune(const vscan_llm_desc *d, const void *q, void *k, void *v, vo
 }
 
 static int check_seq_meta(const vscan_llm_desc *d, const vscan_seq_meta *meta_host,
-                          const vscan_seq_meta *meta_device, int *max_out_rows);
+                          const vscan_seq_meta *meta_device, int zero_tail, int *max_static_rows);
 
+static_assert(sizeof(SeqMeta) == sizeof(vscan_seq_meta), "same layout");
+
+// The ragged entry points.  `upload` (NULL when the caller brings the device table) puts the host
+// table at `meta_device`; such a call also defines what lies past the sequences' results.
 static int llm_prune_ragged_impl(const vscan_llm_desc *d, const vscan_seq_meta *meta_host,
-                           const vscan_seq_meta *meta_device, const void *q, void *k, void *v,
-                           void *hidden, int32_t *kept_idx, void *k_out, void *v_out,
+                           const vscan_seq_meta *meta_device, TableUpload upload, const void *q, void *k,
+                           void *v, void *hidden, int32_t *kept_idx, void *k_out, void *v_out,
                            void *hidden_out, float *scores_out, void *workspace,
                            size_t workspace_bytes, void *stream) {
     if (!d) return VSCAN_ERR_NULL;
@@ -708,13 +746,16 @@ static int llm_prune_ragged_impl(const vscan_llm_desc *d, const vscan_seq_meta *
     LlmPlan p;
     const int rc = plan_llm(&caps, &p);
     if (rc != VSCAN_OK) return rc;
-    int max_out_rows = 0;
-    const int rc2 = check_seq_meta(d, meta_host, meta_device, &max_out_rows);
+    RaggedCall ragged;
+    ragged.meta = reinterpret_cast<const SeqMeta *>(meta_device);
+    ragged.upload_from = reinterpret_cast<const SeqMeta *>(meta_host);
+    ragged.upload = upload;
+    ragged.zero_tail = upload != nullptr;
+    int max_static_rows = 0;
+    const int rc2 = check_seq_meta(d, meta_host, meta_device, ragged.zero_tail, &max_static_rows);
     if (rc2 != VSCAN_OK) return rc2;
-    static_assert(sizeof(SeqMeta) == sizeof(vscan_seq_meta), "same layout");
-    return run_llm(&caps, p, reinterpret_cast<const SeqMeta *>(meta_device), max_out_rows,
-                   d->seq_len, q, k, v, hidden, kept_idx, k_out, v_out, hidden_out, scores_out,
-                   workspace, workspace_bytes, stream);
+    return run_llm(&caps, p, ragged, max_static_rows, d->seq_len, q, k, v, hidden, kept_idx, k_out,
+                   v_out, hidden_out, scores_out, workspace, workspace_bytes, stream);
 }
 
 int vscan_llm_prune_ragged(const vscan_llm_desc *d, const vscan_seq_meta *meta_host,
@@ -722,7 +763,7 @@ int vscan_llm_prune_ragged(const vscan_llm_desc *d, const vscan_seq_meta *meta_h
                            void *hidden, int32_t *kept_idx, void *k_out, void *v_out,
                            void *hidden_out, float *scores_out, void *workspace,
                            size_t workspace_bytes, void *stream) {
-    return finish("vscan_llm_prune_ragged", llm_prune_ragged_impl(d, meta_host, meta_device, q, k, v, hidden, kept_idx, k_out, v_out, hidden_out, scores_out, workspace, workspace_bytes, stream));
+    return finish("vscan_llm_prune_ragged", llm_prune_ragged_impl(d, meta_host, meta_device, nullptr, q, k, v, hidden, kept_idx, k_out, v_out, hidden_out, scores_out, workspace, workspace_bytes, stream));
 }
 
 int vscan_llm_fused_workspace_size(const vscan_llm_desc *desc, size_t *bytes) {
@@ -734,10 +775,9 @@ int vscan_llm_fused_workspace_size(const vscan_llm_desc *desc, size_t *bytes) {
     return VSCAN_OK;
 }
 
-// Shared by the uniform and the ragged form.  `meta` (device) is NULL for a uniform batch;
-// `max_out_rows` is the longest result, `out_rows` the row stride of hidden_out.
-static int run_llm_fused(const vscan_llm_desc *d, const FusedPlan &p, const SeqMeta *meta,
-                         int max_out_rows, int out_rows, void *hidden, const void *w_q,
+// Shared by the uniform and the ragged forms, as run_llm.
+static int run_llm_fused(const vscan_llm_desc *d, const FusedPlan &p, const RaggedCall &ragged,
+                         int max_static_rows, int out_rows, void *hidden, const void *w_q,
                          const void *w_k_t, int32_t *kept_idx, void *hidden_out, float *scores_out,
                          void *workspace, size_t workspace_bytes, void *stream) {
     if (!hidden || !w_q || !w_k_t || (!kept_idx && d->keep > 0)) return VSCAN_ERR_NULL;
@@ -753,6 +793,8 @@ static int run_llm_fused(const vscan_llm_desc *d, const FusedPlan &p, const SeqM
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     unsigned char *ws = reinterpret_cast<unsigned char *>(workspace);
 
+    if (ragged.upload)
+        VSCAN_LAUNCH("table_upload", ragged.upload(const_cast<SeqMeta *>(ragged.meta), ragged.upload_from, d->batch, s));
     FusedArgs fa;
     fa.is_bf16 = d->dtype == VSCAN_BF16;
     fa.hidden = hidden;
@@ -774,21 +816,11 @@ static int run_llm_fused(const vscan_llm_desc *d, const FusedPlan &p, const SeqM
     fa.k0 = p.k0;
     fa.nk = p.nk;
     fa.scale = resolve_scale(d->scale, d->head_dim);
-    fa.meta = meta;
+    fa.meta = ragged.meta;
+    uint32_t *claim = d->in_place ? nullptr : reinterpret_cast<uint32_t *>(ws + p.off_claim);
+    fa.seed = select_seed(d, kept_idx, claim);
     const int rc2 = enqueue_fused_scores(fa, p.f, ws, s);
     if (rc2 != VSCAN_OK) return rc2;
-
-    LlmSelectArgs se;
-    se.part = fa.part;
-    se.B = d->batch;
-    se.Hkv = 1;
-    se.V = d->vis_len;
-    se.keep = d->keep;
-    se.norm = 1.0f / (float)p.R;
-    se.kept_idx = kept_idx;
-    se.scores_out = scores_out;
-    se.meta = meta;
-    VSCAN_LAUNCH("llm_select", launch_llm_select(se, s));
 
     CompactArgs ca;
     ca.k = ca.v = ca.k_out = ca.v_out = nullptr;
@@ -806,8 +838,28 @@ static int run_llm_fused(const vscan_llm_desc *d, const FusedPlan &p, const SeqM
     ca.elem_bytes = elem_bytes(d->dtype);
     ca.in_place = d->in_place;
     ca.out_rows = out_rows;
-    ca.max_out_rows = max_out_rows;
-    ca.meta = meta;
+    ca.max_static_rows = max_static_rows;
+    ca.zero_tail = ragged.zero_tail;
+    ca.meta = ragged.meta;
+
+    LlmSelectArgs se;
+    se.part = fa.part;
+    se.B = d->batch;
+    se.Hkv = 1;
+    se.V = d->vis_len;
+    se.keep = d->keep;
+    se.norm = 1.0f / (float)p.R;
+    se.kept_idx = kept_idx;
+    se.scores_out = scores_out;
+    se.meta = ragged.meta;
+    se.zero_tail = ragged.zero_tail;
+    if (!d->in_place) {
+        se.copy = &ca;
+        se.claim = claim;
+        VSCAN_LAUNCH("select_compact", launch_llm_select(se, s));
+        return VSCAN_OK;
+    }
+    VSCAN_LAUNCH("llm_select", launch_llm_select(se, s));
     VSCAN_LAUNCH("compact", launch_compact(ca, s));
     return VSCAN_OK;
 }
@@ -819,8 +871,8 @@ static int llm_prune_fused_impl(const vscan_llm_desc *d, void *hidden, const voi
     FusedPlan p;
     const int rc = plan_fused(d, &p);
     if (rc != VSCAN_OK) return rc;
-    return run_llm_fused(d, p, nullptr, p.S_out, d->in_place ? d->seq_len : p.S_out, hidden, w_q,
-                         w_k_t, kept_idx, hidden_out, scores_out, workspace, workspace_bytes,
+    return run_llm_fused(d, p, {}, d->seq_len - d->vis_len, d->in_place ? d->seq_len : p.S_out,
+                         hidden, w_q, w_k_t, kept_idx, hidden_out, scores_out, workspace, workspace_bytes,
                          stream);
 }
 
@@ -831,13 +883,13 @@ int vscan_llm_prune_fused(const vscan_llm_desc *d, void *hidden, const void *w_q
     return finish("vscan_llm_prune_fused", llm_prune_fused_impl(d, hidden, w_q, w_k_t, kept_idx, hidden_out, scores_out, workspace, workspace_bytes, stream));
 }
 
-// Validation of a ragged batch's host table against the capacities; *max_out_rows receives the
-// longest result.
+// Validation of a ragged batch's host table against the capacities; *max_static_rows as in
+// CompactArgs.
 static int check_seq_meta(const vscan_llm_desc *d, const vscan_seq_meta *meta_host,
-                          const vscan_seq_meta *meta_device, int *max_out_rows) {
+                          const vscan_seq_meta *meta_device, int zero_tail, int *max_static_rows) {
     if (d->batch > 0 && (!meta_host || !meta_device)) return VSCAN_ERR_NULL;
     if (reinterpret_cast<uintptr_t>(meta_device) & 3u) return VSCAN_ERR_ALIGN;
-    *max_out_rows = 0;
+    *max_static_rows = 0;
     for (int b = 0; b < d->batch; ++b) {
         const vscan_seq_meta &m = meta_host[b];
         if (m.seq_len < 1 || m.seq_len > d->seq_len || m.vis_start < 0 || m.vis_len < 1 ||
@@ -845,14 +897,15 @@ static int check_seq_meta(const vscan_llm_desc *d, const vscan_seq_meta *meta_ho
             return VSCAN_ERR_SHAPE;
         if ((int64_t)m.vis_start + m.vis_len + d->n_query > m.seq_len) return VSCAN_ERR_SHAPE;
         if (m.keep < 0 || m.keep > m.vis_len || m.keep > d->keep) return VSCAN_ERR_BUDGET;
-        *max_out_rows = std::max(*max_out_rows, m.seq_len - m.vis_len + m.keep);
+        *max_static_rows = std::max(*max_static_rows,
+                                    zero_tail ? d->seq_len - m.keep : m.seq_len - m.vis_len);
     }
     return VSCAN_OK;
 }
 
 static int llm_prune_fused_ragged_impl(const vscan_llm_desc *d, const vscan_seq_meta *meta_host,
-                                 const vscan_seq_meta *meta_device, void *hidden, const void *w_q,
-                                 const void *w_k_t, int32_t *kept_idx, void *hidden_out,
+                                 const vscan_seq_meta *meta_device, TableUpload upload, void *hidden,
+                                 const void *w_q, const void *w_k_t, int32_t *kept_idx, void *hidden_out,
                                  float *scores_out, void *workspace, size_t workspace_bytes,
                                  void *stream) {
     if (!d) return VSCAN_ERR_NULL;
@@ -862,12 +915,16 @@ static int llm_prune_fused_ragged_impl(const vscan_llm_desc *d, const vscan_seq_
     FusedPlan p;
     const int rc = plan_fused(&caps, &p);
     if (rc != VSCAN_OK) return rc;
-    int max_out_rows = 0;
-    const int rc2 = check_seq_meta(d, meta_host, meta_device, &max_out_rows);
+    RaggedCall ragged;
+    ragged.meta = reinterpret_cast<const SeqMeta *>(meta_device);
+    ragged.upload_from = reinterpret_cast<const SeqMeta *>(meta_host);
+    ragged.upload = upload;
+    ragged.zero_tail = upload != nullptr;
+    int max_static_rows = 0;
+    const int rc2 = check_seq_meta(d, meta_host, meta_device, ragged.zero_tail, &max_static_rows);
     if (rc2 != VSCAN_OK) return rc2;
-    return run_llm_fused(&caps, p, reinterpret_cast<const SeqMeta *>(meta_device), max_out_rows,
-                         d->seq_len, hidden, w_q, w_k_t, kept_idx, hidden_out, scores_out,
-                         workspace, workspace_bytes, stream);
+    return run_llm_fused(&caps, p, ragged, max_static_rows, d->seq_len, hidden, w_q, w_k_t,
+                         kept_idx, hidden_out, scores_out, workspace, workspace_bytes, stream);
 }
 
 int vscan_llm_prune_fused_ragged(const vscan_llm_desc *d, const vscan_seq_meta *meta_host,
@@ -875,8 +932,43 @@ int vscan_llm_prune_fused_ragged(const vscan_llm_desc *d, const vscan_seq_meta *
                                  const void *w_k_t, int32_t *kept_idx, void *hidden_out,
                                  float *scores_out, void *workspace, size_t workspace_bytes,
                                  void *stream) {
-    return finish("vscan_llm_prune_fused_ragged", llm_prune_fused_ragged_impl(d, meta_host, meta_device, hidden, w_q, w_k_t, kept_idx, hidden_out, scores_out, workspace, workspace_bytes, stream));
+    return finish("vscan_llm_prune_fused_ragged", llm_prune_fused_ragged_impl(d, meta_host, meta_device, nullptr, hidden, w_q, w_k_t, kept_idx, hidden_out, scores_out, workspace, workspace_bytes, stream));
 }
+
+}  // extern "C"
+
+namespace vscan {
+// The padded ragged entry points (ragged_entry.hip): the table takes the first bytes of the
+// workspace, the scratch of the ordinary call what follows.
+size_t ragged_table_bytes(int batch) { return align_up((size_t)std::max(batch, 0) * sizeof(SeqMeta)); }
+
+int llm_prune_ragged_padded(const vscan_llm_desc *d, const vscan_seq_meta *meta_host,
+                            TableUpload upload, const void *q, void *k, void *v, void *hidden,
+                            int32_t *kept_idx, void *k_out, void *v_out, void *hidden_out,
+                            float *scores_out, void *workspace, size_t workspace_bytes, void *stream) {
+    const size_t table = d && d->struct_size == sizeof(*d) ? ragged_table_bytes(d->batch) : 0;
+    if (!workspace || workspace_bytes < table) return VSCAN_ERR_WORKSPACE;
+    return llm_prune_ragged_impl(d, meta_host, reinterpret_cast<const vscan_seq_meta *>(workspace), upload,
+                                 q, k, v, hidden, kept_idx, k_out, v_out, hidden_out, scores_out,
+                                 reinterpret_cast<unsigned char *>(workspace) + table,
+                                 workspace_bytes - table, stream);
+}
+
+int llm_prune_fused_ragged_padded(const vscan_llm_desc *d, const vscan_seq_meta *meta_host,
+                                  TableUpload upload, void *hidden, const void *w_q,
+                                  const void *w_k_t, int32_t *kept_idx, void *hidden_out,
+                                  float *scores_out, void *workspace, size_t workspace_bytes,
+                                  void *stream) {
+    const size_t table = d && d->struct_size == sizeof(*d) ? ragged_table_bytes(d->batch) : 0;
+    if (!workspace || workspace_bytes < table) return VSCAN_ERR_WORKSPACE;
+    return llm_prune_fused_ragged_impl(d, meta_host, reinterpret_cast<const vscan_seq_meta *>(workspace),
+                                       upload, hidden, w_q, w_k_t, kept_idx, hidden_out, scores_out,
+                                       reinterpret_cast<unsigned char *>(workspace) + table,
+                                       workspace_bytes - table, stream);
+}
+}  // namespace vscan
+
+extern "C" {
 
 int vscan_profile_enable(int on) {
     std::lock_guard<std::mutex> lock(g_prof_mutex);

@@ -33,6 +33,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "compact.hpp"
 #include "fused.hpp"
 #include "launch.hpp"
 
@@ -458,7 +459,8 @@ __global__ __launch_bounds__(1024) void fused_softmax_long_kernel(float *__restr
 __global__ __launch_bounds__(256) void fused_colsum_kernel(const float *__restrict__ p, int R,
                                                            int nk_cap, int vis_off, int V_cap,
                                                            int causal, const SeqMeta *meta,
-                                                           float *__restrict__ part) {
+                                                           float *__restrict__ part, SelectSeed seed) {
+    seed_selection(seed, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     __shared__ float red[4][64];
     const int b = blockIdx.y;
     const int nk = domain_keys(meta, b, causal, nk_cap);
@@ -672,7 +674,7 @@ hipError_t launch_fused_project(const ProjectArgs &a, hipStream_t s) {
 
 hipError_t launch_fused_colsum(const FusedArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(fused_colsum_kernel, dim3((a.nk + 63) / 64, a.B), dim3(256), 0, s, a.c_l,
-                       a.Hq * a.Tq, a.nk, a.vis_start - a.k0, a.V, a.causal, a.meta, a.part);
+                       a.Hq * a.Tq, a.nk, a.vis_start - a.k0, a.V, a.causal, a.meta, a.part, a.seed);
     return hipGetLastError();
 }
 

@@ -28,6 +28,7 @@ struct FusedArgs {
     const SeqMeta *meta = nullptr;
     int ks_q, ks_l;            // shares of the contraction axis (fused_ksplit)
     float scale;
+    SelectSeed seed;           // for the selection launch that follows the chain
 };
 // shares of the contraction axis for a contraction of Z problems of rows_s x rows_p outputs
 int fused_ksplit(int rows_s, int rows_p, int Z, int k_elems, int elem_bytes);

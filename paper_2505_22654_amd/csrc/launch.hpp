@@ -87,6 +87,19 @@ struct SeqMeta {
     int32_t seq_len, vis_start, vis_len, keep;
 };
 
+// Puts a host table of `batch` entries into device memory on the stream, without a copy that
+// would make the host wait (ragged_entry.hip).
+using TableUpload = hipError_t (*)(SeqMeta *table, const SeqMeta *from_host, int batch, hipStream_t s);
+
+// Words the selection launch of an out-of-place call hands over through, put into their initial
+// state by the scoring kernel before it: kept indices to kNotYetKept, claims to 0.
+constexpr int32_t kNotYetKept = -2;
+struct SelectSeed {
+    int32_t *kept = nullptr;   // [n_kept]
+    uint32_t *claim = nullptr; // [n_claim]
+    int64_t n_kept = 0, n_claim = 0;
+};
+
 // stage 2 scoring (Eq. 5)
 struct LlmScoreArgs {
     const void *q;             // [B, Hq, Tq, dh]
@@ -99,12 +112,14 @@ struct LlmScoreArgs {
     // scratch of the form that cuts long key domains into chunks (llm_score_split_chunks > 0):
     // e [B*Hkv, rows, V] and per-chunk (maximum, sum) pairs [B*Hkv, chunks, rows, 2]
     float *split_e = nullptr, *split_stats = nullptr;
+    SelectSeed seed;
 };
 hipError_t launch_llm_score(const LlmScoreArgs &a, hipStream_t s);
 int llm_score_split_chunks(int B, int Hkv, int rows, int nk, bool ragged);
 // rows = (Hq/Hkv)*Tq query rows per kv head, nk = keys in the softmax domain
 bool llm_score_supported(int rows, int nk, int row_bytes);
 
+struct CompactArgs;
 struct LlmSelectArgs {
     const float *part;         // [B, Hkv, V]
     int B, Hkv, V, keep;
@@ -112,11 +127,15 @@ struct LlmSelectArgs {
     int32_t *kept_idx;         // [B, keep]; ragged: entries past a sequence's own keep are -1
     float *scores_out;         // optional [B, V]
     const SeqMeta *meta = nullptr;
+    int zero_tail = 0;         // ragged: scores past a sequence's own span are set to zero
+    // out-of-place compaction (host pointer, NULL in place): done by this launch too
+    const CompactArgs *copy = nullptr;
+    uint32_t *claim = nullptr;  // with `copy`: [B] words, 0 before the launch (SelectSeed)
 };
 hipError_t launch_llm_select(const LlmSelectArgs &a, hipStream_t s);
 size_t llm_select_lds_bytes(int V);
 
-// order-preserving compaction ("Remarks on KV Cache")
+// order-preserving compaction ("Remarks on KV Cache"); launch_compact is the in-place form
 struct CompactArgs {
     void *k, *v, *hidden;              // sources (and destinations when in_place)
     void *k_out, *v_out, *hidden_out;  // NULL when in_place
@@ -125,7 +144,11 @@ struct CompactArgs {
     // rows between consecutive slabs of the destinations: S - V + keep for the dense
     // out-of-place result, S when compacting in place or into tensors shaped like the inputs
     int out_rows;
-    int max_out_rows;  // rows of the longest result (S - V + keep when every sequence is alike)
+    // out of place: rows outside the visual span of the sequence that has most of them (S - V
+    // when every sequence is alike); with `zero_tail`, the most rows any sequence has in the
+    // destinations besides its kept ones
+    int max_static_rows;
+    int zero_tail = 0;  // ragged, out of place: rows past a sequence's result are set to zero
     const SeqMeta *meta = nullptr;
 };
 hipError_t launch_compact(const CompactArgs &a, hipStream_t s);

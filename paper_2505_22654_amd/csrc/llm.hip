@@ -3,6 +3,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "compact.hpp"
 #include "launch.hpp"
 
 namespace vscan {
@@ -55,7 +56,8 @@ __global__ __launch_bounds__(kScoreWaves * kWave, (DEPTH == 2 && NC <= 4 && NRB 
                                                         int vis_start_u, int V_cap, int k0_u,
                                                         int nk_u, int domain_all,
                                                         const SeqMeta *__restrict__ meta,
-                                                        float sl2) {
+                                                        float sl2, SelectSeed seed) {
+    seed_selection(seed, blockIdx.x, gridDim.x);
     // S_cap, V_cap: rows per sequence of k and of part (tensor strides).  Without `meta` every
     // sequence has the lengths (S_cap, vis_start_u, V_cap) and the key domain [k0_u, k0_u + nk_u);
     // with it, sequence b has those of meta[b], and nk_u is the longest domain (LDS layout).
@@ -320,7 +322,7 @@ static hipError_t llm_score_launch3(const LlmScoreArgs &a, hipStream_t s, size_t
     hipLaunchKernelGGL((llm_score_kernel<T, NC, NRB, STAGED, DEPTH>), dim3(grid),
                        dim3(kScoreWaves * kWave), smem, s, (const T *)a.q, (const T *)a.k, a.part,
                        a.B, a.Hq, a.Hkv, a.Tq, a.S, a.dh, a.vis_start, a.V, k0, nk, a.domain_all,
-                       a.meta, a.scale * 1.4426950408889634f);
+                       a.meta, a.scale * 1.4426950408889634f, a.seed);
     return hipGetLastError();
 }
 
@@ -467,7 +469,8 @@ __global__ __launch_bounds__(256) void llm_score_combine_kernel(const float *__r
                                                                const float *__restrict__ stats,
                                                                float *__restrict__ part, int R,
                                                                int V, int vis_start, int k0,
-                                                               int nchunks) {
+                                                               int nchunks, SelectSeed seed) {
+    seed_selection(seed, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     extern __shared__ float wgt[];                  // [nchunks][R], then M[R], invL[R], then the pairs
     float *M = wgt + nchunks * R, *invL = M + R, *st = invL + R;
     const int item = blockIdx.y, tid = threadIdx.x;
@@ -535,7 +538,7 @@ static hipError_t llm_score_split_t(const LlmScoreArgs &a, hipStream_t s, int nc
     const size_t smem2 = (size_t)(3 * nchunks * R + 2 * R) * sizeof(float);
     hipLaunchKernelGGL(llm_score_combine_kernel, dim3((a.V + 255) / 256, items), dim3(256), smem2, s,
                        (const float *)a.split_e, (const float *)a.split_stats, a.part, R, a.V,
-                       a.vis_start, k0, nchunks);
+                       a.vis_start, k0, nchunks, a.seed);
     return hipGetLastError();
 }
 
@@ -550,67 +553,8 @@ hipError_t launch_llm_score(const LlmScoreArgs &a, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Compaction.  New row p of a sequence comes from old row
-//   p                          p <  vis_start
-//   vis_start + kept[p - vs]   p <  vis_start + keep
-//   p + (V - keep)             otherwise
-// so sources never lie below destinations.  A "strip" is up to 256 bytes of one
-// row of one slab (K or V: one (sequence, kv head); hidden: one sequence).
+// Compaction in place (rows and strips: compact.hpp).
 // ---------------------------------------------------------------------------
-struct Strip {
-    unsigned char *src, *dst;  // first byte of row 0 of the strip
-    int64_t src_stride, dst_stride;
-    int width;                 // bytes, multiple of 16, <= 256
-    int b;
-};
-
-// slab bases only: valid before the per-sequence lengths of a ragged batch are known
-__device__ __forceinline__ Strip decode_strip(const CompactArgs &a, int id) {
-    const int kv_w = a.dh * a.elem_bytes, hid_w = a.Dh * a.elem_bytes;
-    const int kv_strips = (kv_w + 255) / 256, hid_strips = (hid_w + 255) / 256;
-    const int n_kv = a.B * a.Hkv * kv_strips;
-    Strip s;
-    if (id < 2 * n_kv) {
-        const bool is_v = id >= n_kv;
-        const int r = is_v ? id - n_kv : id;
-        const int slab = r / kv_strips, strip = r - slab * kv_strips;
-        unsigned char *in = reinterpret_cast<unsigned char *>(is_v ? a.v : a.k);
-        unsigned char *out = reinterpret_cast<unsigned char *>(is_v ? a.v_out : a.k_out);
-        s.b = slab / a.Hkv;
-        s.src_stride = kv_w;
-        s.dst_stride = kv_w;
-        s.src = in + (int64_t)slab * a.S * kv_w + strip * 256;
-        s.dst = a.in_place ? s.src : out + (int64_t)slab * a.out_rows * kv_w + strip * 256;
-        s.width = min(256, kv_w - strip * 256);
-    } else {
-        const int r = id - 2 * n_kv;
-        const int b = r / hid_strips, strip = r - b * hid_strips;
-        unsigned char *in = reinterpret_cast<unsigned char *>(a.hidden);
-        unsigned char *out = reinterpret_cast<unsigned char *>(a.hidden_out);
-        s.b = b;
-        s.src_stride = hid_w;
-        s.dst_stride = hid_w;
-        s.src = in + (int64_t)b * a.S * hid_w + strip * 256;
-        s.dst = a.in_place ? s.src : out + (int64_t)b * a.out_rows * hid_w + strip * 256;
-        s.width = min(256, hid_w - strip * 256);
-    }
-    return s;
-}
-
-// Ragged batch: replace the lengths in the (by-value) argument block by those of sequence b.
-// Returns the kept-index row of the sequence.
-__device__ __forceinline__ const int32_t *sequence_view(CompactArgs &a, int b) {
-    const int32_t *kept_b = a.kept_idx + (int64_t)b * a.keep;  // a.keep is still the stride here
-    if (a.meta) {
-        const SeqMeta m = a.meta[b];
-        a.S = m.seq_len;
-        a.vis_start = m.vis_start;
-        a.V = m.vis_len;
-        a.keep = m.keep;
-    }
-    return kept_b;
-}
-
 // Source rows of N output rows p[i].  The kept indices are fetched for every p from a clamped
 // position (never predicated, and pinned ahead of the selects by an empty asm so the compiler
 // cannot sink them into branches): the index loads of a tile are independent of each other and
@@ -634,8 +578,7 @@ __device__ __forceinline__ void src_rows(const CompactArgs &a, const int32_t *ke
     }
 }
 
-constexpr int kCompactRpt = 8;                   // rows per thread per tile
-constexpr int kCompactTile = 16 * kCompactRpt;   // rows per tile (16 threads span a row)
+constexpr int kCompactRpt = kCompactTile / 16;  // rows per thread and tile (16 threads span a row)
 
 // Makes the compiler wait (s_waitcnt vmcnt) until the loads that produced these
 // registers have returned.  A workgroup barrier by itself does not wait for a
@@ -713,42 +656,9 @@ __global__ __launch_bounds__(256) void compact_inplace_kernel(CompactArgs a) {
     }
 }
 
-// Out of place: a plain row gather; grid (strips, row tiles).
-__global__ __launch_bounds__(256) void compact_gather_kernel(CompactArgs a) {
-    const Strip s = decode_strip(a, blockIdx.x);
-    const int32_t *kept_b = sequence_view(a, s.b);
-    const int S_out = a.S - a.V + a.keep;
-    const int piece = threadIdx.x & 15, rloc = threadIdx.x >> 4;
-    if (piece * 16 >= s.width) return;
-    uint4 v[kCompactRpt];
-    int pr[kCompactRpt], sr[kCompactRpt];  // all index fetches first, then all row fetches
-#pragma unroll
-    for (int i = 0; i < kCompactRpt; ++i) pr[i] = blockIdx.y * kCompactTile + i * 16 + rloc;
-    src_rows<kCompactRpt>(a, kept_b, pr, sr);
-#pragma unroll
-    for (int i = 0; i < kCompactRpt; ++i) {
-        const int p = blockIdx.y * kCompactTile + i * 16 + rloc;
-        const bool ok = p < S_out;
-        v[i] = load16_guard(s.src, (int64_t)sr[i] * s.src_stride + piece * 16, ok);
-    }
-#pragma unroll
-    for (int i = 0; i < kCompactRpt; ++i) {
-        const int p = blockIdx.y * kCompactTile + i * 16 + rloc;
-        if (p < S_out)
-            *reinterpret_cast<uint4 *>(s.dst + (int64_t)p * s.dst_stride + piece * 16) = v[i];
-    }
-}
-
 hipError_t launch_compact(const CompactArgs &a, hipStream_t s) {
-    const int kv_strips = (a.dh * a.elem_bytes + 255) / 256;
-    const int hid_strips = (a.Dh * a.elem_bytes + 255) / 256;
-    const int strips = 2 * a.B * a.Hkv * kv_strips + a.B * hid_strips;
-    if (a.in_place) {
-        hipLaunchKernelGGL(compact_inplace_kernel, dim3(strips), dim3(256), 0, s, a);
-    } else {
-        dim3 grid(strips, (a.max_out_rows + kCompactTile - 1) / kCompactTile);
-        hipLaunchKernelGGL(compact_gather_kernel, grid, dim3(256), 0, s, a);
-    }
+    if (!a.in_place) return hipErrorInvalidValue;  // done by the selection launch
+    hipLaunchKernelGGL(compact_inplace_kernel, dim3(compact_strips(a)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -16,6 +16,7 @@
 // threshold is built two bits per step from three independent candidate counts,
 // and the walk stops as soon as some candidate is reached by exactly k keys.
 #include "common.hpp"
+#include "compact.hpp"
 #include "launch.hpp"
 
 namespace vscan {
@@ -561,57 +562,55 @@ __global__ __launch_bounds__(1024) void encoder_select_local_kernel(EncSelectArg
     flag_out[(int64_t)bc * N + j] = cnt < a.kw ? 1 : 0;
 }
 
-// Stage-2 selection, one workgroup per sequence.
-template <bool GLOBAL_WAVE, int NREG>
-__global__ __launch_bounds__(1024) void llm_select_kernel(LlmSelectArgs a) {
-    extern __shared__ __align__(16) unsigned char smem[];
+// Stage-2 selection of sequence b by one workgroup.
+template <bool GLOBAL_WAVE, int NREG, int NT>
+__device__ __forceinline__ void select_sequence(const LlmSelectArgs &a, int b, unsigned char *smem) {
     SelectSmem &sm = *reinterpret_cast<SelectSmem *>(smem);
     uint32_t *key = reinterpret_cast<uint32_t *>(smem + sizeof(SelectSmem));
     uint8_t *flag = reinterpret_cast<uint8_t *>(key + a.V);
-    const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
+    constexpr int nt = NT;
+    const int tid = threadIdx.x;
     // ragged batch: this sequence's own span and budget; a.V and a.keep stay the strides
     const int V = a.meta ? a.meta[b].vis_len : a.V;
     const int keep = a.meta ? a.meta[b].keep : a.keep;
-    if (GLOBAL_WAVE) {
-        for (int j = tid; j < V; j += nt) {  // one token per thread
-            const float s = head_sum(a.part + (int64_t)b * a.Hkv * a.V + j, a.Hkv, a.V) * a.norm;
-            key[j] = float_to_key(s);
-            flag[j] = 0;
-            if (a.scores_out) a.scores_out[(int64_t)b * a.V + j] = s;
-        }
-    } else {
-        // several tokens per thread: the head values of all of them are requested together,
-        // a few heads at a time (clamped positions), and added in head order as head_sum does
-        constexpr int HB = NREG <= 4 ? 8 : NREG <= 16 ? 2 : 1;
-        float acc[NREG];
+    {
+        // the head values of all of a thread's tokens are requested together, a few heads at a
+        // time (clamped positions), and added in head order as head_sum does
+        constexpr int TPT = GLOBAL_WAVE ? NREG * kWave / NT : NREG;
+        static_assert(TPT >= 1 && (!GLOBAL_WAVE || TPT * NT == NREG * kWave), "a token has one thread");
+        constexpr int HB = TPT <= 2 ? 16 : TPT <= 4 ? 8 : TPT <= 8 ? 4 : TPT <= 16 ? 2 : 1;
+        float acc[TPT];
 #pragma unroll
-        for (int r = 0; r < NREG; ++r) acc[r] = 0.f;
+        for (int r = 0; r < TPT; ++r) acc[r] = 0.f;
         const float *pb = a.part + (int64_t)b * a.Hkv * a.V;
         for (int h0 = 0; h0 < a.Hkv; h0 += HB) {
-            float v[NREG][HB];
+            float v[TPT][HB];
 #pragma unroll
-            for (int r = 0; r < NREG; ++r)
+            for (int r = 0; r < TPT; ++r)
 #pragma unroll
                 for (int u = 0; u < HB; ++u)
-                    v[r][u] = pb[(int64_t)min(h0 + u, a.Hkv - 1) * a.V + min(r * nt + tid, V - 1)];
+                    v[r][u] = pb[(int64_t)min(h0 + u, a.Hkv - 1) * a.V + min(r * NT + tid, V - 1)];
 #pragma unroll
-            for (int r = 0; r < NREG; ++r)
+            for (int r = 0; r < TPT; ++r)
 #pragma unroll
                 for (int u = 0; u < HB; ++u) acc[r] += h0 + u < a.Hkv ? v[r][u] : 0.f;
         }
 #pragma unroll
-        for (int r = 0; r < NREG; ++r) {
-            const int j = r * nt + tid;
+        for (int r = 0; r < TPT; ++r) {
+            const int j = r * NT + tid;
             if (j < V) {
                 const float s = acc[r] * a.norm;
-                key[j] = float_to_key(s);
+                key[j] = max(float_to_key(s), 1u);  // every token is a candidate, a NaN score's too
                 flag[j] = 0;
                 if (a.scores_out) a.scores_out[(int64_t)b * a.V + j] = s;
             }
         }
     }
-    if (a.meta)
+    if (a.meta) {
         for (int i = keep + tid; i < a.keep; i += nt) a.kept_idx[(int64_t)b * a.keep + i] = -1;
+        if (a.zero_tail && a.scores_out)
+            for (int j = V + tid; j < a.V; j += nt) a.scores_out[(int64_t)b * a.V + j] = 0.f;
+    }
     __syncthreads();
     auto slot = [&](int sl, int &idx) -> uint32_t {
         idx = sl;
@@ -623,10 +622,35 @@ __global__ __launch_bounds__(1024) void llm_select_kernel(LlmSelectArgs a) {
     } else {
         block_topk_regs<NREG>(slot, V, keep, flag, 1, sm);
     }
-    __syncthreads();  // the keys are no longer needed: their LDS holds the counts of the walk
-    ranked_walk(flag, V, reinterpret_cast<int *>(key), [&](int j, bool kept, int s) {
-        if (kept) a.kept_idx[(int64_t)b * a.keep + s] = j;
+    __syncthreads();
+    // (the counts of the walk in LDS of their own: a short span has fewer keys than waves)
+    ranked_walk(flag, V, sm.wsum, [&](int j, bool kept, int s) {
+        // (device scope: in an out-of-place call workgroups of other XCDs wait for it)
+        if (kept) device_store(a.kept_idx + (int64_t)b * a.keep + s, j);
     });
+}
+
+// Selection, and out of place the copies around it (compact.hpp).
+template <bool GLOBAL_WAVE, int NREG, int NT>
+__global__ __launch_bounds__(NT) void llm_select_kernel(LlmSelectArgs a, CompactArgs copy,
+                                                        CopyUnits units) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    int b = blockIdx.x, unit = -1;  // kept unit of this workgroup
+    if (b >= a.B) {
+        const int id = b - a.B;
+        if (id < units.n_static) {
+            copy_static_rows(copy, units, id);
+            return;
+        }
+        unit = id - units.n_static;
+        b = kept_unit_sequence(copy, units, unit);
+    }
+    // (in place there is nobody to race with)
+    if (!a.claim || claim_selection(a.claim, b, unit >= 0, reinterpret_cast<int *>(smem))) {
+        __syncthreads();  // the claim's LDS word is free
+        select_sequence<GLOBAL_WAVE, NREG, NT>(a, b, smem);
+    }
+    if (unit >= 0) copy_kept_rows<NT>(copy, units, unit);
 }
 
 // ---------------------------------------------------------------------------
@@ -733,16 +757,24 @@ hipError_t launch_encoder_select(const EncSelectArgs &a, hipStream_t s) {
 
 hipError_t launch_llm_select(const LlmSelectArgs &a, hipStream_t s) {
     const size_t smem = llm_select_lds_bytes(a.V);
-    if (a.V <= 1024) {
-        const int threads = (a.V + kWave - 1) / kWave * kWave;
-        if (a.V <= 256)
-            return launch_select<llm_select_kernel<true, 4>>(a.B, threads, smem, s, a);
-        return launch_select<llm_select_kernel<true, 16>>(a.B, threads, smem, s, a);
+    const int threads = a.V <= 1024 ? 256 : a.V <= 4096 ? 512 : 1024;
+    CompactArgs copy{};
+    CopyUnits units{};
+    if (a.copy) {
+        copy = *a.copy;
+        units = copy_units(copy, threads);
     }
-    const int nreg = (a.V + 1023) / 1024;
-    if (nreg <= 4) return launch_select<llm_select_kernel<false, 4>>(a.B, 1024, smem, s, a);
-    if (nreg <= 16) return launch_select<llm_select_kernel<false, 16>>(a.B, 1024, smem, s, a);
-    return launch_select<llm_select_kernel<false, 32>>(a.B, 1024, smem, s, a);
+    const int blocks = a.B + units.n_static + units.n_kept;
+#define VSCAN_LLM_SEL(...) \
+    return launch_select<llm_select_kernel<__VA_ARGS__>>(blocks, threads, smem, s, a, copy, units)
+    if (a.V <= 256) VSCAN_LLM_SEL(true, 4, 256);
+    if (a.V <= 512) VSCAN_LLM_SEL(true, 8, 256);
+    if (a.V <= 1024) VSCAN_LLM_SEL(true, 16, 256);
+    if (a.V <= 2048) VSCAN_LLM_SEL(false, 4, 512);
+    if (a.V <= 4096) VSCAN_LLM_SEL(false, 8, 512);
+    if (a.V <= 16384) VSCAN_LLM_SEL(false, 16, 1024);
+    VSCAN_LLM_SEL(false, 32, 1024);
+#undef VSCAN_LLM_SEL
 }
 
 }  // namespace vscan
