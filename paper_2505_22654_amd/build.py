@@ -11,9 +11,9 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libvscan.so")
 
-SOURCES = ["api.cpp", "budget.cpp", "encoder_score.hip", "select.hip", "sim_merge.hip", "llm.hip", "fused.hip",
+SOURCES = ["api.cpp", "budget.cpp", "encoder_score.hip", "mean_planes.hip", "select.hip", "sim_merge.hip", "llm.hip", "fused.hip",
            "static_entry.hip", "ragged_entry.hip"]
-HEADERS = ["common.hpp", "launch.hpp", "compact.hpp", "fused.hpp", os.path.join("..", "..", "include", "vscan.h")]
+HEADERS = ["common.hpp", "launch.hpp", "compact.hpp", "fused.hpp", "mean.hpp", os.path.join("..", "..", "include", "vscan.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
