@@ -565,12 +565,11 @@ static int encoder_reduce_fused_impl(const vscan_encoder_desc *d, const void *hi
             pa.dh = d->head_dim;
             pa.w = pass ? w_q_local : w_q;
             pa.out = reinterpret_cast<float *>(ws + p.off_qf);
-            VSCAN_LAUNCH("fused_project", launch_fused_project(pa, s));
             VSCAN_LAUNCH("fused_transpose", launch_transpose(pass ? w_k_t_local : w_k_t, ws + p.off_wk,
                                                             d->feat_dim, d->heads * d->head_dim,
                                                             elem_bytes(d->dtype), s));
-            pa.w = ws + p.off_wk;
-            pa.out = reinterpret_cast<float *>(ws + p.off_kf);
+            pa.w_k = ws + p.off_wk;
+            pa.out_k = reinterpret_cast<float *>(ws + p.off_kf);
             VSCAN_LAUNCH("fused_project", launch_fused_project(pa, s));
             sa.head_scores = reinterpret_cast<float *>(ws + (pass ? p.e.off_head_local : p.e.off_head_global));
             VSCAN_LAUNCH("score_mean_lse", launch_score_mean_lse(sa, s));

@@ -166,18 +166,26 @@ struct ProbProject {
     static constexpr int PL = 1;
     static constexpr bool kStreamS = false;
     GemmDims d;
-    const char *hidden, *w;
+    const char *hidden, *w[2];  // batch entry 0: queries, 1: keys
     int S, H, dh, row_bytes;
-    float *out;
+    float *out[2];
+    uint32_t inv_S, inv_dh;  // inverse_of
+    static uint32_t inverse_of(int n) { return n == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / n); }
+    // a / n for 0 <= a < 2^31: a * floor(2^32 / n) / 2^32 falls short of a / n by less than one
+    static __device__ __forceinline__ int quotient(int a, int n, uint32_t inv) {
+        const int q = (int)__umulhi((uint32_t)a, inv);
+        return q + (a - q * n >= n);
+    }
     __device__ int rows_s(int) const { return d.rows_s; }
-    __device__ const char *s_base(int) const { return w; }
+    __device__ const char *s_base(int z) const { return z ? w[1] : w[0]; }
     __device__ uint32_t s_off(int n) const { return (uint32_t)n * (uint32_t)row_bytes; }
     __device__ const char *p_base(int, int) const { return hidden; }
     __device__ uint32_t p_off(int m) const { return (uint32_t)m * (uint32_t)row_bytes; }
-    __device__ void emit(int, int, int p, int s_row, float v) const {
-        const int bc = p / S, t = p - bc * S;
-        const int h = s_row / dh, e = s_row - h * dh;
-        out[(((int64_t)bc * H + h) * S + t) * dh + e] = v;
+    __device__ void emit(int, int z, int p, int s_row, float v) const {
+        // (an integer division each, 64 results a thread, took 11 of 45 us)
+        const int bc = quotient(p, S, inv_S), t = p - bc * S;
+        const int h = quotient(s_row, dh, inv_dh), e = s_row - h * dh;
+        (z ? out[1] : out[0])[(((int64_t)bc * H + h) * S + t) * dh + e] = v;
     }
 };
 
@@ -331,9 +339,8 @@ TileShape tile_shape(int rows_p, int rows_s, int Z) {
 }
 
 template <class Prob>
-hipError_t launch_gemm(Prob pr, int Z, hipStream_t s) {
+hipError_t launch_gemm(Prob pr, int Z, hipStream_t s, TileShape t) {
     GemmDims &d = pr.d;
-    const TileShape t = tile_shape(d.rows_p, d.rows_s, Z);
     d.Z = Z;
     d.s_tiles = (d.rows_s + t.ts - 1) / t.ts;
     d.p_tiles = (d.rows_p + t.tp - 1) / t.tp;
@@ -343,7 +350,9 @@ hipError_t launch_gemm(Prob pr, int Z, hipStream_t s) {
     const dim3 grid(image_affine_grid(Z, d.s_tiles * d.p_tiles * d.ksplit, d.affine != 0));
 #define VSCAN_GEMM(WS, WP, FS, FP, CH) \
     hipLaunchKernelGGL((nt_gemm_kernel<Prob, WS, WP, FS, FP, CH>), grid, dim3(64 * WS * WP), 0, s, pr)
-    if (t.tp == 32 && t.ts == 128)
+    if (t.tp == 128 && t.ts == 128)
+        VSCAN_GEMM(2, 2, 2, 2, 128);
+    else if (t.tp == 32 && t.ts == 128)
         VSCAN_GEMM(4, 1, 1, 1, 128);
     else if (t.tp == 32)
         VSCAN_GEMM(4, 1, 2, 1, 128);
@@ -357,6 +366,10 @@ hipError_t launch_gemm(Prob pr, int Z, hipStream_t s) {
         VSCAN_GEMM(2, 4, 4, 2, 128);
 #undef VSCAN_GEMM
     return hipGetLastError();
+}
+template <class Prob>
+hipError_t launch_gemm(Prob pr, int Z, hipStream_t s) {
+    return launch_gemm(pr, Z, s, tile_shape(pr.d.rows_p, pr.d.rows_s, Z));
 }
 
 // value = sum of PL bf16 planes: plane p is the bf16 rounding of what planes < p left over
@@ -626,20 +639,34 @@ hipError_t launch_fused_softmax(const FusedArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// 64 x 64 tiles of 16- or 32-bit elements through LDS (pitch 65: conflict-free both ways)
+// 64 x 64 tiles of 16- or 32-bit elements through LDS, 16 bytes at a time from and to memory (rows
+// and columns are multiples of eight elements).  Bound by latency at this size: 1280 x 1280 bf16 take
+// 5.2 us, an element per thread and access took 8.6.
 template <typename U>
 __global__ __launch_bounds__(256) void transpose_kernel(const U *__restrict__ in, U *__restrict__ out,
                                                         int rows, int cols) {
-    __shared__ U tile[64][65];
+    constexpr int E = 16 / (int)sizeof(U), PPR = 64 / E, PITCH = 64 + E;
+    __shared__ __align__(16) U tile[64 * PITCH];  // [column][row]
     const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-    for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-        const int r = i >> 6, c = i & 63;
-        if (r0 + r < rows && c0 + c < cols) tile[r][c] = in[(int64_t)(r0 + r) * cols + c0 + c];
+#pragma unroll
+    for (int i = 0; i < 64 * PPR / 256; ++i) {
+        const int p = threadIdx.x + i * 256, r = p / PPR, c = p % PPR * E;
+        // clamped: a piece outside the matrix re-reads one inside, and is not stored below
+        union {
+            uint4 u;
+            U e[E];
+        } v;
+        v.u = load16(in, ((int64_t)min(r0 + r, rows - 1) * cols + min(c0 + c, cols - E)) * (int)sizeof(U));
+#pragma unroll
+        for (int j = 0; j < E; ++j) tile[(c + j) * PITCH + r] = v.e[j];
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-        const int c = i >> 6, r = i & 63;
-        if (r0 + r < rows && c0 + c < cols) out[(int64_t)(c0 + c) * rows + r0 + r] = tile[r][c];
+#pragma unroll
+    for (int i = 0; i < 64 * PPR / 256; ++i) {
+        const int p = threadIdx.x + i * 256, c = p / PPR, r = p % PPR * E;
+        if (r0 + r < rows && c0 + c < cols)
+            *reinterpret_cast<uint4 *>(out + (int64_t)(c0 + c) * rows + r0 + r) =
+                *reinterpret_cast<const uint4 *>(tile + c * PITCH + r);
     }
 }
 
@@ -660,13 +687,24 @@ static hipError_t fused_project_t(const ProjectArgs &a, hipStream_t s) {
     ProbProject<T> pr;
     pr.d = dims(a.H * a.dh, a.BC * a.S, a.Dh, (int)sizeof(T), 1, nullptr);
     pr.hidden = reinterpret_cast<const char *>(a.hidden);
-    pr.w = reinterpret_cast<const char *>(a.w);
+    pr.w[0] = reinterpret_cast<const char *>(a.w);
+    pr.w[1] = reinterpret_cast<const char *>(a.w_k);
     pr.S = a.S;
     pr.H = a.H;
     pr.dh = a.dh;
     pr.row_bytes = a.Dh * (int)sizeof(T);
-    pr.out = a.out;
-    return launch_gemm(pr, 1, s);
+    pr.out[0] = a.out;
+    pr.out[1] = a.out_k;
+    pr.inv_S = ProbProject<T>::inverse_of(a.S);
+    pr.inv_dh = ProbProject<T>::inverse_of(a.dh);
+    // Weights and hidden states are a few megabytes and come from the caches, so what counts is
+    // how many CUs multiply: 256 x 256 tiles only where every CU gets two.  2688 tokens of 1280
+    // features: Q and K as launches of 55 such tiles 70 + 70 us, as one launch of 420 tiles of
+    // 128 x 128 34 us (128 x 64: 40, 256 x 128: 38-41, 128 x 128 with eight waves: 36).
+    const int64_t tiles = (int64_t)((pr.d.rows_s + 255) / 256) * ((pr.d.rows_p + 255) / 256) * 2;
+    TileShape t = tile_shape(pr.d.rows_p, pr.d.rows_s, 2);
+    if (pr.d.rows_p > 64 && tiles < 2 * kCus) t = {128, 128, 128};
+    return launch_gemm(pr, 2, s, t);
 }
 hipError_t launch_fused_project(const ProjectArgs &a, hipStream_t s) {
     return a.is_bf16 ? fused_project_t<bf16_t>(a, s) : fused_project_t<float>(a, s);

@@ -40,15 +40,15 @@ hipError_t launch_fused_softmax(const FusedArgs &a, hipStream_t s);
 hipError_t launch_fused_colsum(const FusedArgs &a, hipStream_t s);
 
 // Mean-attention scoring (last sentence of "Global Scan") from hidden states: every token is a
-// query, so Q and K are projected outright - out[bc][h][t][e] = sum_k hidden[bc][t][k] *
+// query, so Q and K are projected outright, in one launch - out[bc][h][t][e] = sum_k hidden[bc][t][k] *
 // w[h*dh + e][k], fp32, in the layout the mean-attention kernels read - and those kernels run
 // on the result.  `w` has its rows along the output features; W_K arrives the other way round
 // and is transposed first.
 struct ProjectArgs {
     int is_bf16 = 1;      // element type of hidden and w (else fp32)
     const void *hidden;   // [BC, S, Dh]
-    const void *w;        // [H*dh, Dh]
-    float *out;           // [BC, H, S, dh]
+    const void *w, *w_k;  // [H*dh, Dh] each
+    float *out, *out_k;   // [BC, H, S, dh] each
     int BC, S, Dh, H, dh;
 };
 hipError_t launch_fused_project(const ProjectArgs &a, hipStream_t s);
