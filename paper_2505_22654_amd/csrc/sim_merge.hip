@@ -266,6 +266,128 @@ __global__ __launch_bounds__(THREADS) void sim_argmax_kernel(const T *__restrict
 }
 
 // ---------------------------------------------------------------------------
+// The same for few fp32 rows: a workgroup owns 16 R kept slots x 16 R dropped tokens, and its eight
+// waves share the feature axis (partial products meet in LDS).  With 64 x 64 tiles such a call is one
+// row's length of fp32 matrix instructions (14 us at 1024 features) on a few CUs with the chip idle;
+// here more workgroups do a part of that each, and a row's pieces are all in flight at once, straight
+// into matrix-operand registers (nothing goes through LDS twice).
+// ---------------------------------------------------------------------------
+constexpr int kThinWaves = 8;
+
+template <int R>
+__global__ __launch_bounds__(kThinWaves * 64) void sim_argmax_thin_kernel(
+    const float *__restrict__ x, const int32_t *__restrict__ kept_idx,
+    const int32_t *__restrict__ drop_idx, unsigned long long *__restrict__ best, int T_img, int D,
+    int K, int U, int B, int affine) {
+    constexpr int BATCH = 8 / R;  // 64-byte chunks in flight per row
+    __shared__ f32x4_t part[R * R][kThinWaves][kWave];
+    __shared__ float norm[kThinWaves][16 * R];
+    const int tiles_n = (U + 16 * R - 1) / (16 * R), tiles_m = (K + 16 * R - 1) / (16 * R);
+    int b, tile;
+    if (!image_affine_decode(B, tiles_m * tiles_n, affine != 0, b, tile)) return;
+    const int m0 = (tile / tiles_n) * 16 * R, n0 = (tile % tiles_n) * 16 * R;
+    const int lane = lane_id(), w = wave_id(), r16 = lane & 15, q = lane >> 4;
+    const int row_bytes = D * (int)sizeof(float);
+    const unsigned char *xb =
+        reinterpret_cast<const unsigned char *>(x) + (int64_t)b * T_img * row_bytes;
+    // rows outside the problem (slots >= K, columns >= U) stand for some other row of the image:
+    // their results are masked in the epilogue
+    int kept[R], drop[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        kept[i] = kept_idx[(int64_t)b * K + min(m0 + 16 * i + r16, K - 1)];
+        drop[i] = drop_idx[(int64_t)b * U + min(n0 + 16 * i + r16, U - 1)];
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {  // indices come from device memory: stay inside
+        kept[i] = min(max(kept[i], 0), T_img - 1);
+        drop[i] = min(max(drop[i], 0), T_img - 1);
+    }
+    // a wave's share is contiguous and of whole 128-byte lines
+    const int nchunks = (row_bytes + 63) / 64;
+    const int share = ((nchunks + kThinWaves - 1) / kThinWaves + 1) & ~1;
+    const int c_end = min(nchunks, (w + 1) * share);
+
+    f32x4_t acc[R][R];
+    float ss[R];  // partial squared norms of kept rows m0 + 16 i + r16
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        ss[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < R; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    for (int c0 = w * share; c0 < c_end; c0 += BATCH) {
+        uint4 a[BATCH][R], d[BATCH][R];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u)  // clamped, not predicated
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                const int col = min((c0 + u) * 64 + q * 16, row_bytes - 16);
+                a[u][i] = load16(xb, (int64_t)kept[i] * row_bytes + col);
+                d[u][i] = load16(xb, (int64_t)drop[i] * row_bytes + col);
+            }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            // past the share or the row: zeros on both sides (what was re-read may hold anything)
+            const bool valid = c0 + u < c_end && (c0 + u) * 64 + q * 16 < row_bytes;
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                if (!valid) a[u][i] = d[u][i] = zero16();
+                float v[4];
+                unpack16<float>(a[u][i], v);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ss[i] = fmaf(v[e], v[e], ss[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+#pragma unroll
+                for (int j = 0; j < R; ++j) mma16_chunk<float>(acc[i][j], a[u][i], d[u][j]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        // the four quarters of a kept row's chunks sit sixteen lanes apart
+        ss[i] += __shfl_xor(ss[i], 16, kWave);
+        ss[i] += __shfl_xor(ss[i], 32, kWave);
+        if (q == 0) norm[w][16 * i + r16] = ss[i];
+#pragma unroll
+        for (int j = 0; j < R; ++j) part[j * R + i][w][lane] = acc[i][j];
+    }
+    __syncthreads();
+    if (w >= R) return;  // wave j reports the j-th sixteen columns
+    // acc[i][j][r] = x_slot . x_token, slot = m0 + 16 i + 4 q + r, token column n0 + 16 j + r16;
+    // partial sums are added in wave order
+    unsigned long long packed = 0ull;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        f32x4_t sum = part[w * R + i][0][lane];
+#pragma unroll
+        for (int k = 1; k < kThinWaves; ++k) sum += part[w * R + i][k][lane];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float n2 = norm[0][16 * i + 4 * q + r];
+#pragma unroll
+            for (int k = 1; k < kThinWaves; ++k) n2 += norm[k][16 * i + 4 * q + r];
+            const int slot = m0 + 16 * i + 4 * q + r;
+            const float v = sum[r] * (1.0f / fmaxf(sqrtf(n2), kNormEps));
+            const unsigned long long p = ((unsigned long long)float_to_key(v) << 32) |
+                                         (unsigned long long)(uint32_t)~(uint32_t)slot;
+            // (as in the other forms neither a NaN nor minus infinity is a candidate; of equal
+            // similarities the lowest slot's word is the largest)
+            if (slot < K && v > -INFINITY && p > packed) packed = p;
+        }
+    }
+#pragma unroll
+    for (int o = 16; o < kWave; o *= 2) {
+        const unsigned long long other = __shfl_xor(packed, o, kWave);
+        if (other > packed) packed = other;
+    }
+    const int token = w == 0 ? drop[0] : drop[R - 1];
+    if (q == 0 && n0 + 16 * w + r16 < U && packed != 0ull)
+        atomicMax(best + (int64_t)b * T_img + token, packed);
+}
+
+// ---------------------------------------------------------------------------
 // 1 / max(||x_s||, eps) of every kept row, for the large form of the similarity kernel below:
 // one wave per kept row.
 // ---------------------------------------------------------------------------
@@ -957,6 +1079,16 @@ static hipError_t sim_t(const MergeArgs &a, hipStream_t s) {
                        a.D, a.K, U, a.B, (int)affine);
     return hipGetLastError();
 }
+template <int R>
+static hipError_t sim_thin(const MergeArgs &a, hipStream_t s) {
+    constexpr int N = 16 * R;
+    const int U = a.T - a.K, tiles = ((U + N - 1) / N) * ((a.K + N - 1) / N);
+    const bool affine = image_affinity(a);
+    hipLaunchKernelGGL(sim_argmax_thin_kernel<R>, dim3(image_affine_grid(a.B, tiles, affine)),
+                       dim3(kThinWaves * kWave), 0, s, (const float *)a.x, a.kept_idx, a.drop_idx,
+                       (unsigned long long *)a.best, a.T, a.D, a.K, U, a.B, (int)affine);
+    return hipGetLastError();
+}
 template <typename T, int TM, int TN, int WM, int WN, int KC, int NSETS, bool DIRECT>
 static hipError_t sim_large_launch(const MergeArgs &a, hipStream_t s) {
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
@@ -1004,6 +1136,14 @@ hipError_t launch_sim_argmax(const MergeArgs &a, hipStream_t s) {
     if (sim_argmax_uses_large_form(a.B, a.T, a.K))
         return a.is_bf16 ? sim_large_t<bf16_t>(a, s) : sim_large_t<float>(a, s);
     if (a.is_bf16) return sim_t<bf16_t, 1, 1, 8, 2, 512>(a, s);
+    // fp32: the smallest tiles that still give every CU at most one workgroup (1024 features, kept x
+    // dropped: 64 x 512: 24.0 us with 64 x 64 tiles, 13.2 with 32 x 32, 7.3 with 16 x 16; 2 x 64 x
+    // 512: 23.5, 13.2, 7.5; 4 x 64 x 512: 24.4, 13.5, 12.3; 8 x 64 x 512: 24.2, 13.0, 19.7; 4 x 192 x
+    // 384: 24.5, 20.4, 23.7).  bf16 multiplies sixteen times faster and is bound by its fetches: 64 x
+    // 512: 8.9, 7.8, 7.2 us, but 32 x 224 of 512 features 5.8, 7.9, 7.1.
+    auto tiles = [&](int n) { return (int64_t)((a.T - a.K + n - 1) / n) * ((a.K + n - 1) / n) * a.B; };
+    if (tiles(16) <= kCus) return sim_thin<1>(a, s);
+    if (tiles(32) <= kCus) return sim_thin<2>(a, s);
     return sim_t<float, 1, 1, 8, 2, 512>(a, s);
 }
 
