@@ -98,8 +98,8 @@ int plan_encoder(const vscan_encoder_desc *d, int with_local, EncoderPlan *p) {
     p->off_pre_flag = off;
     off += align_up((size_t)p->BC * p->N);
     p->bytes = off ? off : kAlign;
-    p->off_planes = p->bytes;
-    p->plane_stride = p->bytes_planes = 0;
+    p->off_planes = p->bytes_planes = p->bytes;
+    p->plane_stride = 0;
     if (d->score_mode == VSCAN_SCORE_MEAN_RECEIVED && es == 4) {
         p->plane_stride = align_up((size_t)p->BC * d->heads * p->S * d->head_dim * sizeof(float));
         p->bytes_planes = p->off_planes + 2 * p->plane_stride +
@@ -421,7 +421,7 @@ int vscan_encoder_workspace_size(const vscan_encoder_desc *desc, int with_local_
     EncoderPlan p;
     const int rc = plan_encoder(desc, with_local_pair != 0, &p);
     if (rc != VSCAN_OK) return rc;
-    *bytes = std::max(p.bytes, p.bytes_planes);
+    *bytes = p.bytes_planes;
     return VSCAN_OK;
 }
 
@@ -463,22 +463,38 @@ static int encoder_reduce_impl(const vscan_encoder_desc *d, const void *q, const
     sa.domain_all = d->softmax_domain == VSCAN_KEYS_ALL;
     sa.is_bf16 = d->dtype == VSCAN_BF16;
     sa.scale = resolve_scale(d->scale, d->head_dim);
-    for (int pair = 0; pair < (with_local ? 2 : 1); ++pair) {
-        if (pair == 1) {
-            sa.q = q_local;
-            sa.k = k_local;
-            sa.head_scores = reinterpret_cast<float *>(ws + p.off_head_local);
-        }
-        if (mean && p.bytes_planes && workspace_bytes >= p.bytes_planes) {
-            sa.q_planes = ws + p.off_planes;
-            sa.k_planes = ws + p.off_planes + p.plane_stride;
-            sa.plane_exps = reinterpret_cast<int32_t *>(ws + p.off_planes + 2 * p.plane_stride);
-        }
-        if (mean) {
-            VSCAN_LAUNCH("score_mean_lse", launch_score_mean_lse(sa, s));
-            VSCAN_LAUNCH("score_mean_colsum", launch_score_mean_colsum(sa, s));
-        } else {
-            VSCAN_LAUNCH("score_cls", launch_score_cls(sa, s));
+    if (mean && !sa.is_bf16 && workspace_bytes >= p.bytes_planes) {
+        sa.q_planes = ws + p.off_planes;
+        sa.k_planes = ws + p.off_planes + p.plane_stride;
+        sa.plane_exps = reinterpret_cast<int32_t *>(ws + p.off_planes + 2 * p.plane_stride);
+    }
+    if (mean && with_local && mean_pair_launch(sa.is_bf16, sa.dh)) {
+        // Pass 1 of both pairs in one launch.  The second pair's log-sum-exps wait where the first
+        // pair's scores go afterwards, so its second pass runs first.
+        sa.q2 = q_local;
+        sa.k2 = k_local;
+        sa.lse2 = sa.head_scores;
+        VSCAN_LAUNCH("score_mean_lse", launch_score_mean_lse(sa, s));
+        ScoreArgs local = sa;
+        local.q = q_local;
+        local.k = k_local;
+        local.lse = sa.lse2;
+        local.head_scores = reinterpret_cast<float *>(ws + p.off_head_local);
+        VSCAN_LAUNCH("score_mean_colsum", launch_score_mean_colsum(local, s));
+        VSCAN_LAUNCH("score_mean_colsum", launch_score_mean_colsum(sa, s));
+    } else {
+        for (int pair = 0; pair < (with_local ? 2 : 1); ++pair) {
+            if (pair == 1) {
+                sa.q = q_local;
+                sa.k = k_local;
+                sa.head_scores = reinterpret_cast<float *>(ws + p.off_head_local);
+            }
+            if (mean) {
+                VSCAN_LAUNCH("score_mean_lse", launch_score_mean_lse(sa, s));
+                VSCAN_LAUNCH("score_mean_colsum", launch_score_mean_colsum(sa, s));
+            } else {
+                VSCAN_LAUNCH("score_cls", launch_score_cls(sa, s));
+            }
         }
     }
 

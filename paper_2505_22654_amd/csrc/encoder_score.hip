@@ -445,11 +445,16 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict
 // ---------------------------------------------------------------------------
 constexpr int kPipeStageRows = 128;
 
+struct MeanPair {
+    const unsigned char *resident, *streamed;
+    const float *lse_in;
+    float *out;
+};
+
 template <int NC, int HALVES, int PASS>
 __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
-    const unsigned char *__restrict__ resident, const unsigned char *__restrict__ streamed,
-    const float *__restrict__ lse_in, float *__restrict__ out, int n_heads_total, int S, int dh,
-    int res_first, int n_res, int str_first, int n_str, float sl2) {
+    MeanPair first, MeanPair second, int pairs, int n_heads, int S, int dh, int res_first, int n_res,
+    int str_first, int n_str, float sl2) {
     constexpr int NCX = NC + (PASS == 2 ? 1 : 0);      // chunks per streamed row (pass 2: the lse chunk)
     // With an odd number of 32-byte chunks per row the unpadded row pitch serves the 16-byte
     // operand reads at 92 % of the LDS rate (measured; 25 % for an even number), and a stage
@@ -467,14 +472,21 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
     __shared__ __align__(16) unsigned char lse_lds[DIRECT && PASS == 2 ? 2 : 1][DIRECT && PASS == 2 ? kPipeStageRows * 32 : 16];
 
     const int nblk = (n_res + RB - 1) / RB;
-    const int total = n_heads_total * nblk;
+    const int total = pairs * n_heads * nblk;
     const int item = xcd_contiguous_item(total);
     if (item >= total) return;
-    const int bh = item / nblk, blk = item - bh * nblk;
+    int bh = item / nblk;
+    const int blk = item - bh * nblk;
+    const bool is_second = bh >= n_heads;
+    if (is_second) bh -= n_heads;
+    float *__restrict__ out = is_second ? second.out : first.out;
     const int row_bytes = dh * 2;
-    const unsigned char *rbase = resident + ((int64_t)bh * S + res_first) * row_bytes;
-    const unsigned char *sbase = streamed + ((int64_t)bh * S + str_first) * row_bytes;
-    const float *lse_h = PASS == 2 ? lse_in + (int64_t)bh * n_str : nullptr;
+    const unsigned char *__restrict__ rbase = (is_second ? second.resident : first.resident) +
+                                              ((int64_t)bh * S + res_first) * row_bytes;
+    const unsigned char *__restrict__ sbase = (is_second ? second.streamed : first.streamed) +
+                                              ((int64_t)bh * S + str_first) * row_bytes;
+    const float *__restrict__ lse_h =
+        PASS == 2 ? (is_second ? second.lse_in : first.lse_in) + (int64_t)bh * n_str : nullptr;
 
     const int tid = threadIdx.x, lane = lane_id(), g = lane >> 5, w = wave_id();
     uint4 kf[HALVES][NC];
@@ -850,19 +862,22 @@ static hipError_t launch_mean_pipe(const ScoreArgs &a, hipStream_t s, int pass) 
     const int key_first = a.domain_all ? 0 : a.has_cls;
     const int n_keys = a.S - key_first;
     constexpr int RB = 4 * 32 * HALVES;
-    const int total = a.BC * a.H * ((a.N + RB - 1) / RB);
+    // (two pairs: with workgroups of 256 rows a pair leaves most CUs one or two of them; the CUs that
+    // are done early take the other pair's.  2 images of 2745 tokens, 16 heads of 80: 68 + 68 -> 110 us)
+    const int pairs = pass == 1 && a.q2 ? 2 : 1;
+    const int total = pairs * a.BC * a.H * ((a.N + RB - 1) / RB);
     const int grid = ((total + 7) / 8) * 8;
     const float sl2 = a.scale * 1.4426950408889634f;
-    const unsigned char *q = reinterpret_cast<const unsigned char *>(a.q);
-    const unsigned char *k = reinterpret_cast<const unsigned char *>(a.k);
+    using Bytes = const unsigned char *;
     if (pass == 1)  // resident query rows (patch rows), streamed keys of the softmax domain
-        hipLaunchKernelGGL((mean_pipe_kernel<NC, HALVES, 1>), dim3(grid), dim3(256), 0, s, q, k,
-                           (const float *)nullptr, a.lse, a.BC * a.H, a.S, a.dh, row_first, a.N,
-                           key_first, n_keys, sl2);
+        hipLaunchKernelGGL((mean_pipe_kernel<NC, HALVES, 1>), dim3(grid), dim3(256), 0, s,
+                           (MeanPair{(Bytes)a.q, (Bytes)a.k, nullptr, a.lse}),
+                           (MeanPair{(Bytes)a.q2, (Bytes)a.k2, nullptr, a.lse2}), pairs, a.BC * a.H,
+                           a.S, a.dh, row_first, a.N, key_first, n_keys, sl2);
     else            // resident patch keys, streamed query rows (patch rows) with their lse
-        hipLaunchKernelGGL((mean_pipe_kernel<NC, HALVES, 2>), dim3(grid), dim3(256), 0, s, k, q,
-                           (const float *)a.lse, a.head_scores, a.BC * a.H, a.S, a.dh, row_first,
-                           a.N, row_first, a.N, sl2);
+        hipLaunchKernelGGL((mean_pipe_kernel<NC, HALVES, 2>), dim3(grid), dim3(256), 0, s,
+                           (MeanPair{(Bytes)a.k, (Bytes)a.q, a.lse, a.head_scores}), MeanPair{}, pairs,
+                           a.BC * a.H, a.S, a.dh, row_first, a.N, row_first, a.N, sl2);
     return hipGetLastError();
 }
 

@@ -42,7 +42,12 @@ struct ScoreArgs {
     // exponents (mean_planes_exponents ints)
     void *q_planes = nullptr, *k_planes = nullptr;
     int32_t *plane_exps = nullptr;
+    // a second pair for pass 1 to take along (mean_pair_launch), or NULL
+    const void *q2 = nullptr, *k2 = nullptr;
+    float *lse2 = nullptr;
 };
+// whether pass 1 of mean attention takes two pairs in one launch: the pipelined bf16 form
+inline bool mean_pair_launch(int is_bf16, int dh) { return is_bf16 && dh <= 80; }
 constexpr int kPlaneBlock = 128;  // rows that share a power-of-two scale
 inline size_t mean_planes_exponents(int BC, int H, int N, int has_cls) {
     return (size_t)2 * BC * H * ((N + has_cls + kPlaneBlock - 1) / kPlaneBlock);
