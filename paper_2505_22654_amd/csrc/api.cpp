@@ -319,7 +319,8 @@ struct ProfScope {
         logf("enqueued %s", name);                                                \
     } while (0)
 
-// The score chain: part[seq][token] = sum over the query rows of their softmax weights.
+// The score chain: part[seq][token] = sum over the query rows of their softmax weights, or with
+// `keep_rows` those weights, c_l[seq][row][token].
 int enqueue_fused_scores(FusedArgs &fa, const FusedScratch &f, unsigned char *ws, hipStream_t s) {
     fa.c_q = reinterpret_cast<float *>(ws + f.off_cq);
     fa.q_planes = reinterpret_cast<uint16_t *>(ws + f.off_qpl);
@@ -328,11 +329,11 @@ int enqueue_fused_scores(FusedArgs &fa, const FusedScratch &f, unsigned char *ws
     fa.ks_q = f.ks_q;
     fa.ks_l = f.ks_l;
     VSCAN_LAUNCH("fused_q", launch_fused_q(fa, s));
-    VSCAN_LAUNCH("fused_split_q", launch_fused_split_q(fa, s));
+    if (!fused_q_whole(fa.B, fa.Tq)) VSCAN_LAUNCH("fused_split_q", launch_fused_split_q(fa, s));
     VSCAN_LAUNCH("fused_qt", launch_fused_qt(fa, s));
     VSCAN_LAUNCH("fused_logits", launch_fused_logits(fa, s));
     VSCAN_LAUNCH("fused_softmax", launch_fused_softmax(fa, s));
-    VSCAN_LAUNCH("fused_colsum", launch_fused_colsum(fa, s));
+    if (!fa.keep_rows) VSCAN_LAUNCH("fused_colsum", launch_fused_colsum(fa, s));
     return VSCAN_OK;
 }
 
@@ -340,9 +341,9 @@ int enqueue_fused_scores(FusedArgs &fa, const FusedScratch &f, unsigned char *ws
 int enqueue_encoder_tail(const vscan_encoder_desc *d, const EncoderPlan &p, bool with_local,
                          int score_heads, float norm, const void *x, int32_t *kept_idx,
                          void *merged, int32_t *assign_out, float *scores_out, unsigned char *ws,
-                         hipStream_t s) {
+                         hipStream_t s, size_t off_scores) {
     EncSelectArgs se;
-    se.head_global = reinterpret_cast<const float *>(ws + p.off_head_global);
+    se.head_global = reinterpret_cast<const float *>(ws + off_scores);
     se.head_local = with_local ? reinterpret_cast<const float *>(ws + p.off_head_local) : nullptr;
     se.B = d->batch;
     se.C = d->n_segments;
@@ -500,7 +501,7 @@ static int encoder_reduce_impl(const vscan_encoder_desc *d, const void *q, const
 
     return enqueue_encoder_tail(d, p, with_local, d->heads,
                                 mean ? 1.0f / ((float)d->heads * (float)p.N) : 1.0f / (float)d->heads,
-                                x, kept_idx, merged, assign_out, scores_out, ws, s);
+                                x, kept_idx, merged, assign_out, scores_out, ws, s, p.off_head_global);
 }
 
 int vscan_encoder_reduce(const vscan_encoder_desc *d, const void *q, const void *k,
@@ -593,8 +594,10 @@ static int encoder_reduce_fused_impl(const vscan_encoder_desc *d, const void *hi
         }
         return enqueue_encoder_tail(d, p.e, with_local, d->heads,
                                     1.0f / ((float)d->heads * (float)p.e.N), x, kept_idx, merged,
-                                    assign_out, scores_out, ws, s);
+                                    assign_out, scores_out, ws, s, p.e.off_head_global);
     }
+    // (a second triple overwrites the first one's rows)
+    const bool keep_rows = !with_local && fused_keep_rows(d->heads, p.nk, p.e.N);
     for (int pass = 0; pass < (with_local ? 2 : 1); ++pass) {
         FusedArgs fa;
         fa.is_bf16 = d->dtype == VSCAN_BF16;
@@ -615,12 +618,14 @@ static int encoder_reduce_fused_impl(const vscan_encoder_desc *d, const void *hi
         fa.k0 = p.k0;
         fa.nk = p.nk;
         fa.scale = resolve_scale(d->scale, d->head_dim);
+        fa.keep_rows = keep_rows;
         const int rc2 = enqueue_fused_scores(fa, p.f, ws, s);
         if (rc2 != VSCAN_OK) return rc2;
     }
-    // the chain leaves one row of head sums per segment: [BC, 1, N]
-    return enqueue_encoder_tail(d, p.e, with_local, 1, 1.0f / (float)d->heads, x, kept_idx, merged,
-                                assign_out, scores_out, ws, s);
+    // the chain leaves one row of head sums per segment, [BC, 1, N], or the heads' rows
+    return enqueue_encoder_tail(d, p.e, with_local, keep_rows ? d->heads : 1, 1.0f / (float)d->heads, x,
+                                kept_idx, merged, assign_out, scores_out, ws, s,
+                                keep_rows ? p.f.off_cl : p.e.off_head_global);
 }
 
 int vscan_encoder_reduce_fused(const vscan_encoder_desc *d, const void *hidden, const void *w_q,
@@ -858,6 +863,7 @@ static int run_llm_fused(const vscan_llm_desc *d, const FusedPlan &p, const Ragg
     fa.meta = ragged.meta;
     uint32_t *claim = d->in_place ? nullptr : reinterpret_cast<uint32_t *>(ws + p.off_claim);
     fa.seed = select_seed(d, kept_idx, claim);
+    fa.keep_rows = !fa.causal && fused_keep_rows(p.R, p.nk, d->vis_len);
     const int rc2 = enqueue_fused_scores(fa, p.f, ws, s);
     if (rc2 != VSCAN_OK) return rc2;
 
@@ -882,9 +888,9 @@ static int run_llm_fused(const vscan_llm_desc *d, const FusedPlan &p, const Ragg
     ca.meta = ragged.meta;
 
     LlmSelectArgs se;
-    se.part = fa.part;
+    se.part = fa.keep_rows ? fa.c_l : fa.part;
     se.B = d->batch;
-    se.Hkv = 1;
+    se.Hkv = fa.keep_rows ? p.R : 1;
     se.V = d->vis_len;
     se.keep = d->keep;
     se.norm = 1.0f / (float)p.R;

@@ -26,7 +26,8 @@
 //   2. qt  [Hkv][B*g*Tq, Dh]    P = q planes of the group's heads,         S = W_K^T rows
 //      (stored as bf16 planes straight from the accumulators)
 //   3. l   [B][Hq*Tq, nk]       P = qt planes,                             S = hidden rows
-//   4. softmax of every (sequence, query row), in place; 5. per key the sum over rows.
+//   4. softmax of every (sequence, query row), in place; 5. per key the sum over rows (where the
+//      selection does not add the rows itself: fused_keep_rows).
 // Contractions with few output tiles split the contraction axis over `ksplit` workgroups;
 // partial results are stored side by side and summed, in fixed order, by whichever kernel reads
 // them next.
@@ -407,7 +408,8 @@ template <int THREADS, int NREG>
 __global__ __launch_bounds__(THREADS) void fused_softmax_kernel(float *__restrict__ c, int ksplit,
                                                                 int64_t ks_stride, int nk_cap,
                                                                 float scale, int Tq, int causal,
-                                                                const SeqMeta *meta) {
+                                                                const SeqMeta *meta, SelectSeed seed) {
+    seed_selection(seed, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     __shared__ float red[16];
     const int64_t row = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
     float *l = c + row * nk_cap;
@@ -444,7 +446,8 @@ __global__ __launch_bounds__(THREADS) void fused_softmax_kernel(float *__restric
 __global__ __launch_bounds__(1024) void fused_softmax_long_kernel(float *__restrict__ c, int ksplit,
                                                                   int64_t ks_stride, int nk_cap,
                                                                   float scale, int Tq, int causal,
-                                                                  const SeqMeta *meta) {
+                                                                  const SeqMeta *meta, SelectSeed seed) {
+    seed_selection(seed, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     __shared__ float red[16];
     const int64_t row = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
     float *l = c + row * nk_cap;
@@ -526,6 +529,83 @@ int fused_ksplit(int rows_s, int rows_p, int Z, int k_elems, int elem_bytes) {
     return ks;
 }
 
+// q for few query rows (B * Tq <= 16 R): a workgroup owns 16 output features, its eight waves share
+// the contraction axis (each a contiguous stretch of W_Q's rows, straight into matrix-operand
+// registers), the partial sums meet in LDS and q leaves in its final form.  Bound by reading W_Q once.
+// Splitting the axis over workgroups instead, with a launch that adds the shares, took 10.4 + 5.5 us
+// for 16 rows against 4096 x 4096 bf16 weights, this form 12.6 us (2.7 TB/s); 1024 x 1024: 4.6 + 4.4
+// and 5.4 us.
+constexpr int kThinWaves = 8;
+__host__ __device__ constexpr int thin_share(int nchunks) {  // chunks of a wave, whole 128-byte lines
+    return ((nchunks + kThinWaves - 1) / kThinWaves + 1) & ~1;
+}
+
+// BATCH: 64-byte chunks in flight per row and wave.
+template <typename T, int R, int BATCH>
+__global__ __launch_bounds__(kThinWaves * 64) void fused_q_thin_kernel(ProbQ<T> pr,
+                                                                       uint16_t *__restrict__ q_out) {
+    __shared__ f32x4_t part[R][kThinWaves][kWave];
+    const int N = pr.d.rows_s, M = pr.d.rows_p;
+    const int s0 = blockIdx.x * 16;
+    const int lane = lane_id(), w = wave_id(), r16 = lane & 15, quarter = lane >> 4;
+    const uint32_t s_off = pr.s_off(min(s0 + r16, N - 1));
+    uint32_t p_off[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) p_off[i] = pr.p_off(min(16 * i + r16, M - 1));
+    const int nchunks = (pr.d.k_bytes + 63) / 64;
+    const int share = thin_share(nchunks);
+    const int c_end = min(nchunks, (w + 1) * share);
+    f32x4_t acc[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int c0 = w * share; c0 < c_end; c0 += BATCH) {
+        uint4 a[BATCH][R], b[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {  // clamped, not predicated
+            const int col = min((c0 + u) * 64 + quarter * 16, pr.d.k_bytes - 16);
+            b[u] = load16_stream(pr.w_q, (int64_t)s_off + col);
+#pragma unroll
+            for (int i = 0; i < R; ++i) a[u][i] = load16(pr.hidden, (int64_t)p_off[i] + col);
+        }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            // past the share or the row: zeros on both sides (what was re-read may hold anything)
+            const bool valid = c0 + u < c_end && (c0 + u) * 64 + quarter * 16 < pr.d.k_bytes;
+            if (!valid) b[u] = zero16();
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                mma16_chunk<T>(acc[i], valid ? a[u][i] : zero16(), b[u]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) part[i][w][lane] = acc[i];
+    __syncthreads();
+    if (w >= R) return;  // wave i finishes rows 16 i ..
+    f32x4_t sum = part[w][0][lane];
+#pragma unroll
+    for (int k = 1; k < kThinWaves; ++k) sum += part[w][k][lane];
+    // sum[r] = q[16 w + 4 quarter + r][s0 + r16]
+    if (s0 + r16 >= N) return;
+    const int64_t n = (int64_t)M * N;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = 16 * w + 4 * quarter + r;
+        if (row >= M) break;
+        const int64_t at = (int64_t)row * N + s0 + r16;
+        float v = sum[r];
+        if constexpr (sizeof(T) == 4) {
+            reinterpret_cast<float *>(q_out)[at] = v;
+        } else {
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) {  // as split_planes_kernel
+                const uint32_t bits = f32_to_bf16_rne(v);
+                q_out[pl * n + at] = (uint16_t)bits;
+                v -= __uint_as_float(bits << 16);
+            }
+        }
+    }
+}
+
 template <typename T>
 static hipError_t fused_q_t(const FusedArgs &a, hipStream_t s) {
     ProbQ<T> pr;
@@ -537,6 +617,22 @@ static hipError_t fused_q_t(const FusedArgs &a, hipStream_t s) {
     pr.q_row0 = a.q_row0;
     pr.meta = a.meta;
     pr.row_bytes = a.Dh * (int)sizeof(T);
+    if (fused_q_whole(a.B, a.Tq)) {
+        static_assert(kThinQueries == 32, "two forms of sixteen rows each");
+        const dim3 grid((pr.d.rows_s + 15) / 16), block(kThinWaves * kWave);
+        const int share = thin_share((pr.d.k_bytes + 63) / 64);
+#define VSCAN_THIN(R, BATCH) \
+    hipLaunchKernelGGL((fused_q_thin_kernel<T, R, BATCH>), grid, block, 0, s, pr, a.q_planes)
+        // eight chunks in flight (sixteen measured the same at 4096 features: 12.6 us), four where a
+        // share has no more (1024 features: 5.4 us, 7.2 with eight)
+        if (pr.d.rows_p > 16) {
+            if (share <= 4) VSCAN_THIN(2, 4);
+            else VSCAN_THIN(2, 8);
+        } else if (share <= 4) VSCAN_THIN(1, 4);
+        else VSCAN_THIN(1, 8);
+#undef VSCAN_THIN
+        return hipGetLastError();
+    }
     return launch_gemm(pr, 1, s);
 }
 hipError_t launch_fused_q(const FusedArgs &a, hipStream_t s) {
@@ -621,9 +717,11 @@ hipError_t launch_fused_softmax(const FusedArgs &a, hipStream_t s) {
     const int R = a.Hq * a.Tq;
     const int64_t ks_stride = (int64_t)a.B * R * a.nk;
     const dim3 grid(R, a.B);
+    // the last kernel before the selection launch prepares the words that launch hands over through
+    const SelectSeed seed = a.keep_rows ? a.seed : SelectSeed{};
 #define VSCAN_SOFTMAX(T, N)                                                                      \
     hipLaunchKernelGGL((fused_softmax_kernel<T, N>), grid, dim3(T), 0, s, a.c_l, a.ks_l, ks_stride, \
-                       a.nk, a.scale, a.Tq, a.causal, a.meta)
+                       a.nk, a.scale, a.Tq, a.causal, a.meta, seed)
     if (a.nk <= 256)
         VSCAN_SOFTMAX(256, 1);
     else if (a.nk <= 1024)
@@ -634,7 +732,7 @@ hipError_t launch_fused_softmax(const FusedArgs &a, hipStream_t s) {
         VSCAN_SOFTMAX(1024, 16);
     else
         hipLaunchKernelGGL(fused_softmax_long_kernel, grid, dim3(1024), 0, s, a.c_l, a.ks_l,
-                           ks_stride, a.nk, a.scale, a.Tq, a.causal, a.meta);
+                           ks_stride, a.nk, a.scale, a.Tq, a.causal, a.meta, seed);
 #undef VSCAN_SOFTMAX
     return hipGetLastError();
 }

@@ -29,7 +29,17 @@ struct FusedArgs {
     int ks_q, ks_l;            // shares of the contraction axis (fused_ksplit)
     float scale;
     SelectSeed seed;           // for the selection launch that follows the chain
+    int keep_rows = 0;         // the chain ends with the rows' softmax weights in c_l (fused_keep_rows)
 };
+// Whether q leaves launch_fused_q in its final form (no launch_fused_split_q): few query rows.
+constexpr int kThinQueries = 32;
+inline bool fused_q_whole(int B, int Tq) { return (int64_t)B * Tq <= kThinQueries; }
+// Whether the selection adds the R rows of softmax weights up itself, as it does the heads of the
+// Q/K forms (no launch_fused_colsum): its key domain is the visual tokens, and the one workgroup
+// that selects for a sequence has no more than 128 KiB of them to read.  The launch that added them
+// up took 4.6 us for 16 x 32 rows of 576 keys, the selection takes 3 us longer and a boundary
+// between launches goes; 16 x 16 rows: 3.2 us, and the selection takes no longer.
+inline bool fused_keep_rows(int R, int nk, int V) { return nk == V && (int64_t)R * nk <= 32768; }
 // shares of the contraction axis for a contraction of Z problems of rows_s x rows_p outputs
 int fused_ksplit(int rows_s, int rows_p, int Z, int k_elems, int elem_bytes);
 hipError_t launch_fused_q(const FusedArgs &a, hipStream_t s);
