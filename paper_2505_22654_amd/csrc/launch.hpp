@@ -124,7 +124,7 @@ struct LlmScoreArgs {
     float scale;
     const SeqMeta *meta = nullptr;
     // scratch of the form that cuts long key domains into chunks (llm_score_split_chunks > 0):
-    // e [B*Hkv, rows, V] and per-chunk (maximum, sum) pairs [B*Hkv, chunks, rows, 2]
+    // logits [B*Hkv, rows, V] and per-chunk (maximum, sum) pairs [B*Hkv, chunks, rows, 2]
     float *split_e = nullptr, *split_stats = nullptr;
     SelectSeed seed;
 };

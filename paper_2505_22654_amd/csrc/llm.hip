@@ -362,117 +362,97 @@ static hipError_t llm_score_t(const LlmScoreArgs &a, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // Few (sequence, kv head) items with long key domains: one workgroup per item would leave most
 // of the chip idle (a 4096-token span under 4 kv heads: 4 workgroups on 256 CUs), so the key
-// domain is cut into chunks of 256 keys, one workgroup each.
-//   llm_score_split_kernel    thread = key: logits of all R query rows against it, then per
-//                             chunk and row the maximum m_c[r], the sum l_c[r] of
-//                             e = 2^(z - m_c[r]), and e itself for the visual columns
+// domain is cut into chunks of kSplitChunk keys, one workgroup each.
+//   llm_score_split_kernel    lane = key: logits of all R query rows against it, then per
+//                             chunk and row the maximum m_c[r] and the sum l_c[r] of
+//                             2^(z - m_c[r]), and z itself for the visual columns
 //   llm_score_combine_kernel  M_r = max_c m_c[r], L_r = sum_c l_c[r] 2^(m_c[r] - M_r) in chunk
-//                             order, part[j] = sum_r e[r][j] 2^(m_c(j)[r] - M_r) / L_r in row
-//                             order: fixed orders throughout, no atomics
+//                             order, part[j] = sum_r 2^(z[r][j] - M_r) / L_r in row order:
+//                             fixed orders throughout, no atomics.  (The chunk does not enter
+//                             a key's weight, so equal keys have equal scores wherever they are.)
 // ---------------------------------------------------------------------------
-constexpr int kSplitChunk = 64;   // keys per workgroup: four lanes share a key row
+constexpr int kSplitChunk = 64;   // keys per workgroup: sixteen per wave
 
-template <typename T, int RB>
+// Each wave multiplies its sixteen keys with the item's query rows (up to sixteen) on the matrix
+// cores; both operands come from memory straight into operand registers, everything a wave needs
+// in one round trip (128-element bf16 rows).  Bound by that latency: 4096 keys under 28/4 heads of 128
+// take 5.1 us; multiplied on the vector units, with q in LDS and four lanes to a key, 10.7.
+template <typename T>
 __global__ __launch_bounds__(256) void llm_score_split_kernel(
-    const T *__restrict__ q, const T *__restrict__ k, float *__restrict__ e_out,
-    float *__restrict__ stats, int Hkv, int R, int Tq, int S, int dh, int vis_start, int V, int k0,
-    int nk, float sl2) {
-    constexpr int E = ElemTraits<T>::kPer16B;
-    extern __shared__ __align__(16) unsigned char smem[];
-    float *qs = reinterpret_cast<float *>(smem);   // [R][dh]
-    float *red = qs + RB * dh;                      // [RB][4]: per-wave partial results
+    const T *__restrict__ q, const T *__restrict__ k, float *__restrict__ z_out,
+    float *__restrict__ stats, int R, int Tq, int S, int dh, int vis_start, int V, int k0, int nk,
+    float sl2) {
+    constexpr int BATCH = sizeof(T) == 2 ? 4 : 8;  // 64-byte chunks of a row in flight
+    __shared__ __align__(16) float red_m[16][4], red_l[16][4];   // per query row and wave
     const int item = blockIdx.y, chunk = blockIdx.x, nchunks = gridDim.x;
-    const int tid = threadIdx.x;
-    const T *qrow = q + (int64_t)item * R * dh;     // the item's query rows are contiguous
-    for (int i = tid; i < R * dh; i += 256) qs[i] = load_elem<T>(qrow + i);
-    for (int i = R * dh + tid; i < RB * dh; i += 256) qs[i] = 0.f;
-    __syncthreads();
-
-    // Four adjacent lanes share a key: lane `sub` takes the 16-byte pieces sub, sub + 4, ... of
-    // its row (the four lanes read 64 contiguous bytes per request), so the serial chain of
-    // multiply-adds per lane is a quarter of the row, and the chip sees four times the workgroups.
-    const int sub = tid & 3;
-    const int kk = chunk * kSplitChunk + (tid >> 2);  // key inside the domain
-    const unsigned char *krow = reinterpret_cast<const unsigned char *>(
-        k + ((int64_t)item * S + k0 + min(kk, nk - 1)) * dh);   // clamped: always readable
-    float acc[RB];
+    const int lane = lane_id(), w = wave_id(), r16 = lane & 15, quarter = lane >> 4;
+    const int kk = chunk * kSplitChunk + w * 16 + r16;  // key inside the domain
+    const int row_bytes = dh * (int)sizeof(T);
+    // clamped: always readable.  Rows of q past R repeat the last one and are not reported.
+    const T *krow = k + ((int64_t)item * S + k0 + min(kk, nk - 1)) * dh;
+    const T *qrow = q + ((int64_t)item * R + min(r16, R - 1)) * dh;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    for (int c0 = 0; c0 * 64 < row_bytes; c0 += BATCH) {
+        uint4 a[BATCH], b[BATCH];
 #pragma unroll
-    for (int r = 0; r < RB; ++r) acc[r] = 0.f;
-    const int npieces = dh / E;
-    // eight pieces per lane at a time (a 256-element bf16 row in one round trip)
-    constexpr int PB = 8;
-    for (int p0 = 0; p0 < npieces; p0 += 4 * PB) {
-        uint4 raw[PB];
+        for (int u = 0; u < BATCH; ++u) {
+            const int col = min((c0 + u) * 64 + quarter * 16, row_bytes - 16);
+            a[u] = load16(qrow, col);
+            b[u] = load16_stream(krow, col);
+        }
 #pragma unroll
-        for (int u = 0; u < PB; ++u)
-            raw[u] = load16_stream(krow, (int64_t)min(p0 + 4 * u + sub, npieces - 1) * 16);
-#pragma unroll
-        for (int u = 0; u < PB; ++u) {
-            const int piece = p0 + 4 * u + sub;
-            if (p0 + 4 * u < npieces) {  // uniform; a lane past the end of the row adds zeros
-                float v[E];
-                unpack16<T>(raw[u], v);
-                const bool live = piece < npieces;
-#pragma unroll
-                for (int r = 0; r < RB; ++r) {
-                    const float *qr = qs + r * dh + min(piece, npieces - 1) * E;
-#pragma unroll
-                    for (int e = 0; e < E; ++e) acc[r] = fmaf(live ? v[e] : 0.f, qr[e], acc[r]);
-                }
-            }
+        for (int u = 0; u < BATCH; ++u) {
+            // past the row: zeros on both sides (what was re-read may hold anything)
+            const bool valid = (c0 + u) * 64 + quarter * 16 < row_bytes;
+            mma16_chunk<T>(acc, valid ? a[u] : zero16(), valid ? b[u] : zero16());
         }
     }
+    // acc[r] = logit of query row 4 quarter + r against key kk.  Masked: keys past the domain, and
+    // for a causal row the keys behind its query.
+    float z[4];
 #pragma unroll
-    for (int r = 0; r < RB; ++r) acc[r] = group_sum<4>(acc[r]);  // every lane of a key: its logit
-    // masking: keys past the domain, and for a causal row the keys behind its query
-    float z[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        const int last_pos = S - Tq + (r < R ? r % Tq : 0);
-        z[r] = (r < R && kk < nk && k0 + kk <= last_pos) ? acc[r] * sl2 : -INFINITY;
+    for (int r = 0; r < 4; ++r) {
+        const int row = 4 * quarter + r;
+        const int last_pos = S - Tq + (row < R ? row % Tq : 0);
+        z[r] = kk < nk && k0 + kk <= last_pos ? acc[r] * sl2 : -INFINITY;
     }
     // per row: maximum over the chunk, then e and its sum
-    const int lane = lane_id(), w = wave_id();
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        const float m = wave_max(z[r]);
-        if (lane == 0) red[r * 4 + w] = m;
+    for (int r = 0; r < 4; ++r) {
+        const float m = group_reduce<16>(z[r], [](float x, float y) { return fmaxf(x, y); });
+        if (r16 == 0) red_m[4 * quarter + r][w] = m;
     }
-    __syncthreads();
-    float mrow[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-        mrow[r] = fmaxf(fmaxf(red[r * 4], red[r * 4 + 1]), fmaxf(red[r * 4 + 2], red[r * 4 + 3]));
     __syncthreads();
     const int col = k0 + kk - vis_start;            // visual column of this key
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        const float e = mrow[r] > -INFINITY ? __builtin_amdgcn_exp2f(z[r] - mrow[r]) : 0.f;
-        if (sub == 0 && r < R && kk < nk && col >= 0 && col < V)
-            e_out[((int64_t)item * R + r) * V + col] = e;
-        const float sum = wave_sum(sub == 0 ? e : 0.f);  // one lane per key counts
-        if (lane == 0) red[r * 4 + w] = sum;
+    for (int r = 0; r < 4; ++r) {
+        const int row = 4 * quarter + r;
+        const float4 m4 = *reinterpret_cast<const float4 *>(red_m[row]);
+        const float m = fmaxf(fmaxf(m4.x, m4.y), fmaxf(m4.z, m4.w));
+        const float e = m > -INFINITY ? __builtin_amdgcn_exp2f(z[r] - m) : 0.f;
+        if (row < R && kk < nk && col >= 0 && col < V)
+            z_out[((int64_t)item * R + row) * V + col] = z[r];
+        const float sum = group_sum<16>(e);
+        if (r16 == 0) red_l[row][w] = sum;
     }
     __syncthreads();
-    if (tid < R) {
-        float m = -INFINITY;  // mrow[tid] without indexing registers by a run-time value
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-            if (r == tid) m = mrow[r];
-        float *st = stats + (((int64_t)item * nchunks + chunk) * R + tid) * 2;
-        st[0] = m;
-        st[1] = (red[tid * 4] + red[tid * 4 + 1]) + (red[tid * 4 + 2] + red[tid * 4 + 3]);
+    if ((int)threadIdx.x < R) {
+        const float4 m = *reinterpret_cast<const float4 *>(red_m[threadIdx.x]);
+        const float4 l = *reinterpret_cast<const float4 *>(red_l[threadIdx.x]);
+        float *st = stats + (((int64_t)item * nchunks + chunk) * R + threadIdx.x) * 2;
+        st[0] = fmaxf(fmaxf(m.x, m.y), fmaxf(m.z, m.w));
+        st[1] = (l.x + l.y) + (l.z + l.w);
     }
 }
 
-__global__ __launch_bounds__(256) void llm_score_combine_kernel(const float *__restrict__ e_in,
+__global__ __launch_bounds__(256) void llm_score_combine_kernel(const float *__restrict__ z_in,
                                                                const float *__restrict__ stats,
                                                                float *__restrict__ part, int R,
-                                                               int V, int vis_start, int k0,
-                                                               int nchunks, SelectSeed seed) {
+                                                               int V, int nchunks,
+                                                               SelectSeed seed) {
     seed_selection(seed, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
-    extern __shared__ float wgt[];                  // [nchunks][R], then M[R], invL[R], then the pairs
-    float *M = wgt + nchunks * R, *invL = M + R, *st = invL + R;
+    extern __shared__ float M[];                    // [R], then invL[R], then the pairs
+    float *invL = M + R, *st = invL + R;
     const int item = blockIdx.y, tid = threadIdx.x;
     // all (maximum, sum) pairs of the item into LDS at once: the row loops below would
     // otherwise be chains of dependent global loads
@@ -496,17 +476,11 @@ __global__ __launch_bounds__(256) void llm_score_combine_kernel(const float *__r
         }
     }
     __syncthreads();
-    for (int i = tid; i < nchunks * R; i += 256) {
-        const int r = i % R;
-        const float mc = st[i * 2];
-        wgt[i] = mc > -INFINITY ? __builtin_amdgcn_exp2f(mc - M[r]) * invL[r] : 0.f;
-    }
-    __syncthreads();
     const int col = blockIdx.x * 256 + tid;
     if (col >= V) return;
-    const int c = (vis_start + col - k0) / kSplitChunk;
     float sum = 0.f;
-    for (int r = 0; r < R; ++r) sum += e_in[((int64_t)item * R + r) * V + col] * wgt[c * R + r];
+    for (int r = 0; r < R; ++r)
+        sum += __builtin_amdgcn_exp2f(z_in[((int64_t)item * R + r) * V + col] - M[r]) * invL[r];
     part[(int64_t)item * V + col] = sum;
 }
 
@@ -522,23 +496,15 @@ static hipError_t llm_score_split_t(const LlmScoreArgs &a, hipStream_t s, int nc
     const int k0 = a.domain_all ? 0 : a.vis_start, nk = a.domain_all ? a.S : a.V;
     const float sl2 = a.scale * 1.4426950408889634f;
     dim3 grid(nchunks, items);
-    if (R <= 8) {
-        const size_t smem = (size_t)(8 * a.dh + 8 * 4) * sizeof(float);
-        hipLaunchKernelGGL((llm_score_split_kernel<T, 8>), grid, dim3(256), smem, s, (const T *)a.q,
-                           (const T *)a.k, a.split_e, a.split_stats, a.Hkv, R, a.Tq, a.S, a.dh,
-                           a.vis_start, a.V, k0, nk, sl2);
-    } else {
-        const size_t smem = (size_t)(16 * a.dh + 16 * 4) * sizeof(float);
-        hipLaunchKernelGGL((llm_score_split_kernel<T, 16>), grid, dim3(256), smem, s, (const T *)a.q,
-                           (const T *)a.k, a.split_e, a.split_stats, a.Hkv, R, a.Tq, a.S, a.dh,
-                           a.vis_start, a.V, k0, nk, sl2);
-    }
+    hipLaunchKernelGGL(llm_score_split_kernel<T>, grid, dim3(256), 0, s, (const T *)a.q,
+                       (const T *)a.k, a.split_e, a.split_stats, R, a.Tq, a.S, a.dh, a.vis_start, a.V,
+                       k0, nk, sl2);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const size_t smem2 = (size_t)(3 * nchunks * R + 2 * R) * sizeof(float);
+    const size_t smem2 = (size_t)(2 * nchunks * R + 2 * R) * sizeof(float);
     hipLaunchKernelGGL(llm_score_combine_kernel, dim3((a.V + 255) / 256, items), dim3(256), smem2, s,
                        (const float *)a.split_e, (const float *)a.split_stats, a.part, R, a.V,
-                       a.vis_start, k0, nchunks, a.seed);
+                       nchunks, a.seed);
     return hipGetLastError();
 }
 
