@@ -560,9 +560,7 @@ __device__ __forceinline__ void wait_for_loads(const uint4 *regs, int n) {
 // end.  Per tile: every thread's loads have returned (wait_for_loads), barrier,
 // then the stores.  Tiles are written in ascending order while the next tile's
 // loads are already in flight, which is safe because a tile's stores end below
-// every later tile's sources (source row >= destination row, both ascending).  Bound by memory:
-// 1.26 GB (32 sequences of 2880 visual tokens, 288 kept) in 251 us = 5.0 TB/s, with plain stores
-// 256 us; a copy of a gigabyte runs at 5.1 TB/s.
+// every later tile's sources (source row >= destination row, both ascending).
 __global__ __launch_bounds__(256) void compact_inplace_kernel(CompactArgs a) {
     __shared__ int red[4];
     const Strip s = decode_strip(a, blockIdx.x);
@@ -604,7 +602,7 @@ __global__ __launch_bounds__(256) void compact_inplace_kernel(CompactArgs a) {
         for (int i = 0; i < kCompactRpt; ++i) {
             const int p = p0 + tile * kCompactTile + i * 16 + rloc;
             if (col_ok && p < S_out)
-                store16_stream(s.dst + (int64_t)p * s.dst_stride + piece * 16, v[i]);
+                *reinterpret_cast<uint4 *>(s.dst + (int64_t)p * s.dst_stride + piece * 16) = v[i];
         }
     };
     const int ntiles = (S_out - p0 + kCompactTile - 1) / kCompactTile;
