@@ -6,9 +6,9 @@
 //     q . k = 2^-(eq + ek) (lo_q . hi_k + hi_q . lo_k + hi_q . hi_k) ,
 // three fp16 contractions with fp32 accumulation.  hi + lo holds 22 to 23 bits of every value down
 // to 2^-18 of the block's maximum (below that, 2^-40 of the maximum), the dropped lo_q . lo_k is
-// below 2^-22 of a product, and five accumulation steps of sixteen products replace forty steps of
-// two: against 64 bits, logits of 80 N(0, 1) products are off by 0.9e-7 of their root mean square,
-// those of the fp32 instructions by 1.6e-7.
+// below 2^-22 of a product.  Scores against 64 bits (1600 and 2688 tokens): largest relative error
+// 5.6e-7 to 9.5e-7 (fp32 instructions 7.5e-7 to 1.4e-6), 2-norm 3.6e-7 to 6.5e-7 (1.2e-7 to 1.9e-7): the
+// single errors are smaller but lean to one side.
 //
 // Measured, lse + column sums, fp32 instructions -> this form: 2688 tokens, 16 heads of 80:
 // 266 + 266 us -> 76 + 71 us and 10 us for the planes; 6400 tokens: 1236 + 1237 -> 336 + 316 us
@@ -200,9 +200,14 @@ __global__ __launch_bounds__(256, 2) void mean_planes_kernel(
     };
     const f32x16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                            0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    // product i of chunk c: streamed plane (lo, hi, hi) with resident plane (hi, lo, hi)
+    // The small products of all chunks go first, while the accumulator is small.
+    // Product i of chunk c: lo_k hi_q, hi_k lo_q, hi_k hi_q.  Both passes add in this order, whichever
+    // side streams: a logit has the same bits in both, so its rounding leaves the large weights
+    // (2^(s - lse) with lse close to s) alone.
+    constexpr int kLo = PASS == 1 ? 0 : 1;  // the product that takes the streamed lo plane
     auto multiply = [&](f32x16_t(&to)[HALVES], int c, int i, int h) {
-        to[h] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fr[i == 0 ? 1 : 0][c], kf[h][i == 1 ? 1 : 0][c],
+        to[h] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fr[i == kLo ? 1 : 0][c],
+                                                       kf[h][i == 1 - kLo ? 1 : 0][c],
                                                        c == 0 && i == 0 ? zero : to[h], 0, 0, 0);
     };
 
@@ -270,10 +275,11 @@ __global__ __launch_bounds__(256, 2) void mean_planes_kernel(
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
             if constexpr (MULT) {
-                const int c = m / (3 * HALVES), i = m / HALVES % 3, h = m % HALVES;
+                const int n = m / HALVES, h = m % HALVES;
+                const int i = n < 2 * NC ? n & 1 : 2, c = n < 2 * NC ? n >> 1 : n - 2 * NC;
                 multiply(nxt, c, i, h);
                 if constexpr (REFILL) {
-                    if (h == HALVES - 1 && i == 0) fr[1][c] = read_frag(t + 2, 1, c);
+                    if (h == HALVES - 1 && i == kLo) fr[1][c] = read_frag(t + 2, 1, c);
                     if (h == HALVES - 1 && i == 2) fr[0][c] = read_frag(t + 2, 0, c);
                 }
             }
@@ -321,11 +327,10 @@ __global__ __launch_bounds__(256, 2) void mean_planes_kernel(
         fr[1][c] = read_frag(0, 1, c);
     }
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
+    for (int n = 0; n < 3 * NC; ++n)
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int h = 0; h < HALVES; ++h) multiply(acc[0], c, i, h);
+        for (int h = 0; h < HALVES; ++h)
+            multiply(acc[0], n < 2 * NC ? n >> 1 : n - 2 * NC, n < 2 * NC ? n & 1 : 2, h);
     if (ntiles > 1) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
