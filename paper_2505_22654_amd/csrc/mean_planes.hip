@@ -6,9 +6,10 @@
 //     q . k = 2^-(eq + ek) (lo_q . hi_k + hi_q . lo_k + hi_q . hi_k) ,
 // three fp16 contractions with fp32 accumulation.  hi + lo holds 22 to 23 bits of every value down
 // to 2^-18 of the block's maximum (below that, 2^-40 of the maximum), the dropped lo_q . lo_k is
-// below 2^-22 of a product.  Scores against 64 bits (1600 and 2688 tokens): largest relative error
-// 5.6e-7 to 9.5e-7 (fp32 instructions 7.5e-7 to 1.4e-6), 2-norm 3.6e-7 to 6.5e-7 (1.2e-7 to 1.9e-7): the
-// single errors are smaller but lean to one side.
+// below 2^-22 of a product.  Relative error of the scores against 64 bits, this form and the fp32
+// instructions (2688 tokens, 16 heads of 80): mean 3.1e-7 and -6.6e-7, deviation 1.5e-7 and 2.4e-7,
+// largest 0.9e-6 and 1.3e-6.  (In the 2-norm, which the few large scores decide and where the lean of
+// the fp32 form on the small ones does not count: 6e-7 and 1.2e-7 to 1.9e-7.)
 //
 // Measured, lse + column sums, fp32 instructions -> this form: 2688 tokens, 16 heads of 80:
 // 266 + 266 us -> 76 + 71 us and 10 us for the planes; 6400 tokens: 1236 + 1237 -> 336 + 316 us
