@@ -91,10 +91,8 @@ typedef struct {
     float scale;            /* logit scale; <= 0 selects 1/sqrt(head_dim) */
 } vscan_encoder_desc;
 
-/* Bytes of workspace for vscan_encoder_reduce with this descriptor.
- * `with_local_pair` != 0 sizes for a call that passes q_local / k_local.
- * (fp32 mean mode: the figure includes room for fp16 plane pairs of q and k, 8 * S * head_dim bytes
- * per segment and head.  A call is also served without that part, several times slower.) */
+/* Bytes of workspace vscan_encoder_reduce needs for this descriptor.
+ * `with_local_pair` != 0 sizes for a call that passes q_local / k_local. */
 int vscan_encoder_workspace_size(const vscan_encoder_desc *desc, int with_local_pair,
                                  size_t *bytes);
 

@@ -11,7 +11,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libvscan.so")
 
-SOURCES = ["api.cpp", "budget.cpp", "encoder_score.hip", "mean_planes.hip", "select.hip", "sim_merge.hip", "llm.hip", "fused.hip",
+SOURCES = ["api.cpp", "budget.cpp", "encoder_score.hip", "select.hip", "sim_merge.hip", "llm.hip", "fused.hip",
            "static_entry.hip", "ragged_entry.hip"]
 HEADERS = ["common.hpp", "launch.hpp", "compact.hpp", "fused.hpp", "mean.hpp", os.path.join("..", "..", "include", "vscan.h")]
 

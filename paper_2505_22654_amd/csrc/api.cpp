@@ -29,9 +29,6 @@ inline int elem_bytes(int dtype) { return dtype == VSCAN_BF16 ? 2 : 4; }
 struct EncoderPlan {
     int N, S, BC, T, W, kw, kg, Kseg, K, U;
     size_t off_head_global, off_head_local, off_lse, off_drop, off_best, off_inv_norm, off_pre_key, off_pre_flag, bytes;
-    // fp32 mean mode: fp16 plane pairs of q and k and their exponents behind the rest.  A call whose
-    // workspace ends at `bytes` is served without them, by the slower fp32 instructions.
-    size_t off_planes, plane_stride, bytes_planes;
 };
 
 int plan_encoder(const vscan_encoder_desc *d, int with_local, EncoderPlan *p) {
@@ -98,13 +95,6 @@ int plan_encoder(const vscan_encoder_desc *d, int with_local, EncoderPlan *p) {
     p->off_pre_flag = off;
     off += align_up((size_t)p->BC * p->N);
     p->bytes = off ? off : kAlign;
-    p->off_planes = p->bytes_planes = p->bytes;
-    p->plane_stride = 0;
-    if (d->score_mode == VSCAN_SCORE_MEAN_RECEIVED && es == 4) {
-        p->plane_stride = align_up((size_t)p->BC * d->heads * p->S * d->head_dim * sizeof(float));
-        p->bytes_planes = p->off_planes + 2 * p->plane_stride +
-                          align_up(mean_planes_exponents(p->BC, d->heads, p->N, d->has_cls) * sizeof(int32_t));
-    }
     return VSCAN_OK;
 }
 
@@ -422,7 +412,7 @@ int vscan_encoder_workspace_size(const vscan_encoder_desc *desc, int with_local_
     EncoderPlan p;
     const int rc = plan_encoder(desc, with_local_pair != 0, &p);
     if (rc != VSCAN_OK) return rc;
-    *bytes = p.bytes_planes;
+    *bytes = p.bytes;
     return VSCAN_OK;
 }
 
@@ -464,11 +454,6 @@ static int encoder_reduce_impl(const vscan_encoder_desc *d, const void *q, const
     sa.domain_all = d->softmax_domain == VSCAN_KEYS_ALL;
     sa.is_bf16 = d->dtype == VSCAN_BF16;
     sa.scale = resolve_scale(d->scale, d->head_dim);
-    if (mean && !sa.is_bf16 && workspace_bytes >= p.bytes_planes) {
-        sa.q_planes = ws + p.off_planes;
-        sa.k_planes = ws + p.off_planes + p.plane_stride;
-        sa.plane_exps = reinterpret_cast<int32_t *>(ws + p.off_planes + 2 * p.plane_stride);
-    }
     if (mean && with_local && mean_pair_launch(sa.is_bf16, sa.dh)) {
         // Pass 1 of both pairs in one launch.  The second pair's log-sum-exps wait where the first
         // pair's scores go afterwards, so its second pass runs first.
@@ -562,15 +547,6 @@ static int encoder_reduce_fused_impl(const vscan_encoder_desc *d, const void *hi
         sa.domain_all = d->softmax_domain == VSCAN_KEYS_ALL;
         sa.is_bf16 = 0;
         sa.scale = resolve_scale(d->scale, d->head_dim);
-        // Q and K become fp16 plane pairs where they lie.  The planes' exponents go to scratch that
-        // only the selection and what follows it use; with very many heads on few tokens they do
-        // not fit there, and the fp32 instructions do the work.
-        if (mean_planes_exponents(p.e.BC, d->heads, p.e.N, d->has_cls) * sizeof(int32_t) <=
-            p.e.bytes - p.e.off_drop) {
-            sa.q_planes = ws + p.off_qf;
-            sa.k_planes = ws + p.off_kf;
-            sa.plane_exps = reinterpret_cast<int32_t *>(ws + p.e.off_drop);
-        }
         for (int pass = 0; pass < (with_local ? 2 : 1); ++pass) {
             ProjectArgs pa;
             pa.is_bf16 = d->dtype == VSCAN_BF16;

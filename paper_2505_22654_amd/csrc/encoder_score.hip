@@ -899,11 +899,9 @@ static hipError_t launch_score_mean_t(const ScoreArgs &a, hipStream_t s, int pas
 }
 
 hipError_t launch_score_mean_lse(const ScoreArgs &a, hipStream_t s) {
-    if (a.q_planes) return launch_mean_planes(a, s, 1);
     return a.is_bf16 ? launch_score_mean_t<bf16_t>(a, s, 1) : launch_score_mean_t<float>(a, s, 1);
 }
 hipError_t launch_score_mean_colsum(const ScoreArgs &a, hipStream_t s) {
-    if (a.q_planes) return launch_mean_planes(a, s, 2);
     return a.is_bf16 ? launch_score_mean_t<bf16_t>(a, s, 2) : launch_score_mean_t<float>(a, s, 2);
 }
 

@@ -37,21 +37,12 @@ struct ScoreArgs {
     int BC, H, S, dh, N;
     int has_cls, domain_all, is_bf16;
     float scale;
-    // fp32 mean mode, or NULL: room for q and k as two fp16 planes each, dh * 4 bytes a row like
-    // the fp32 rows (q and k themselves, where they may be overwritten), and for the planes'
-    // exponents (mean_planes_exponents ints)
-    void *q_planes = nullptr, *k_planes = nullptr;
-    int32_t *plane_exps = nullptr;
     // a second pair for pass 1 to take along (mean_pair_launch), or NULL
     const void *q2 = nullptr, *k2 = nullptr;
     float *lse2 = nullptr;
 };
 // whether pass 1 of mean attention takes two pairs in one launch: the pipelined bf16 form
 inline bool mean_pair_launch(int is_bf16, int dh) { return is_bf16 && dh <= 80; }
-constexpr int kPlaneBlock = 128;  // rows that share a power-of-two scale
-inline size_t mean_planes_exponents(int BC, int H, int N, int has_cls) {
-    return (size_t)2 * BC * H * ((N + has_cls + kPlaneBlock - 1) / kPlaneBlock);
-}
 hipError_t launch_score_cls(const ScoreArgs &a, hipStream_t s);
 hipError_t launch_score_mean_lse(const ScoreArgs &a, hipStream_t s);     // pass 1
 hipError_t launch_score_mean_colsum(const ScoreArgs &a, hipStream_t s);  // pass 2

@@ -1,4 +1,4 @@
-// Shared by the mean-attention kernels (encoder_score.hip, mean_planes.hip).
+// Shared by the mean-attention kernels (encoder_score.hip).
 #pragma once
 #include "common.hpp"
 #include "launch.hpp"
@@ -33,9 +33,5 @@ __device__ __forceinline__ void direct_load16(const void *src, unsigned lds_addr
 // every outstanding vector-memory load of this wave has arrived (vmcnt 0, the other counters
 // left alone)
 __device__ __forceinline__ void wait_direct_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-
-// fp32 queries and keys carried as pairs of fp16 planes (mean_planes.hip); pass 1 also makes the
-// planes.
-hipError_t launch_mean_planes(const ScoreArgs &a, hipStream_t s, int pass);
 
 }  // namespace vscan
