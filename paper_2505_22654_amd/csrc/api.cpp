@@ -623,13 +623,11 @@ int vscan_llm_workspace_size(const vscan_llm_desc *desc, size_t *bytes) {
 }
 
 // Initial state of the words an out-of-place selection launch hands over through.
-static SelectSeed select_seed(const vscan_llm_desc *d, int32_t *kept_idx, uint32_t *claim) {
+static SelectSeed select_seed(const vscan_llm_desc *d, int32_t *kept_idx) {
     SelectSeed seed;
-    if (!claim) return seed;
+    if (d->in_place) return seed;
     seed.kept = kept_idx;
     seed.n_kept = (int64_t)d->batch * d->keep;
-    seed.claim = claim;
-    seed.n_claim = d->batch;
     return seed;
 }
 
@@ -677,8 +675,7 @@ static int run_llm(const vscan_llm_desc *d, const LlmPlan &p, const RaggedCall &
     sa.meta = ragged.meta;
     sa.split_e = reinterpret_cast<float *>(ws + p.off_split_e);
     sa.split_stats = reinterpret_cast<float *>(ws + p.off_split_stats);
-    uint32_t *claim = d->in_place ? nullptr : reinterpret_cast<uint32_t *>(ws + p.off_claim);
-    sa.seed = select_seed(d, kept_idx, claim);
+    sa.seed = select_seed(d, kept_idx);
     VSCAN_LAUNCH("llm_score", launch_llm_score(sa, s));
 
     CompactArgs ca;
@@ -720,7 +717,6 @@ static int run_llm(const vscan_llm_desc *d, const LlmPlan &p, const RaggedCall &
     se.zero_tail = ragged.zero_tail;
     if (!d->in_place) {
         se.copy = &ca;
-        se.claim = claim;
         VSCAN_LAUNCH("select_compact", launch_llm_select(se, s));
         return VSCAN_OK;
     }
@@ -837,8 +833,7 @@ static int run_llm_fused(const vscan_llm_desc *d, const FusedPlan &p, const Ragg
     fa.nk = p.nk;
     fa.scale = resolve_scale(d->scale, d->head_dim);
     fa.meta = ragged.meta;
-    uint32_t *claim = d->in_place ? nullptr : reinterpret_cast<uint32_t *>(ws + p.off_claim);
-    fa.seed = select_seed(d, kept_idx, claim);
+    fa.seed = select_seed(d, kept_idx);
     fa.keep_rows = !fa.causal && fused_keep_rows(p.R, p.nk, d->vis_len);
     const int rc2 = enqueue_fused_scores(fa, p.f, ws, s);
     if (rc2 != VSCAN_OK) return rc2;
@@ -876,7 +871,6 @@ static int run_llm_fused(const vscan_llm_desc *d, const FusedPlan &p, const Ragg
     se.zero_tail = ragged.zero_tail;
     if (!d->in_place) {
         se.copy = &ca;
-        se.claim = claim;
         VSCAN_LAUNCH("select_compact", launch_llm_select(se, s));
         return VSCAN_OK;
     }

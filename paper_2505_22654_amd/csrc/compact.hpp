@@ -89,10 +89,10 @@ __device__ __forceinline__ const int32_t *sequence_view(CompactArgs &a, int b) {
 //               be there: a thread re-reads its entries until none is kNotYetKept
 // Kept indices are written and polled with device-scope accesses, which pass the L2s of the eight
 // XCDs; an index is its own flag, so no ordering between memory operations is relied upon.
-// No workgroup waits for one that has not started: the workgroup that selects for a sequence
-// is whoever claims it first (`claim`, one atomic exchange), normally the one launched for it; a
-// gathering workgroup that finds its sequence unclaimed makes the selection itself.  A selection
-// waits for nobody and writes all of its sequence's indices, whatever the scores are.
+// A gathering workgroup waits a bounded time; then it makes its sequence's selection itself.  A
+// selection waits for nobody, writes all of its sequence's indices whatever the scores are, and
+// writes the same ones whoever makes it, so every workgroup ends, in whatever order they start and
+// whatever else writes to the kept indices meanwhile.
 // Measured (kernel durations): 16 sequences of 192 visual tokens, hidden 4096: 5.7 + 28.8 us for
 // selection and compaction as two launches, 27.2 us as one (154 MB: 5.7 TB/s); 12 ragged
 // sequences of up to 1500 tokens: 10.6 + 25.6 us and 30 us of fills -> 39 us with the zero rows.
@@ -107,27 +107,7 @@ __device__ __forceinline__ void device_store(int32_t *p, int32_t v) {
 __device__ __forceinline__ void seed_selection(const SelectSeed &s, int wg, int nwg) {
     const int64_t first = (int64_t)wg * blockDim.x + threadIdx.x, step = (int64_t)nwg * blockDim.x;
     for (int64_t i = first; i < s.n_kept; i += step) s.kept[i] = kNotYetKept;
-    for (int64_t i = first; i < s.n_claim; i += step) s.claim[i] = 0u;
 }
-// whether this workgroup selects for sequence b; one that is here to gather (`patient`) leaves the
-// workgroup launched for it a few microseconds to start
-__device__ __forceinline__ bool claim_selection(uint32_t *claim, int b, bool patient, int *lds) {
-    if (threadIdx.x == 0) {
-        auto taken = [&]() {
-            return __hip_atomic_load(claim + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
-        };
-        bool gone = false;
-        for (int i = 0; patient && i < 8 && !gone; ++i) {
-            gone = taken();
-            if (!gone) __builtin_amdgcn_s_sleep(8);
-        }
-        *lds = !gone &&
-               __hip_atomic_exchange(claim + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
-    }
-    __syncthreads();
-    return *lds != 0;
-}
-
 constexpr int kCopyPieces = 4;  // 16-byte pieces per thread of a static unit
 
 struct CopyUnits {
@@ -194,54 +174,86 @@ __device__ __forceinline__ void copy_static_rows(CompactArgs a, const CopyUnits 
     }
 }
 
-// sequence of a kept unit
-__device__ __forceinline__ int kept_unit_sequence(const CompactArgs &a, const CopyUnits &u, int id) {
-    return decode_strip(a, id % u.strips).b;
+// A kept unit: positions first .. last of the kept rows of one strip.
+struct KeptUnit {
+    Strip s;
+    const int32_t *kept_b;
+    int first, last, vis_start, V;
+};
+// false: the sequence keeps no row of that tile
+__device__ __forceinline__ bool kept_unit(CompactArgs a, const CopyUnits &u, int id, KeptUnit *k) {
+    k->s = decode_strip(a, id % u.strips);
+    k->kept_b = sequence_view(a, k->s.b);
+    k->first = id / u.strips * kCompactTile;
+    k->last = min(k->first + kCompactTile, a.keep) - 1;
+    k->vis_start = a.vis_start;
+    k->V = a.V;
+    return k->first < a.keep;
 }
 
+// sixteen threads span a strip; a thread's rows of the unit
 template <int NT>
-__device__ __forceinline__ void copy_kept_rows(CompactArgs a, const CopyUnits &u, int id) {
-    constexpr int RPT = kCompactTile * 16 / NT;  // rows per thread
+struct KeptRows {
+    static constexpr int RPT = kCompactTile * 16 / NT;
     static_assert(RPT >= 1 && NT * RPT == kCompactTile * 16, "sixteen threads span a strip");
-    const Strip s = decode_strip(a, id % u.strips);
-    const int tile = id / u.strips;
-    const int32_t *kept_b = sequence_view(a, s.b);
-    const int piece = threadIdx.x & 15, row0 = tile * kCompactTile + (threadIdx.x >> 4);
-    if (tile * kCompactTile >= a.keep) return;
+    int kv[RPT];
+    // true: all of them are there
+    __device__ __forceinline__ bool load(const KeptUnit &u) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i)  // clamped positions: the loads are in flight together
+            kv[i] = device_load(u.kept_b + min(u.first + (int)(threadIdx.x >> 4) + i * (NT / 16), u.last));
+        bool there = true;
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) there &= kv[i] != kNotYetKept;
+        return there;
+    }
+};
+
+// Waits for the unit's indices, `polls` looks at the last one at most: whether they are there (for
+// every thread of the workgroup alike).  `lds`: two free words, free again after a barrier.
+template <int NT>
+__device__ __forceinline__ bool wait_kept_rows(const KeptUnit &u, KeptRows<NT> &rows, int polls, int *lds) {
     // one thread waits for the tile's last index first: a thousand workgroups that poll with
     // every thread are traffic the selection has to get through
     if (threadIdx.x == 0) {
-        const int32_t *last = kept_b + min((tile + 1) * kCompactTile, a.keep) - 1;
-        while (device_load(last) == kNotYetKept) __builtin_amdgcn_s_sleep(16);
+        int left = polls;
+        while (left > 0 && device_load(u.kept_b + u.last) == kNotYetKept) {
+            __builtin_amdgcn_s_sleep(16);
+            --left;
+        }
+        lds[0] = left;
+        lds[1] = 0;
     }
     __syncthreads();
-    if (piece * 16 >= s.width) return;
-    int kv[RPT];
-#pragma unroll
-    for (int i = 0; i < RPT; ++i)  // clamped positions: the loads are in flight together
-        kv[i] = device_load(kept_b + min(row0 + i * (NT / 16), a.keep - 1));
-    for (;;) {
-        bool wait = false;
-#pragma unroll
-        for (int i = 0; i < RPT; ++i) wait |= kv[i] == kNotYetKept;
-        if (!wait) break;
+    const int left = lds[0];
+    if (left <= 0) return false;
+    bool there = rows.load(u);
+    for (int i = 0; i < left && !there; ++i) {  // the tile's other indices may be under way still
         __builtin_amdgcn_s_sleep(8);
-#pragma unroll
-        for (int i = 0; i < RPT; ++i)
-            kv[i] = device_load(kept_b + min(row0 + i * (NT / 16), a.keep - 1));
+        there = rows.load(u);
     }
+    if (!there) lds[1] = 1;
+    __syncthreads();
+    return lds[1] == 0;
+}
+
+template <int NT>
+__device__ __forceinline__ void copy_kept_rows(const KeptUnit &u, const KeptRows<NT> &rows) {
+    constexpr int RPT = KeptRows<NT>::RPT;
+    const int piece = threadIdx.x & 15, row0 = u.first + (threadIdx.x >> 4);
+    if (piece * 16 >= u.s.width) return;
     uint4 v[RPT];
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
         // clamped: the index comes from device memory
-        const int src = a.vis_start + min(max(kv[i], 0), a.V - 1);
-        v[i] = load16(s.src, (int64_t)src * s.src_stride + piece * 16);
+        const int src = u.vis_start + min(max(rows.kv[i], 0), u.V - 1);
+        v[i] = load16(u.s.src, (int64_t)src * u.s.src_stride + piece * 16);
     }
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
         const int r = row0 + i * (NT / 16);
-        if (r < a.keep)
-            store16_stream(s.dst + (int64_t)(a.vis_start + r) * s.dst_stride + piece * 16, v[i]);
+        if (r <= u.last)
+            store16_stream(u.s.dst + (int64_t)(u.vis_start + r) * u.s.dst_stride + piece * 16, v[i]);
     }
 }
 

@@ -96,14 +96,16 @@ struct SeqMeta {
 // would make the host wait (ragged_entry.hip).
 using TableUpload = hipError_t (*)(SeqMeta *table, const SeqMeta *from_host, int batch, hipStream_t s);
 
-// Words the selection launch of an out-of-place call hands over through, put into their initial
-// state by the scoring kernel before it: kept indices to kNotYetKept, claims to 0.
+// The kept indices are what the selection launch of an out-of-place call hands over through: the
+// scoring kernel before it sets them to kNotYetKept.
 constexpr int32_t kNotYetKept = -2;
 struct SelectSeed {
     int32_t *kept = nullptr;   // [n_kept]
-    uint32_t *claim = nullptr; // [n_claim]
-    int64_t n_kept = 0, n_claim = 0;
+    int64_t n_kept = 0;
 };
+// Looks (about a microsecond apart) that a gathering workgroup of that launch takes at an index
+// before it makes the selection itself: well above the longest selection.
+constexpr int kSelectPolls = 1024;
 
 // stage 2 scoring (Eq. 5)
 struct LlmScoreArgs {
@@ -135,7 +137,7 @@ struct LlmSelectArgs {
     int zero_tail = 0;         // ragged: scores past a sequence's own span are set to zero
     // out-of-place compaction (host pointer, NULL in place): done by this launch too
     const CompactArgs *copy = nullptr;
-    uint32_t *claim = nullptr;  // with `copy`: [B] words, 0 before the launch (SelectSeed)
+    int polls = kSelectPolls;  // with `copy`; 0: every gathering workgroup selects
 };
 hipError_t launch_llm_select(const LlmSelectArgs &a, hipStream_t s);
 size_t llm_select_lds_bytes(int V);

@@ -635,22 +635,33 @@ template <bool GLOBAL_WAVE, int NREG, int NT>
 __global__ __launch_bounds__(NT) void llm_select_kernel(LlmSelectArgs a, CompactArgs copy,
                                                         CopyUnits units) {
     extern __shared__ __align__(16) unsigned char smem[];
-    int b = blockIdx.x, unit = -1;  // kept unit of this workgroup
-    if (b >= a.B) {
-        const int id = b - a.B;
-        if (id < units.n_static) {
-            copy_static_rows(copy, units, id);
+    const int id = (int)blockIdx.x - a.B;
+    if (id >= 0 && id < units.n_static) {
+        copy_static_rows(copy, units, id);
+        return;
+    }
+    int b = blockIdx.x;
+    if (id >= 0) {  // here to gather
+        KeptUnit u;
+        KeptRows<NT> rows;
+        if (!kept_unit(copy, units, id - units.n_static, &u)) return;
+        if (wait_kept_rows<NT>(u, rows, a.polls, reinterpret_cast<int *>(smem))) {
+            copy_kept_rows<NT>(u, rows);
             return;
         }
-        unit = id - units.n_static;
-        b = kept_unit_sequence(copy, units, unit);
+        b = u.s.b;
+        __syncthreads();  // the wait's LDS words are free
     }
-    // (in place there is nobody to race with)
-    if (!a.claim || claim_selection(a.claim, b, unit >= 0, reinterpret_cast<int *>(smem))) {
-        __syncthreads();  // the claim's LDS word is free
-        select_sequence<GLOBAL_WAVE, NREG, NT>(a, b, smem);
+    select_sequence<GLOBAL_WAVE, NREG, NT>(a, b, smem);
+    if (id >= 0) {
+        __threadfence();  // this workgroup's own stores, before other threads of it read them
+        __syncthreads();
+        KeptUnit u;
+        KeptRows<NT> rows;
+        kept_unit(copy, units, id - units.n_static, &u);
+        rows.load(u);
+        copy_kept_rows<NT>(u, rows);
     }
-    if (unit >= 0) copy_kept_rows<NT>(copy, units, unit);
 }
 
 // ---------------------------------------------------------------------------

@@ -1,0 +1,61 @@
+"""The wait of the out-of-place stage-2 launch is bounded: a gathering workgroup that does not find
+its indices makes the selection itself, with the same result."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    from paper_2505_22654_amd import binding as vb
+    vb.lib()
+    path = str(tmp_path_factory.mktemp("shim") / "libselect_shim.so")
+    pkg = os.path.dirname(vb.LIB_PATH)
+    subprocess.check_call(["g++", "-O1", "-fPIC", "-shared", "-std=c++17", "-D__HIP_PLATFORM_AMD__",
+                           "-I/opt/rocm/include", "-Wno-unused-result",
+                           os.path.join(ROOT, "tests", "select_shim.cpp"), "-o", path, vb.LIB_PATH,
+                           f"-Wl,-rpath,{pkg}"])
+    return ctypes.CDLL(path)
+
+
+# one span per instantiation of the launch (spans up to 256, 512, 1024, 2048, 4096, 16384, above),
+# kept rows of one and of several tiles
+@pytest.mark.parametrize("V,keep,B", [(33, 11, 3), (300, 129, 2), (1000, 400, 2), (1500, 600, 1),
+                                      (4000, 513, 1), (9000, 1000, 1), (20000, 700, 1)])
+def test_gathering_workgroups_that_select_themselves(shim, V, keep, B):
+    import torch
+    Hkv, dh, Dh, vis_start, text = 2, 24, 136, 3, 5
+    S = vis_start + V + text
+    So = S - V + keep
+    g = torch.Generator(device="cuda").manual_seed(V)
+    part = torch.randint(0, 4 * V, (B, Hkv, V), generator=g, device="cuda").float()
+    src = [torch.randint(0, 9999, shape, generator=g, device="cuda", dtype=torch.int16)
+           for shape in ((B, Hkv, S, dh), (B, Hkv, S, dh), (B, S, Dh))]
+    dims = (ctypes.c_int * 9)(B, Hkv, S, dh, Dh, vis_start, V, keep, 2)
+    # ties to the lowest index: a stable descending sort of whole numbers
+    want = part.sum(1).sort(dim=1, descending=True, stable=True).indices[:, :keep].sort(dim=1).values
+    rows = torch.cat([torch.arange(vis_start, device="cuda").expand(B, -1), vis_start + want,
+                      torch.arange(vis_start + V, S, device="cuda").expand(B, -1)], dim=1)
+    for polls in (0, -1):  # nobody waits; the usual wait
+        kept = torch.full((B, keep), -2, dtype=torch.int32, device="cuda")
+        scores = torch.full((B, V), -1.0, device="cuda")
+        dst = [torch.zeros((B, Hkv, So, dh), dtype=torch.int16, device="cuda"),
+               torch.zeros((B, Hkv, So, dh), dtype=torch.int16, device="cuda"),
+               torch.zeros((B, So, Dh), dtype=torch.int16, device="cuda")]
+        p = lambda ts: (ctypes.c_void_p * 3)(*[t.data_ptr() for t in ts])
+        rc = shim.vscan_test_select_compact(dims, polls, ctypes.c_void_p(part.data_ptr()), None,
+                                            ctypes.c_void_p(kept.data_ptr()),
+                                            ctypes.c_void_p(scores.data_ptr()), p(src), p(dst), None)
+        torch.cuda.synchronize()
+        assert rc == 0
+        assert torch.equal(kept.long(), want) and torch.equal(scores, part.sum(1))
+        for a, b in zip(src, dst):
+            a = a if a.dim() == 4 else a[:, None]
+            b = b if b.dim() == 4 else b[:, None]
+            for i in range(B):
+                assert torch.equal(b[i], a[i][:, rows[i]])
