@@ -100,7 +100,7 @@ int plan_encoder(const vscan_encoder_desc *d, int with_local, EncoderPlan *p) {
 
 struct LlmPlan {
     int rows, k0, nk, S_out;
-    size_t off_part, off_split_e, off_split_stats, off_claim, bytes;
+    size_t off_part, off_split_e, off_split_stats, bytes;
 };
 
 int plan_llm(const vscan_llm_desc *d, LlmPlan *p) {
@@ -135,8 +135,6 @@ int plan_llm(const vscan_llm_desc *d, LlmPlan *p) {
     if (chunks > 0) off += align_up((size_t)d->batch * d->kv_heads * p->rows * d->vis_len * sizeof(float));
     p->off_split_stats = off;
     if (chunks > 0) off += align_up((size_t)d->batch * d->kv_heads * chunks * p->rows * 2 * sizeof(float));
-    p->off_claim = off;
-    if (!d->in_place) off += align_up((size_t)d->batch * sizeof(uint32_t));
     p->bytes = off ? off : kAlign;
     return VSCAN_OK;
 }
@@ -179,7 +177,7 @@ int plan_fused_scratch(int64_t seqs, int S, int hidden, int q_heads, int kv_head
 struct FusedPlan {
     int k0, nk, S_out, R;
     FusedScratch f;
-    size_t off_part, off_claim, bytes;
+    size_t off_part, bytes;
 };
 
 int plan_fused(const vscan_llm_desc *d, FusedPlan *p) {
@@ -206,8 +204,7 @@ int plan_fused(const vscan_llm_desc *d, FusedPlan *p) {
                                       d->head_dim, d->n_query, p->nk, elem_bytes(d->dtype), 0, &p->f);
     if (rc != VSCAN_OK) return rc;
     p->off_part = p->f.end;
-    p->off_claim = p->off_part + align_up((size_t)d->batch * d->vis_len * sizeof(float));
-    p->bytes = p->off_claim + (d->in_place ? 0 : align_up((size_t)d->batch * sizeof(uint32_t)));
+    p->bytes = p->off_part + align_up((size_t)d->batch * d->vis_len * sizeof(float));
     return VSCAN_OK;
 }
 
