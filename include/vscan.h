@@ -173,7 +173,7 @@ int vscan_llm_prune(const vscan_llm_desc *desc, const void *q, void *k, void *v,
  *     symbol query, no allocation); make that call outside graph capture.
  *   - All calls on one GPU share the one array, which keeps the last call's
  *     contents: calls must be ordered (one stream, or events between streams);
- *     calls that overlap on one GPU race.
+ *     calls that overlap on one GPU race (they end, with unspecified results).
  * ------------------------------------------------------------------------- */
 #define VSCAN_STATIC_SCRATCH_BYTES (16u << 20)
 int vscan_llm_prune_static(const vscan_llm_desc *desc, const void *q, void *k, void *v,
@@ -220,6 +220,8 @@ int vscan_profile_read(vscan_kernel_time *out, int capacity, int *count);
  * meta_host and meta_device hold the same `batch` entries, on the host (read and
  * validated by the call) and on the device (read by the kernels, so it must stay
  * valid and unchanged until the enqueued work has run).
+ * Of a device entry, vis_len is held inside desc->vis_len and keep inside desc->keep
+ * and vis_len; lengths and starts that differ from the host's reach outside the tensors.
  * Sequence b: scores_out[b, 0 .. vis_len_b), kept_idx[b, 0 .. keep_b) ascending and
  * -1 in the entries after them; its result occupies rows [0, seq_len_b - vis_len_b
  * + keep_b) of the destinations, later rows are left as they were.

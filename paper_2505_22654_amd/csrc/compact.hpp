@@ -61,16 +61,30 @@ inline int compact_strips(const CompactArgs &a) {
 }
 constexpr int kCompactTile = 128;  // rows of a strip that are moved together
 
+// Visual and kept tokens of a sequence of a ragged batch.  The table is device memory, and what the
+// host validated is its copy: the counts stay inside the capacities, and no more is kept than there
+// is, so that the selection writes every index that a copy waits for.
+struct SpanCounts {
+    int V, keep;
+};
+__device__ __forceinline__ SpanCounts span_counts(const SeqMeta &m, int V_cap, int keep_cap) {
+    SpanCounts c;
+    c.V = min(max(m.vis_len, 1), V_cap);
+    c.keep = min(max(m.keep, 0), min(c.V, keep_cap));
+    return c;
+}
+
 // Ragged batch: replace the lengths in the (by-value) argument block by those of sequence b.
 // Returns the kept-index row of the sequence.
 __device__ __forceinline__ const int32_t *sequence_view(CompactArgs &a, int b) {
     const int32_t *kept_b = a.kept_idx + (int64_t)b * a.keep;  // a.keep is still the stride here
     if (a.meta) {
         const SeqMeta m = a.meta[b];
+        const SpanCounts c = span_counts(m, a.V, a.keep);  // (both are still the capacities)
         a.S = m.seq_len;
         a.vis_start = m.vis_start;
-        a.V = m.vis_len;
-        a.keep = m.keep;
+        a.V = c.V;
+        a.keep = c.keep;
     }
     return kept_b;
 }

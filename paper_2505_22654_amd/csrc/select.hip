@@ -571,8 +571,8 @@ __device__ __forceinline__ void select_sequence(const LlmSelectArgs &a, int b, u
     constexpr int nt = NT;
     const int tid = threadIdx.x;
     // ragged batch: this sequence's own span and budget; a.V and a.keep stay the strides
-    const int V = a.meta ? a.meta[b].vis_len : a.V;
-    const int keep = a.meta ? a.meta[b].keep : a.keep;
+    const SpanCounts own = a.meta ? span_counts(a.meta[b], a.V, a.keep) : SpanCounts{a.V, a.keep};
+    const int V = own.V, keep = own.keep;
     {
         // the head values of all of a thread's tokens are requested together, a few heads at a
         // time (clamped positions), and added in head order as head_sum does

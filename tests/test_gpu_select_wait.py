@@ -59,3 +59,36 @@ def test_gathering_workgroups_that_select_themselves(shim, V, keep, B):
             b = b if b.dim() == 4 else b[:, None]
             for i in range(B):
                 assert torch.equal(b[i], a[i][:, rows[i]])
+
+
+def test_a_device_table_that_keeps_more_than_there_is_ends():
+    """The host table is what gets validated; a device table whose `keep` exceeds its `vis_len` counts
+    as keeping the whole span."""
+    import torch
+    from paper_2505_22654_amd import binding as vb
+    from paper_2505_22654_amd import workloads as wl
+    B, S = 3, 90
+    caps = wl.LlmShape(dtype=wl.BF16, batch=B, prefix=0, vis_len=60, text=30, n_query=1, q_heads=4,
+                       kv_heads=2, head_dim=32, hidden=72, keep=40)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
+    q, k, v, h = r(B, 4, 1, 32), r(B, 2, S, 32), r(B, 2, S, 32), r(B, S, 72)
+    good = [(90, 5, 50, 20), (70, 3, 7, 7), (80, 0, 60, 40)]
+    bad = [(90, 5, 50, 20), (70, 3, 7, 39), (80, 0, 60, 60)]  # 39 of 7 tokens; above the capacity
+    want = vb.llm_prune_ragged(caps, good, q, k, v, h, want_scores=True)
+    desc = vb.llm_desc(caps)
+    host = (ctypes.c_int32 * (4 * B))(*[x for m in good for x in m])
+    table = torch.tensor(bad, dtype=torch.int32, device="cuda")
+    ws = torch.empty(vb.llm_workspace_size(desc), dtype=torch.uint8, device="cuda")
+    kept = torch.empty_like(want["kept_idx"])
+    ko, vo, ho = (torch.full_like(t, 7.0) for t in (k, v, h))
+    sc = torch.full((B, 60), 7.0, device="cuda")
+    p = lambda t: t.data_ptr()
+    rc = vb.lib().vscan_llm_prune_ragged(ctypes.byref(desc), ctypes.addressof(host), p(table), p(q), p(k),
+                                         p(v), p(h), p(kept), p(ko), p(vo), p(ho), p(sc), p(ws),
+                                         ws.numel(), None)
+    torch.cuda.synchronize()
+    assert rc == 0 and torch.equal(kept, want["kept_idx"])
+    for b, (n, _, V, kp) in enumerate(good):
+        for a, c in ((ko, want["k"]), (vo, want["v"]), (ho, want["hidden"])):
+            assert torch.equal(a[b, ..., :n - V + kp, :], c[b, ..., :n - V + kp, :])
