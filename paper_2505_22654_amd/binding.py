@@ -6,6 +6,7 @@ There is no fallback: if the library is missing the first call raises.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 from typing import Dict, Optional
@@ -200,7 +201,11 @@ def _ragged_setup(desc, meta, batch: int, from_hidden: bool, device):
     """The host table of a ragged call and a workspace whose first bytes become the device table."""
     import torch
     assert len(meta) == batch
-    host = (ctypes.c_int32 * (4 * max(batch, 1)))(*[int(x) for m in meta for x in m])
+    if any(len(m) != 4 for m in meta):
+        raise ValueError("a ragged entry is (seq_len, vis_start, vis_len, keep)")
+    # (a value outside 32 bits raises OverflowError here; ctypes would cut it down)
+    flat = array.array("i", [int(x) for m in meta for x in m] or [0] * 4)
+    host = (ctypes.c_int32 * len(flat)).from_buffer(flat)
     n = ctypes.c_size_t(0)
     rc = lib().vscan_llm_ragged_workspace_size(ctypes.byref(desc), int(from_hidden), ctypes.byref(n))
     if rc != VSCAN_OK:

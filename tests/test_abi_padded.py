@@ -36,3 +36,19 @@ def test_padded_ragged_calls_validate_before_they_enqueue(rows, kw, status, from
         rc = vb.lib().vscan_llm_prune_ragged_padded(*args, FAKE, FAKE, FAKE, hidden, FAKE, FAKE, FAKE,
                                                     FAKE, FAKE, ws, nbytes, None)
     assert rc == status
+
+
+@pytest.mark.parametrize("rows,error", [
+    ([(139, 35, 64, 32), (139 + 2 ** 32, 35, 64, 32)], OverflowError),
+    ([(139, 35, 64, 32), (139, 35, 64)], ValueError),
+    ([(139, 35, 64, 32, 139), (35, 64, 32)], ValueError),
+])
+def test_binding_refuses_tables_that_are_no_rows_of_four_32_bit_numbers(rows, error):
+    shape = wl.LlmShape(dtype=wl.BF16, batch=2, prefix=35, vis_len=64, text=40, n_query=1, q_heads=8,
+                        kv_heads=8, head_dim=64, hidden=512, keep=32)
+    desc = vb.llm_desc(shape)
+    with pytest.raises(error):
+        vb._ragged_setup(desc, rows, 2, False, "cpu")
+    host, _, table = vb._ragged_setup(desc, rows[:1] * 2 if error is OverflowError else [(1, 2, 3, 4)] * 2,
+                                      2, False, "cpu")
+    assert len(host) == 8 and host[4] == host[0] and tuple(table.shape) == (2, 4)
