@@ -562,13 +562,14 @@ __global__ __launch_bounds__(1024) void encoder_select_local_kernel(EncSelectArg
     flag_out[(int64_t)bc * N + j] = cnt < a.kw ? 1 : 0;
 }
 
-// Stage-2 selection of sequence b by one workgroup.
-template <bool GLOBAL_WAVE, int NREG, int NT>
+// Stage-2 selection of sequence b by one workgroup of NT threads, or (NT = 0) of a thread per token.
+// HANDOVER: workgroups of other XCDs wait for the indices.
+template <bool GLOBAL_WAVE, int NREG, int NT, bool HANDOVER>
 __device__ __forceinline__ void select_sequence(const LlmSelectArgs &a, int b, unsigned char *smem) {
     SelectSmem &sm = *reinterpret_cast<SelectSmem *>(smem);
     uint32_t *key = reinterpret_cast<uint32_t *>(smem + sizeof(SelectSmem));
     uint8_t *flag = reinterpret_cast<uint8_t *>(key + a.V);
-    constexpr int nt = NT;
+    const int nt = NT ? NT : (int)blockDim.x;
     const int tid = threadIdx.x;
     // ragged batch: this sequence's own span and budget; a.V and a.keep stay the strides
     const SpanCounts own = a.meta ? span_counts(a.meta[b], a.V, a.keep) : SpanCounts{a.V, a.keep};
@@ -576,8 +577,9 @@ __device__ __forceinline__ void select_sequence(const LlmSelectArgs &a, int b, u
     {
         // the head values of all of a thread's tokens are requested together, a few heads at a
         // time (clamped positions), and added in head order as head_sum does
-        constexpr int TPT = GLOBAL_WAVE ? NREG * kWave / NT : NREG;
-        static_assert(TPT >= 1 && (!GLOBAL_WAVE || TPT * NT == NREG * kWave), "a token has one thread");
+        constexpr int TPT = NT == 0 ? 1 : GLOBAL_WAVE ? NREG * kWave / (NT ? NT : 1) : NREG;
+        static_assert(NT == 0 || !GLOBAL_WAVE || (TPT >= 1 && TPT * NT == NREG * kWave),
+                      "a token has one thread");
         constexpr int HB = TPT <= 2 ? 16 : TPT <= 4 ? 8 : TPT <= 8 ? 4 : TPT <= 16 ? 2 : 1;
         float acc[TPT];
 #pragma unroll
@@ -589,7 +591,7 @@ __device__ __forceinline__ void select_sequence(const LlmSelectArgs &a, int b, u
             for (int r = 0; r < TPT; ++r)
 #pragma unroll
                 for (int u = 0; u < HB; ++u)
-                    v[r][u] = pb[(int64_t)min(h0 + u, a.Hkv - 1) * a.V + min(r * NT + tid, V - 1)];
+                    v[r][u] = pb[(int64_t)min(h0 + u, a.Hkv - 1) * a.V + min(r * nt + tid, V - 1)];
 #pragma unroll
             for (int r = 0; r < TPT; ++r)
 #pragma unroll
@@ -597,7 +599,7 @@ __device__ __forceinline__ void select_sequence(const LlmSelectArgs &a, int b, u
         }
 #pragma unroll
         for (int r = 0; r < TPT; ++r) {
-            const int j = r * NT + tid;
+            const int j = r * nt + tid;
             if (j < V) {
                 const float s = acc[r] * a.norm;
                 key[j] = max(float_to_key(s), 1u);  // every token is a candidate, a NaN score's too
@@ -625,15 +627,23 @@ __device__ __forceinline__ void select_sequence(const LlmSelectArgs &a, int b, u
     __syncthreads();
     // (the counts of the walk in LDS of their own: a short span has fewer keys than waves)
     ranked_walk(flag, V, sm.wsum, [&](int j, bool kept, int s) {
-        // (device scope: in an out-of-place call workgroups of other XCDs wait for it)
-        if (kept) device_store(a.kept_idx + (int64_t)b * a.keep + s, j);
+        int32_t *at = a.kept_idx + (int64_t)b * a.keep + s;
+        if (kept && HANDOVER) device_store(at, j);
+        if (kept && !HANDOVER) *at = j;
     });
 }
 
-// Selection, and out of place the copies around it (compact.hpp).
+// In place: selection alone.
 template <bool GLOBAL_WAVE, int NREG, int NT>
-__global__ __launch_bounds__(NT) void llm_select_kernel(LlmSelectArgs a, CompactArgs copy,
-                                                        CopyUnits units) {
+__global__ __launch_bounds__(NT ? NT : 1024) void llm_select_kernel(LlmSelectArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    select_sequence<GLOBAL_WAVE, NREG, NT, false>(a, blockIdx.x, smem);
+}
+
+// Out of place: selection and the copies around it (compact.hpp).
+template <bool GLOBAL_WAVE, int NREG, int NT>
+__global__ __launch_bounds__(NT) void select_compact_kernel(LlmSelectArgs a, CompactArgs copy,
+                                                            CopyUnits units) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int id = (int)blockIdx.x - a.B;
     if (id >= 0 && id < units.n_static) {
@@ -652,7 +662,7 @@ __global__ __launch_bounds__(NT) void llm_select_kernel(LlmSelectArgs a, Compact
         b = u.s.b;
         __syncthreads();  // the wait's LDS words are free
     }
-    select_sequence<GLOBAL_WAVE, NREG, NT>(a, b, smem);
+    select_sequence<GLOBAL_WAVE, NREG, NT, true>(a, b, smem);
     if (id >= 0) {
         __threadfence();  // this workgroup's own stores, before other threads of it read them
         __syncthreads();
@@ -766,21 +776,44 @@ hipError_t launch_encoder_select(const EncSelectArgs &a, hipStream_t s) {
 #undef VSCAN_SEL_WM
 }
 
+// The global search of a span of up to 1024 tokens is one wave's; the head sums before it and the walk
+// behind it are all the workgroup's.  In place a thread per token serves best (one sequence, 32 kv
+// heads: 192 tokens 15.0 us a call and 576 tokens 22.4, with 256 threads 15.4 and 24.5).
+static hipError_t launch_select_in_place(const LlmSelectArgs &a, size_t smem, hipStream_t s) {
+    const int threads = a.V <= 1024 ? (a.V + kWave - 1) / kWave * kWave : a.V <= 4096 ? 512 : 1024;
+#define VSCAN_LLM_SEL(...) \
+    return launch_select<llm_select_kernel<__VA_ARGS__>>(a.B, threads, smem, s, a)
+    if (a.V <= 64) VSCAN_LLM_SEL(true, 1, 0);
+    if (a.V <= 128) VSCAN_LLM_SEL(true, 2, 0);
+    if (a.V <= 256) VSCAN_LLM_SEL(true, 4, 0);
+    if (a.V <= 512) VSCAN_LLM_SEL(true, 8, 0);
+    if (a.V <= 1024) VSCAN_LLM_SEL(true, 16, 0);
+    if (a.V <= 2048) VSCAN_LLM_SEL(false, 4, 512);
+    if (a.V <= 4096) VSCAN_LLM_SEL(false, 8, 512);
+    if (a.V <= 16384) VSCAN_LLM_SEL(false, 16, 1024);
+    VSCAN_LLM_SEL(false, 32, 1024);
+#undef VSCAN_LLM_SEL
+}
+
 hipError_t launch_llm_select(const LlmSelectArgs &a, hipStream_t s) {
     const size_t smem = llm_select_lds_bytes(a.V);
-    const int threads = a.V <= 1024 ? 256 : a.V <= 4096 ? 512 : 1024;
-    CompactArgs copy{};
-    CopyUnits units{};
-    if (a.copy) {
-        copy = *a.copy;
-        units = copy_units(copy, threads);
-    }
+    if (!a.copy) return launch_select_in_place(a, smem, s);
+    const CompactArgs &copy = *a.copy;
+    // 513 to 1024 tokens: 512 threads shorten the selection (576 tokens, 32 kv heads: 1 sequence 21.4
+    // -> 20.4 us a call, 16 sequences 58.5 -> 56.8), but copies of more than the last-level cache run
+    // faster in workgroups of 256 (343 MB 81.6 and 82.2 us, 457 MB 112.9 and 115.8; 332 MB 82.8 and
+    // 80.9).  Up to 512 tokens the two are alike (14.9 and 14.5 us, 59.2 and 60.2).
+    const int64_t row = (int64_t)(2 * copy.Hkv * copy.dh + copy.Dh) * copy.elem_bytes;
+    const bool long_copy = 2 * (int64_t)(copy.max_static_rows + a.keep) * a.B * row > (int64_t)320 << 20;
+    const int threads = a.V <= 512 || (a.V <= 1024 && long_copy) ? 256 : a.V <= 4096 ? 512 : 1024;
+    const CopyUnits units = copy_units(copy, threads);
     const int blocks = a.B + units.n_static + units.n_kept;
 #define VSCAN_LLM_SEL(...) \
-    return launch_select<llm_select_kernel<__VA_ARGS__>>(blocks, threads, smem, s, a, copy, units)
+    return launch_select<select_compact_kernel<__VA_ARGS__>>(blocks, threads, smem, s, a, copy, units)
     if (a.V <= 256) VSCAN_LLM_SEL(true, 4, 256);
     if (a.V <= 512) VSCAN_LLM_SEL(true, 8, 256);
-    if (a.V <= 1024) VSCAN_LLM_SEL(true, 16, 256);
+    if (a.V <= 1024 && long_copy) VSCAN_LLM_SEL(true, 16, 256);
+    if (a.V <= 1024) VSCAN_LLM_SEL(true, 16, 512);
     if (a.V <= 2048) VSCAN_LLM_SEL(false, 4, 512);
     if (a.V <= 4096) VSCAN_LLM_SEL(false, 8, 512);
     if (a.V <= 16384) VSCAN_LLM_SEL(false, 16, 1024);
