@@ -15,6 +15,8 @@
 // per lane with vector compares and summed with DPP row operations, the
 // threshold is built two bits per step from three independent candidate counts,
 // and the walk stops as soon as some candidate is reached by exactly k keys.
+#include <algorithm>
+
 #include "common.hpp"
 #include "compact.hpp"
 #include "launch.hpp"
@@ -645,12 +647,14 @@ template <bool GLOBAL_WAVE, int NREG, int NT>
 __global__ __launch_bounds__(NT) void select_compact_kernel(LlmSelectArgs a, CompactArgs copy,
                                                             CopyUnits units) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int id = (int)blockIdx.x - a.B;
+    const int wg = blockIdx.y * gridDim.x + blockIdx.x;
+    const int id = wg - a.B;
+    if (id >= units.n_static + units.n_kept) return;
     if (id >= 0 && id < units.n_static) {
         copy_static_rows(copy, units, id);
         return;
     }
-    int b = blockIdx.x;
+    int b = wg;
     if (id >= 0) {  // here to gather
         KeptUnit u;
         KeptRows<NT> rows;
@@ -685,14 +689,14 @@ size_t encoder_select_lds_bytes(int N, int has_local) {
 size_t llm_select_lds_bytes(int V) { return sizeof(SelectSmem) + (size_t)V * 4 + round16((size_t)V); }
 
 template <auto kernel, typename... Args>
-static hipError_t launch_select(int blocks, int threads, size_t smem, hipStream_t s,
+static hipError_t launch_select(dim3 blocks, int threads, size_t smem, hipStream_t s,
                                 const Args &...args) {
     static std::atomic<uint64_t> lds_allowed{0};  // one per kernel instantiation
     if (smem > 64 * 1024) {
         hipError_t e = allow_large_lds(kernel, lds_allowed);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), smem, s, args...);
+    hipLaunchKernelGGL(kernel, blocks, dim3(threads), smem, s, args...);
     return hipGetLastError();
 }
 
@@ -807,7 +811,10 @@ hipError_t launch_llm_select(const LlmSelectArgs &a, hipStream_t s) {
     const bool long_copy = 2 * (int64_t)(copy.max_static_rows + a.keep) * a.B * row > (int64_t)320 << 20;
     const int threads = a.V <= 512 || (a.V <= 1024 && long_copy) ? 256 : a.V <= 4096 ? 512 : 1024;
     const CopyUnits units = copy_units(copy, threads);
-    const int blocks = a.B + units.n_static + units.n_kept;
+    // (a grid dimension holds fewer than 2^32 threads: many narrow slabs take a second one)
+    const int64_t total = (int64_t)a.B + units.n_static + units.n_kept;
+    constexpr int64_t kPerRow = 1 << 21;
+    const dim3 blocks((unsigned)std::min(total, kPerRow), (unsigned)((total + kPerRow - 1) / kPerRow));
 #define VSCAN_LLM_SEL(...) \
     return launch_select<select_compact_kernel<__VA_ARGS__>>(blocks, threads, smem, s, a, copy, units)
     if (a.V <= 256) VSCAN_LLM_SEL(true, 4, 256);

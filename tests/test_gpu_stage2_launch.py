@@ -76,3 +76,24 @@ def test_padded_ragged_call_equals_the_one_with_a_device_table(batch):
         for a, c in ((ko, pad["k"]), (vo, pad["v"]), (ho, pad["hidden"])):
             assert torch.equal(a[b, ..., :n, :], c[b, ..., :n, :])
             assert (a[b, ..., n:, :] == 7).all() and not c[b, ..., n:, :].any()
+
+
+def test_more_workgroups_than_one_grid_dimension_holds():
+    """4.48 million slabs of three 16-byte rows: four workgroups to a slab, and a grid dimension ends
+    below 2^32 threads."""
+    import torch
+    shape = _llm(batch=140000, prefix=0, vis_len=2, text=1, q_heads=32, kv_heads=32, head_dim=8,
+                 hidden=8, keep=1)
+    assert shape.batch * shape.kv_heads * 4 * 256 > 2 ** 32
+    g = torch.Generator(device="cuda").manual_seed(3)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
+    B = shape.batch
+    q, k, v, h = r(B, 32, 1, 8), r(B, 32, 3, 8), r(B, 32, 3, 8), r(B, 3, 8)
+    out = vb.llm_prune(shape, q, k, v, h, want_scores=True)
+    torch.cuda.synchronize()
+    kept = out["kept_idx"].long()
+    assert torch.equal(kept[:, 0], (out["scores"][:, 1] > out["scores"][:, 0]).long())
+    rows = torch.cat([kept, torch.full_like(kept, 2)], dim=1)
+    for got, src in ((out["k"], k), (out["v"], v), (out["hidden"][:, None], h[:, None])):
+        want = torch.gather(src, 2, rows[:, None, :, None].expand(-1, src.shape[1], -1, 8))
+        assert torch.equal(got, want)
