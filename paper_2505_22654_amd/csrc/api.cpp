@@ -316,7 +316,7 @@ int enqueue_fused_scores(FusedArgs &fa, const FusedScratch &f, unsigned char *ws
     fa.ks_q = f.ks_q;
     fa.ks_l = f.ks_l;
     VSCAN_LAUNCH("fused_q", launch_fused_q(fa, s));
-    if (!fused_q_whole(fa.B, fa.Tq)) VSCAN_LAUNCH("fused_split_q", launch_fused_split_q(fa, s));
+    if (!fused_q_whole(fa)) VSCAN_LAUNCH("fused_split_q", launch_fused_split_q(fa, s));
     VSCAN_LAUNCH("fused_qt", launch_fused_qt(fa, s));
     VSCAN_LAUNCH("fused_logits", launch_fused_logits(fa, s));
     VSCAN_LAUNCH("fused_softmax", launch_fused_softmax(fa, s));

@@ -529,7 +529,7 @@ int fused_ksplit(int rows_s, int rows_p, int Z, int k_elems, int elem_bytes) {
     return ks;
 }
 
-// q for few query rows (B * Tq <= 16 R): a workgroup owns 16 output features, its eight waves share
+// q for few query rows (fused_q_whole; B * Tq <= 16 R): a workgroup owns 16 output features, its eight waves share
 // the contraction axis (each a contiguous stretch of W_Q's rows, straight into matrix-operand
 // registers), the partial sums meet in LDS and q leaves in its final form.  Bound by reading W_Q once.
 // Splitting the axis over workgroups instead, with a launch that adds the shares, took 10.4 + 5.5 us
@@ -617,7 +617,7 @@ static hipError_t fused_q_t(const FusedArgs &a, hipStream_t s) {
     pr.q_row0 = a.q_row0;
     pr.meta = a.meta;
     pr.row_bytes = a.Dh * (int)sizeof(T);
-    if (fused_q_whole(a.B, a.Tq)) {
+    if (fused_q_whole(a)) {
         static_assert(kThinQueries == 32, "two forms of sixteen rows each");
         const dim3 grid((pr.d.rows_s + 15) / 16), block(kThinWaves * kWave);
         const int share = thin_share((pr.d.k_bytes + 63) / 64);

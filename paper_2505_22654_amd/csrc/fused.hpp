@@ -31,9 +31,23 @@ struct FusedArgs {
     SelectSeed seed;           // for the selection launch that follows the chain
     int keep_rows = 0;         // the chain ends with the rows' softmax weights in c_l (fused_keep_rows)
 };
-// Whether q leaves launch_fused_q in its final form (no launch_fused_split_q): few query rows.
-constexpr int kThinQueries = 32;
-inline bool fused_q_whole(int B, int Tq) { return (int64_t)B * Tq <= kThinQueries; }
+// Whether q leaves launch_fused_q in its final form (no launch_fused_split_q): few query rows, no more
+// than one workgroup of sixteen output features for each CU, and weight rows of which a wave's eighth is
+// one batch of loads (17 to 32 query rows, which take twice the registers) or two.  Stage-2 calls with q
+// in one launch and with the axis split over workgroups, us (features out x in, query rows):
+//   4096 x 4096 bf16  1: 33.6, 40.5;  8: 42.1, 45.3;  16: 49.0, 51.2;  24: 88.7, 88.6;  32: 112.2, 110.5
+//   2048 x 2048 bf16  1: 29.1, 32.8;  16: 39.4, 43.7;  17: 51.9, 54.4;  32: 54.7, 56.6
+//   2560 x 2560 bf16  8: 40.0, 41.3;  16: 48.2, 47.3;  17: 61.1, 58.6;  32: 65.3, 61.2
+//   5120 x 5120 bf16  1: 53.4, 45.9;  8: 65.6, 54.6;  16: 80.4, 63.0   (rows of 10 KiB)
+//   8192 x 2048 bf16  1: 35.8, 38.9;  8: 44.3, 43.4;  16: 49.9, 49.3   (two workgroups on a CU)
+//   1024 x 1024 fp32  1: 29.1, 33.3;  16: 38.9, 43.1;  17: 50.4, 53.1;  32: 52.2, 54.7
+//   2048 x 2048 fp32  1: 36.4, 38.6;  16: 49.7, 52.1;  24: 72.9, 72.5;  32: 76.5, 75.2
+constexpr int kThinQueries = 32, kThinOutputs = 4096, kThinRowBytes = 8192;
+inline bool fused_q_whole(const FusedArgs &a) {
+    const int64_t rows = (int64_t)a.B * a.Tq, row_bytes = (int64_t)a.Dh * (a.is_bf16 ? 2 : 4);
+    return rows <= kThinQueries && a.Hq * a.dh <= kThinOutputs &&
+           row_bytes <= (rows <= kThinQueries / 2 ? kThinRowBytes : kThinRowBytes / 2);
+}
 // Whether the selection adds the R rows of softmax weights up itself, as it does the heads of the
 // Q/K forms (no launch_fused_colsum): its key domain is the visual tokens, and the one workgroup
 // that selects for a sequence has no more than 128 KiB of them to read.  The launch that added them
