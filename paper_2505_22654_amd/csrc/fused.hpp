@@ -49,11 +49,18 @@ inline bool fused_q_whole(const FusedArgs &a) {
            row_bytes <= (rows <= kThinQueries / 2 ? kThinRowBytes : kThinRowBytes / 2);
 }
 // Whether the selection adds the R rows of softmax weights up itself, as it does the heads of the
-// Q/K forms (no launch_fused_colsum): its key domain is the visual tokens, and the one workgroup
-// that selects for a sequence has no more than 128 KiB of them to read.  The launch that added them
-// up took 4.6 us for 16 x 32 rows of 576 keys, the selection takes 3 us longer and a boundary
-// between launches goes; 16 x 16 rows: 3.2 us, and the selection takes no longer.
-inline bool fused_keep_rows(int R, int nk, int V) { return nk == V && (int64_t)R * nk <= 32768; }
+// Q/K forms (no launch_fused_colsum): its key domain is the visual tokens, and the one workgroup that
+// selects for a sequence has no more than 64 rows and 128 KiB of them to read.  A launch goes (3 to 5 us);
+// the selection takes longer, and beside it in an out-of-place call the copies slow its reads down.
+// Stage-2 calls with the rows added by the selection and by a launch of their own, us (bf16):
+//   16 rows, hidden 1024  1 x 576 tokens: 26.0, 28.4;  16 x 576: 33.6, 36.2;  32 x 1000: 44.1, 46.7
+//   28 rows, hidden 3584  1 x 576: 36.8, 39.4;  16 x 576: 70.7, 73.0;  32 x 1000: 137.2, 137.5
+//   32 rows, hidden 4096  1 x 576: 43.7, 44.9;  16 x 576: 65.6, 66.1;  24 x 576: 87.1, 86.5
+//   64 rows, hidden 4096  1 x 500: 46.9, 47.2;  8 x 500: 60.1, 60.0
+//   128 rows, hidden 4096  1 x 250: 54.8, 54.1;  8 x 250: 72.2, 71.0;  256 rows  4 x 125: 80.4, 76.9
+inline bool fused_keep_rows(int R, int nk, int V) {
+    return nk == V && R <= 64 && (int64_t)R * nk <= 32768;
+}
 // shares of the contraction axis for a contraction of Z problems of rows_s x rows_p outputs
 int fused_ksplit(int rows_s, int rows_p, int Z, int k_elems, int elem_bytes);
 hipError_t launch_fused_q(const FusedArgs &a, hipStream_t s);

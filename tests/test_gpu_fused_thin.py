@@ -14,6 +14,7 @@ LLM = {  # batch, n_query, q_heads, kv_heads, head_dim, hidden, vis_len
     "seventeen-rows": (17, 1, 2, 2, 40, 136, 64), "thirty-two-rows": (8, 4, 3, 1, 16, 1000, 50),
     "thirty-three-rows": (11, 3, 2, 1, 16, 72, 50), "several-batches": (2, 2, 2, 1, 32, 4096, 70),
     "most-rows-kept": (1, 8, 8, 8, 16, 64, 512), "summed-before": (1, 8, 8, 8, 16, 64, 513),
+    "rows-past-the-rule": (1, 9, 8, 8, 16, 64, 400),
     # the widest weights that q takes in one launch, and the first wider ones
     "two-batches-f32": (1, 2, 2, 1, 16, 2048, 40), "past-two-batches": (1, 2, 2, 1, 16, 4104, 40),
     "one-batch": (9, 2, 2, 1, 16, 2048, 40), "past-one-batch": (9, 2, 2, 1, 16, 2056, 40),
