@@ -796,12 +796,17 @@ static hipError_t fused_project_t(const ProjectArgs &a, hipStream_t s) {
     pr.inv_S = ProbProject<T>::inverse_of(a.S);
     pr.inv_dh = ProbProject<T>::inverse_of(a.dh);
     // Weights and hidden states are a few megabytes and come from the caches, so what counts is
-    // how many CUs multiply: 256 x 256 tiles only where every CU gets two.  2688 tokens of 1280
-    // features: Q and K as launches of 55 such tiles 70 + 70 us, as one launch of 420 tiles of
-    // 128 x 128 34 us (128 x 64: 40, 256 x 128: 38-41, 128 x 128 with eight waves: 36).
+    // how many CUs multiply: 128 x 128 tiles (2688 tokens of 1280 features: Q and K as two launches
+    // of 55 tiles of 256 x 256 70 + 70 us, as one launch of 420 tiles 34 us; 128 x 64: 40, 256 x 128:
+    // 38-41, eight waves: 36), for bf16 up to one and a half tiles of 256 x 256 for every CU.  Whole
+    // calls with 128 x 128 and 256 x 256 tiles, us, by the number of the latter (bf16, segments of
+    // 144 tokens):  288: 209, 225;  320: 254, 268;  360: 273, 279;  410: 313, 302;  452: 288, 279;
+    // 500: 361, 337;  900: 616, 631.  fp32 multiplies sixteen times slower and gains nothing from the
+    // operands' reuse:  450: 866, 866;  544: 835, 1025;  590: 1082, 1235;  900: 1628, 1700.  81 tokens
+    // with 256 x 128: bf16 60.6, 72.6, fp32 158, 232.
     const int64_t tiles = (int64_t)((pr.d.rows_s + 255) / 256) * ((pr.d.rows_p + 255) / 256) * 2;
     TileShape t = tile_shape(pr.d.rows_p, pr.d.rows_s, 2);
-    if (pr.d.rows_p > 64 && tiles < 2 * kCus) t = {128, 128, 128};
+    if (pr.d.rows_p > 64 && (sizeof(T) == 4 || tiles < kCus * 3 / 2)) t = {128, 128, 128};
     return launch_gemm(pr, 2, s, t);
 }
 hipError_t launch_fused_project(const ProjectArgs &a, hipStream_t s) {

@@ -327,7 +327,7 @@ FUSED_ENCODER_MEAN = {
     # a [CLS] row that only takes part as a key
     "cls-all-keys": _enc(has_cls=1, score_mode=1, softmax_domain=1, keep_global=30, keep_local=16),
     "cls-patch-keys": _enc(has_cls=1, score_mode=1, grid_h=9, grid_w=14, heads=2, head_dim=64),
-    # more tokens than one 256-row tile of the projection, 128-wide heads (the fp32 limit)
+    # several tiles of tokens and of output features in the projection, 128-wide heads (the fp32 limit)
     "many-rows-wide-heads": _enc(has_cls=0, score_mode=1, batch=3, n_segments=2, grid_h=16,
                                  grid_w=15, heads=2, head_dim=128, feat_dim=256, keep_global=12,
                                  keep_local=8),
