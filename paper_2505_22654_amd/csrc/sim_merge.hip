@@ -1136,11 +1136,18 @@ hipError_t launch_sim_argmax(const MergeArgs &a, hipStream_t s) {
     if (sim_argmax_uses_large_form(a.B, a.T, a.K))
         return a.is_bf16 ? sim_large_t<bf16_t>(a, s) : sim_large_t<float>(a, s);
     if (a.is_bf16) return sim_t<bf16_t, 1, 1, 8, 2, 512>(a, s);
-    // fp32: the smallest tiles that still give every CU at most one workgroup (1024 features, kept x
-    // dropped: 64 x 512: 24.0 us with 64 x 64 tiles, 13.2 with 32 x 32, 7.3 with 16 x 16; 2 x 64 x
-    // 512: 23.5, 13.2, 7.5; 4 x 64 x 512: 24.4, 13.5, 12.3; 8 x 64 x 512: 24.2, 13.0, 19.7; 4 x 192 x
-    // 384: 24.5, 20.4, 23.7).  bf16 multiplies sixteen times faster and is bound by its fetches: 64 x
-    // 512: 8.9, 7.8, 7.2 us, but 32 x 224 of 512 features 5.8, 7.9, 7.1.
+    // fp32: the smallest tiles that still give every CU at most one workgroup.  Whole calls, us, by
+    // the number of the smaller tiles (576 tokens an image):
+    //   16 x 16, 32 x 32, 64 x 64   128: 30.7, 35.5, 47.4 (1024 features)   224: 29.0, 29.8, 35.3 (512),
+    //                               36.2, 40.6, 53.9 (1280)   256: 32.1, 36.7, 48.6 (1024)
+    //   past one for each CU        384: 27.6, 24.9, 30.3 (512), 35.5, 36.4, 47.9 (1024)   448: 34.2,
+    //                               35.7, 41.9 (768), 45.9, 44.0, 56.2 (1280)   672: 38.0, 31.7, 36.9
+    //   32 x 32, 64 x 64            224: 34.0, 38.5 (512), 42.5, 53.3 (1024)
+    //   past one for each CU        280: 40.0, 40.2 (512), 47.8, 46.8 (768), 47.9, 51.7 (1024)   448:
+    //                               35.7, 37.0 (512), 45.4, 44.7 (768)   504: 46.4, 39.4 (512), 62.4,
+    //                               48.0 (768; nine images: one XCD has two)
+    // bf16 multiplies sixteen times faster and is bound by its fetches: 64 x 512: 8.9, 7.8, 7.2 us of
+    // the kernel with 64 x 64, 32 x 32 and 16 x 16 tiles, but 32 x 224 of 512 features 5.8, 7.9, 7.1.
     auto tiles = [&](int n) { return (int64_t)((a.T - a.K + n - 1) / n) * ((a.K + n - 1) / n) * a.B; };
     if (tiles(16) <= kCus) return sim_thin<1>(a, s);
     if (tiles(32) <= kCus) return sim_thin<2>(a, s);
