@@ -372,15 +372,11 @@ def cpu_baseline(points, hosts, budget_s=12.0, inputs: str = "qk", one_thread: b
 
 
 def kernel_source_digest(kernel: str) -> str:
-    """sha256 over the kernel's source file and the headers every kernel includes."""
+    """sha256 over the kernel's source file and every header of the library."""
+    from paper_2505_22654_amd import build
     h = hashlib.sha256()
-    names = [KERNEL_SOURCE[kernel], "common.hpp", "launch.hpp"]
-    if KERNEL_SOURCE[kernel] == "fused.hip":
-        names.append("fused.hpp")
-    if kernel in ("compact", "select_compact", "llm_select"):
-        names.append("compact.hpp")
-    for name in names:
-        with open(os.path.join(ROOT, "paper_2505_22654_amd", "csrc", name), "rb") as f:
+    for name in [KERNEL_SOURCE[kernel], *build.HEADERS]:
+        with open(os.path.join(build.CSRC, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()
 
