@@ -11,12 +11,14 @@
 #include <utility>
 #include <vector>
 
+#include "../include/vscan.h"
 #include "../paper_2505_22654_amd/csrc/fused.hpp"
 #include "../paper_2505_22654_amd/csrc/launch.hpp"
 
 namespace {
 uintptr_t g_lo = 0, g_hi = 0;
 int g_calls = 0, g_regions = 0, g_violations = 0;
+vscan::SelectSeed g_seed;  // what the last scoring launch was asked to prepare
 
 void region(const char *who, const char *what, const void *p, size_t bytes) {
     ++g_regions;
@@ -39,9 +41,15 @@ void distinct(const char *who, std::vector<std::pair<const void *, size_t>> rs) 
             fprintf(stderr, "host_stubs: %s: scratch regions overlap\n", who);
         }
 }
+void expect(const char *who, const char *what, bool ok) {
+    if (ok) return;
+    ++g_violations;
+    fprintf(stderr, "host_stubs: %s: %s\n", who, what);
+}
 }  // namespace
 
 extern "C" void vscan_test_window(const void *lo, size_t bytes) {
+    g_seed = {};
     g_lo = reinterpret_cast<uintptr_t>(lo);
     g_hi = g_lo + bytes;
 }
@@ -68,6 +76,12 @@ hipError_t launch_score_cls(const ScoreArgs &a, hipStream_t) {
 }
 hipError_t launch_score_mean_lse(const ScoreArgs &a, hipStream_t) {
     check_score("score_mean_lse", a, true);
+    if (a.q2) {  // the second pair's log-sum-exps
+        const size_t n = (size_t)a.BC * a.H * a.N * sizeof(float);
+        region("score_mean_lse", "lse2", a.lse2, n);
+        distinct("score_mean_lse", {{a.lse2, n}, {a.lse, n}});
+        expect("score_mean_lse", "second pair without keys", a.k2 != nullptr);
+    }
     return hipSuccess;
 }
 hipError_t launch_score_mean_colsum(const ScoreArgs &a, hipStream_t) {
@@ -135,11 +149,25 @@ hipError_t launch_llm_score(const LlmScoreArgs &a, hipStream_t) {
         region("llm_score", "split_stats", a.split_stats, st);
         distinct("llm_score", {{a.part, part}, {a.split_e, e}, {a.split_stats, st}});
     }
+    g_seed = a.seed;
     return hipSuccess;
 }
 hipError_t launch_llm_select(const LlmSelectArgs &a, hipStream_t) {
     ++g_calls;
     region("llm_select", "part", a.part, (size_t)a.B * a.Hkv * a.V * 4);
+    // out of place the indices are handed over inside the launch, and the scoring launch before it
+    // must have been asked to prepare every one of them; in place none
+    if (a.copy) {
+        expect("llm_select", "indices not prepared",
+               g_seed.kept == a.kept_idx && g_seed.n_kept == (int64_t)a.B * a.keep);
+        expect("llm_select", "copies other indices",
+               (a.keep == 0 || a.copy->kept_idx == a.kept_idx) && !a.copy->in_place);
+        expect("llm_select", "copies another table", a.copy->meta == a.meta && a.copy->B == a.B);
+        expect("llm_select", "does not wait", a.polls > 0);
+    } else {
+        expect("llm_select", "indices prepared in place", g_seed.n_kept == 0);
+    }
+    g_seed = {};
     return hipSuccess;
 }
 size_t llm_select_lds_bytes(int V) { return 1024 + (size_t)V * 5; }
@@ -162,11 +190,18 @@ static hipError_t check_fused(const char *who, const FusedArgs &a) {
     region(who, "part", a.part, (size_t)a.B * a.V * 4);
     distinct(who, {{a.c_q, cq}, {a.q_planes, qp}, {a.qt_planes, qt}, {a.c_l, cl},
                    {a.part, (size_t)a.B * a.V * 4}});
+    if (a.keep_rows)
+        expect(who, "softmax rows of another length than the span", a.nk == a.V && !a.causal);
     return hipSuccess;
 }
 hipError_t launch_fused_project(const ProjectArgs &a, hipStream_t) {
     ++g_calls;
-    region("fused_project", "out", a.out, (size_t)a.BC * a.H * a.S * a.dh * 4);
+    const size_t out = (size_t)a.BC * a.H * a.S * a.dh * 4;
+    const size_t w = (size_t)a.H * a.dh * a.Dh * (a.is_bf16 ? 2 : 4);
+    region("fused_project", "out", a.out, out);
+    region("fused_project", "out_k", a.out_k, out);
+    region("fused_project", "w_k", a.w_k, w);  // transposed into the workspace by the launch before
+    distinct("fused_project", {{a.out, out}, {a.out_k, out}, {a.w_k, w}});
     return hipSuccess;
 }
 hipError_t launch_transpose(const void *, void *out, int rows, int cols, int es, hipStream_t) {
@@ -178,7 +213,48 @@ hipError_t launch_fused_q(const FusedArgs &a, hipStream_t) { return check_fused(
 hipError_t launch_fused_split_q(const FusedArgs &a, hipStream_t) { return check_fused("fused_split_q", a); }
 hipError_t launch_fused_qt(const FusedArgs &a, hipStream_t) { return check_fused("fused_qt", a); }
 hipError_t launch_fused_logits(const FusedArgs &a, hipStream_t) { return check_fused("fused_logits", a); }
-hipError_t launch_fused_softmax(const FusedArgs &a, hipStream_t) { return check_fused("fused_softmax", a); }
-hipError_t launch_fused_colsum(const FusedArgs &a, hipStream_t) { return check_fused("fused_colsum", a); }
+hipError_t launch_fused_softmax(const FusedArgs &a, hipStream_t) {
+    if (a.keep_rows) g_seed = a.seed;  // the last launch before the selection
+    return check_fused("fused_softmax", a);
+}
+hipError_t launch_fused_colsum(const FusedArgs &a, hipStream_t) {
+    expect("fused_colsum", "launched although the selection adds the rows", !a.keep_rows);
+    g_seed = a.seed;
+    return check_fused("fused_colsum", a);
+}
+
+// The padded ragged calls (api.cpp), with an upload that checks where the table goes: at the start
+// of the window, and everything else behind it.
+size_t ragged_table_bytes(int batch);
+int llm_prune_ragged_padded(const vscan_llm_desc *d, const vscan_seq_meta *meta_host,
+                            TableUpload upload, const void *q, void *k, void *v, void *hidden,
+                            int32_t *kept_idx, void *k_out, void *v_out, void *hidden_out,
+                            float *scores_out, void *workspace, size_t workspace_bytes, void *stream);
+int llm_prune_fused_ragged_padded(const vscan_llm_desc *d, const vscan_seq_meta *meta_host,
+                                  TableUpload upload, void *hidden, const void *w_q,
+                                  const void *w_k_t, int32_t *kept_idx, void *hidden_out,
+                                  float *scores_out, void *workspace, size_t workspace_bytes,
+                                  void *stream);
 
 }  // namespace vscan
+
+static hipError_t checking_upload(vscan::SeqMeta *table, const vscan::SeqMeta *from_host, int batch,
+                                  hipStream_t) {
+    ++g_calls;
+    region("table_upload", "table", table, (size_t)batch * sizeof(vscan::SeqMeta));
+    expect("table_upload", "not at the start of the workspace", reinterpret_cast<uintptr_t>(table) == g_lo);
+    expect("table_upload", "no host table", from_host != nullptr);
+    g_lo += (size_t)batch * sizeof(vscan::SeqMeta);
+    return hipSuccess;
+}
+extern "C" size_t vscan_test_table_bytes(int batch) { return vscan::ragged_table_bytes(batch); }
+extern "C" int vscan_test_ragged_padded(const vscan_llm_desc *d, const vscan_seq_meta *meta, void *t,
+                                        void *out, int from_hidden, void *ws, size_t bytes) {
+    // `t` stands for every input tensor, `out` for every out-of-place result (NULL in place)
+    int32_t *kept = static_cast<int32_t *>(t);
+    float *scores = static_cast<float *>(t);
+    return from_hidden ? vscan::llm_prune_fused_ragged_padded(d, meta, checking_upload, t, t, t, kept, out,
+                                                              scores, ws, bytes, nullptr)
+                       : vscan::llm_prune_ragged_padded(d, meta, checking_upload, t, t, t, t, kept, out,
+                                                        out, out, scores, ws, bytes, nullptr);
+}

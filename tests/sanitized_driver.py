@@ -57,7 +57,20 @@ L.vscan_llm_prune_fused_ragged.argtypes = ([ctypes.POINTER(vb.LlmDesc)] + [vp] *
                                            [ctypes.c_size_t, vp])
 L.vscan_test_window.argtypes = [vp, ctypes.c_size_t]
 L.vscan_test_report.argtypes = [ctypes.POINTER(ctypes.c_int)] * 3
+L.vscan_test_table_bytes.restype = ctypes.c_size_t
+L.vscan_test_ragged_padded.argtypes = [ctypes.POINTER(vb.LlmDesc), vp, vp, vp, ctypes.c_int, vp,
+                                       ctypes.c_size_t]
 L.vscan_status_string.restype = ctypes.c_char_p
+
+
+def padded(desc, meta, out, from_hidden, scratch):
+    """A padded ragged call: the table, then the scratch of the ordinary one; a byte less is refused."""
+    n = L.vscan_test_table_bytes(desc.batch) + scratch
+    L.vscan_test_window(WS, n)
+    args = ctypes.byref(desc), ctypes.addressof(meta), FAKE, out, from_hidden, WS
+    if n:  # (nothing is needed for no sequence from hidden states)
+        assert L.vscan_test_ragged_padded(*args, n - 1) == vb.VSCAN_ERR_WORKSPACE
+    assert L.vscan_test_ragged_padded(*args, n) == 0
 
 FAKE = 0x7F0000001000      # user tensors: aligned, outside every window, never dereferenced
 WS = 0x500000000000        # workspace base: aligned, never dereferenced
@@ -123,6 +136,8 @@ for idx in (1, 2, 3, 4, 5, 6):
                                       FAKE, FAKE, *outs, FAKE, WS, n, None)
         assert rc == 0, (idx, rc)
         ok += 1
+        padded(d, meta, outs[0], 0, n)
+        ok += 1
         # both element types
         rc, n = size(L.vscan_llm_fused_workspace_size, d)
         if rc == 0:
@@ -132,7 +147,8 @@ for idx in (1, 2, 3, 4, 5, 6):
                                            None) == 0
             assert L.vscan_llm_prune_fused_ragged(ctypes.byref(d), ctypes.addressof(meta), FAKE, FAKE,
                                                   FAKE, FAKE, FAKE, ho, FAKE, WS, n, None) == 0
-            ok += 2
+            padded(d, meta, ho, 1, n)
+            ok += 3
         else:
             assert rc == vb.VSCAN_ERR_UNSUPPORTED, rc
 
