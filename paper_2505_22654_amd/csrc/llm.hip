@@ -363,8 +363,8 @@ static hipError_t llm_score_t(const LlmScoreArgs &a, hipStream_t s) {
 // Few (sequence, kv head) items with long key domains: one workgroup per item would leave most
 // of the chip idle (a 4096-token span under 4 kv heads: 4 workgroups on 256 CUs), so the key
 // domain is cut into chunks of kSplitChunk keys, one workgroup each.
-//   llm_score_split_kernel    lane = key: logits of all R query rows against it, then per
-//                             chunk and row the maximum m_c[r] and the sum l_c[r] of
+//   llm_score_split_kernel    a wave multiplies sixteen keys with all R query rows (16 x 16 tiles);
+//                             then per chunk and row the maximum m_c[r] and the sum l_c[r] of
 //                             2^(z - m_c[r]), and z itself for the visual columns
 //   llm_score_combine_kernel  M_r = max_c m_c[r], L_r = sum_c l_c[r] 2^(m_c[r] - M_r) in chunk
 //                             order, part[j] = sum_r 2^(z[r][j] - M_r) / L_r in row order:

@@ -27,8 +27,7 @@ EDGES.update({
     # static rows of several units per slab, and rows of more than one 256-byte strip
     "long-text": _llm(text=700, prefix=300, head_dim=256, hidden=1032),
     "f32": _llm(dtype=wl.F32, head_dim=128),
-    # more sequences than the chip holds workgroups: gathering workgroups start before every
-    # selection has
+    # more sequences than the chip holds workgroups: the selections alone take several rounds
     "many-sequences": _llm(batch=2500, vis_len=33, keep=11, q_heads=2, hidden=64),
 })
 
