@@ -803,12 +803,16 @@ hipError_t launch_llm_select(const LlmSelectArgs &a, hipStream_t s) {
     const size_t smem = llm_select_lds_bytes(a.V);
     if (!a.copy) return launch_select_in_place(a, smem, s);
     const CompactArgs &copy = *a.copy;
-    // 513 to 1024 tokens: 512 threads shorten the selection (576 tokens, 32 kv heads: 1 sequence 21.4
-    // -> 20.4 us a call, 16 sequences 58.5 -> 56.8), but copies of more than the last-level cache run
-    // faster in workgroups of 256 (343 MB 81.6 and 82.2 us, 457 MB 112.9 and 115.8; 332 MB 82.8 and
-    // 80.9).  Up to 512 tokens the two are alike (14.9 and 14.5 us, 59.2 and 60.2).
+    // 513 to 1024 tokens: 512 threads shorten the selection, but copy more slowly.  The rows around the
+    // span are copied meanwhile, so what counts is how long they take; us a call with 256 and with 512
+    // threads, by the bytes of those rows (read and written):
+    //   13 MB  1 x 576: 18.8, 18.1   53 MB  4 x 576: 22.8, 21.2   61 MB  25 x 576: 32.4, 29.9
+    //   78 MB  16 x 576: 48.4, 44.5;  16 x 1000: 64.4, 62.2;  8 x 576: 24.9, 24.9
+    //   84 MB  12 x 576: 28.0, 28.3;  12 x 800: 30.8, 31.5;  16 x 1000: 33.8, 33.1
+    //   112 MB  16 x 576: 33.7, 33.4   122 MB  25 x 1000: 96.9, 98.2   182 MB  25 x 1000: 51.6, 53.0
+    // Up to 512 tokens the two are alike (14.9 and 14.5 us, 59.2 and 60.2).
     const int64_t row = (int64_t)(2 * copy.Hkv * copy.dh + copy.Dh) * copy.elem_bytes;
-    const bool long_copy = 2 * (int64_t)(copy.max_static_rows + a.keep) * a.B * row > (int64_t)320 << 20;
+    const bool long_copy = 2 * (int64_t)copy.max_static_rows * a.B * row > 80 * 1000 * 1000;
     const int threads = a.V <= 512 || (a.V <= 1024 && long_copy) ? 256 : a.V <= 4096 ? 512 : 1024;
     const CopyUnits units = copy_units(copy, threads);
     // (a grid dimension holds fewer than 2^32 threads: many narrow slabs take a second one)
