@@ -33,20 +33,26 @@ struct FusedArgs {
 };
 // Whether q leaves launch_fused_q in its final form (no launch_fused_split_q): few query rows, no more
 // than one workgroup of sixteen output features for each CU, and weight rows of which a wave's eighth is
-// one batch of loads (17 to 32 query rows, which take twice the registers) or two.  Stage-2 calls with q
-// in one launch and with the axis split over workgroups, us (features out x in, query rows):
-//   4096 x 4096 bf16  1: 33.6, 40.5;  8: 42.1, 45.3;  16: 49.0, 51.2;  24: 88.7, 88.6;  32: 112.2, 110.5
-//   2048 x 2048 bf16  1: 29.1, 32.8;  16: 39.4, 43.7;  17: 51.9, 54.4;  32: 54.7, 56.6
-//   2560 x 2560 bf16  8: 40.0, 41.3;  16: 48.2, 47.3;  17: 61.1, 58.6;  32: 65.3, 61.2
-//   5120 x 5120 bf16  1: 53.4, 45.9;  8: 65.6, 54.6;  16: 80.4, 63.0   (rows of 10 KiB)
-//   8192 x 2048 bf16  1: 35.8, 38.9;  8: 44.3, 43.4;  16: 49.9, 49.3   (two workgroups on a CU)
-//   1024 x 1024 fp32  1: 29.1, 33.3;  16: 38.9, 43.1;  17: 50.4, 53.1;  32: 52.2, 54.7
-//   2048 x 2048 fp32  1: 36.4, 38.6;  16: 49.7, 52.1;  24: 72.9, 72.5;  32: 76.5, 75.2
-constexpr int kThinQueries = 32, kThinOutputs = 4096, kThinRowBytes = 8192;
+// one batch of loads (17 to 32 query rows, which take twice the registers), two, or (fp32, whose split
+// form is the slower one, up to 8 query rows) four.  Stage-2 calls with q in one launch and with the axis
+// split over workgroups, us (features out x in, query rows):
+//   bf16  4096 x 4096  1: 33.6, 40.5;  8: 42.1, 45.3;  16: 49.0, 51.2;  24: 88.7, 88.6;  32: 112.2, 110.5
+//         2048 x 2048  1: 29.1, 32.8;  16: 39.4, 43.7;  17: 51.9, 54.4;  32: 54.7, 56.6
+//         2560 x 2560  8: 40.0, 41.3;  16: 48.2, 47.3;  17: 61.1, 58.6;  32: 65.3, 61.2
+//         2048 x 5120  1: 34.4, 35.1;  8: 42.1, 40.5;  16: 48.5, 44.0   (rows of 10 KiB)
+//         8192 x 2048  1: 35.8, 38.9;  8: 44.3, 43.4;  16: 49.9, 49.3   (two workgroups on a CU)
+//         5120 x 5120  1: 50.6, 43.7;  8: 61.2, 49.0;  16: 72.8, 56.5   (both)
+//   fp32  1024 x 1024  1: 29.1, 33.3;  16: 38.9, 43.1;  17: 50.4, 53.1;  32: 52.2, 54.7
+//         2048 x 2048  1: 31.6, 34.1;  8: 36.2, 41.1;  16: 42.0, 45.4;  17: 60.4, 60.0;  32: 64.1, 62.6
+//         4096 x 2560  1: 38.1, 43.7;  8: 45.3, 46.4;  16: 52.5, 50.0
+//         4096 x 4096  1: 44.4, 51.9;  8: 50.8, 55.2;  16: 58.5, 59.1;  17: 76.9, 75.7
+//         1024 x 4096  1: 39.8, 41.3;  8: 46.7, 49.5;  16: 54.8, 52.0
+//         4096 x 5120  1: 53.5, 55.7;  8: 60.9, 59.8;  16: 72.0, 66.7
+constexpr int kThinQueries = 32, kThinOutputs = 4096;
 inline bool fused_q_whole(const FusedArgs &a) {
     const int64_t rows = (int64_t)a.B * a.Tq, row_bytes = (int64_t)a.Dh * (a.is_bf16 ? 2 : 4);
-    return rows <= kThinQueries && a.Hq * a.dh <= kThinOutputs &&
-           row_bytes <= (rows <= kThinQueries / 2 ? kThinRowBytes : kThinRowBytes / 2);
+    const int64_t most = rows <= 8 && !a.is_bf16 ? 16384 : rows <= 16 ? 8192 : 4096;
+    return rows <= kThinQueries && a.Hq * a.dh <= kThinOutputs && row_bytes <= most;
 }
 // Whether the selection adds the R rows of softmax weights up itself, as it does the heads of the
 // Q/K forms (no launch_fused_colsum): its key domain is the visual tokens, and the one workgroup that

@@ -14,9 +14,12 @@ LLM = {  # batch, n_query, q_heads, kv_heads, head_dim, hidden, vis_len
     "seventeen-rows": (17, 1, 2, 2, 40, 136, 64), "thirty-two-rows": (8, 4, 3, 1, 16, 1000, 50),
     "thirty-three-rows": (11, 3, 2, 1, 16, 72, 50), "several-batches": (2, 2, 2, 1, 32, 4096, 70),
     "most-rows-kept": (1, 8, 8, 8, 16, 64, 512), "summed-before": (1, 8, 8, 8, 16, 64, 513),
+}
+EDGES = {  # the same fields
     "rows-past-the-rule": (1, 9, 8, 8, 16, 64, 400),
     # the widest weights that q takes in one launch, and the first wider ones
-    "two-batches-f32": (1, 2, 2, 1, 16, 2048, 40), "past-two-batches": (1, 2, 2, 1, 16, 4104, 40),
+    "two-batches-f32": (9, 1, 2, 1, 16, 2048, 40), "past-two-or-four-batches": (1, 2, 2, 1, 16, 4104, 40),
+    "past-two-batches-f32": (9, 1, 2, 1, 16, 2056, 40),
     "one-batch": (9, 2, 2, 1, 16, 2048, 40), "past-one-batch": (9, 2, 2, 1, 16, 2056, 40),
     "one-batch-f32": (9, 2, 2, 1, 16, 1024, 40), "past-one-batch-f32": (9, 2, 2, 1, 16, 1032, 40),
     "most-outputs": (1, 1, 32, 32, 128, 64, 40), "past-most-outputs": (1, 1, 33, 33, 128, 64, 40),
@@ -32,6 +35,18 @@ def test_stage2(name, dtype, in_place):
                    hidden=hidden, vis_len=vis, keep=vis // 3, in_place=in_place)
     inp, ref, info = pu.screened_fused_case(shape, 7300 + sorted(LLM).index(name) * 31)
     print("case", name, dtype, in_place, info, flush=True)
+    out = _run(shape, inp)
+    print(pu.check_fused(shape, ref, out, name, hidden=inp["hidden"]))
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
+@pytest.mark.parametrize("name", sorted(EDGES))
+def test_stage2_at_the_edges_of_the_rules(name, dtype):
+    batch, n_query, hq, hkv, dh, hidden, vis = EDGES[name]
+    shape = _shape(dtype=dtype, batch=batch, n_query=n_query, q_heads=hq, kv_heads=hkv, head_dim=dh,
+                   hidden=hidden, vis_len=vis, keep=vis // 3)
+    inp, ref, info = pu.screened_fused_case(shape, 7500 + sorted(EDGES).index(name) * 31)
+    print("case", name, dtype, info, flush=True)
     out = _run(shape, inp)
     print(pu.check_fused(shape, ref, out, name, hidden=inp["hidden"]))
 
