@@ -201,11 +201,9 @@ def _ragged_setup(desc, meta, batch: int, from_hidden: bool, device):
     """The host table of a ragged call and a workspace whose first bytes become the device table."""
     import torch
     assert len(meta) == batch
-    if any(len(m) != 4 for m in meta):
-        raise ValueError("a ragged entry is (seq_len, vis_start, vis_len, keep)")
-    # (a value outside 32 bits raises OverflowError here; ctypes would cut it down)
-    flat = array.array("i", [int(x) for m in meta for x in m] or [0] * 4)
-    host = (ctypes.c_int32 * len(flat)).from_buffer(flat)
+    # rows of another length raise ValueError here, values outside 32 bits OverflowError (ctypes would
+    # cut those down)
+    host = array.array("i", [int(x) for a, b, c, d in meta for x in (a, b, c, d)])
     n = ctypes.c_size_t(0)
     rc = lib().vscan_llm_ragged_workspace_size(ctypes.byref(desc), int(from_hidden), ctypes.byref(n))
     if rc != VSCAN_OK:
@@ -231,7 +229,7 @@ def llm_prune_ragged(shape, meta, q, k, v, hidden, want_scores: bool = False) ->
         ko = vo = ho = None
     else:
         ko, vo, ho = torch.empty_like(k), torch.empty_like(v), torch.empty_like(hidden)
-    rc = lib().vscan_llm_prune_ragged_padded(ctypes.byref(desc), ctypes.addressof(host), _ptr(q),
+    rc = lib().vscan_llm_prune_ragged_padded(ctypes.byref(desc), host.buffer_info()[0], _ptr(q),
                                              _ptr(k), _ptr(v), _ptr(hidden), _ptr(out["kept_idx"]),
                                              _ptr(ko), _ptr(vo), _ptr(ho), _ptr(out.get("scores")),
                                              _ptr(workspace), workspace.numel(), _stream_handle())
@@ -495,7 +493,7 @@ def llm_prune_fused_ragged(shape, meta, hidden, w_q, w_k_t, want_scores: bool = 
     if want_scores:
         out["scores"] = torch.empty((shape.batch, shape.vis_len), dtype=torch.float32, device=dev)
     ho = None if shape.in_place else torch.empty_like(hidden)
-    rc = lib().vscan_llm_prune_fused_ragged_padded(ctypes.byref(desc), ctypes.addressof(host),
+    rc = lib().vscan_llm_prune_fused_ragged_padded(ctypes.byref(desc), host.buffer_info()[0],
                                                    _ptr(hidden), _ptr(w_q), _ptr(w_k_t),
                                                    _ptr(out["kept_idx"]), _ptr(ho),
                                                    _ptr(out.get("scores")), _ptr(workspace),
