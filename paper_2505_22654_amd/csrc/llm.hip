@@ -57,7 +57,6 @@ __global__ __launch_bounds__(kScoreWaves * kWave, (DEPTH == 2 && NC <= 4 && NRB 
                                                         int nk_u, int domain_all,
                                                         const SeqMeta *__restrict__ meta,
                                                         float sl2, SelectSeed seed) {
-    seed_selection(seed, blockIdx.x, gridDim.x);
     // S_cap, V_cap: rows per sequence of k and of part (tensor strides).  Without `meta` every
     // sequence has the lengths (S_cap, vis_start_u, V_cap) and the key domain [k0_u, k0_u + nk_u);
     // with it, sequence b has those of meta[b], and nk_u is the longest domain (LDS layout).
@@ -291,6 +290,7 @@ __global__ __launch_bounds__(kScoreWaves * kWave, (DEPTH == 2 && NC <= 4 && NRB 
         kbase = kbase_next;
         gc = gn;
     }
+    seed_selection(seed, blockIdx.x, gridDim.x);
 }
 
 // LDS bytes: header, logits, and (staged) one tile per wave
