@@ -811,6 +811,9 @@ hipError_t launch_llm_select(const LlmSelectArgs &a, hipStream_t s) {
     //   84 MB  12 x 576: 28.0, 28.3;  12 x 800: 30.8, 31.5;  16 x 1000: 33.8, 33.1
     //   112 MB  16 x 576: 33.7, 33.4   122 MB  25 x 1000: 96.9, 98.2   182 MB  25 x 1000: 51.6, 53.0
     // Up to 512 tokens the two are alike (14.9 and 14.5 us, 59.2 and 60.2).
+    // Above 4096 tokens the copying workgroups carry the selection's 1024 threads and its LDS; the call
+    // is still shorter than as two launches (28 / 4 heads, 1 x 4097: 40.4, 35.6;  16 / 4, 8 x 8192: 146.7,
+    // 131.4;  8 / 4, 4 x 17000: 179.4, 164.9;  4 / 4, 4 x 32000: 226.7, 210.3).
     const int64_t row = (int64_t)(2 * copy.Hkv * copy.dh + copy.Dh) * copy.elem_bytes;
     const bool long_copy = 2 * (int64_t)copy.max_static_rows * a.B * row > 80 * 1000 * 1000;
     const int threads = a.V <= 512 || (a.V <= 1024 && long_copy) ? 256 : a.V <= 4096 ? 512 : 1024;
