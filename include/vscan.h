@@ -91,8 +91,11 @@ typedef struct {
     float scale;            /* logit scale; <= 0 selects 1/sqrt(head_dim) */
 } vscan_encoder_desc;
 
-/* Bytes of workspace vscan_encoder_reduce needs for this descriptor.
- * `with_local_pair` != 0 sizes for a call that passes q_local / k_local. */
+/* Bytes of workspace for vscan_encoder_reduce with this descriptor.
+ * `with_local_pair` != 0 sizes for a call that passes q_local / k_local.
+ * Where the tokens leave compute units idle, mean attention asks for room to cut
+ * its rows into parts; a buffer without that room is taken too (the call is
+ * slower, scores may differ in the last bits), one smaller than that is refused. */
 int vscan_encoder_workspace_size(const vscan_encoder_desc *desc, int with_local_pair,
                                  size_t *bytes);
 

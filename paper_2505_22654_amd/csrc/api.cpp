@@ -98,6 +98,37 @@ int plan_encoder(const vscan_encoder_desc *d, int with_local, EncoderPlan *p) {
     return VSCAN_OK;
 }
 
+// Mean attention with its streamed rows in parts, or with the second pair's scores in the launch of the
+// first pair's: the statistics and score rows of all parts, for one pair or for both, behind everything
+// else a call needs.  A workspace without this room (callers keep buffers of a size they once asked for)
+// is scored in one part, pair by pair.
+struct MeanParts {
+    int parts = 1;
+    bool used = false;
+    size_t off_lse[2], off_scores[2], end;
+};
+
+MeanParts plan_mean_parts(const vscan_encoder_desc *d, const EncoderPlan &p, int scored_as_bf16,
+                          bool with_local, size_t base) {
+    MeanParts m;
+    m.end = base;
+    if (d->score_mode != VSCAN_SCORE_MEAN_RECEIVED || !mean_pair_launch(scored_as_bf16, d->head_dim))
+        return m;
+    const int pairs = with_local ? 2 : 1;
+    const int64_t heads = (int64_t)p.BC * d->heads;
+    m.parts = mean_parts(scored_as_bf16, d->head_dim, heads * pairs, p.N);
+    m.used = mean_cost(heads * pairs, p.N, m.parts) < 0.95 * pairs * mean_cost(heads, p.N, 1);
+    if (!m.used) return m;
+    const size_t rows = (size_t)heads * m.parts * p.N;
+    for (int i = 0; i < pairs; ++i) {
+        m.off_lse[i] = m.end;
+        m.end += align_up(rows * (m.parts > 1 ? 2 : 1) * sizeof(float));
+        m.off_scores[i] = m.end;
+        m.end += align_up(rows * sizeof(float));
+    }
+    return m;
+}
+
 struct LlmPlan {
     int rows, k0, nk, S_out;
     size_t off_part, off_split_e, off_split_stats, bytes;
@@ -328,10 +359,10 @@ int enqueue_fused_scores(FusedArgs &fa, const FusedScratch &f, unsigned char *ws
 int enqueue_encoder_tail(const vscan_encoder_desc *d, const EncoderPlan &p, bool with_local,
                          int score_heads, float norm, const void *x, int32_t *kept_idx,
                          void *merged, int32_t *assign_out, float *scores_out, unsigned char *ws,
-                         hipStream_t s, size_t off_scores) {
+                         hipStream_t s, size_t off_scores, size_t off_scores_local) {
     EncSelectArgs se;
     se.head_global = reinterpret_cast<const float *>(ws + off_scores);
-    se.head_local = with_local ? reinterpret_cast<const float *>(ws + p.off_head_local) : nullptr;
+    se.head_local = with_local ? reinterpret_cast<const float *>(ws + off_scores_local) : nullptr;
     se.B = d->batch;
     se.C = d->n_segments;
     se.H = score_heads;
@@ -409,7 +440,7 @@ int vscan_encoder_workspace_size(const vscan_encoder_desc *desc, int with_local_
     EncoderPlan p;
     const int rc = plan_encoder(desc, with_local_pair != 0, &p);
     if (rc != VSCAN_OK) return rc;
-    *bytes = p.bytes;
+    *bytes = plan_mean_parts(desc, p, desc->dtype == VSCAN_BF16, with_local_pair != 0, p.bytes).end;
     return VSCAN_OK;
 }
 
@@ -451,6 +482,23 @@ static int encoder_reduce_impl(const vscan_encoder_desc *d, const void *q, const
     sa.domain_all = d->softmax_domain == VSCAN_KEYS_ALL;
     sa.is_bf16 = d->dtype == VSCAN_BF16;
     sa.scale = resolve_scale(d->scale, d->head_dim);
+    const float norm = mean ? 1.0f / ((float)d->heads * (float)p.N) : 1.0f / (float)d->heads;
+    const MeanParts mp = plan_mean_parts(d, p, sa.is_bf16, with_local, p.bytes);
+    if (mp.used && workspace_bytes >= mp.end) {
+        sa.parts = mp.parts;
+        sa.lse = reinterpret_cast<float *>(ws + mp.off_lse[0]);
+        sa.head_scores = reinterpret_cast<float *>(ws + mp.off_scores[0]);
+        if (with_local) {
+            sa.q2 = q_local;
+            sa.k2 = k_local;
+            sa.lse2 = reinterpret_cast<float *>(ws + mp.off_lse[1]);
+            sa.head_scores2 = reinterpret_cast<float *>(ws + mp.off_scores[1]);
+        }
+        VSCAN_LAUNCH("score_mean_lse", launch_score_mean_lse(sa, s));
+        VSCAN_LAUNCH("score_mean_colsum", launch_score_mean_colsum(sa, s));
+        return enqueue_encoder_tail(d, p, with_local, d->heads * mp.parts, norm, x, kept_idx, merged,
+                                    assign_out, scores_out, ws, s, mp.off_scores[0], mp.off_scores[1]);
+    }
     if (mean && with_local && mean_pair_launch(sa.is_bf16, sa.dh)) {
         // Pass 1 of both pairs in one launch.  The second pair's log-sum-exps wait where the first
         // pair's scores go afterwards, so its second pass runs first.
@@ -481,9 +529,8 @@ static int encoder_reduce_impl(const vscan_encoder_desc *d, const void *q, const
         }
     }
 
-    return enqueue_encoder_tail(d, p, with_local, d->heads,
-                                mean ? 1.0f / ((float)d->heads * (float)p.N) : 1.0f / (float)d->heads,
-                                x, kept_idx, merged, assign_out, scores_out, ws, s, p.off_head_global);
+    return enqueue_encoder_tail(d, p, with_local, d->heads, norm, x, kept_idx, merged, assign_out,
+                                scores_out, ws, s, p.off_head_global, p.off_head_local);
 }
 
 int vscan_encoder_reduce(const vscan_encoder_desc *d, const void *q, const void *k,
@@ -567,7 +614,8 @@ static int encoder_reduce_fused_impl(const vscan_encoder_desc *d, const void *hi
         }
         return enqueue_encoder_tail(d, p.e, with_local, d->heads,
                                     1.0f / ((float)d->heads * (float)p.e.N), x, kept_idx, merged,
-                                    assign_out, scores_out, ws, s, p.e.off_head_global);
+                                    assign_out, scores_out, ws, s, p.e.off_head_global,
+                                    p.e.off_head_local);
     }
     // (a second triple overwrites the first one's rows)
     const bool keep_rows = !with_local && fused_keep_rows(d->heads, p.nk, p.e.N);
@@ -598,7 +646,7 @@ static int encoder_reduce_fused_impl(const vscan_encoder_desc *d, const void *hi
     // the chain leaves one row of head sums per segment, [BC, 1, N], or the heads' rows
     return enqueue_encoder_tail(d, p.e, with_local, keep_rows ? d->heads : 1, 1.0f / (float)d->heads, x,
                                 kept_idx, merged, assign_out, scores_out, ws, s,
-                                keep_rows ? p.f.off_cl : p.e.off_head_global);
+                                keep_rows ? p.f.off_cl : p.e.off_head_global, p.e.off_head_local);
 }
 
 int vscan_encoder_reduce_fused(const vscan_encoder_desc *d, const void *hidden, const void *w_q,

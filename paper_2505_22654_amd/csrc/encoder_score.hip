@@ -239,6 +239,14 @@ __device__ __forceinline__ int xcd_contiguous_item(int total) {
     return (id & 7) * per + (id >> 3);
 }
 
+// log2 of a sum of exponentials.  The hardware logarithm rounds one way: a whole row's weights would be
+// too large by the same 2e-7 to 3e-7 in every row (measured), so its residual, which the hardware
+// exponential shows, is added back.
+__device__ __forceinline__ float log2_sum(float l) {
+    const float y = __builtin_amdgcn_logf(l);
+    return y + 1.4426950408889634f * fmaf(l, __builtin_amdgcn_exp2f(-y), -1.0f);
+}
+
 // Pass 1: lse2[i] = log2 sum_j 2^(sl2 * q_i . k_j) over the key domain.
 template <typename T, int NC>
 __global__ __launch_bounds__(256, 2) void mean_lse_kernel(const T *__restrict__ q,
@@ -339,7 +347,26 @@ __global__ __launch_bounds__(256, 2) void mean_lse_kernel(const T *__restrict__ 
     float L = 0.f;
     if (m_run > -INFINITY) L += l_run * __builtin_amdgcn_exp2f(m_run - M);
     if (m_o > -INFINITY) L += l_o * __builtin_amdgcn_exp2f(m_o - M);
-    if (g == 0 && qrow < N) lse[(int64_t)bh * N + qrow] = M + log2f(L);
+    if (g == 0 && qrow < N) lse[(int64_t)bh * N + qrow] = M + log2_sum(L);
+}
+
+// Sum over the 32 streamed rows that the lanes of a half-wave hold, for each of the sixteen resident rows
+// of a 32x32 accumulator: lane l < 16 of half g gets the sum of resident row acc_row(l).  Every step
+// adds pairs of lanes and leaves each lane with half of the rows (31 exchanges instead of 80).
+__device__ __forceinline__ float resident_row_sum(float (&v)[16]) {
+    const int l = lane_id();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] += __shfl_xor(v[r], 16, kWave);
+#pragma unroll
+    for (int n = 8; n >= 1; n >>= 1) {
+        const bool upper = (l & n) != 0;
+#pragma unroll
+        for (int r = 0; r < n; ++r) {
+            const float mine = upper ? v[r + n] : v[r], other = upper ? v[r] : v[r + n];
+            v[r] = mine + __shfl_xor(other, n, kWave);
+        }
+    }
+    return v[0];
 }
 
 // Pass 2: head_scores[j] = sum_i 2^(sl2 * q_i . k_j - lse2[i]) for patch keys j.
@@ -375,7 +402,9 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict
         kfrag[c] = load16_guard(kbase, (int64_t)key * row_bytes + 32 * c + 16 * g,
                                 key < N && 32 * c + 16 * g < row_bytes);
 
-    float colsum = 0.f;
+    float colsum[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) colsum[r] = 0.f;
     Stage st;
     const int ntiles = (N + kMeanTile - 1) / kMeanTile;
     const int tid = threadIdx.x;
@@ -387,7 +416,6 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict
     __syncthreads();
     for (int t = 0; t < ntiles; ++t) {
         const unsigned char *cur = lds[t & 1];
-        const float *lcur = lse_s[t & 1];
         if (t + 1 < ntiles) {
             st.load(qbase, (t + 1) * kMeanTile, N, row_bytes);
             const int r = (t + 1) * kMeanTile + tid;
@@ -402,18 +430,14 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const uint4 a = *reinterpret_cast<const uint4 *>(arow + 32 * c);
-                mma32_chunk<T>(acc, a, kfrag[c]);
+                mma32_chunk<T>(acc, kfrag[c], a);
             }
-            // acc[r] = q_(row0 + acc_row(r)) . k_key ; rows past N carry lse = +inf -> 0
+            // acc[r] = k_(key0 + acc_row(r)) . q_(row0 + lane%32): a lane's logits belong to one query
+            // row, whose log-sum-exp is one LDS read; rows past N carry +inf -> 0
+            const float lse_i = lse_s[t & 1][sub * 32 + (lane & 31)];
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                const float4 l4 =
-                    *reinterpret_cast<const float4 *>(lcur + sub * 32 + 8 * rg + 4 * g);
-                colsum += __builtin_amdgcn_exp2f(fmaf(acc[4 * rg + 0], sl2, -l4.x));
-                colsum += __builtin_amdgcn_exp2f(fmaf(acc[4 * rg + 1], sl2, -l4.y));
-                colsum += __builtin_amdgcn_exp2f(fmaf(acc[4 * rg + 2], sl2, -l4.z));
-                colsum += __builtin_amdgcn_exp2f(fmaf(acc[4 * rg + 3], sl2, -l4.w));
-            }
+            for (int r = 0; r < 16; ++r)
+                colsum[r] += __builtin_amdgcn_exp2f(fmaf(acc[r], sl2, -lse_i));
         }
         if (t + 1 < ntiles) {
             st.store(lds[(t + 1) & 1]);
@@ -421,8 +445,9 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict
         }
         __syncthreads();
     }
-    colsum += __shfl_xor(colsum, 32, kWave);
-    if (g == 0 && key < N) head_scores[(int64_t)bh * N + key] = colsum;
+    const float sum = resident_row_sum(colsum);
+    const int l = lane & 31, out_key = kb * kMeanBlock + w * 32 + 8 * (l >> 2) + 4 * g + (l & 3);
+    if (l < 16 && out_key < N) head_scores[(int64_t)bh * N + out_key] = sum;
 }
 
 // ---------------------------------------------------------------------------
@@ -440,17 +465,21 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict
 // A workgroup (4 waves) owns 4 x 32 x HALVES resident rows, held in registers as matrix
 // operands (pass 1: query rows, pass 2: key rows).  The other operand streams through LDS in
 // stages of 128 rows (4 tiles), two stages in LDS, the next one in flight in registers: one
-// workgroup barrier per 128 streamed rows.  Accumulator layout as in mma32_chunk: a lane owns
-// resident row (lane % 32) of each half and 16 of the 32 streamed rows of a tile.
+// workgroup barrier per 128 streamed rows.
 //   PASS 1: lse2[i] = log2 sum_j 2^(sl2 * q_i . k_j)      (resident i, streamed j)
 //   PASS 2: head_scores[j] = sum_i 2^(sl2 * q_i . k_j - lse2[i])   (resident j, streamed i)
-// In pass 2 the subtraction rides on the matrix cores: every streamed row carries one more
-// 32-byte chunk holding -lse2[i] / sl2 as three bf16 pieces (24 significant bits: the fp32 value
-// exactly), the resident operand holds ones against them, so the accumulator comes out as
-// q_i . k_j - lse2[i] / sl2 and a logit costs multiply, exponential, add with no per-row
-// operand to fetch.  Rows past the end carry -inf and contribute 2^-inf = 0.
+// In both passes a lane's sixteen logits of a tile belong to one query row, whose reference is one
+// register: in pass 1 the resident rows are the columns of the accumulator (a lane owns resident row
+// lane % 32 and sixteen streamed rows), in pass 2 its rows (a lane owns streamed row lane % 32 and sums
+// for its sixteen resident rows; the lanes are added once, at the end).  Subtracting the reference is
+// the multiply-add that scales the logit.  (Pass 2 had the log-sum-exp as one more 32-byte chunk of the
+// contraction before, a sixth more matrix instructions: 16384 tokens, 16 heads of 80, 911 -> 861 us.)  Rows past the end carry -inf and contribute 2^-inf = 0.
+//
+// With `parts` > 1 the streamed rows are cut into runs of whole stages with a workgroup each
+// (mean_parts): pass 1 leaves a reference m and l = sum_j 2^(sl2 * q_i . k_j - m) per row and part, which
+// pass 2 adds up where it fetches them, and pass 2 a row of sums per part, which the selection adds like
+// further heads.
 // ---------------------------------------------------------------------------
-constexpr int kPipeStageRows = 128;
 
 // 16-byte loads from global memory straight into LDS (no pass through vector registers, no LDS
 // write instruction): lane l's data lands 16*l bytes behind the wave-uniform LDS address.  Issued
@@ -475,46 +504,63 @@ __device__ __forceinline__ void wait_direct_loads() { __builtin_amdgcn_s_waitcnt
 
 struct MeanPair {
     const unsigned char *resident, *streamed;
-    const float *lse_in;
-    float *out;
+    float *lse;          // [n_heads, rows], or [n_heads, parts, rows] pairs (m, l)
+    float *head_scores;  // [n_heads, parts, rows], pass 2
 };
 
-template <int NC, int HALVES, int PASS>
+// lse2 of a row from its parts' pairs, two of them in either lane of a pair of lanes
+__device__ __forceinline__ float merged_lse(const float2 (&p)[kMeanMaxParts / 2], int first, int parts) {
+    static_assert(kMeanMaxParts == 4, "two parts a lane");
+    const auto larger = [](float a, float b) { return fmaxf(a, b); };
+    // (past the last part its pair is repeated: no weight, and the maximum stays)
+    const float m = group_reduce<2>(fmaxf(p[0].x, p[1].x), larger);
+    float l = first < parts ? p[0].y * __builtin_amdgcn_exp2f(p[0].x - m) : 0.f;
+    l += first + 1 < parts ? p[1].y * __builtin_amdgcn_exp2f(p[1].x - m) : 0.f;
+    return m + log2_sum(group_sum<2>(l));
+}
+
+// (PARTED, pass 2: the statistics come in parts.  A branch on `parts` where they are fetched would wait,
+// where its sides join, for every load in flight.)
+template <int NC, int HALVES, int PASS, bool PARTED>
 __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
     MeanPair first, MeanPair second, int pairs, int n_heads, int S, int dh, int res_first, int n_res,
-    int str_first, int n_str, float sl2) {
-    constexpr int NCX = NC + (PASS == 2 ? 1 : 0);      // chunks per streamed row (pass 2: the lse chunk)
+    int str_first, int n_streamed, int parts, float sl2) {
     // With an odd number of 32-byte chunks per row the unpadded row pitch serves the 16-byte
     // operand reads at 92 % of the LDS rate (measured; 25 % for an even number), and a stage
     // is then one contiguous block in memory and in LDS alike: it is fetched with direct loads.
-    // The lse chunk of pass 2 lives in an array of its own (32-byte rows).  Otherwise: padded
-    // rows (pitch 32 NCX + 16, conflict-free) staged through registers.
+    // Otherwise: padded rows (pitch 32 NC + 16, conflict-free) staged through registers.
     constexpr bool DIRECT = (NC & 1) != 0;
-    constexpr int STRIDE = DIRECT ? NC * 32 : NCX * 32 + 16;
+    constexpr int STRIDE = DIRECT ? NC * 32 : NC * 32 + 16;
     constexpr int PPR = NC * 2;                        // 16-byte pieces per streamed row in memory
     constexpr int RB = 4 * 32 * HALVES;                // resident rows per workgroup
-    constexpr int NM = NCX * HALVES;                   // matrix instructions per tile
+    constexpr int NM = NC * HALVES;                    // matrix instructions per tile
     constexpr int NL = 16 * HALVES;                    // logits per lane and tile
-    static_assert(kPipeStageRows * PPR == 256 * NC, "NC pieces per thread and stage");
-    __shared__ __align__(16) unsigned char lds[2][kPipeStageRows * STRIDE];
-    __shared__ __align__(16) unsigned char lse_lds[DIRECT && PASS == 2 ? 2 : 1][DIRECT && PASS == 2 ? kPipeStageRows * 32 : 16];
+    static_assert(kMeanStageRows * PPR == 256 * NC, "NC pieces per thread and stage");
+    __shared__ __align__(16) unsigned char lds[2][kMeanStageRows * STRIDE];
+    __shared__ __align__(16) float neg_lse[2][PASS == 2 ? kMeanStageRows : 1];
 
     const int nblk = (n_res + RB - 1) / RB;
-    const int total = pairs * n_heads * nblk;
+    const int total = pairs * n_heads * parts * nblk;
     const int item = xcd_contiguous_item(total);
     if (item >= total) return;
-    int bh = item / nblk;
-    const int blk = item - bh * nblk;
+    const int run = item / nblk;  // (pair, head, part)
+    const int blk = item - run * nblk;
+    int bh = run / parts;
+    const int part = run - bh * parts;
     const bool is_second = bh >= n_heads;
     if (is_second) bh -= n_heads;
-    float *__restrict__ out = is_second ? second.out : first.out;
     const int row_bytes = dh * 2;
+    // this part's stages of the streamed rows
+    const int all_stages = (n_streamed + kMeanStageRows - 1) / kMeanStageRows;
+    const int row0 = part * all_stages / parts * kMeanStageRows;
+    const int n_str = min((part + 1) * all_stages / parts * kMeanStageRows, n_streamed) - row0;
     const unsigned char *__restrict__ rbase = (is_second ? second.resident : first.resident) +
                                               ((int64_t)bh * S + res_first) * row_bytes;
     const unsigned char *__restrict__ sbase = (is_second ? second.streamed : first.streamed) +
-                                              ((int64_t)bh * S + str_first) * row_bytes;
-    const float *__restrict__ lse_h =
-        PASS == 2 ? (is_second ? second.lse_in : first.lse_in) + (int64_t)bh * n_str : nullptr;
+                                              ((int64_t)bh * S + str_first + row0) * row_bytes;
+    float *__restrict__ lse = is_second ? second.lse : first.lse;
+    float2 *__restrict__ pair = reinterpret_cast<float2 *>(lse);  // parts > 1
+    const int64_t at = PASS == 1 ? ((int64_t)bh * parts + part) * n_res : (int64_t)bh * parts * n_streamed + row0;
 
     const int tid = threadIdx.x, lane = lane_id(), g = lane >> 5, w = wave_id();
     uint4 kf[HALVES][NC];
@@ -526,15 +572,14 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
             kf[h][c] = load16_guard(rbase, (int64_t)row * row_bytes + 32 * c + 16 * g,
                                     row < n_res && 32 * c + 16 * g < row_bytes);
     }
-    // pass 2: the resident side of the extra chunk, three ones (bf16 0x3f80) in the lower half
-    const uint4 ones = g == 0 ? make_uint4(0x3f803f80u, 0x00003f80u, 0u, 0u) : zero16();
-
     const int ntiles = (n_str + 31) >> 5;
-    const int nstages = (n_str + kPipeStageRows - 1) / kPipeStageRows;
+    const int nstages = (n_str + kMeanStageRows - 1) / kMeanStageRows;
 
     // ---- staging of the streamed operand: thread t carries pieces t, t + 256, ... of a stage
     uint4 sreg[DIRECT ? 1 : NC];
-    float lse_reg = 0.f;
+    // pass 2: threads 2r and 2r + 1 carry the statistics of a stage's row r, two parts each
+    float2 stat_reg[PARTED ? kMeanMaxParts / 2 : 1];
+    const int first_part = (tid & 1) * (kMeanMaxParts / 2);
     auto stage_load = [&](int s) {
 #pragma unroll
         for (int it = 0; it < NC; ++it) {
@@ -543,7 +588,7 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
             // clamped, not predicated: rows past the end re-read the last row (finite data that
             // the consumers neutralise), pieces past the end of a row its last piece (the
             // resident operand is zero there)
-            const int row = min(s * kPipeStageRows + r, n_str - 1);
+            const int row = min(s * kMeanStageRows + r, n_str - 1);
             const int64_t off = (int64_t)row * row_bytes + min(piece * 16, row_bytes - 16);
             if constexpr (DIRECT) {
                 // piece p of the stage goes to byte 16 p of the stage's buffer: the wave's 64
@@ -554,10 +599,17 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
                 sreg[it] = load16(sbase, off);
             }
         }
-        if (PASS == 2 && tid < kPipeStageRows)
-            lse_reg = lse_h[min(s * kPipeStageRows + tid, n_str - 1)];
+        if constexpr (PASS == 2) {
+            const int64_t row = at + min(s * kMeanStageRows + (tid >> 1), n_str - 1);
+            if constexpr (!PARTED) {
+                stat_reg[0].x = lse[row];
+            } else {
+#pragma unroll
+                for (int u = 0; u < kMeanMaxParts / 2; ++u)
+                    stat_reg[u] = pair[row + (int64_t)min(first_part + u, parts - 1) * n_streamed];
+            }
+        }
     };
-    const float inv_sl2 = 1.0f / sl2;
     auto stage_store = [&](int s) {
         unsigned char *dst = lds[s & 1];
         if constexpr (DIRECT) {
@@ -570,57 +622,51 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
                 *reinterpret_cast<uint4 *>(dst + r * STRIDE + piece * 16) = sreg[it];
             }
         }
-        if (PASS == 2 && tid < kPipeStageRows) {
-            // -lse / sl2 as hi + mid + lo; each residual is exact in fp32 and the third piece
-            // takes what is left of the 24 bits.  (Decided here, not where the value was
-            // fetched: arithmetic right behind the load would make the wave wait for it.)
-            uint4 x = zero16();
-            if (s * kPipeStageRows + tid < n_str) {
-                const float v = -lse_reg * inv_sl2;
-                const uint32_t hi = f32_to_bf16_rne(v);
-                const float r1 = v - __uint_as_float(hi << 16);
-                const uint32_t mid = f32_to_bf16_rne(r1);
-                const float r2 = r1 - __uint_as_float(mid << 16);
-                x.x = hi | (mid << 16);
-                x.y = f32_to_bf16_rne(r2);
-            } else {
-                x.x = 0xff80u;  // -inf
-            }
-            unsigned char *e = DIRECT ? lse_lds[s & 1] + tid * 32 : dst + tid * STRIDE + NC * 32;
-            *reinterpret_cast<uint4 *>(e) = x;
-            *reinterpret_cast<uint4 *>(e + 16) = zero16();
+        if constexpr (PASS == 2) {
+            float x;
+            if constexpr (PARTED)
+                x = merged_lse(stat_reg, first_part, parts);
+            else
+                x = stat_reg[0].x;
+            if ((tid & 1) == 0)
+                neg_lse[s & 1][tid >> 1] = s * kMeanStageRows + (tid >> 1) < n_str ? -x : -INFINITY;
         }
     };
 
-    u32x4_t fr[NCX];      // streamed operand of one tile in matrix-operand layout, refilled in place
+    u32x4_t fr[NC];      // streamed operand of one tile in matrix-operand layout, refilled in place
     f32x16_t acc[2][HALVES];
     auto frag_ptr = [&](int t) {
         return lds[(t >> 2) & 1] + ((t & 3) * 32 + (lane & 31)) * STRIDE + 16 * g;
     };
-    // chunk c of tile t in matrix-operand layout (`base` = frag_ptr(t))
-    auto read_frag = [&](const unsigned char *base, int t, int c) {
-        if (DIRECT && c == NC)  // the lse chunk of pass 2
-            return *reinterpret_cast<const u32x4_t *>(lse_lds[(t >> 2) & 1] +
-                                                      ((t & 3) * 32 + (lane & 31)) * 32 + 16 * g);
+    // chunk c of a tile in matrix-operand layout (`base` = frag_ptr(t))
+    auto read_frag = [&](const unsigned char *base, int c) {
         return *reinterpret_cast<const u32x4_t *>(base + 32 * c);
     };
-    auto resident_frag = [&](int h, int c) {
+    auto multiply = [&](const f32x16_t &sum, int h, int c) {
         union {
             uint4 u;
             bf16x8_t v;
         } x;
-        x.u = c < NC ? kf[h][c < NC ? c : 0] : ones;
-        return x.v;
+        x.u = kf[h][c];
+        const bf16x8_t y = __builtin_bit_cast(bf16x8_t, fr[c]);
+        return PASS == 1 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(y, x.v, sum, 0, 0, 0)
+                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.v, y, sum, 0, 0, 0);
     };
+    // pass 2: -lse2 of this lane's streamed row, of the present and of the next tile
+    float row_lse[2];
+    auto read_lse = [&](int t) { return neg_lse[(t >> 2) & 1][(t & 3) * 32 + (lane & 31)]; };
 
-    float m_run[HALVES], l_run[HALVES], colsum[HALVES];
+    float m_run[HALVES], l_run[HALVES], colsum[HALVES][PASS == 2 ? 16 : 1];
     bool have_ref[HALVES];
 #pragma unroll
     for (int h = 0; h < HALVES; ++h) {
         m_run[h] = -INFINITY;
         l_run[h] = 0.f;
-        colsum[h] = 0.f;
         have_ref[h] = false;
+        if constexpr (PASS == 2) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) colsum[h][r] = 0.f;
+        }
     }
 
     // One pipeline step: the vector work of tile t (accumulators `cur`); when MULT is set, the
@@ -632,6 +678,7 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
         constexpr bool MULT = decltype(mult_tag)::value, REFILL = decltype(refill_tag)::value,
                        MASK = decltype(mask_tag)::value;
         float ref[HALVES], part[HALVES];
+        const float now = PASS == 2 ? row_lse[t & 1] : 0.f;
         if constexpr (PASS == 1) {
             if constexpr (MASK) {
 #pragma unroll
@@ -672,11 +719,9 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
                 // (the first chunk starts from a constant zero: no registers to clear)
                 const f32x16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                                        0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                nxt[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    __builtin_bit_cast(bf16x8_t, fr[c]), resident_frag(h, c), c == 0 ? zero : nxt[h],
-                    0, 0, 0);
+                nxt[h] = multiply(c == 0 ? zero : nxt[h], h, c);
                 if constexpr (REFILL) {
-                    if (h == HALVES - 1) fr[c] = read_frag(next_frags, t + 2, c);
+                    if (h == HALVES - 1) fr[c] = read_frag(next_frags, c);
                 }
             }
 #pragma unroll
@@ -685,14 +730,13 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
                 if constexpr (PASS == 1)
                     part[h] += __builtin_amdgcn_exp2f(fmaf(cur[h][r], sl2, -ref[h]));
                 else
-                    part[h] += __builtin_amdgcn_exp2f(cur[h][r] * sl2);
+                    colsum[h][r] += __builtin_amdgcn_exp2f(fmaf(cur[h][r], sl2, now));
             }
         }
+        if constexpr (PASS == 2 && REFILL) row_lse[t & 1] = read_lse(t + 2);
+        if constexpr (PASS == 1) {
 #pragma unroll
-        for (int h = 0; h < HALVES; ++h) {
-            if constexpr (PASS == 2) {
-                colsum[h] += part[h];
-            } else {
+            for (int h = 0; h < HALVES; ++h) {
                 if (part[h] < 0x1p100f) {
                     l_run[h] += part[h];
                 } else {  // a logit far above the reference: re-base on this tile's maximum
@@ -724,20 +768,20 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
     {
         const unsigned char *f0 = frag_ptr(0);
 #pragma unroll
-        for (int c = 0; c < NCX; ++c) fr[c] = read_frag(f0, 0, c);
+        for (int c = 0; c < NC; ++c) fr[c] = read_frag(f0, c);
+        if constexpr (PASS == 2) row_lse[0] = read_lse(0);
 #pragma unroll
         for (int h = 0; h < HALVES; ++h) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[0][h][r] = 0.f;
 #pragma unroll
-            for (int c = 0; c < NCX; ++c)
-                acc[0][h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    __builtin_bit_cast(bf16x8_t, fr[c]), resident_frag(h, c), acc[0][h], 0, 0, 0);
+            for (int c = 0; c < NC; ++c) acc[0][h] = multiply(acc[0][h], h, c);
         }
         if (ntiles > 1) {
             const unsigned char *f1 = frag_ptr(1);
 #pragma unroll
-            for (int c = 0; c < NCX; ++c) fr[c] = read_frag(f1, 1, c);
+            for (int c = 0; c < NC; ++c) fr[c] = read_frag(f1, c);
+            if constexpr (PASS == 2) row_lse[1] = read_lse(1);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -789,20 +833,28 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
         }
     }
 
-    // the two half-waves hold disjoint streamed rows of the same resident row
 #pragma unroll
     for (int h = 0; h < HALVES; ++h) {
-        const int row = blk * RB + (w * HALVES + h) * 32 + (lane & 31);
+        const int first_row = blk * RB + (w * HALVES + h) * 32, l = lane & 31;
         if constexpr (PASS == 1) {
+            // the two half-waves hold disjoint streamed rows of the same resident row
+            const int row = first_row + l;
             const float m_o = __shfl_xor(m_run[h], 32, kWave), l_o = __shfl_xor(l_run[h], 32, kWave);
             const float M = fmaxf(m_run[h], m_o);
             float L = 0.f;
             if (m_run[h] > -INFINITY) L += l_run[h] * __builtin_amdgcn_exp2f(m_run[h] - M);
             if (m_o > -INFINITY) L += l_o * __builtin_amdgcn_exp2f(m_o - M);
-            if (g == 0 && row < n_res) out[(int64_t)bh * n_res + row] = M + log2f(L);
+            if (g == 0 && row < n_res) {
+                if (parts == 1)
+                    lse[at + row] = M + log2_sum(L);
+                else
+                    pair[at + row] = make_float2(M, L);
+            }
         } else {
-            const float c = colsum[h] + __shfl_xor(colsum[h], 32, kWave);
-            if (g == 0 && row < n_res) out[(int64_t)bh * n_res + row] = c;
+            const float sum = resident_row_sum(colsum[h]);
+            const int row = first_row + 8 * (l >> 2) + 4 * g + (l & 3);
+            if (l < 16 && row < n_res)
+                (is_second ? second.head_scores : first.head_scores)[((int64_t)bh * parts + part) * n_res + row] = sum;
         }
     }
 }
@@ -890,22 +942,22 @@ static hipError_t launch_mean_pipe(const ScoreArgs &a, hipStream_t s, int pass) 
     const int key_first = a.domain_all ? 0 : a.has_cls;
     const int n_keys = a.S - key_first;
     constexpr int RB = 4 * 32 * HALVES;
-    // (two pairs: with workgroups of 256 rows a pair leaves most CUs one or two of them; the CUs that
-    // are done early take the other pair's.  2 images of 2745 tokens, 16 heads of 80: 68 + 68 -> 110 us)
-    const int pairs = pass == 1 && a.q2 ? 2 : 1;
-    const int total = pairs * a.BC * a.H * ((a.N + RB - 1) / RB);
+    const int pairs = (pass == 1 ? a.q2 != nullptr : a.head_scores2 != nullptr) ? 2 : 1;
+    const int total = pairs * a.BC * a.H * a.parts * ((a.N + RB - 1) / RB);
     const int grid = ((total + 7) / 8) * 8;
     const float sl2 = a.scale * 1.4426950408889634f;
     using Bytes = const unsigned char *;
     if (pass == 1)  // resident query rows (patch rows), streamed keys of the softmax domain
-        hipLaunchKernelGGL((mean_pipe_kernel<NC, HALVES, 1>), dim3(grid), dim3(256), 0, s,
-                           (MeanPair{(Bytes)a.q, (Bytes)a.k, nullptr, a.lse}),
-                           (MeanPair{(Bytes)a.q2, (Bytes)a.k2, nullptr, a.lse2}), pairs, a.BC * a.H,
-                           a.S, a.dh, row_first, a.N, key_first, n_keys, sl2);
-    else            // resident patch keys, streamed query rows (patch rows) with their lse
-        hipLaunchKernelGGL((mean_pipe_kernel<NC, HALVES, 2>), dim3(grid), dim3(256), 0, s,
-                           (MeanPair{(Bytes)a.k, (Bytes)a.q, a.lse, a.head_scores}), MeanPair{}, pairs,
-                           a.BC * a.H, a.S, a.dh, row_first, a.N, row_first, a.N, sl2);
+        hipLaunchKernelGGL((mean_pipe_kernel<NC, HALVES, 1, false>), dim3(grid), dim3(256), 0, s,
+                           (MeanPair{(Bytes)a.q, (Bytes)a.k, a.lse, nullptr}),
+                           (MeanPair{(Bytes)a.q2, (Bytes)a.k2, a.lse2, nullptr}), pairs,
+                           a.BC * a.H, a.S, a.dh, row_first, a.N, key_first, n_keys, a.parts, sl2);
+    else            // resident patch keys, streamed query rows (patch rows) with their log-sum-exps
+        hipLaunchKernelGGL((a.parts > 1 ? mean_pipe_kernel<NC, HALVES, 2, true> : mean_pipe_kernel<NC, HALVES, 2, false>),
+                           dim3(grid), dim3(256), 0, s,
+                           (MeanPair{(Bytes)a.k, (Bytes)a.q, a.lse, a.head_scores}),
+                           (MeanPair{(Bytes)a.k2, (Bytes)a.q2, a.lse2, a.head_scores2}), pairs,
+                           a.BC * a.H, a.S, a.dh, row_first, a.N, row_first, a.N, a.parts, sl2);
     return hipGetLastError();
 }
 

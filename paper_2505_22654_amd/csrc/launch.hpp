@@ -32,17 +32,44 @@ inline hipError_t allow_large_lds(Kernel kernel, std::atomic<uint64_t> &done,
 // encoder attention scoring (Eq. 1-2)
 struct ScoreArgs {
     const void *q, *k;    // [BC, H, S, dh]
-    float *head_scores;   // [BC, H, N] un-averaged per-head scores
-    float *lse;           // [BC, H, N] scratch, mean mode only
+    float *head_scores;   // [BC, H, N] un-averaged per-head scores; mean mode [BC, H, parts, N]
+    float *lse;           // [BC, H, N] scratch, mean mode only; parts > 1: [BC, H, parts, N] pairs
     int BC, H, S, dh, N;
     int has_cls, domain_all, is_bf16;
     float scale;
-    // a second pair for pass 1 to take along (mean_pair_launch), or NULL
+    // a second pair to take along (mean_pair_launch), or NULL: pass 1 always may, pass 2 where
+    // head_scores2 is given
     const void *q2 = nullptr, *k2 = nullptr;
     float *lse2 = nullptr;
+    int parts = 1;        // mean_parts
+    float *head_scores2 = nullptr;
 };
-// whether pass 1 of mean attention takes two pairs in one launch: the pipelined bf16 form
+// whether mean attention takes two pairs in one launch, and streamed rows in parts: the pipelined form
 inline bool mean_pair_launch(int is_bf16, int dh) { return is_bf16 && dh <= 80; }
+
+// Into how many parts the streamed rows of mean attention are cut.  A workgroup owns 256 resident rows of
+// a head and takes as long as its stages of streamed rows and about one and a half more (its own rows, the
+// first stage, the sums at the end); the launch takes as long as the CU with most workgroups.
+// A call in one part and in the number chosen, us (16 heads of 80 unless said): 324 tokens 55, 50 (3
+// parts); 576 and a second pair 85, 58 (4); 1023: 79, 64 (4); 1296, 8 heads of 64: 84, 61 (4); 2000: 113,
+// 91 (2); 7200, 12 heads of 64: 418, 372 (4); 10000: 871, 786 (2).  Where the line lies on one part the
+// next best number is no faster: 2745 tokens 140 and 140 (4 parts), 2 x 3120, 64 wide 211 and 220 (4).
+constexpr int kMeanMaxParts = 4;
+constexpr int kMeanStageRows = 128;
+constexpr double kMeanStart = 1.5;  // stages
+inline double mean_cost(int64_t heads, int N, int parts) {
+    const int64_t items = heads * ((N + 255) / 256);
+    const int stages = (N + kMeanStageRows - 1) / kMeanStageRows;
+    return (double)((items * parts + 255) / 256) * ((stages + parts - 1) / parts + kMeanStart);
+}
+inline int mean_parts(int is_bf16, int dh, int64_t heads, int N) {
+    int best = 1;
+    if (!mean_pair_launch(is_bf16, dh)) return best;
+    const int stages = (N + kMeanStageRows - 1) / kMeanStageRows;
+    for (int p = 2; p <= kMeanMaxParts && p <= stages; ++p)
+        if (mean_cost(heads, N, p) < 0.95 * mean_cost(heads, N, best)) best = p;
+    return best;
+}
 hipError_t launch_score_cls(const ScoreArgs &a, hipStream_t s);
 hipError_t launch_score_mean_lse(const ScoreArgs &a, hipStream_t s);     // pass 1
 hipError_t launch_score_mean_colsum(const ScoreArgs &a, hipStream_t s);  // pass 2

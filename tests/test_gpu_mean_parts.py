@@ -1,0 +1,52 @@
+"""Mean attention with its streamed rows cut into parts, and with two pairs in one launch: tiles and stages
+that end inside a part, parts of one stage, and the same call in a workspace without the room for either."""
+import pytest
+
+from paper_2505_22654_amd import binding as vb
+from paper_2505_22654_amd import workloads as wl
+from tests import parity_utils as pu
+from tests.test_gpu_parity import _enc
+
+pytestmark = pytest.mark.gpu
+
+
+def _one_part_bytes(shape, with_local):
+    """What a call needs without parts: head scores, log-sum-exps and the selection's and merge's scratch."""
+    up = lambda v: (v + 255) // 256 * 256
+    tokens, kept = shape.batch * shape.n_tokens, shape.batch * shape.keep
+    return ((3 if with_local else 2) * up(4 * tokens * shape.heads) + up(4 * (tokens - kept)) +
+            up(8 * tokens) + up(4 * kept) + up(4 * tokens) + up(tokens))
+
+
+# (dtype, batch, grid, heads, head size, second pair, [CLS] row in the tensors, softmax over it); `room`:
+# whether the call asks for more than one part's workspace
+@pytest.mark.parametrize("dtype,batch,gh,gw,heads,dh,local,cls,all_keys,room", [
+    (wl.BF16, 1, 8, 16, 2, 80, 0, 0, 0, False),   # one stage: one part
+    (wl.BF16, 1, 3, 43, 2, 80, 0, 0, 0, True),    # 129 rows: a second part of one row
+    (wl.BF16, 1, 15, 17, 3, 64, 0, 1, 1, True),   # 256 keys with the [CLS] row, 255 queries
+    (wl.BF16, 1, 16, 16, 3, 64, 0, 1, 1, True),   # 257 keys: a stage more than query stages
+    (wl.BF16, 2, 19, 27, 2, 32, 1, 0, 0, True),   # 513 rows, both pairs: four parts, the last of a row
+    (wl.BF16, 1, 24, 24, 16, 72, 1, 1, 0, True),  # two parts, rows that end inside a chunk
+    (wl.BF16, 1, 31, 33, 2, 80, 0, 0, 0, True),
+    (wl.BF16, 5, 18, 18, 30, 16, 1, 0, 0, True),  # both pairs in one launch, one part
+])
+def test_parts(dtype, batch, gh, gw, heads, dh, local, cls, all_keys, room):
+    shape = _enc(dtype, batch=batch, grid_h=gh, grid_w=gw, heads=heads, head_dim=dh, feat_dim=64,
+                 win_rows=2, win_cols=2, keep_global=9, keep_local=8, has_cls=cls, score_mode=1,
+                 softmax_domain=all_keys)
+    name = f"{batch}x{gh}x{gw}-{heads}-{dh}"
+    print("case", name, flush=True)
+    inp, loc, ref, info = pu.screened_encoder_case(shape, 8700 + gw, 0.25, bool(local), max_tries=2)
+    dev = lambda d, n: pu.to_device(d[n], shape.dtype)
+    args = [dev(inp, n) for n in ("q", "k", "x")] + ([dev(loc, n) for n in ("q", "k")] if loc else [])
+    import torch
+    size = vb.encoder_workspace_size(vb.encoder_desc(shape), bool(local))
+    least = _one_part_bytes(shape, local)
+    assert (size > least) == room
+    for n in {size, least}:
+        ws = torch.full((n,), 0xff, dtype=torch.uint8, device="cuda")  # every float a NaN
+        out = vb.encoder_reduce(shape, *args, want_assign=True, want_scores=True, workspace=ws)
+        torch.cuda.synchronize()
+        print(name, n, info, pu.check_encoder(shape, inp, ref, out, name), flush=True)
+    with pytest.raises(vb.VscanError):
+        vb.encoder_reduce(shape, *args, workspace=ws[:least - 1])
