@@ -105,24 +105,27 @@ int plan_encoder(const vscan_encoder_desc *d, int with_local, EncoderPlan *p) {
 struct MeanParts {
     int parts = 1;
     bool used = false;
-    size_t off_lse[2], off_scores[2], end;
+    size_t off_lse[2] = {}, off_scores[2] = {}, end = 0;
 };
 
+// `together`: both pairs can share launches; otherwise they are scored one after the other, with the
+// same statistics.
 MeanParts plan_mean_parts(const vscan_encoder_desc *d, const EncoderPlan &p, int scored_as_bf16,
-                          bool with_local, size_t base) {
+                          bool with_local, bool together, size_t base) {
     MeanParts m;
     m.end = base;
     if (d->score_mode != VSCAN_SCORE_MEAN_RECEIVED || !mean_pair_launch(scored_as_bf16, d->head_dim))
         return m;
-    const int pairs = with_local ? 2 : 1;
+    const int sets = with_local ? 2 : 1, pairs = together ? sets : 1;
     const int64_t heads = (int64_t)p.BC * d->heads;
     m.parts = mean_parts(scored_as_bf16, d->head_dim, heads * pairs, p.N);
-    m.used = mean_cost(heads * pairs, p.N, m.parts) < 0.95 * pairs * mean_cost(heads, p.N, 1);
+    const int block = mean_block_rows(scored_as_bf16, d->head_dim);
+    m.used = mean_cost(heads * pairs, p.N, block, m.parts) < 0.95 * pairs * mean_cost(heads, p.N, block, 1);
     if (!m.used) return m;
     const size_t rows = (size_t)heads * m.parts * p.N;
-    for (int i = 0; i < pairs; ++i) {
-        m.off_lse[i] = m.end;
-        m.end += align_up(rows * (m.parts > 1 ? 2 : 1) * sizeof(float));
+    for (int i = 0; i < sets; ++i) {
+        m.off_lse[i] = i < pairs ? m.end : m.off_lse[0];
+        if (i < pairs) m.end += align_up(rows * (m.parts > 1 ? 2 : 1) * sizeof(float));
         m.off_scores[i] = m.end;
         m.end += align_up(rows * sizeof(float));
     }
@@ -440,7 +443,7 @@ int vscan_encoder_workspace_size(const vscan_encoder_desc *desc, int with_local_
     EncoderPlan p;
     const int rc = plan_encoder(desc, with_local_pair != 0, &p);
     if (rc != VSCAN_OK) return rc;
-    *bytes = plan_mean_parts(desc, p, desc->dtype == VSCAN_BF16, with_local_pair != 0, p.bytes).end;
+    *bytes = plan_mean_parts(desc, p, desc->dtype == VSCAN_BF16, with_local_pair != 0, true, p.bytes).end;
     return VSCAN_OK;
 }
 
@@ -483,7 +486,7 @@ static int encoder_reduce_impl(const vscan_encoder_desc *d, const void *q, const
     sa.is_bf16 = d->dtype == VSCAN_BF16;
     sa.scale = resolve_scale(d->scale, d->head_dim);
     const float norm = mean ? 1.0f / ((float)d->heads * (float)p.N) : 1.0f / (float)d->heads;
-    const MeanParts mp = plan_mean_parts(d, p, sa.is_bf16, with_local, p.bytes);
+    const MeanParts mp = plan_mean_parts(d, p, sa.is_bf16, with_local, true, p.bytes);
     if (mp.used && workspace_bytes >= mp.end) {
         sa.parts = mp.parts;
         sa.lse = reinterpret_cast<float *>(ws + mp.off_lse[0]);
@@ -546,7 +549,7 @@ int vscan_encoder_fused_workspace_size(const vscan_encoder_desc *desc, int with_
     EncoderFusedPlan p;
     const int rc = plan_encoder_fused(desc, with_local_triple != 0, &p);
     if (rc != VSCAN_OK) return rc;
-    *bytes = p.bytes;
+    *bytes = plan_mean_parts(desc, p.e, 0, with_local_triple != 0, false, p.bytes).end;
     return VSCAN_OK;
 }
 
@@ -581,7 +584,15 @@ static int encoder_reduce_fused_impl(const vscan_encoder_desc *d, const void *hi
         ScoreArgs sa;
         sa.q = ws + p.off_qf;
         sa.k = ws + p.off_kf;
-        sa.lse = reinterpret_cast<float *>(ws + p.e.off_lse);
+        MeanParts mp = plan_mean_parts(d, p.e, 0, with_local, false, p.bytes);
+        if (!mp.used || workspace_bytes < mp.end) {
+            mp.parts = 1;
+            mp.off_lse[0] = mp.off_lse[1] = p.e.off_lse;
+            mp.off_scores[0] = p.e.off_head_global;
+            mp.off_scores[1] = p.e.off_head_local;
+        }
+        sa.parts = mp.parts;
+        sa.lse = reinterpret_cast<float *>(ws + mp.off_lse[0]);
         sa.BC = p.e.BC;
         sa.H = d->heads;
         sa.S = p.e.S;
@@ -608,14 +619,13 @@ static int encoder_reduce_fused_impl(const vscan_encoder_desc *d, const void *hi
             pa.w_k = ws + p.off_wk;
             pa.out_k = reinterpret_cast<float *>(ws + p.off_kf);
             VSCAN_LAUNCH("fused_project", launch_fused_project(pa, s));
-            sa.head_scores = reinterpret_cast<float *>(ws + (pass ? p.e.off_head_local : p.e.off_head_global));
+            sa.head_scores = reinterpret_cast<float *>(ws + mp.off_scores[pass]);
             VSCAN_LAUNCH("score_mean_lse", launch_score_mean_lse(sa, s));
             VSCAN_LAUNCH("score_mean_colsum", launch_score_mean_colsum(sa, s));
         }
-        return enqueue_encoder_tail(d, p.e, with_local, d->heads,
+        return enqueue_encoder_tail(d, p.e, with_local, d->heads * mp.parts,
                                     1.0f / ((float)d->heads * (float)p.e.N), x, kept_idx, merged,
-                                    assign_out, scores_out, ws, s, p.e.off_head_global,
-                                    p.e.off_head_local);
+                                    assign_out, scores_out, ws, s, mp.off_scores[0], mp.off_scores[1]);
     }
     // (a second triple overwrites the first one's rows)
     const bool keep_rows = !with_local && fused_keep_rows(d->heads, p.nk, p.e.N);

@@ -10,6 +10,7 @@
 //                then column sums of exp(s - lse_i); the N x N matrix is never
 //                stored)
 #include <type_traits>
+#include <utility>
 
 #include "common.hpp"
 #include "launch.hpp"
@@ -247,6 +248,53 @@ __device__ __forceinline__ float log2_sum(float l) {
     return y + 1.4426950408889634f * fmaf(l, __builtin_amdgcn_exp2f(-y), -1.0f);
 }
 
+// Sixteen logits of a lane's row into its running sum.  Lazy reference: exponentials are taken against a
+// per-lane reference m_run that is an actual logit of the row (so the sum is >= 1 and small terms may
+// underflow harmlessly) and is only raised when the partial sum threatens to overflow.  That removes the
+// per-element running max; the rescue path is rare.
+__device__ __forceinline__ void add_to_row_sum(const f32x16_t &acc, float sl2, float &m_run, float &l_run,
+                                               bool &have_ref) {
+    auto largest = [&] {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[r]);
+        return mx * sl2;
+    };
+    auto sum = [&](float m) {
+        float add = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) add += __builtin_amdgcn_exp2f(fmaf(acc[r], sl2, -m));
+        return add;
+    };
+    if (!have_ref) {
+        const float mx = largest();
+        if (mx > -INFINITY) {
+            m_run = mx;
+            have_ref = true;
+        }
+    }
+    if (have_ref) {
+        float add = sum(m_run);
+        if (add < 0x1p100f) {
+            l_run += add;
+        } else {  // a logit far above the reference: re-base on this tile's maximum
+            const float m_new = fmaxf(m_run, largest());
+            add = sum(m_new);
+            l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_new) + add;
+            m_run = m_new;
+        }
+    }
+}
+
+// The two half-waves hold disjoint streamed rows of the same resident row: reference and sum over both.
+__device__ __forceinline__ void join_half_waves(float m, float l, float &M, float &L) {
+    const float m_o = __shfl_xor(m, 32, kWave), l_o = __shfl_xor(l, 32, kWave);
+    M = fmaxf(m, m_o);
+    L = 0.f;
+    if (m > -INFINITY) L += l * __builtin_amdgcn_exp2f(m - M);
+    if (m_o > -INFINITY) L += l_o * __builtin_amdgcn_exp2f(m_o - M);
+}
+
 // Pass 1: lse2[i] = log2 sum_j 2^(sl2 * q_i . k_j) over the key domain.
 template <typename T, int NC>
 __global__ __launch_bounds__(256, 2) void mean_lse_kernel(const T *__restrict__ q,
@@ -304,69 +352,37 @@ __global__ __launch_bounds__(256, 2) void mean_lse_kernel(const T *__restrict__ 
                 for (int r = 0; r < 16; ++r)
                     if (key0 + acc_row(r) >= n_keys) acc[r] = -INFINITY;
             }
-            // Lazy reference: exponentials are taken against a per-lane reference m_run that
-            // is an actual logit of the row (so the sum is >= 1 and small terms may underflow
-            // harmlessly) and is only raised when the partial sum threatens to overflow.  That
-            // removes the per-element running max; the rescue path is rare.
-            if (!have_ref) {
-                float mx = -INFINITY;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[r]);
-                if (mx > -INFINITY) {
-                    m_run = mx * sl2;
-                    have_ref = true;
-                }
-            }
-            if (have_ref) {
-                float add = 0.f;
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    add += __builtin_amdgcn_exp2f(fmaf(acc[r], sl2, -m_run));
-                if (add < 0x1p100f) {
-                    l_run += add;
-                } else {  // a logit far above the reference: re-base on this tile's maximum
-                    float mx = -INFINITY;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[r]);
-                    const float m_new = fmaxf(m_run, mx * sl2);
-                    add = 0.f;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        add += __builtin_amdgcn_exp2f(fmaf(acc[r], sl2, -m_new));
-                    l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_new) + add;
-                    m_run = m_new;
-                }
-            }
+            add_to_row_sum(acc, sl2, m_run, l_run, have_ref);
         }
         if (t + 1 < ntiles) st.store(lds[(t + 1) & 1]);
         __syncthreads();
     }
-    // the two half-waves hold disjoint key subsets of the same query row
-    const float m_o = __shfl_xor(m_run, 32, kWave), l_o = __shfl_xor(l_run, 32, kWave);
-    const float M = fmaxf(m_run, m_o);
-    float L = 0.f;
-    if (m_run > -INFINITY) L += l_run * __builtin_amdgcn_exp2f(m_run - M);
-    if (m_o > -INFINITY) L += l_o * __builtin_amdgcn_exp2f(m_o - M);
+    float M, L;
+    join_half_waves(m_run, l_run, M, L);
     if (g == 0 && qrow < N) lse[(int64_t)bh * N + qrow] = M + log2_sum(L);
 }
 
 // Sum over the 32 streamed rows that the lanes of a half-wave hold, for each of the sixteen resident rows
 // of a 32x32 accumulator: lane l < 16 of half g gets the sum of resident row acc_row(l).  Every step
 // adds pairs of lanes and leaves each lane with half of the rows (31 exchanges instead of 80).
+template <int ROWS>  // lanes n < ROWS apart have yet to be added, ROWS rows are left to this one
 __device__ __forceinline__ float resident_row_sum(float (&v)[16]) {
-    const int l = lane_id();
+    if constexpr (ROWS == 16) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] += __shfl_xor(v[r], 16, kWave);
-#pragma unroll
-    for (int n = 8; n >= 1; n >>= 1) {
-        const bool upper = (l & n) != 0;
+        for (int r = 0; r < 16; ++r) v[r] += __shfl_xor(v[r], 16, kWave);
+    }
+    if constexpr (ROWS > 1) {
+        constexpr int n = ROWS / 2;
+        const bool upper = (lane_id() & n) != 0;
 #pragma unroll
         for (int r = 0; r < n; ++r) {
             const float mine = upper ? v[r + n] : v[r], other = upper ? v[r] : v[r + n];
             v[r] = mine + __shfl_xor(other, n, kWave);
         }
+        return resident_row_sum<n>(v);
+    } else {
+        return v[0];
     }
-    return v[0];
 }
 
 // Pass 2: head_scores[j] = sum_i 2^(sl2 * q_i . k_j - lse2[i]) for patch keys j.
@@ -445,13 +461,13 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict
         }
         __syncthreads();
     }
-    const float sum = resident_row_sum(colsum);
+    const float sum = resident_row_sum<16>(colsum);
     const int l = lane & 31, out_key = kb * kMeanBlock + w * 32 + 8 * (l >> 2) + 4 * g + (l & 3);
     if (l < 16 && out_key < N) head_scores[(int64_t)bh * N + out_key] = sum;
 }
 
 // ---------------------------------------------------------------------------
-// Both passes for bf16 rows of up to 160 bytes, software-pipelined inside each wave.
+// Both passes for bf16 rows of up to 160 bytes and for fp32, software-pipelined inside each wave.
 //
 // Measured on this GPU (issue rates in core cycles per wave instruction): v_fma / v_mul / v_add
 // 4, v_exp_f32 8, a 32x32x16 matrix instruction occupies the matrix pipe for 32 and takes about
@@ -473,7 +489,7 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict
 // lane % 32 and sixteen streamed rows), in pass 2 its rows (a lane owns streamed row lane % 32 and sums
 // for its sixteen resident rows; the lanes are added once, at the end).  Subtracting the reference is
 // the multiply-add that scales the logit.  (Pass 2 had the log-sum-exp as one more 32-byte chunk of the
-// contraction before, a sixth more matrix instructions: 16384 tokens, 16 heads of 80, 911 -> 861 us.)  Rows past the end carry -inf and contribute 2^-inf = 0.
+// contraction before, a sixth more matrix instructions: 16384 tokens, 16 heads of 80, 911 -> 851 us.)  Rows past the end carry -inf and contribute 2^-inf = 0.
 //
 // With `parts` > 1 the streamed rows are cut into runs of whole stages with a workgroup each
 // (mean_parts): pass 1 leaves a reference m and l = sum_j 2^(sl2 * q_i . k_j - m) per row and part, which
@@ -519,25 +535,103 @@ __device__ __forceinline__ float merged_lse(const float2 (&p)[kMeanMaxParts / 2]
     return m + log2_sum(group_sum<2>(l));
 }
 
+// fp32 on the bf16 matrix instructions: an fp32 value is the sum of three bf16 values (each the rounding of
+// what the previous ones left over: 24 significant bits, the same exponents), a product of two fp32 values
+// the sum of nine products of bf16 values, which are exact.  Six are formed; the three left out (mid x lo,
+// lo x mid, lo x lo) are below 2^-26 of the product, under the rounding of an fp32 product itself.  The
+// small products are added first, so that only the last, hi x hi, are rounded at the size of the result: 5
+// roundings for rows of 80 instead of the 40 of fp32 instructions.  Error of the scores against 64 bits (2-norm;
+// 24 calls of 324 to 3500 tokens on fp32 rows, given or projected): 2.4e-7 on average and 6.9e-7 at worst with
+// fp32 instructions, 1.2e-7 and 3.3e-7 so.
+// Six bf16 instructions take the matrix pipe 192 cycles, the eight fp32 instructions for the same chunk 512.
+// That is still four times what the vector work of a tile takes, so the matrix pipe is the bound: one
+// workgroup a CU (up to 512 registers a lane), whose waves never wait for anything but the pipe: the planes of
+// the resident rows and of a whole tile of streamed rows are in registers, and the streamed rows are split
+// once per workgroup on their way into LDS, a few at a time between the matrix instructions.
+// 2688 tokens, 16 heads of 80: 277 + 276 -> 145 + 134 us for the two passes; 16384 tokens, a call: 13.2 -> 7.2 ms,
+// 1.2 PFLOP/s in the passes, which is what an 8192^3 product of the bf16 library reaches on this card.
+template <typename T>
+struct MeanForm;
+template <>
+struct MeanForm<bf16_t> {
+    static constexpr int kPlanes = 1, kProducts = 1;
+    static constexpr int kWorkgroupsPerCu = 2;
+    static __device__ constexpr int streamed_plane(int) { return 0; }
+    static __device__ constexpr int resident_plane(int) { return 0; }
+};
+template <>
+struct MeanForm<float> {
+    static constexpr int kPlanes = 3, kProducts = 6;  // planes hi, mid, lo
+    static constexpr int kWorkgroupsPerCu = 1;
+    static __device__ constexpr int streamed_plane(int p) { return p == 0 ? 2 : p < 3 ? 1 : 0; }
+    static __device__ constexpr int resident_plane(int p) { return p == 1 || p == 4 ? 1 : p == 3 ? 2 : 0; }
+};
+
+// eight consecutive elements -> their planes
+__device__ __forceinline__ void split_planes(const uint4 &a, const uint4 &b, uint4 *out) {
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    float v[8];
+    unpack16<float>(a, v);
+    unpack16<float>(b, v + 4);
+#pragma unroll
+    for (int p = 0; p < MeanForm<float>::kPlanes; ++p) {
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f32x2_t two = {v[2 * i], v[2 * i + 1]};
+            w[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2_t));
+            v[2 * i] -= bf16_lo(w[i]);  // exact
+            v[2 * i + 1] -= bf16_hi(w[i]);
+        }
+        out[p] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+}
+
 // (PARTED, pass 2: the statistics come in parts.  A branch on `parts` where they are fetched would wait,
 // where its sides join, for every load in flight.)
-template <int NC, int HALVES, int PASS, bool PARTED>
-__global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
+// f(0), ..., f(N - 1) with constants
+template <int... I, typename F>
+__device__ __forceinline__ void for_constants(std::integer_sequence<int, I...>, F f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// LDS of the kernel below: two stages of kRows streamed rows, in dynamic LDS where they pass 64 KB.
+template <typename T, int NC, int PASS>
+struct MeanLds {
+    static constexpr int kPlanes = MeanForm<T>::kPlanes;
+    static constexpr int kRows = kPlanes * NC * 32 * 2 * 128 > 144 * 1024 ? 64 : 128;
+    static constexpr int kStride = kPlanes * NC * 32 + (kPlanes == 1 && (NC & 1) ? 0 : 16);
+    static constexpr int kBytes = 2 * kRows * kStride;
+    static constexpr bool kDynamic = kBytes > 62 * 1024;
+};
+
+template <typename T, int NC, int HALVES, int PASS, bool PARTED>
+__global__ __launch_bounds__(256, MeanForm<T>::kWorkgroupsPerCu) void mean_pipe_kernel(
     MeanPair first, MeanPair second, int pairs, int n_heads, int S, int dh, int res_first, int n_res,
     int str_first, int n_streamed, int parts, float sl2) {
+    using Form = MeanForm<T>;
+    constexpr int PL = Form::kPlanes;
+    constexpr bool SPLIT = PL > 1;
     // With an odd number of 32-byte chunks per row the unpadded row pitch serves the 16-byte
     // operand reads at 92 % of the LDS rate (measured; 25 % for an even number), and a stage
     // is then one contiguous block in memory and in LDS alike: it is fetched with direct loads.
-    // Otherwise: padded rows (pitch 32 NC + 16, conflict-free) staged through registers.
-    constexpr bool DIRECT = (NC & 1) != 0;
-    constexpr int STRIDE = DIRECT ? NC * 32 : NC * 32 + 16;
-    constexpr int PPR = NC * 2;                        // 16-byte pieces per streamed row in memory
+    // Otherwise: padded rows (an odd number of 16-byte pieces, conflict-free) staged through registers.
+    constexpr bool DIRECT = !SPLIT && (NC & 1) != 0;
+    using Lds = MeanLds<T, NC, PASS>;
+    constexpr int ROWS = Lds::kRows, TILES = ROWS / 32, STRIDE = Lds::kStride;
+    constexpr int PPR = NC * 2;                        // 16-byte pieces per plane of a streamed row
+    constexpr int PER = (ROWS * PPR + 255) / 256;      // pieces per thread and stage
     constexpr int RB = 4 * 32 * HALVES;                // resident rows per workgroup
-    constexpr int NM = NC * HALVES;                    // matrix instructions per tile
+    constexpr int NM = Form::kProducts * NC * HALVES;  // matrix instructions per tile
     constexpr int NL = 16 * HALVES;                    // logits per lane and tile
-    static_assert(kMeanStageRows * PPR == 256 * NC, "NC pieces per thread and stage");
-    __shared__ __align__(16) unsigned char lds[2][kMeanStageRows * STRIDE];
-    __shared__ __align__(16) float neg_lse[2][PASS == 2 ? kMeanStageRows : 1];
+    static_assert(ROWS * PPR == 256 * PER, "PER pieces per thread and stage");
+    static_assert((TILES & (TILES - 1)) == 0 && kMeanStageRows % ROWS == 0, "whole stages per part");
+    extern __shared__ __align__(16) unsigned char dynamic_lds[];
+    __shared__ __align__(16) unsigned char static_lds[Lds::kDynamic ? 16 : 2 * ROWS * STRIDE];
+    unsigned char *const lds_base = Lds::kDynamic ? dynamic_lds : static_lds;
+    auto lds = [&](int buffer) { return lds_base + buffer * (ROWS * STRIDE); };
+    __shared__ __align__(16) float neg_lse[2][PASS == 2 ? ROWS : 1];
 
     const int nblk = (n_res + RB - 1) / RB;
     const int total = pairs * n_heads * parts * nblk;
@@ -549,7 +643,7 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
     const int part = run - bh * parts;
     const bool is_second = bh >= n_heads;
     if (is_second) bh -= n_heads;
-    const int row_bytes = dh * 2;
+    const int row_bytes = dh * (int)sizeof(T);
     // this part's stages of the streamed rows
     const int all_stages = (n_streamed + kMeanStageRows - 1) / kMeanStageRows;
     const int row0 = part * all_stages / parts * kMeanStageRows;
@@ -563,44 +657,52 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
     const int64_t at = PASS == 1 ? ((int64_t)bh * parts + part) * n_res : (int64_t)bh * parts * n_streamed + row0;
 
     const int tid = threadIdx.x, lane = lane_id(), g = lane >> 5, w = wave_id();
-    uint4 kf[HALVES][NC];
+    uint4 kf[HALVES][NC][PL];
 #pragma unroll
     for (int h = 0; h < HALVES; ++h) {
         const int row = blk * RB + (w * HALVES + h) * 32 + (lane & 31);
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-            kf[h][c] = load16_guard(rbase, (int64_t)row * row_bytes + 32 * c + 16 * g,
-                                    row < n_res && 32 * c + 16 * g < row_bytes);
+        for (int c = 0; c < NC; ++c) {
+            const int64_t off = (int64_t)row * row_bytes + (16 * c + 8 * g) * (int)sizeof(T);
+            const bool valid = row < n_res && 16 * c + 8 * g < dh;  // dh is a multiple of eight
+            const uint4 a = load16_guard(rbase, off, valid);
+            if constexpr (SPLIT)
+                split_planes(a, load16_guard(rbase, off + 16, valid), kf[h][c]);
+            else
+                kf[h][c][0] = a;
+        }
     }
     const int ntiles = (n_str + 31) >> 5;
-    const int nstages = (n_str + kMeanStageRows - 1) / kMeanStageRows;
+    const int nstages = (n_str + ROWS - 1) / ROWS;
 
     // ---- staging of the streamed operand: thread t carries pieces t, t + 256, ... of a stage
-    uint4 sreg[DIRECT ? 1 : NC];
+    // (fp32: of eight elements, which become a piece of every plane)
+    uint4 sreg[DIRECT ? 1 : PER][SPLIT ? 2 : 1];
     // pass 2: threads 2r and 2r + 1 carry the statistics of a stage's row r, two parts each
     float2 stat_reg[PARTED ? kMeanMaxParts / 2 : 1];
     const int first_part = (tid & 1) * (kMeanMaxParts / 2);
-    auto stage_load = [&](int s) {
+    auto stage_load = [&](int s) __attribute__((always_inline)) {
 #pragma unroll
-        for (int it = 0; it < NC; ++it) {
+        for (int it = 0; it < PER; ++it) {
             const int p = tid + it * 256;
             const int r = p / PPR, piece = p - r * PPR;
             // clamped, not predicated: rows past the end re-read the last row (finite data that
             // the consumers neutralise), pieces past the end of a row its last piece (the
             // resident operand is zero there)
-            const int row = min(s * kMeanStageRows + r, n_str - 1);
-            const int64_t off = (int64_t)row * row_bytes + min(piece * 16, row_bytes - 16);
+            const int row = min(s * ROWS + r, n_str - 1);
+            const int64_t off = (int64_t)row * row_bytes + min(piece * 8, dh - 8) * (int)sizeof(T);
             if constexpr (DIRECT) {
                 // piece p of the stage goes to byte 16 p of the stage's buffer: the wave's 64
                 // pieces of this round form one contiguous kilobyte
                 direct_load16(sbase + off, __builtin_amdgcn_readfirstlane(lds_byte_address(
-                                               lds[s & 1] + 16 * (it * 256 + w * kWave))));
+                                               lds(s & 1) + 16 * (it * 256 + w * kWave))));
             } else {
-                sreg[it] = load16(sbase, off);
+                sreg[it][0] = load16(sbase, off);
+                if constexpr (SPLIT) sreg[it][1] = load16(sbase, off + 16);
             }
         }
         if constexpr (PASS == 2) {
-            const int64_t row = at + min(s * kMeanStageRows + (tid >> 1), n_str - 1);
+            const int64_t row = at + min(s * ROWS + min(tid >> 1, ROWS - 1), n_str - 1);
             if constexpr (!PARTED) {
                 stat_reg[0].x = lse[row];
             } else {
@@ -610,17 +712,25 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
             }
         }
     };
-    auto stage_store = [&](int s) {
-        unsigned char *dst = lds[s & 1];
+    auto piece_store = [&](int s, int it) __attribute__((always_inline)) {
+        const int p = tid + it * 256;
+        const int r = p / PPR, piece = p - r * PPR;
+        unsigned char *dst = lds(s & 1) + r * STRIDE + piece * 16;
+        uint4 out[PL];
+        if constexpr (SPLIT)
+            split_planes(sreg[it][0], sreg[it][1], out);
+        else
+            out[0] = sreg[it][0];
+#pragma unroll
+        for (int pl = 0; pl < PL; ++pl) *reinterpret_cast<uint4 *>(dst + pl * NC * 32) = out[pl];
+    };
+    // `spread`: the pieces are in LDS already
+    auto stage_store = [&](int s, bool spread) __attribute__((always_inline)) {
         if constexpr (DIRECT) {
             wait_direct_loads();  // this wave's share of the stage is in LDS
-        } else {
+        } else if (!spread) {
 #pragma unroll
-            for (int it = 0; it < NC; ++it) {
-                const int p = tid + it * 256;
-                const int r = p / PPR, piece = p - r * PPR;
-                *reinterpret_cast<uint4 *>(dst + r * STRIDE + piece * 16) = sreg[it];
-            }
+            for (int it = 0; it < PER; ++it) piece_store(s, it);
         }
         if constexpr (PASS == 2) {
             float x;
@@ -628,33 +738,34 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
                 x = merged_lse(stat_reg, first_part, parts);
             else
                 x = stat_reg[0].x;
-            if ((tid & 1) == 0)
-                neg_lse[s & 1][tid >> 1] = s * kMeanStageRows + (tid >> 1) < n_str ? -x : -INFINITY;
+            if ((tid & 1) == 0 && tid < 2 * ROWS)
+                neg_lse[s & 1][tid >> 1] = s * ROWS + (tid >> 1) < n_str ? -x : -INFINITY;
         }
     };
 
-    u32x4_t fr[NC];      // streamed operand of one tile in matrix-operand layout, refilled in place
+    u32x4_t fr[PL][NC];      // streamed operand of one tile in matrix-operand layout, refilled in place
     f32x16_t acc[2][HALVES];
     auto frag_ptr = [&](int t) {
-        return lds[(t >> 2) & 1] + ((t & 3) * 32 + (lane & 31)) * STRIDE + 16 * g;
+        return lds((t / TILES) & 1) + ((t & (TILES - 1)) * 32 + (lane & 31)) * STRIDE + 16 * g;
     };
     // chunk c of a tile in matrix-operand layout (`base` = frag_ptr(t))
-    auto read_frag = [&](const unsigned char *base, int c) {
-        return *reinterpret_cast<const u32x4_t *>(base + 32 * c);
+    auto read_frag = [&](const unsigned char *base, int pl, int c) {
+        return *reinterpret_cast<const u32x4_t *>(base + 32 * (pl * NC + c));
     };
-    auto multiply = [&](const f32x16_t &sum, int h, int c) {
+    // product p of chunk c
+    auto multiply = [&](const f32x16_t &sum, int h, int p, int c) {
         union {
             uint4 u;
             bf16x8_t v;
         } x;
-        x.u = kf[h][c];
-        const bf16x8_t y = __builtin_bit_cast(bf16x8_t, fr[c]);
+        x.u = kf[h][c][Form::resident_plane(p)];
+        const bf16x8_t y = __builtin_bit_cast(bf16x8_t, fr[Form::streamed_plane(p)][c]);
         return PASS == 1 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(y, x.v, sum, 0, 0, 0)
                          : __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.v, y, sum, 0, 0, 0);
     };
     // pass 2: -lse2 of this lane's streamed row, of the present and of the next tile
     float row_lse[2];
-    auto read_lse = [&](int t) { return neg_lse[(t >> 2) & 1][(t & 3) * 32 + (lane & 31)]; };
+    auto read_lse = [&](int t) { return neg_lse[(t / TILES) & 1][(t & (TILES - 1)) * 32 + (lane & 31)]; };
 
     float m_run[HALVES], l_run[HALVES], colsum[HALVES][PASS == 2 ? 16 : 1];
     bool have_ref[HALVES];
@@ -669,18 +780,18 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
         }
     }
 
-    // One pipeline step: the vector work of tile t (accumulators `cur`); when MULT is set, the
-    // matrix instructions of tile t + 1 (operands in `fr`, accumulators `nxt`) are issued in
-    // between, and every operand chunk is refilled with tile t + 2's (REFILL) right after its
-    // last use.  MASK: tile t is the ragged last tile of pass 1.
-    auto step = [&](int t, f32x16_t(&cur)[HALVES], f32x16_t(&nxt)[HALVES], auto mult_tag,
-                    auto refill_tag, auto mask_tag) {
-        constexpr bool MULT = decltype(mult_tag)::value, REFILL = decltype(refill_tag)::value,
-                       MASK = decltype(mask_tag)::value;
+    // One pipeline step: the vector work of tile t (accumulators `cur`), with the matrix instructions of
+    // tile t + 1 (operands in `fr`, accumulators `nxt`) issued in between; every operand chunk is refilled
+    // with tile t + 2's right after its last use, and `between(m)` runs behind matrix instruction m.
+    // (Past the last tile the refills read what lies there and nobody uses it.)  LAST: tile t is the last
+    // one, nothing is multiplied.
+    auto step = [&](int t, f32x16_t(&cur)[HALVES], f32x16_t(&nxt)[HALVES], auto last_tag,
+                    auto between) __attribute__((always_inline)) {
+        constexpr bool LAST = decltype(last_tag)::value;
         float ref[HALVES], part[HALVES];
         const float now = PASS == 2 ? row_lse[t & 1] : 0.f;
         if constexpr (PASS == 1) {
-            if constexpr (MASK) {
+            if (LAST && (n_str & 31) != 0) {
 #pragma unroll
                 for (int h = 0; h < HALVES; ++h)
 #pragma unroll
@@ -706,23 +817,23 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
         }
 #pragma unroll
         for (int h = 0; h < HALVES; ++h) part[h] = 0.f;
-        const unsigned char *next_frags = REFILL ? frag_ptr(t + 2) : nullptr;
+        const unsigned char *next_frags = frag_ptr(t + 2);
         // Slot by slot: one matrix instruction, the LDS read that refills an operand chunk
-        // after its last use, and a slice of tile t's logits (about three: forty cycles of
+        // after its last use, and a slice of tile t's logits (one plane: about three, forty cycles of
         // vector work, which is what one matrix instruction keeps its pipe busy for).  (Pinning
         // this order with scheduling groups, or tying the step's inputs to this point with
         // empty asm statements, measured the same as leaving the order to the compiler.)
-#pragma unroll
-        for (int m = 0; m < NM; ++m) {
-            if constexpr (MULT) {
-                const int c = m / HALVES, h = m % HALVES;
+        for_constants(std::make_integer_sequence<int, NM>{}, [&](auto slot) __attribute__((always_inline)) {
+            constexpr int m = decltype(slot)::value;
+            if constexpr (!LAST) {
+                constexpr int p = m / (NC * HALVES), c = m / HALVES % NC, h = m % HALVES;
                 // (the first chunk starts from a constant zero: no registers to clear)
                 const f32x16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                                        0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                nxt[h] = multiply(c == 0 ? zero : nxt[h], h, c);
-                if constexpr (REFILL) {
-                    if (h == HALVES - 1) fr[c] = read_frag(next_frags, c);
-                }
+                nxt[h] = multiply(m < HALVES ? zero : nxt[h], h, p, c);
+                constexpr int sp = Form::streamed_plane(p);
+                constexpr bool used = p + 1 == Form::kProducts || Form::streamed_plane(p + 1) != sp;
+                if constexpr (h == HALVES - 1 && used) fr[sp][c] = read_frag(next_frags, sp, c);
             }
 #pragma unroll
             for (int i = m * NL / NM; i < (m + 1) * NL / NM; ++i) {
@@ -732,8 +843,9 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
                 else
                     colsum[h][r] += __builtin_amdgcn_exp2f(fmaf(cur[h][r], sl2, now));
             }
-        }
-        if constexpr (PASS == 2 && REFILL) row_lse[t & 1] = read_lse(t + 2);
+            between(slot);
+        });
+        if constexpr (PASS == 2 && !LAST) row_lse[t & 1] = read_lse(t + 2);
         if constexpr (PASS == 1) {
 #pragma unroll
             for (int h = 0; h < HALVES; ++h) {
@@ -762,88 +874,88 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
 
     // ---- prologue: stage 0 in LDS, stage 1 in flight, tile 0 multiplied, tile 1's operands read
     stage_load(0);
-    stage_store(0);
+    stage_store(0, false);
     __syncthreads();
     if (nstages > 1) stage_load(1);
     {
         const unsigned char *f0 = frag_ptr(0);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) fr[c] = read_frag(f0, c);
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int pl = 0; pl < PL; ++pl) fr[pl][c] = read_frag(f0, pl, c);
         if constexpr (PASS == 2) row_lse[0] = read_lse(0);
 #pragma unroll
         for (int h = 0; h < HALVES; ++h) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[0][h][r] = 0.f;
 #pragma unroll
-            for (int c = 0; c < NC; ++c) acc[0][h] = multiply(acc[0][h], h, c);
+            for (int m = 0; m < Form::kProducts * NC; ++m) acc[0][h] = multiply(acc[0][h], h, m / NC, m % NC);
         }
         if (ntiles > 1) {
             const unsigned char *f1 = frag_ptr(1);
 #pragma unroll
-            for (int c = 0; c < NC; ++c) fr[c] = read_frag(f1, c);
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int pl = 0; pl < PL; ++pl) fr[pl][c] = read_frag(f1, pl, c);
             if constexpr (PASS == 2) row_lse[1] = read_lse(1);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
 
-    const bool ragged = PASS == 1 && (n_str & 31) != 0;
+    const auto nothing = [](auto) {};
     int t0 = 0;
-    // Steady state, four tiles (one stage) per trip: every step here has a tile t + 2 to fetch
-    // operands for and a tile t + 1 to multiply, so the body is straight-line code.
-    for (; t0 + 6 <= ntiles; t0 += 4) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t = t0 + j;
-            if (j == 2) {
-                // the next stage goes to LDS now (its loads were issued four tiles ago), and
-                // the one after it takes over the staging registers
-                const int s = t >> 2;
-                stage_store(s + 1);
+    // Steady state, one stage per trip: straight-line code.  The next stage goes to LDS (its loads were
+    // issued a stage ago) before the last two tiles, the first to fetch operands from it, and the one
+    // after it takes over the staging registers.  Where it is split on the way, the pieces go one by one
+    // between the matrix instructions of the tiles before: their place in LDS has been free since the
+    // last barrier.
+    constexpr bool SPREAD = SPLIT && TILES == 4;
+    for (; t0 + TILES + 2 <= ntiles; t0 += TILES) {
+        const int s = t0 / TILES;
+        for_constants(std::make_integer_sequence<int, TILES>{}, [&](auto tile) __attribute__((always_inline)) {
+            constexpr int j = decltype(tile)::value;
+            if constexpr (j == TILES - 2) {
+                stage_store(s + 1, SPREAD);
                 __syncthreads();
                 if (s + 2 < nstages) stage_load(s + 2);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            step(t, acc[j & 1], acc[(j + 1) & 1], yes{}, yes{}, no{});
-        }
+            step(t0 + j, acc[j & 1], acc[(j + 1) & 1], no{}, [&](auto slot) __attribute__((always_inline)) {
+                constexpr int m = decltype(slot)::value;
+                constexpr int EACH = (PER + 1) / 2, GAP = NM / EACH;  // pieces per tile of the first two
+                constexpr int piece = j * EACH + m / GAP;
+                if constexpr (SPREAD && j < 2 && m % GAP == GAP / 2 && m / GAP < EACH && piece < PER)
+                    piece_store(s + 1, piece);
+            });
+        });
     }
-    // The last tiles: the same steps with their conditions spelled out.
-    for (; t0 < ntiles; t0 += 4) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t = t0 + j;
-            if (t < ntiles) {
-                if (j == 2) {
-                    const int s = t >> 2;
-                    if (s + 1 < nstages) {
-                        stage_store(s + 1);
-                        __syncthreads();
-                        if (s + 2 < nstages) stage_load(s + 2);
-                    }
+    // The last tiles.
+    for (; t0 + 1 < ntiles; t0 += TILES) {
+        const int s = t0 / TILES;
+        for_constants(std::make_integer_sequence<int, TILES>{}, [&](auto tile) __attribute__((always_inline)) {
+            constexpr int j = decltype(tile)::value;
+            if (t0 + j + 1 < ntiles) {
+                if (j == TILES - 2 && s + 1 < nstages) {
+                    stage_store(s + 1, false);
+                    __syncthreads();
+                    if (s + 2 < nstages) stage_load(s + 2);
                 }
-                if (t + 2 < ntiles) {
-                    step(t, acc[j & 1], acc[(j + 1) & 1], yes{}, yes{}, no{});
-                } else if (t + 1 < ntiles) {
-                    step(t, acc[j & 1], acc[(j + 1) & 1], yes{}, no{}, no{});
-                } else if (ragged) {
-                    step(t, acc[j & 1], acc[(j + 1) & 1], no{}, no{}, yes{});
-                } else {
-                    step(t, acc[j & 1], acc[(j + 1) & 1], no{}, no{}, no{});
-                }
+                step(t0 + j, acc[j & 1], acc[(j + 1) & 1], no{}, nothing);
             }
-        }
+        });
     }
+    if (ntiles & 1)
+        step(ntiles - 1, acc[0], acc[1], yes{}, nothing);
+    else
+        step(ntiles - 1, acc[1], acc[0], yes{}, nothing);
 
 #pragma unroll
     for (int h = 0; h < HALVES; ++h) {
         const int first_row = blk * RB + (w * HALVES + h) * 32, l = lane & 31;
         if constexpr (PASS == 1) {
-            // the two half-waves hold disjoint streamed rows of the same resident row
             const int row = first_row + l;
-            const float m_o = __shfl_xor(m_run[h], 32, kWave), l_o = __shfl_xor(l_run[h], 32, kWave);
-            const float M = fmaxf(m_run[h], m_o);
-            float L = 0.f;
-            if (m_run[h] > -INFINITY) L += l_run[h] * __builtin_amdgcn_exp2f(m_run[h] - M);
-            if (m_o > -INFINITY) L += l_o * __builtin_amdgcn_exp2f(m_o - M);
+            float M, L;
+            join_half_waves(m_run[h], l_run[h], M, L);
             if (g == 0 && row < n_res) {
                 if (parts == 1)
                     lse[at + row] = M + log2_sum(L);
@@ -851,7 +963,7 @@ __global__ __launch_bounds__(256, 2) void mean_pipe_kernel(
                     pair[at + row] = make_float2(M, L);
             }
         } else {
-            const float sum = resident_row_sum(colsum[h]);
+            const float sum = resident_row_sum<16>(colsum[h]);
             const int row = first_row + 8 * (l >> 2) + 4 * g + (l & 3);
             if (l < 16 && row < n_res)
                 (is_second ? second.head_scores : first.head_scores)[((int64_t)bh * parts + part) * n_res + row] = sum;
@@ -935,8 +1047,8 @@ static hipError_t launch_score_mean_nc(const ScoreArgs &a, hipStream_t s, int pa
     return hipGetLastError();
 }
 
-// The pipelined form: bf16 rows of up to 160 bytes (head sizes up to 80).
-template <int NC, int HALVES>
+// The forms that take pairs and parts (mean_pair_launch).
+template <typename T, int NC, int HALVES>
 static hipError_t launch_mean_pipe(const ScoreArgs &a, hipStream_t s, int pass) {
     const int row_first = a.has_cls;
     const int key_first = a.domain_all ? 0 : a.has_cls;
@@ -947,42 +1059,49 @@ static hipError_t launch_mean_pipe(const ScoreArgs &a, hipStream_t s, int pass) 
     const int grid = ((total + 7) / 8) * 8;
     const float sl2 = a.scale * 1.4426950408889634f;
     using Bytes = const unsigned char *;
+    constexpr auto pass1 = mean_pipe_kernel<T, NC, HALVES, 1, false>, pass2 = mean_pipe_kernel<T, NC, HALVES, 2, false>,
+                   pass2_parted = mean_pipe_kernel<T, NC, HALVES, 2, true>;
+    using Lds = MeanLds<T, NC, 1>;
+    constexpr int lds = Lds::kDynamic ? Lds::kBytes : 0;
+    if constexpr (Lds::kDynamic) {
+        static std::atomic<uint64_t> allowed[3];
+        hipError_t e = pass == 1 ? allow_large_lds(pass1, allowed[0], lds)
+                       : a.parts > 1 ? allow_large_lds(pass2_parted, allowed[1], lds)
+                                     : allow_large_lds(pass2, allowed[2], lds);
+        if (e != hipSuccess) return e;
+    }
     if (pass == 1)  // resident query rows (patch rows), streamed keys of the softmax domain
-        hipLaunchKernelGGL((mean_pipe_kernel<NC, HALVES, 1, false>), dim3(grid), dim3(256), 0, s,
+        hipLaunchKernelGGL(pass1, dim3(grid), dim3(256), lds, s,
                            (MeanPair{(Bytes)a.q, (Bytes)a.k, a.lse, nullptr}),
                            (MeanPair{(Bytes)a.q2, (Bytes)a.k2, a.lse2, nullptr}), pairs,
                            a.BC * a.H, a.S, a.dh, row_first, a.N, key_first, n_keys, a.parts, sl2);
     else            // resident patch keys, streamed query rows (patch rows) with their log-sum-exps
-        hipLaunchKernelGGL((a.parts > 1 ? mean_pipe_kernel<NC, HALVES, 2, true> : mean_pipe_kernel<NC, HALVES, 2, false>),
-                           dim3(grid), dim3(256), 0, s,
+        hipLaunchKernelGGL((a.parts > 1 ? pass2_parted : pass2), dim3(grid), dim3(256), lds, s,
                            (MeanPair{(Bytes)a.k, (Bytes)a.q, a.lse, a.head_scores}),
                            (MeanPair{(Bytes)a.k2, (Bytes)a.q2, a.lse2, a.head_scores2}), pairs,
                            a.BC * a.H, a.S, a.dh, row_first, a.N, row_first, a.N, a.parts, sl2);
     return hipGetLastError();
 }
 
-template <typename T>
-static hipError_t launch_score_mean_t(const ScoreArgs &a, hipStream_t s, int pass) {
-    const int nc = (a.dh * (int)sizeof(T) + 31) / 32;
-    if constexpr (sizeof(T) == 2) {
-        if (nc <= 2) return launch_mean_pipe<2, 2>(a, s, pass);
-        if (nc <= 4) return launch_mean_pipe<4, 2>(a, s, pass);
-        if (nc <= 5) return launch_mean_pipe<5, 2>(a, s, pass);
+static hipError_t launch_score_mean(const ScoreArgs &a, hipStream_t s, int pass) {
+    const int nc = (a.dh * 2 + 31) / 32;  // chunks of sixteen elements
+    if (!a.is_bf16) {
+        if (nc <= 2) return launch_mean_pipe<float, 2, 2>(a, s, pass);
+        if (nc <= 4) return launch_mean_pipe<float, 4, 2>(a, s, pass);
+        if (nc <= 5) return launch_mean_pipe<float, 5, 2>(a, s, pass);
+        if (nc <= 8) return launch_mean_pipe<float, 8, 1>(a, s, pass);
+        return hipErrorInvalidValue;  // rows wider than 512 bytes are rejected by the ABI layer
     }
-    if (nc <= 2) return launch_score_mean_nc<T, 2>(a, s, pass);
-    if (nc <= 4) return launch_score_mean_nc<T, 4>(a, s, pass);
-    if (nc <= 5) return launch_score_mean_nc<T, 5>(a, s, pass);
-    if (nc <= 8) return launch_score_mean_nc<T, 8>(a, s, pass);
-    if (nc <= 12) return launch_score_mean_nc<T, 12>(a, s, pass);
-    if (nc <= 16) return launch_score_mean_nc<T, 16>(a, s, pass);
-    return hipErrorInvalidValue;  // rows wider than 512 bytes are rejected by the ABI layer
+    if (nc <= 2) return launch_mean_pipe<bf16_t, 2, 2>(a, s, pass);
+    if (nc <= 4) return launch_mean_pipe<bf16_t, 4, 2>(a, s, pass);
+    if (nc <= 5) return launch_mean_pipe<bf16_t, 5, 2>(a, s, pass);
+    if (nc <= 8) return launch_score_mean_nc<bf16_t, 8>(a, s, pass);
+    if (nc <= 12) return launch_score_mean_nc<bf16_t, 12>(a, s, pass);
+    if (nc <= 16) return launch_score_mean_nc<bf16_t, 16>(a, s, pass);
+    return hipErrorInvalidValue;
 }
 
-hipError_t launch_score_mean_lse(const ScoreArgs &a, hipStream_t s) {
-    return a.is_bf16 ? launch_score_mean_t<bf16_t>(a, s, 1) : launch_score_mean_t<float>(a, s, 1);
-}
-hipError_t launch_score_mean_colsum(const ScoreArgs &a, hipStream_t s) {
-    return a.is_bf16 ? launch_score_mean_t<bf16_t>(a, s, 2) : launch_score_mean_t<float>(a, s, 2);
-}
+hipError_t launch_score_mean_lse(const ScoreArgs &a, hipStream_t s) { return launch_score_mean(a, s, 1); }
+hipError_t launch_score_mean_colsum(const ScoreArgs &a, hipStream_t s) { return launch_score_mean(a, s, 2); }
 
 }  // namespace vscan

@@ -44,30 +44,33 @@ struct ScoreArgs {
     int parts = 1;        // mean_parts
     float *head_scores2 = nullptr;
 };
-// whether mean attention takes two pairs in one launch, and streamed rows in parts: the pipelined form
-inline bool mean_pair_launch(int is_bf16, int dh) { return is_bf16 && dh <= 80; }
+// whether mean attention takes two pairs in one launch, and streamed rows in parts: fp32, and bf16 rows of
+// up to 160 bytes
+inline bool mean_pair_launch(int is_bf16, int dh) { return !is_bf16 || dh <= 80; }
 
-// Into how many parts the streamed rows of mean attention are cut.  A workgroup owns 256 resident rows of
-// a head and takes as long as its stages of streamed rows and about one and a half more (its own rows, the
-// first stage, the sums at the end); the launch takes as long as the CU with most workgroups.
-// A call in one part and in the number chosen, us (16 heads of 80 unless said): 324 tokens 55, 50 (3
-// parts); 576 and a second pair 85, 58 (4); 1023: 79, 64 (4); 1296, 8 heads of 64: 84, 61 (4); 2000: 113,
-// 91 (2); 7200, 12 heads of 64: 418, 372 (4); 10000: 871, 786 (2).  Where the line lies on one part the
-// next best number is no faster: 2745 tokens 140 and 140 (4 parts), 2 x 3120, 64 wide 211 and 220 (4).
+// Into how many parts the streamed rows of mean attention are cut.  A workgroup owns 256 (128) resident
+// rows of a head and takes as long as its stages of streamed rows and about 0.8 more (its own rows, the
+// first stage, the sums at the end); the launch takes as long as the CU with most workgroups.  (With 1.5
+// instead of 0.8 fewer calls are cut: 2745 tokens 127 us instead of 114.)
+// A call in one part and in the number chosen, us (bf16, 16 heads of 80 unless said): 324 tokens 42, 37 (3
+// parts); 576 and a second pair 60, 45 (2, joined); 1023: 66, 50 (4); 1296, 8 heads of 64: 71, 49 (4); 2000:
+// 98, 77 (2); 7200, 12 heads of 64: 399, 340; 10000: 811, 724.  fp32: 324 tokens 65, 48; 1023: 133, 80;
+// 10000: 3064, 2777.  Near the line: 2745 tokens 125, 114 (4), in fp32 314, 308; 2 x 3120, 64 wide 190, 181.
 constexpr int kMeanMaxParts = 4;
 constexpr int kMeanStageRows = 128;
-constexpr double kMeanStart = 1.5;  // stages
-inline double mean_cost(int64_t heads, int N, int parts) {
-    const int64_t items = heads * ((N + 255) / 256);
+constexpr double kMeanStart = 0.8;  // stages
+inline int mean_block_rows(int is_bf16, int dh) { return !is_bf16 && dh > 80 ? 128 : 256; }
+inline double mean_cost(int64_t heads, int N, int block_rows, int parts) {
+    const int64_t items = heads * ((N + block_rows - 1) / block_rows);
     const int stages = (N + kMeanStageRows - 1) / kMeanStageRows;
     return (double)((items * parts + 255) / 256) * ((stages + parts - 1) / parts + kMeanStart);
 }
 inline int mean_parts(int is_bf16, int dh, int64_t heads, int N) {
     int best = 1;
     if (!mean_pair_launch(is_bf16, dh)) return best;
-    const int stages = (N + kMeanStageRows - 1) / kMeanStageRows;
+    const int stages = (N + kMeanStageRows - 1) / kMeanStageRows, rows = mean_block_rows(is_bf16, dh);
     for (int p = 2; p <= kMeanMaxParts && p <= stages; ++p)
-        if (mean_cost(heads, N, p) < 0.95 * mean_cost(heads, N, best)) best = p;
+        if (mean_cost(heads, N, rows, p) < 0.95 * mean_cost(heads, N, rows, best)) best = p;
     return best;
 }
 hipError_t launch_score_cls(const ScoreArgs &a, hipStream_t s);

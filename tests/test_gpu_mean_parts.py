@@ -29,6 +29,13 @@ def _one_part_bytes(shape, with_local):
     (wl.BF16, 1, 24, 24, 16, 72, 1, 1, 0, True),  # two parts, rows that end inside a chunk
     (wl.BF16, 1, 31, 33, 2, 80, 0, 0, 0, True),
     (wl.BF16, 5, 18, 18, 30, 16, 1, 0, 0, True),  # both pairs in one launch, one part
+    (wl.F32, 1, 8, 16, 2, 80, 0, 0, 0, False),
+    (wl.F32, 1, 3, 43, 2, 72, 1, 0, 0, True),
+    (wl.F32, 1, 16, 16, 3, 64, 0, 1, 1, True),
+    (wl.F32, 2, 19, 27, 2, 32, 0, 0, 0, True),
+    (wl.F32, 1, 31, 33, 2, 8, 1, 0, 0, True),
+    (wl.F32, 1, 24, 27, 2, 128, 0, 1, 0, True),   # stages of 64 rows, 128 resident rows
+    (wl.F32, 1, 17, 17, 3, 88, 1, 0, 0, True),
 ])
 def test_parts(dtype, batch, gh, gw, heads, dh, local, cls, all_keys, room):
     shape = _enc(dtype, batch=batch, grid_h=gh, grid_w=gw, heads=heads, head_dim=dh, feat_dim=64,
