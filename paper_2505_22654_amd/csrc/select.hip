@@ -510,7 +510,7 @@ __global__ __launch_bounds__(1024) void encoder_select_kernel(EncSelectArgs a, i
     });
 }
 
-// Large segments, first half: one workgroup per window (or per 1024 tokens when there is no local
+// Long segments, first half: one workgroup per window (or per 1024 tokens when there is no local
 // scan).  A single workgroup that walks a 16384-token segment spends most of its time fetching
 // H values per token at the rate one compute unit can take them; here every window's tokens are
 // summed over the heads, turned into keys and ranked inside the window (by counting: window
@@ -737,8 +737,13 @@ hipError_t launch_encoder_select(const EncSelectArgs &a, hipStream_t s) {
     const int threads = 1024;  // large segment: block-wide global scan, ceil(N/1024) registers
     const int nreg = (N + threads - 1) / threads;
     const int max_window = ((a.gh + a.wr - 1) / a.wr) * ((a.gw + a.wc - 1) / a.wc);
-    if (N > 4096 && a.pre_key_ws && a.pre_flag_ws && (a.kw <= 0 || max_window <= 1024)) {
-        // windows (and head sums) by a workgroup each, then the global scan by one per segment
+    // Windows (and head sums) by a workgroup each, then the global scan by one per segment: where a segment
+    // is long or has many values to add (mean attention in parts has a row per head and part).  A call with
+    // one launch and with two, us: 1089 tokens, 16 rows 39.5, 40.8; 2000 tokens, 8 rows 45.5, 46.8 and 64
+    // rows 75.6, 75.2; 2688, 64 rows 107.6, 104.5; 2745, two sets of 16 rows 257.3, 252.6; 4080, 8 rows
+    // 93.5, 83.7 and 16 rows 187.0, 174.3.
+    const int64_t values = (int64_t)(a.head_local ? 2 : 1) * a.H * N;
+    if ((N > 3072 || values > 48000) && a.pre_key_ws && a.pre_flag_ws && (a.kw <= 0 || max_window <= 1024)) {
         const int wthreads = a.kw > 0 ? (max_window + kWave - 1) / kWave * kWave : 1024;
         dim3 grid(a.kw > 0 ? a.wr * a.wc : (N + 1023) / 1024, blocks);
         hipLaunchKernelGGL(encoder_select_local_kernel, grid, dim3(wthreads), 0, s, a, a.pre_key_ws,
