@@ -162,8 +162,7 @@ int plan_llm(const vscan_llm_desc *d, LlmPlan *p) {
     if (llm_select_lds_bytes(d->vis_len) > kLdsBudget) return VSCAN_ERR_UNSUPPORTED;
     p->off_part = 0;
     size_t off = align_up((size_t)d->batch * d->kv_heads * d->vis_len * sizeof(float));
-    // few items with long key domains are scored chunk by chunk (uniform batches only; the
-    // space is part of the plan whenever the shape qualifies)
+    // few items with long key domains are scored chunk by chunk
     const int chunks = llm_score_split_chunks(d->batch, d->kv_heads, p->rows, p->nk, false);
     p->off_split_e = off;
     if (chunks > 0) off += align_up((size_t)d->batch * d->kv_heads * p->rows * d->vis_len * sizeof(float));

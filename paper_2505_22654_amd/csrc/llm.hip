@@ -370,6 +370,8 @@ static hipError_t llm_score_t(const LlmScoreArgs &a, hipStream_t s) {
 //                             order, part[j] = sum_r 2^(z[r][j] - M_r) / L_r in row order:
 //                             fixed orders throughout, no atomics.  (The chunk does not enter
 //                             a key's weight, so equal keys have equal scores wherever they are.)
+// Ragged batches (`meta`): the lengths passed are capacities and decide the grid and the strides, a
+// workgroup past its sequence's own keys or columns ends at once.
 // ---------------------------------------------------------------------------
 constexpr int kSplitChunk = 64;   // keys per workgroup: sixteen per wave
 
@@ -380,16 +382,26 @@ constexpr int kSplitChunk = 64;   // keys per workgroup: sixteen per wave
 template <typename T>
 __global__ __launch_bounds__(256) void llm_score_split_kernel(
     const T *__restrict__ q, const T *__restrict__ k, float *__restrict__ z_out,
-    float *__restrict__ stats, int R, int Tq, int S, int dh, int vis_start, int V, int k0, int nk,
-    float sl2) {
+    float *__restrict__ stats, int R, int Tq, int S_cap, int dh, int vis_start, int V_cap, int k0, int nk,
+    int Hkv, int domain_all, const SeqMeta *__restrict__ meta, float sl2) {
     constexpr int BATCH = sizeof(T) == 2 ? 4 : 8;  // 64-byte chunks of a row in flight
     __shared__ __align__(16) float red_m[16][4], red_l[16][4];   // per query row and wave
     const int item = blockIdx.y, chunk = blockIdx.x, nchunks = gridDim.x;
     const int lane = lane_id(), w = wave_id(), r16 = lane & 15, quarter = lane >> 4;
     const int kk = chunk * kSplitChunk + w * 16 + r16;  // key inside the domain
+    int S = S_cap, V = V_cap;
+    if (meta) {
+        const SeqMeta m = meta[item / Hkv];
+        S = min(m.seq_len, S_cap);
+        vis_start = min(max(m.vis_start, 0), S_cap - 1);
+        V = min(m.vis_len, V_cap);
+        k0 = domain_all ? 0 : vis_start;
+        nk = min(domain_all ? S : V, nk);
+        if (chunk * kSplitChunk >= nk) return;
+    }
     const int row_bytes = dh * (int)sizeof(T);
     // clamped: always readable.  Rows of q past R repeat the last one and are not reported.
-    const T *krow = k + ((int64_t)item * S + k0 + min(kk, nk - 1)) * dh;
+    const T *krow = k + ((int64_t)item * S_cap + min(k0 + min(kk, nk - 1), S_cap - 1)) * dh;
     const T *qrow = q + ((int64_t)item * R + min(r16, R - 1)) * dh;
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
     for (int c0 = 0; c0 * 64 < row_bytes; c0 += BATCH) {
@@ -431,7 +443,7 @@ __global__ __launch_bounds__(256) void llm_score_split_kernel(
         const float m = fmaxf(fmaxf(m4.x, m4.y), fmaxf(m4.z, m4.w));
         const float e = m > -INFINITY ? __builtin_amdgcn_exp2f(z[r] - m) : 0.f;
         if (row < R && kk < nk && col >= 0 && col < V)
-            z_out[((int64_t)item * R + row) * V + col] = z[r];
+            z_out[((int64_t)item * R + row) * V_cap + col] = z[r];
         const float sum = group_sum<16>(e);
         if (r16 == 0) red_l[row][w] = sum;
     }
@@ -448,15 +460,24 @@ __global__ __launch_bounds__(256) void llm_score_split_kernel(
 __global__ __launch_bounds__(256) void llm_score_combine_kernel(const float *__restrict__ z_in,
                                                                const float *__restrict__ stats,
                                                                float *__restrict__ part, int R,
-                                                               int V, int nchunks,
+                                                               int V_cap, int chunks_cap, int Hkv,
+                                                               int domain_all,
+                                                               const SeqMeta *__restrict__ meta,
                                                                SelectSeed seed) {
     seed_selection(seed, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+    int V = V_cap, nchunks = chunks_cap;
+    if (meta) {
+        const SeqMeta m = meta[blockIdx.y / Hkv];
+        V = min(m.vis_len, V_cap);
+        nchunks = min(((domain_all ? m.seq_len : V) + kSplitChunk - 1) / kSplitChunk, chunks_cap);
+        if ((int)blockIdx.x * 256 >= V) return;
+    }
     extern __shared__ float M[];                    // [R], then invL[R], then the pairs
     float *invL = M + R, *st = invL + R;
     const int item = blockIdx.y, tid = threadIdx.x;
     // all (maximum, sum) pairs of the item into LDS at once: the row loops below would
     // otherwise be chains of dependent global loads
-    for (int i = tid; i < nchunks * R * 2; i += 256) st[i] = stats[(int64_t)item * nchunks * R * 2 + i];
+    for (int i = tid; i < nchunks * R * 2; i += 256) st[i] = stats[(int64_t)item * chunks_cap * R * 2 + i];
     __syncthreads();
     // per row: maximum and rescaled sum over the chunks, one wave per row, lanes over chunks
     // (a fixed reduction tree: the result does not depend on scheduling)
@@ -480,13 +501,14 @@ __global__ __launch_bounds__(256) void llm_score_combine_kernel(const float *__r
     if (col >= V) return;
     float sum = 0.f;
     for (int r = 0; r < R; ++r)
-        sum += __builtin_amdgcn_exp2f(z_in[((int64_t)item * R + r) * V + col] - M[r]) * invL[r];
-    part[(int64_t)item * V + col] = sum;
+        sum += __builtin_amdgcn_exp2f(z_in[((int64_t)item * R + r) * V_cap + col] - M[r]) * invL[r];
+    part[(int64_t)item * V_cap + col] = sum;
 }
 
-// chunks the key domain is cut into, 0 when the one-workgroup-per-item kernel is the better fit
-int llm_score_split_chunks(int B, int Hkv, int rows, int nk, bool ragged) {
-    if (ragged || rows > 16 || nk < 1024 || (int64_t)B * Hkv > kCus / 4) return 0;
+// chunks the key domain (of a ragged batch: the longest) is cut into, 0 when the one-workgroup-per-item
+// kernel is the better fit
+int llm_score_split_chunks(int B, int Hkv, int rows, int nk, bool /*ragged*/) {
+    if (rows > 16 || nk < 1024 || (int64_t)B * Hkv > kCus / 4) return 0;
     return (nk + kSplitChunk - 1) / kSplitChunk;
 }
 
@@ -498,13 +520,13 @@ static hipError_t llm_score_split_t(const LlmScoreArgs &a, hipStream_t s, int nc
     dim3 grid(nchunks, items);
     hipLaunchKernelGGL(llm_score_split_kernel<T>, grid, dim3(256), 0, s, (const T *)a.q,
                        (const T *)a.k, a.split_e, a.split_stats, R, a.Tq, a.S, a.dh, a.vis_start, a.V,
-                       k0, nk, sl2);
+                       k0, nk, a.Hkv, a.domain_all, a.meta, sl2);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t smem2 = (size_t)(2 * nchunks * R + 2 * R) * sizeof(float);
     hipLaunchKernelGGL(llm_score_combine_kernel, dim3((a.V + 255) / 256, items), dim3(256), smem2, s,
                        (const float *)a.split_e, (const float *)a.split_stats, a.part, R, a.V,
-                       nchunks, a.seed);
+                       nchunks, a.Hkv, a.domain_all, a.meta, a.seed);
     return hipGetLastError();
 }
 
@@ -512,7 +534,13 @@ hipError_t launch_llm_score(const LlmScoreArgs &a, hipStream_t s) {
     const int rows = (a.Hq / a.Hkv) * a.Tq;
     const int nchunks = llm_score_split_chunks(a.B, a.Hkv, rows, a.domain_all ? a.S : a.V,
                                                a.meta != nullptr);
-    if (nchunks > 0 && a.split_e && a.split_stats)
+    // Ragged batches: the second launch is paid back where an item's longest keys are half a megabyte.  A
+    // call with one workgroup per item and with chunks, us (28 / 4 heads of 128 unless said): bf16, 1 and 12 x
+    // 1700 tokens 31.4, 33.6 and 60.3, 59.9; 1, 6 and 12 x 2100: 31.1, 32.3; 45.0, 40.7; 72.4, 70.4; 12 x 2700
+    // 89.4, 85.7; 3 x 4000: 51.4, 38.5; 16 heads of 64, 4 x 2700: 37.1, 37.4; fp32, 12 x 1100: 82.9, 77.0.
+    const int64_t key_bytes = (int64_t)(a.domain_all ? a.S : a.V) * a.dh * (a.is_bf16 ? 2 : 4);
+    const bool chunks_pay = !a.meta || key_bytes >= 512 * 1024;
+    if (nchunks > 0 && chunks_pay && a.split_e && a.split_stats)
         return a.is_bf16 ? llm_score_split_t<bf16_t>(a, s, nchunks)
                          : llm_score_split_t<float>(a, s, nchunks);
     return a.is_bf16 ? llm_score_t<bf16_t>(a, s) : llm_score_t<float>(a, s);
