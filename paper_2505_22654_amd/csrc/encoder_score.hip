@@ -22,13 +22,18 @@ namespace vscan {
 // bound by reading K once.  A key row is split into 16-byte pieces over adjacent
 // lanes, so a wave reads whole rows contiguously.
 // ---------------------------------------------------------------------------
+constexpr int kClsThreads = 512, kClsLoads = 10;  // loads in flight per thread
+
+// Rows of any number of pieces: as many whole rows as fit a wave per load, ten loads in flight, a row's
+// pieces added in a tree of lane shifts (with 256 threads, four guarded loads and one shuffle per piece,
+// heads of 80: 576 bf16 tokens 45.2 us a call, now 37.4; 8 x 900 64.8, 46.7; fp32, 1296 tokens 163, 71).
 template <typename T>
-__global__ __launch_bounds__(256) void score_cls_generic_kernel(const T *__restrict__ q,
+__global__ __launch_bounds__(kClsThreads) void score_cls_generic_kernel(const T *__restrict__ q,
                                                         const T *__restrict__ k,
                                                         float *__restrict__ head_scores, int H,
                                                         int S, int dh, int first_key, int col0,
                                                         int N, float scale_log2e) {
-    constexpr int E = ElemTraits<T>::kPer16B;
+    constexpr int E = ElemTraits<T>::kPer16B, UNR = kClsLoads;
     extern __shared__ __align__(16) unsigned char smem[];
     float *red = reinterpret_cast<float *>(smem);  // 16 floats
     float *qf = red + 16;                           // dh floats (dh <= 256)
@@ -41,50 +46,56 @@ __global__ __launch_bounds__(256) void score_cls_generic_kernel(const T *__restr
     const int n_keys = S - first_key;
     const int tid = threadIdx.x;
 
-    for (int e = tid; e < dh; e += blockDim.x) qf[e] = load_elem<T>(qrow + e) * scale_log2e;
-    __syncthreads();
-
     const int cpr = dh / E;          // 16-byte pieces per key row (<= 64)
-    const int rpw = kWave / cpr;     // key rows per wave per step
+    const int rpw = kWave / cpr;     // key rows per wave per load; the lanes past them repeat the last row's
     const int lane = lane_id();
-    const int row_in_wave = lane / cpr;
-    const int piece = lane - row_in_wave * cpr;
-    const bool active = row_in_wave < rpw;
-    const int seg0 = row_in_wave * cpr;
+    const int row_in_wave = min(lane / cpr, rpw - 1);
+    const int piece = lane < rpw * cpr ? lane - row_in_wave * cpr : cpr - 1;
+    constexpr int nw = kClsThreads / kWave;
+    const int64_t row_bytes = (int64_t)dh * sizeof(T);
+    auto row_of = [&](int base, int u) { return base + (u * nw + wave_id()) * rpw + row_in_wave; };
+    auto fetch = [&](int base, uint4(&raw)[UNR]) {  // clamped: independent loads, in flight together
+#pragma unroll
+        for (int u = 0; u < UNR; ++u)
+            raw[u] = load16_stream(kbase, min(row_of(base, u), n_keys - 1) * row_bytes + piece * 16);
+    };
+    uint4 raw[UNR];
+    fetch(0, raw);
+    for (int e = tid; e < dh; e += kClsThreads) qf[e] = load_elem<T>(qrow + e) * scale_log2e;
+    __syncthreads();
     float qreg[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) qreg[e] = active ? qf[piece * E + e] : 0.f;
+    for (int e = 0; e < E; ++e) qreg[e] = qf[piece * E + e];
 
-    const int nw = blockDim.x / kWave;
-    constexpr int UNR = 4;
-    const int64_t row_bytes = (int64_t)dh * sizeof(T);
-    for (int base = wave_id() * rpw; base < n_keys; base += nw * rpw * UNR) {
-        uint4 raw[UNR];
+    const int step = nw * rpw * UNR;
+    for (int base = 0; base < n_keys; base += step) {
+        uint4 nxt[UNR];
+        if (base + step < n_keys) fetch(base + step, nxt);
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-            const int row = base + u * nw * rpw + row_in_wave;
-            raw[u] = load16_stream_guard(kbase, row * row_bytes + piece * 16, active && row < n_keys);
-        }
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const int row = base + u * nw * rpw + row_in_wave;
             float kv[E];
             unpack16<T>(raw[u], kv);
             float part = 0.f;
 #pragma unroll
             for (int e = 0; e < E; ++e) part = fmaf(kv[e], qreg[e], part);
-            float tot = 0.f;
-            for (int d = 0; d < cpr; ++d) tot += __shfl(part, (seg0 + d) & (kWave - 1), kWave);
-            if (active && piece == 0 && row < n_keys) z[row] = tot;
+            // a row's pieces sit in adjacent lanes: lane d adds lane d + n while both belong to the row
+            for (int n = 32; n >= 1; n >>= 1) {
+                if (n >= cpr) continue;
+                const float up = __shfl_down(part, n, kWave);
+                if (piece + n < min(2 * n, cpr)) part += up;
+            }
+            if (piece == 0 && row_of(base, u) < n_keys) z[row_of(base, u)] = part;
         }
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) raw[u] = nxt[u];
     }
     __syncthreads();
 
     float m = -INFINITY;
-    for (int j = tid; j < n_keys; j += blockDim.x) m = fmaxf(m, z[j]);
+    for (int j = tid; j < n_keys; j += kClsThreads) m = fmaxf(m, z[j]);
     m = block_max(m, red);
     float sum = 0.f;
-    for (int j = tid; j < n_keys; j += blockDim.x) {
+    for (int j = tid; j < n_keys; j += kClsThreads) {
         const float e = __builtin_amdgcn_exp2f(z[j] - m);
         z[j] = e;
         sum += e;
@@ -92,20 +103,25 @@ __global__ __launch_bounds__(256) void score_cls_generic_kernel(const T *__restr
     sum = block_sum(sum, red);
     const float inv = 1.0f / sum;
     float *out = head_scores + ((int64_t)bc * H + h) * N;
-    for (int j = tid; j < N; j += blockDim.x) out[j] = z[col0 + j] * inv;
+    for (int j = tid; j < N; j += kClsThreads) out[j] = z[col0 + j] * inv;
 }
 
 // Same computation for rows whose piece count is a power of two (every common head
-// size).  The key block is read as one flat, fully coalesced stream with up to 16
+// size).  The key block is read as one flat, fully coalesced stream with ten
 // independent 16-byte loads per thread in flight: at these sizes the kernel's time
-// is the number of serialised memory round-trips, so all of them are issued at once.
-template <typename T, int LOG2_CPR, int UNR>
-__global__ __launch_bounds__(256) void score_cls_kernel(const T *__restrict__ q,
+// is the number of serialised memory round-trips, so all of them are issued at once
+// (a 24 x 24 encoder's 577 rows of 128 bytes in one batch).  With 512 threads a CU has
+// the loads of more waves to wait for at the same time and fewer rounds of softmax than
+// with 256 threads and 16 or 20 loads: a call 16 x 576 35.4 -> 34.3 us, 24 x 576 37.7 ->
+// 35.0, 8 x 5 x 576 61.4 -> 58.9, one image in fp32 (9232 pieces) 32.6 -> 30.8; 12 loads,
+// or 1024 threads and 5, measured the same.
+template <typename T, int LOG2_CPR>
+__global__ __launch_bounds__(kClsThreads) void score_cls_kernel(const T *__restrict__ q,
                                                         const T *__restrict__ k,
                                                         float *__restrict__ head_scores, int H,
                                                         int S, int dh, int first_key, int col0,
                                                         int N, float scale_log2e) {
-    constexpr int E = ElemTraits<T>::kPer16B;
+    constexpr int E = ElemTraits<T>::kPer16B, THREADS = kClsThreads, UNR = kClsLoads;
     constexpr int cpr = 1 << LOG2_CPR;  // 16-byte pieces per key row
     constexpr int shift = LOG2_CPR;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -126,28 +142,28 @@ __global__ __launch_bounds__(256) void score_cls_kernel(const T *__restrict__ q,
     for (int u = 0; u < UNR; ++u) {
         // clamped, not predicated: the loads of a batch stay independent of each other; what a
         // thread past the end fetched is dropped where the logits are filed
-        const int p = min(u * 256 + tid, total - 1);
+        const int p = min(u * THREADS + tid, total - 1);
         raw[u] = load16_stream(kbase, (int64_t)p * 16);
     }
-    for (int e = tid; e < dh; e += 256) qf[e] = load_elem<T>(qrow + e) * scale_log2e;
+    for (int e = tid; e < dh; e += THREADS) qf[e] = load_elem<T>(qrow + e) * scale_log2e;
     __syncthreads();
     float qreg[E];
     const int piece = tid & (cpr - 1);
 #pragma unroll
     for (int e = 0; e < E; ++e) qreg[e] = qf[piece * E + e];
 
-    for (int base = 0; base < total; base += 256 * UNR) {
+    for (int base = 0; base < total; base += THREADS * UNR) {
         uint4 nxt[UNR];
-        if (base + 256 * UNR < total) {
+        if (base + THREADS * UNR < total) {
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
-                const int p = min(base + 256 * UNR + u * 256 + tid, total - 1);
+                const int p = min(base + THREADS * UNR + u * THREADS + tid, total - 1);
                 nxt[u] = load16_stream(kbase, (int64_t)p * 16);
             }
         }
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-            const int p = base + u * 256 + tid;
+            const int p = base + u * THREADS + tid;
             float kv[E];
             unpack16<T>(raw[u], kv);
             float part = 0.f;
@@ -162,12 +178,12 @@ __global__ __launch_bounds__(256) void score_cls_kernel(const T *__restrict__ q,
     __syncthreads();
 
     // softmax with one exchange between the waves: every wave normalises against its own
-    // maximum, posts (maximum, sum) and rescales by what the four pairs combine to
+    // maximum, posts (maximum, sum) and rescales by what the pairs combine to
     float m = -INFINITY;
-    for (int j = tid; j < n_keys; j += 256) m = fmaxf(m, z[j]);
+    for (int j = tid; j < n_keys; j += THREADS) m = fmaxf(m, z[j]);
     m = wave_max(m);
     float sum = 0.f;
-    for (int j = tid; j < n_keys; j += 256) {
+    for (int j = tid; j < n_keys; j += THREADS) {
         const float e = __builtin_amdgcn_exp2f(z[j] - m);
         z[j] = e;  // read again below by this same thread only
         sum += e;
@@ -175,17 +191,20 @@ __global__ __launch_bounds__(256) void score_cls_kernel(const T *__restrict__ q,
     sum = wave_sum(sum);
     if (lane_id() == 0) {
         red[wave_id()] = m;
-        red[4 + wave_id()] = sum;
+        qf[wave_id()] = sum;  // (the query is in registers)
     }
     __syncthreads();
-    const float mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    constexpr int NW = THREADS / kWave;
+    float mx = red[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mx = fmaxf(mx, red[w]);
     float denom = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) denom += red[4 + w] * __builtin_amdgcn_exp2f(red[w] - mx);
+    for (int w = 0; w < NW; ++w) denom += qf[w] * __builtin_amdgcn_exp2f(red[w] - mx);
     // a wave without keys posted (-inf, 0): its term is 0 * 0
     const float f = __builtin_amdgcn_exp2f(m - mx) / denom;
     float *out = head_scores + ((int64_t)bc * H + h) * N;
-    for (int j = tid; j < n_keys; j += 256)
+    for (int j = tid; j < n_keys; j += THREADS)
         if (j >= col0 && j - col0 < N) out[j - col0] = z[j] * f;
 }
 
@@ -986,27 +1005,18 @@ static hipError_t launch_score_cls_t(const ScoreArgs &a, hipStream_t s) {
     }
     dim3 grid(a.H, a.BC);
     const int cpr = a.dh / ElemTraits<T>::kPer16B;
-    // 16 pieces per thread and batch; 20 when that takes the whole key block in one batch (the
-    // 577-row blocks of a 24 x 24 encoder with 128-byte heads: one memory round-trip less)
-    const int64_t total = (int64_t)n_keys * cpr;
-    // (only while every workgroup gets a CU to itself: the larger register set halves occupancy)
-    const bool one_shot = total > 256 * 16 && total <= 256 * 20 && (int64_t)a.H * a.BC <= 256;
-#define VSCAN_CLS_U(L, U)                                                                     \
-    {                                                                                         \
+#define VSCAN_CLS(L)                                                                          \
+    case L: {                                                                                 \
         if (smem > 64 * 1024) {                                                               \
             static std::atomic<uint64_t> lds_allowed{0};                                      \
-            hipError_t e = allow_large_lds(score_cls_kernel<T, L, U>, lds_allowed);           \
+            hipError_t e = allow_large_lds(score_cls_kernel<T, L>, lds_allowed);              \
             if (e != hipSuccess) return e;                                                    \
         }                                                                                     \
-        hipLaunchKernelGGL((score_cls_kernel<T, L, U>), grid, dim3(256), smem, s,             \
+        hipLaunchKernelGGL((score_cls_kernel<T, L>), grid, dim3(kClsThreads), smem, s,        \
                            (const T *)a.q, (const T *)a.k, a.head_scores, a.H, a.S, a.dh,     \
                            first_key, 1 - first_key, a.N, a.scale * 1.4426950408889634f);     \
         return hipGetLastError();                                                             \
     }
-#define VSCAN_CLS(L)                                                                          \
-    case L:                                                                                   \
-        if (one_shot) VSCAN_CLS_U(L, 20)                                                      \
-        VSCAN_CLS_U(L, 16)
     if ((cpr & (cpr - 1)) == 0) {
         switch (__builtin_ctz(cpr)) {
             VSCAN_CLS(0) VSCAN_CLS(1) VSCAN_CLS(2) VSCAN_CLS(3) VSCAN_CLS(4) VSCAN_CLS(5)
@@ -1014,9 +1024,8 @@ static hipError_t launch_score_cls_t(const ScoreArgs &a, hipStream_t s) {
         }
     }
 #undef VSCAN_CLS
-#undef VSCAN_CLS_U
     {
-        hipLaunchKernelGGL(score_cls_generic_kernel<T>, grid, dim3(256), smem, s, (const T *)a.q,
+        hipLaunchKernelGGL(score_cls_generic_kernel<T>, grid, dim3(kClsThreads), smem, s, (const T *)a.q,
                            (const T *)a.k, a.head_scores, a.H, a.S, a.dh, first_key,
                            1 - first_key, a.N, a.scale * 1.4426950408889634f);
     }
