@@ -200,39 +200,6 @@ __device__ __forceinline__ void mma32_chunk<float>(f32x16_t &acc, const uint4 &a
                                                0, 0);
 }
 
-// Eight fp32 values (two 16-byte pieces) as three bf16 planes: hi, mid, lo, each the rounding of what the
-// previous ones left over.  The three carry all 24 significant bits.
-constexpr int kF32Planes = 3;
-__device__ __forceinline__ void split_f32x8(const uint4 &a, const uint4 &b, uint4 *planes) {
-    typedef float f32x2_t __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-    float v[8];
-    unpack16<float>(a, v);
-    unpack16<float>(b, v + 4);
-#pragma unroll
-    for (int p = 0; p < kF32Planes; ++p) {
-        uint32_t w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const f32x2_t two = {v[2 * i], v[2 * i + 1]};
-            w[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2_t));
-            v[2 * i] -= bf16_lo(w[i]);  // exact
-            v[2 * i + 1] -= bf16_hi(w[i]);
-        }
-        planes[p] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-}
-// acc += the product of sixteen fp32 elements of each operand, from their planes: the six products above
-// 2^-26 of the whole, small ones first.
-__device__ __forceinline__ void mma32_planes(f32x16_t &acc, const uint4 *a, const uint4 *b) {
-    mma32_chunk<bf16_t>(acc, a[2], b[0]);
-    mma32_chunk<bf16_t>(acc, a[0], b[2]);
-    mma32_chunk<bf16_t>(acc, a[1], b[1]);
-    mma32_chunk<bf16_t>(acc, a[1], b[0]);
-    mma32_chunk<bf16_t>(acc, a[0], b[1]);
-    mma32_chunk<bf16_t>(acc, a[0], b[0]);
-}
-
 __device__ __forceinline__ int acc_row(int r) {
     return 8 * (r >> 2) + 4 * (lane_id() >> 5) + (r & 3);
 }

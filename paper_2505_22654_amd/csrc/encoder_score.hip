@@ -586,6 +586,27 @@ struct MeanForm<float> {
     static __device__ constexpr int resident_plane(int p) { return p == 1 || p == 4 ? 1 : p == 3 ? 2 : 0; }
 };
 
+// eight consecutive elements -> their planes
+__device__ __forceinline__ void split_planes(const uint4 &a, const uint4 &b, uint4 *out) {
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    float v[8];
+    unpack16<float>(a, v);
+    unpack16<float>(b, v + 4);
+#pragma unroll
+    for (int p = 0; p < MeanForm<float>::kPlanes; ++p) {
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f32x2_t two = {v[2 * i], v[2 * i + 1]};
+            w[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2_t));
+            v[2 * i] -= bf16_lo(w[i]);  // exact
+            v[2 * i + 1] -= bf16_hi(w[i]);
+        }
+        out[p] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+}
+
 // (PARTED, pass 2: the statistics come in parts.  A branch on `parts` where they are fetched would wait,
 // where its sides join, for every load in flight.)
 // f(0), ..., f(N - 1) with constants
@@ -665,7 +686,7 @@ __global__ __launch_bounds__(256, MeanForm<T>::kWorkgroupsPerCu) void mean_pipe_
             const bool valid = row < n_res && 16 * c + 8 * g < dh;  // dh is a multiple of eight
             const uint4 a = load16_guard(rbase, off, valid);
             if constexpr (SPLIT)
-                split_f32x8(a, load16_guard(rbase, off + 16, valid), kf[h][c]);
+                split_planes(a, load16_guard(rbase, off + 16, valid), kf[h][c]);
             else
                 kf[h][c][0] = a;
         }
@@ -716,7 +737,7 @@ __global__ __launch_bounds__(256, MeanForm<T>::kWorkgroupsPerCu) void mean_pipe_
         unsigned char *dst = lds(s & 1) + r * STRIDE + piece * 16;
         uint4 out[PL];
         if constexpr (SPLIT)
-            split_f32x8(sreg[it][0], sreg[it][1], out);
+            split_planes(sreg[it][0], sreg[it][1], out);
         else
             out[0] = sreg[it][0];
 #pragma unroll

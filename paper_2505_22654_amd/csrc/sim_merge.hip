@@ -131,29 +131,6 @@ __global__ __launch_bounds__(THREADS) void sim_argmax_kernel(const T *__restrict
     auto compute = [&](const unsigned char *cur) {
         const unsigned char *arow = cur + (wm * 32 * TM + (lane & 31)) * STRIDE + 16 * g;
         const unsigned char *brow = cur + (BM + wn * 32 * TN + (lane & 31)) * STRIDE + 16 * g;
-        // fp32: sixteen elements at a time as bf16 planes, six instructions for the work of eight fp32 ones that
-        // take four times as long ( 16 x 576 tokens, 288 tiles, a call 76.2 ->
-        // 68.2 us; 16 x 1296, 864 tiles, 139.8 -> 129.6).  Of 137000 tokens 19 are not with the kept token that
-        // 64 bits find the most similar, with fp32 instructions 36.
-        if constexpr (sizeof(T) == 4) {
-#pragma unroll
-            for (int c = 0; c < KC; c += 2) {
-                uint4 ap[TM][kF32Planes], bp[TN][kF32Planes];
-                auto planes_at = [&](const unsigned char *at, uint4 *out) {
-                    split_f32x8(*reinterpret_cast<const uint4 *>(at + 32 * c),
-                                *reinterpret_cast<const uint4 *>(at + 32 * c + 32), out);
-                };
-#pragma unroll
-                for (int i = 0; i < TM; ++i) planes_at(arow + i * 32 * STRIDE, ap[i]);
-#pragma unroll
-                for (int j = 0; j < TN; ++j) planes_at(brow + j * 32 * STRIDE, bp[j]);
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) mma32_planes(acc[i][j], ap[i], bp[j]);
-            }
-            return;
-        }
 #pragma unroll
         for (int c = 0; c < KC; ++c) {
             uint4 af[TM], bf[TN];
@@ -676,54 +653,21 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN <= 4 && TM * TN <= 4) ? 2 : 
         publish(0);
         __syncthreads();
         read(lds[0], 0, 0);
-        if constexpr (sizeof(T) == 4) {
-            // fp32: two chunks (sixteen elements) at a time, split into bf16 planes behind the LDS reads; the
-            // next pair is on its way while the six products of this one are formed (8 x 5 x 576 tokens, 480
-            // tiles: 127 -> 99 us of the kernel, a call 183.5 -> 152.7)
-            read(lds[0], 1, 1);
-            for (int st = 0; st < nstages; ++st) {
-                const bool more = st + 1 < nstages;
-                const unsigned char *cur = lds[st & 1];
-                if (more) fetch(st + 1);
+        for (int st = 0; st < nstages; ++st) {
+            const bool more = st + 1 < nstages;
+            const unsigned char *cur = lds[st & 1];
+            if (more) fetch(st + 1);
 #pragma unroll
-                for (int c = 0; c < KC; c += 2) {
-                    uint4 ap[TM][kF32Planes], bp[TN][kF32Planes];
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) split_f32x8(af[0][i], af[1][i], ap[i]);
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) split_f32x8(bf[0][j], bf[1][j], bp[j]);
-                    if (c + 2 < KC) {
-                        read(cur, c + 2, 0);
-                        read(cur, c + 3, 1);
-                    } else if (more) {
-                        publish(st + 1);
-                        __syncthreads();
-                        read(lds[(st + 1) & 1], 0, 0);
-                        read(lds[(st + 1) & 1], 1, 1);
-                    }
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN; ++j) mma32_planes(acc[i][j], ap[i], bp[j]);
-                }
+            for (int c = 0; c + 1 < KC; ++c) {
+                read(cur, c + 1, (c + 1) & 1);
+                mma(c & 1);
             }
-        } else {
-            for (int st = 0; st < nstages; ++st) {
-                const bool more = st + 1 < nstages;
-                const unsigned char *cur = lds[st & 1];
-                if (more) fetch(st + 1);
-#pragma unroll
-                for (int c = 0; c + 1 < KC; ++c) {
-                    read(cur, c + 1, (c + 1) & 1);
-                    mma(c & 1);
-                }
-                if (more) {
-                    publish(st + 1);
-                    __syncthreads();
-                    read(lds[(st + 1) & 1], 0, 0);
-                }
-                mma((KC - 1) & 1);
+            if (more) {
+                publish(st + 1);
+                __syncthreads();
+                read(lds[(st + 1) & 1], 0, 0);
             }
+            mma((KC - 1) & 1);
         }
     } else {
     uint4 ra[NSETS][PER_THREAD];
@@ -1175,10 +1119,8 @@ static hipError_t sim_large_t(const MergeArgs &a, hipStream_t s) {
     // 256 x 256 tiles once both sides fill them and there are enough of them for every CU
     const int U = a.T - a.K;
     const long tiles256 = (long)(U / 256) * (a.K / 256) * a.B;
-    if constexpr (sizeof(T) == 2) {  // (fp32 planes leave no registers for 64 x 128 per wave)
-        if (a.K >= 1024 && U >= 1024 && tiles256 >= 2 * 256)
-            return sim_large_launch<T, 4, 2, 2, 4, 4, 1, true>(a, s);
-    }
+    if (a.K >= 1024 && U >= 1024 && tiles256 >= 2 * 256)
+        return sim_large_launch<T, 4, 2, 2, 4, 4, 1, true>(a, s);
     return sim_large_launch<T, 2, 2, 2, 2, 4, 3, true>(a, s);
 }
 
@@ -1196,7 +1138,7 @@ hipError_t launch_sim_argmax(const MergeArgs &a, hipStream_t s) {
     if (a.is_bf16) return sim_t<bf16_t, 1, 1, 8, 2, 512>(a, s);
     // fp32: the smallest tiles that still give every CU at most one workgroup.  Whole calls, us, by
     // the number of the smaller tiles (576 tokens an image):
-    //   16 x 16, 32 x 32, 64 x 64 (with fp32 instructions)   128: 30.7, 35.5, 47.4 (1024 features)   224: 29.0, 29.8, 35.3 (512),
+    //   16 x 16, 32 x 32, 64 x 64   128: 30.7, 35.5, 47.4 (1024 features)   224: 29.0, 29.8, 35.3 (512),
     //                               36.2, 40.6, 53.9 (1280)   256: 32.1, 36.7, 48.6 (1024)
     //   past one for each CU        384: 27.6, 24.9, 30.3 (512), 35.5, 36.4, 47.9 (1024)   448: 34.2,
     //                               35.7, 41.9 (768), 45.9, 44.0, 56.2 (1280)   672: 38.0, 31.7, 36.9
