@@ -586,10 +586,13 @@ struct MeanForm<float> {
     static __device__ constexpr int resident_plane(int p) { return p == 1 || p == 4 ? 1 : p == 3 ? 2 : 0; }
 };
 
-// eight consecutive elements -> their planes
+// eight consecutive elements -> their planes.  From 3.396e38 on, rounding would make hi infinite and the other
+// planes NaN: hi stops at the largest finite bf16 value and the others take the rest, exactly.  (The two
+// comparisons an element cost a call 0 to 0.5 % up to heads of 80 and 2 % at 128: 1600 tokens, 8 heads, 132 -> 134.6 us.)
 __device__ __forceinline__ void split_planes(const uint4 &a, const uint4 &b, uint4 *out) {
     typedef float f32x2_t __attribute__((ext_vector_type(2)));
     typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    constexpr float kLargestBf16 = 0x1.fep127f;
     float v[8];
     unpack16<float>(a, v);
     unpack16<float>(b, v + 4);
@@ -598,7 +601,11 @@ __device__ __forceinline__ void split_planes(const uint4 &a, const uint4 &b, uin
         uint32_t w[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const f32x2_t two = {v[2 * i], v[2 * i + 1]};
+            f32x2_t two = {v[2 * i], v[2 * i + 1]};
+            if (p == 0) {
+                two.x = __builtin_amdgcn_fmed3f(two.x, -kLargestBf16, kLargestBf16);
+                two.y = __builtin_amdgcn_fmed3f(two.y, -kLargestBf16, kLargestBf16);
+            }
             w[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2_t));
             v[2 * i] -= bf16_lo(w[i]);  // exact
             v[2 * i + 1] -= bf16_hi(w[i]);
