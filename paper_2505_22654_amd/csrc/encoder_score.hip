@@ -556,12 +556,15 @@ __device__ __forceinline__ float merged_lse(const float2 (&p)[kMeanMaxParts / 2]
 
 // fp32 on the bf16 matrix instructions: an fp32 value is the sum of three bf16 values (each the rounding of
 // what the previous ones left over: 24 significant bits, the same exponents), a product of two fp32 values
-// the sum of nine products of bf16 values, which are exact.  Six are formed; the three left out (mid x lo,
-// lo x mid, lo x lo) are below 2^-26 of the product, under the rounding of an fp32 product itself.  The
-// small products are added first, so that only the last, hi x hi, are rounded at the size of the result: 5
-// roundings for rows of 80 instead of the 40 of fp32 instructions.  Error of the scores against 64 bits (2-norm;
-// 24 calls of 324 to 3500 tokens on fp32 rows, given or projected): 2.4e-7 on average and 6.9e-7 at worst with
-// fp32 instructions, 1.2e-7 and 3.3e-7 so.
+// the sum of nine products of bf16 values, which are exact.  Six are formed.  The three left out (mid x lo,
+// lo x mid, lo x lo) come to at most 2^-24 of the product (mid up to 2^-8 of the value, lo up to 2^-17; below 2^-26
+// for 97 % of mantissas), which is what rounding an fp32 product may cost.  The small products are added first, so
+// that only the last, hi x hi, are rounded at the size of the result: 5 roundings for rows of 80 instead of the 40
+// of fp32 instructions.  Error of the scores against 64 bits (2-norm; 324 to 1023 tokens, three seeds of four
+// shapes): given rows 2.8e-7 on average and 5.6e-7 at worst with fp32 instructions, 0.9e-7 and 1.6e-7 so;
+// projected rows 7.0e-7 and 12.8e-7, 2.6e-7 and 4.8e-7; rows of values that leave out the most 1.9 to 4.2e-7, 0.7
+// to 3.3e-7.  Below 2^-110 (7.7e-34) the low planes run out of exponents; what a value loses there, less than
+// 2^-126, is seen in a logit only against values of 2^100 and more.
 // Six bf16 instructions take the matrix pipe 192 cycles, the eight fp32 instructions for the same chunk 512.
 // That is still four times what the vector work of a tile takes, so the matrix pipe is the bound: one
 // workgroup a CU (up to 512 registers a lane), whose waves never wait for anything but the pipe: the planes of
