@@ -737,13 +737,25 @@ hipError_t launch_encoder_select(const EncSelectArgs &a, hipStream_t s) {
     const int threads = 1024;  // large segment: block-wide global scan, ceil(N/1024) registers
     const int nreg = (N + threads - 1) / threads;
     const int max_window = ((a.gh + a.wr - 1) / a.wr) * ((a.gw + a.wc - 1) / a.wc);
-    // Windows (and head sums) by a workgroup each, then the global scan by one per segment: where a segment
-    // is long or has many values to add (mean attention in parts has a row per head and part).  A call with
-    // one launch and with two, us: 1089 tokens, 16 rows 39.5, 40.8; 2000 tokens, 8 rows 45.5, 46.8 and 64
-    // rows 75.6, 75.2; 2688, 64 rows 107.6, 104.5; 2745, two sets of 16 rows 257.3, 252.6; 4080, 8 rows
-    // 93.5, 83.7 and 16 rows 187.0, 174.3.
+    // Windows (and head sums) by a workgroup each, then the global scan by one per segment: a launch more, and
+    // every token of a window looks at the others, for what one workgroup takes over ranking windows in
+    // several rounds or adding many rows.  From 1900 to 4096 tokens, calls with one launch and with two, us:
+    //   windows ranked in rounds (counted one by one, more than two to a wave, or 32 registers a lane): 2745 tokens,
+    //   8 x 8 windows, 16 rows 39.9, 30.8; 20 x 20 33.1, 27.8; 4080, 4 x 4 46.5, 41.3.  Two to a wave: 2880, 6 x 3 34.2,
+    //   35.4.  Shorter segments: 1980, 10 x 8 34.4, 29.3, but 1521, 8 x 8 27.0, 26.3 and 20 x 20 24.1, 25.1.
+    //   one window a wave, or none: 2745, 4 x 4 windows, 16 rows 31.8, 34.2; 100352 values 37.9, 38.3; 122880
+    //   47.5, 48.6; 2000, 64 rows (128000) 35.1, 32.4; 2745, 64 rows (mean attention in parts has a row per head and part) 39.1, 35.7.
+    //   larger windows: 3136, 2 x 2 (784 tokens each) 40, 65; 2256, 8 x 1 (288) 36.3, 37.8; 2592, 3 x 3 (288), 82944
+    //   values 41.7, 38.4; 2592, 4 x 2 (324), 82944 values 38.9, 40.3.
+    //   more segments fill the chip by themselves: 2745, 20 x 20, 8 of them 41.5, 38.8; 16 52.0, 52.5; 24 60.5, 62.5; 64,
+    //   64 rows 139, 175.  One window a wave, 64 rows: 4 44, 40.6; 8 (2 x 14 of 2772) 46.3, 47.3; 24 61.6, 63.9.
     const int64_t values = (int64_t)(a.head_local ? 2 : 1) * a.H * N;
-    if ((N > 3072 || values > 48000) && a.pre_key_ws && a.pre_flag_ws && (a.kw <= 0 || max_window <= 1024)) {
+    const bool slow_ranking = a.kw > 0 && (win_slots * nreg <= 128 || a.wr * a.wc > 32 || win_slots > 256);
+    const bool small_windows = a.kw <= 0 || max_window <= (values > 80000 ? 288 : 256);
+    const bool two_launches = N > 4096 ? a.kw <= 0 || max_window <= 1024
+                                       : N >= 1900 && blocks <= 8 && small_windows &&
+                                             (slow_ranking || (values >= 128000 && blocks <= 4));
+    if (two_launches && a.pre_key_ws && a.pre_flag_ws) {
         const int wthreads = a.kw > 0 ? (max_window + kWave - 1) / kWave * kWave : 1024;
         dim3 grid(a.kw > 0 ? a.wr * a.wc : (N + 1023) / 1024, blocks);
         hipLaunchKernelGGL(encoder_select_local_kernel, grid, dim3(wthreads), 0, s, a, a.pre_key_ws,
