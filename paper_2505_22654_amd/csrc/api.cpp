@@ -163,7 +163,7 @@ int plan_llm(const vscan_llm_desc *d, LlmPlan *p) {
     p->off_part = 0;
     size_t off = align_up((size_t)d->batch * d->kv_heads * d->vis_len * sizeof(float));
     // few items with long key domains are scored chunk by chunk
-    const int chunks = llm_score_split_chunks(d->batch, d->kv_heads, p->rows, p->nk, false);
+    const int chunks = llm_score_split_chunks(d->batch, d->kv_heads, p->rows, p->nk);
     p->off_split_e = off;
     if (chunks > 0) off += align_up((size_t)d->batch * d->kv_heads * p->rows * d->vis_len * sizeof(float));
     p->off_split_stats = off;

@@ -152,7 +152,7 @@ struct LlmScoreArgs {
     SelectSeed seed;
 };
 hipError_t launch_llm_score(const LlmScoreArgs &a, hipStream_t s);
-int llm_score_split_chunks(int B, int Hkv, int rows, int nk, bool ragged);
+int llm_score_split_chunks(int B, int Hkv, int rows, int nk);
 // rows = (Hq/Hkv)*Tq query rows per kv head, nk = keys in the softmax domain
 bool llm_score_supported(int rows, int nk, int row_bytes);
 

@@ -507,7 +507,7 @@ __global__ __launch_bounds__(256) void llm_score_combine_kernel(const float *__r
 
 // chunks the key domain (of a ragged batch: the longest) is cut into, 0 when the one-workgroup-per-item
 // kernel is the better fit
-int llm_score_split_chunks(int B, int Hkv, int rows, int nk, bool /*ragged*/) {
+int llm_score_split_chunks(int B, int Hkv, int rows, int nk) {
     if (rows > 16 || nk < 1024 || (int64_t)B * Hkv > kCus / 4) return 0;
     return (nk + kSplitChunk - 1) / kSplitChunk;
 }
@@ -530,17 +530,30 @@ static hipError_t llm_score_split_t(const LlmScoreArgs &a, hipStream_t s, int nc
     return hipGetLastError();
 }
 
+// Whether a ragged batch is scored in chunks (where llm_score_split_chunks gives any).  The second launch and the
+// logits' way through memory are paid back where the one workgroup of an item has long keys, or so many logits that
+// no LDS is left to stage them, and where there are few logits in all.  Calls with one workgroup per item and with
+// chunks, us (heads of 128, out of place, sequences of equal length; query rows per kv head x items; of 28 us a call
+// the host has most):
+//   bf16, 2100 tokens (525 KB of keys) 7 x 4 28.3, 30.0; 7 x 24 31.3, 30.9; 4 x 8 30.0, 31.0; 2300, 7 x 8 29.0, 30.2;
+//   3000 (750 KB) 7 x 4 32.0, 30.7; 7 x 24 37, 31.6; 7 x 48 42, 41; but 7 x 64 49.0, 50.0 (in place 2750 tokens 44.6,
+//   46.9), 4 x 48 41.0, 36.8; 4000, 7 x 12 42, 31.
+//   unstaged: 14 rows of 2300 tokens x 48 46, 40 and x 64 51, 47 (2100 tokens, staged, x 48 37.0, 38.6); 16 rows of
+//   2050 tokens, 64 wide (256 KB), in place, x 4 35, 32 and x 64 38, 47.
+//   fp32, 1040 tokens (520 KB) 7 x 4 32.4, 31.1; 4 x 12 32, 31.7; 14 x 64 45, 45; 16 x 64 of 64 wide, 2050 tokens
+//   52.0, 55.4; 2100, 7 x 24 51, 35.
+static bool ragged_chunks_pay(const LlmScoreArgs &a, int rows, int nk) {
+    const int64_t row_bytes = (int64_t)a.dh * (a.is_bf16 ? 2 : 4), key_bytes = nk * row_bytes;
+    const int nc = row_bytes <= 128 ? 2 : row_bytes <= 256 ? 4 : 8;  // as llm_score_t has it
+    const bool slow = !a.is_bf16 || llm_score_lds(rows, nk, nc, true) > kScoreLdsMax;  // one workgroup's way
+    const int64_t logit_rows = (int64_t)rows * a.B * a.Hkv;
+    return slow ? key_bytes >= 512 * 1024 && logit_rows <= 900 : key_bytes >= 704 * 1024 && logit_rows <= 400;
+}
+
 hipError_t launch_llm_score(const LlmScoreArgs &a, hipStream_t s) {
-    const int rows = (a.Hq / a.Hkv) * a.Tq;
-    const int nchunks = llm_score_split_chunks(a.B, a.Hkv, rows, a.domain_all ? a.S : a.V,
-                                               a.meta != nullptr);
-    // Ragged batches: the second launch is paid back where an item's longest keys are half a megabyte.  A
-    // call with one workgroup per item and with chunks, us (28 / 4 heads of 128 unless said): bf16, 1 and 12 x
-    // 1700 tokens 31.4, 33.6 and 60.3, 59.9; 1, 6 and 12 x 2100: 31.1, 32.3; 45.0, 40.7; 72.4, 70.4; 12 x 2700
-    // 89.4, 85.7; 3 x 4000: 51.4, 38.5; 16 heads of 64, 4 x 2700: 37.1, 37.4; fp32, 12 x 1100: 82.9, 77.0.
-    const int64_t key_bytes = (int64_t)(a.domain_all ? a.S : a.V) * a.dh * (a.is_bf16 ? 2 : 4);
-    const bool chunks_pay = !a.meta || key_bytes >= 512 * 1024;
-    if (nchunks > 0 && chunks_pay && a.split_e && a.split_stats)
+    const int rows = (a.Hq / a.Hkv) * a.Tq, nk = a.domain_all ? a.S : a.V;
+    const int nchunks = llm_score_split_chunks(a.B, a.Hkv, rows, nk);
+    if (nchunks > 0 && a.split_e && a.split_stats && (!a.meta || ragged_chunks_pay(a, rows, nk)))
         return a.is_bf16 ? llm_score_split_t<bf16_t>(a, s, nchunks)
                          : llm_score_split_t<float>(a, s, nchunks);
     return a.is_bf16 ? llm_score_t<bf16_t>(a, s) : llm_score_t<float>(a, s);

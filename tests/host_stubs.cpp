@@ -131,8 +131,8 @@ hipError_t launch_merge(const MergeArgs &a, hipStream_t) {
     return hipSuccess;
 }
 
-int llm_score_split_chunks(int B, int Hkv, int rows, int nk, bool ragged) {
-    if (ragged || rows > 16 || nk < 1024 || (int64_t)B * Hkv > 64) return 0;
+int llm_score_split_chunks(int B, int Hkv, int rows, int nk) {
+    if (rows > 16 || nk < 1024 || (int64_t)B * Hkv > 64) return 0;
     return (nk + 63) / 64;
 }
 bool llm_score_supported(int rows, int, int row_bytes) { return rows <= 64 && row_bytes <= 512; }
@@ -142,7 +142,7 @@ hipError_t launch_llm_score(const LlmScoreArgs &a, hipStream_t) {
     const size_t part = items * a.V * 4;
     region("llm_score", "part", a.part, part);
     const int nk = a.domain_all ? a.S : a.V;
-    const int chunks = llm_score_split_chunks(a.B, a.Hkv, (int)rows, nk, a.meta != nullptr);
+    const int chunks = llm_score_split_chunks(a.B, a.Hkv, (int)rows, nk);
     if (chunks > 0) {
         const size_t e = items * rows * a.V * 4, st = items * chunks * rows * 2 * 4;
         region("llm_score", "split_e", a.split_e, e);
