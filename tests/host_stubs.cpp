@@ -19,6 +19,8 @@ namespace {
 uintptr_t g_lo = 0, g_hi = 0;
 int g_calls = 0, g_regions = 0, g_violations = 0;
 vscan::SelectSeed g_seed;  // what the last scoring launch was asked to prepare
+std::vector<std::pair<const void *, size_t>> g_lse;  // statistics left by the first pass of mean attention
+int g_parted = 0, g_joined = 0, g_chunked = 0;       // second passes in parts, for both pairs; ragged chunks
 
 void region(const char *who, const char *what, const void *p, size_t bytes) {
     ++g_regions;
@@ -50,6 +52,7 @@ void expect(const char *who, const char *what, bool ok) {
 
 extern "C" void vscan_test_window(const void *lo, size_t bytes) {
     g_seed = {};
+    g_lse.clear();
     g_lo = reinterpret_cast<uintptr_t>(lo);
     g_hi = g_lo + bytes;
 }
@@ -58,34 +61,60 @@ extern "C" void vscan_test_report(int *calls, int *regions, int *violations) {
     *regions = g_regions;
     *violations = g_violations;
 }
+extern "C" void vscan_test_forms(int *parted, int *joined, int *chunked) {
+    *parted = g_parted;
+    *joined = g_joined;
+    *chunked = g_chunked;
+}
 
 namespace vscan {
 
-static void check_score(const char *who, const ScoreArgs &a, bool mean) {
-    ++g_calls;
-    const size_t n = (size_t)a.BC * a.H * a.N * sizeof(float);
-    region(who, "head_scores", a.head_scores, n);
-    if (mean) {
-        region(who, "lse", a.lse, n);
-        distinct(who, {{a.head_scores, n}, {a.lse, n}});
-    }
-}
 hipError_t launch_score_cls(const ScoreArgs &a, hipStream_t) {
-    check_score("score_cls", a, false);
+    ++g_calls;
+    expect("score_cls", "parts of a form without them", a.parts == 1);
+    region("score_cls", "head_scores", a.head_scores, (size_t)a.BC * a.H * a.N * sizeof(float));
     return hipSuccess;
 }
+
+// Mean attention: scores of all parts of the streamed rows, and a row's statistics, of one pair or of both.
+static size_t mean_scores_bytes(const ScoreArgs &a) { return (size_t)a.BC * a.H * a.parts * a.N * sizeof(float); }
+static size_t mean_lse_bytes(const ScoreArgs &a) { return mean_scores_bytes(a) * (a.parts > 1 ? 2 : 1); }
+static void check_mean(const char *who, const ScoreArgs &a, bool both) {
+    ++g_calls;
+    const int stages = (a.N + kMeanStageRows - 1) / kMeanStageRows;
+    expect(who, "more parts than stages or than the kernels add",
+           a.parts >= 1 && a.parts <= kMeanMaxParts && a.parts <= stages);
+    expect(who, "parts or two pairs in a form of one",
+           mean_pair_launch(a.is_bf16, a.dh) || (a.parts == 1 && !both));
+    if (both) expect(who, "second pair without rows", a.q2 && a.k2);
+}
 hipError_t launch_score_mean_lse(const ScoreArgs &a, hipStream_t) {
-    check_score("score_mean_lse", a, true);
-    if (a.q2) {  // the second pair's log-sum-exps
-        const size_t n = (size_t)a.BC * a.H * a.N * sizeof(float);
-        region("score_mean_lse", "lse2", a.lse2, n);
-        distinct("score_mean_lse", {{a.lse2, n}, {a.lse, n}});
-        expect("score_mean_lse", "second pair without keys", a.k2 != nullptr);
-    }
+    const char *who = "score_mean_lse";
+    check_mean(who, a, a.q2 != nullptr);
+    expect(who, "statistics of the launch before not read", g_lse.empty());
+    g_lse = {{a.lse, mean_lse_bytes(a)}};
+    if (a.q2) g_lse.push_back({a.lse2, mean_lse_bytes(a)});
+    for (const auto &r : g_lse) region(who, "lse", r.first, r.second);
+    distinct(who, g_lse);
     return hipSuccess;
 }
 hipError_t launch_score_mean_colsum(const ScoreArgs &a, hipStream_t) {
-    check_score("score_mean_colsum", a, true);
+    const char *who = "score_mean_colsum";
+    const bool both = a.head_scores2 != nullptr;
+    check_mean(who, a, both);
+    std::vector<std::pair<const void *, size_t>> all = g_lse;  // read here or by the next launch
+    auto one = [&](float *scores, float *lse) {
+        region(who, "head_scores", scores, mean_scores_bytes(a));
+        all.push_back({scores, mean_scores_bytes(a)});
+        const auto mine = std::find(g_lse.begin(), g_lse.end(), std::pair<const void *, size_t>(lse, mean_lse_bytes(a)));
+        expect(who, "statistics that the launch before did not leave", mine != g_lse.end());
+        if (mine != g_lse.end()) g_lse.erase(mine);
+    };
+    one(a.head_scores, a.lse);
+    if (both) one(a.head_scores2, a.lse2);
+    distinct(who, all);
+    g_joined += both;
+    g_parted += a.parts > 1;
     return hipSuccess;
 }
 
@@ -148,6 +177,7 @@ hipError_t launch_llm_score(const LlmScoreArgs &a, hipStream_t) {
         region("llm_score", "split_e", a.split_e, e);
         region("llm_score", "split_stats", a.split_stats, st);
         distinct("llm_score", {{a.part, part}, {a.split_e, e}, {a.split_stats, st}});
+        g_chunked += a.meta != nullptr;
     }
     g_seed = a.seed;
     return hipSuccess;

@@ -57,6 +57,7 @@ L.vscan_llm_prune_fused_ragged.argtypes = ([ctypes.POINTER(vb.LlmDesc)] + [vp] *
                                            [ctypes.c_size_t, vp])
 L.vscan_test_window.argtypes = [vp, ctypes.c_size_t]
 L.vscan_test_report.argtypes = [ctypes.POINTER(ctypes.c_int)] * 3
+L.vscan_test_forms.argtypes = [ctypes.POINTER(ctypes.c_int)] * 3
 L.vscan_test_table_bytes.restype = ctypes.c_size_t
 L.vscan_test_ragged_padded.argtypes = [ctypes.POINTER(vb.LlmDesc), vp, vp, vp, ctypes.c_int, vp,
                                        ctypes.c_size_t]
@@ -151,6 +152,73 @@ for idx in (1, 2, 3, 4, 5, 6):
             ok += 3
         else:
             assert rc == vb.VSCAN_ERR_UNSUPPORTED, rc
+
+# Mean attention in parts and with both pairs in one launch, in a workspace of the size asked for and in the least
+# that is taken (one part, pair by pair); bf16, fp32, wide bf16 rows, which have neither, and from hidden states.
+
+
+def forms():
+    n = [ctypes.c_int(0) for _ in range(3)]
+    L.vscan_test_forms(*(ctypes.byref(x) for x in n))
+    return [x.value for x in n]
+
+
+up = lambda n: (n + 255) // 256 * 256
+m1 = wl.EncoderShape(dtype=wl.BF16, batch=1, n_segments=1, grid_h=31, grid_w=33, has_cls=0, score_mode=1, heads=4,
+                     head_dim=64, feat_dim=64, win_rows=2, win_cols=2, keep_global=9, keep_local=8)
+# (cut into parts alone, cut with a second pair, joined with it)
+for change, alone, paired, joined in (
+        (dict(), 1, 1, 1), (dict(dtype=wl.F32), 1, 1, 1), (dict(head_dim=128), 0, 0, 0),
+        (dict(dtype=wl.F32, head_dim=128, grid_h=17), 1, 1, 1),
+        (dict(batch=5, grid_h=18, grid_w=18, heads=30, head_dim=16), 1, 0, 1),
+        (dict(batch=2, heads=16, grid_h=45, grid_w=61), 1, 0, 1), (dict(grid_h=8, grid_w=16, batch=256), 0, 0, 0)):
+    shape = dataclasses.replace(m1, **change)
+    d, tokens, kept = vb.encoder_desc(shape), shape.batch * shape.n_tokens, shape.batch * shape.keep
+    tail = up(4 * (tokens - kept)) + up(8 * tokens) + up(4 * kept) + up(4 * tokens) + up(tokens)
+    for with_local in (0, 1):
+        loc = FAKE if with_local else None
+        parted = paired if with_local else alone
+        rc, n = size(L.vscan_encoder_workspace_size, d, with_local)
+        least = (2 + with_local) * up(4 * tokens * shape.heads) + tail
+        assert rc == 0 and n >= least and (n > least) == bool(parted or (joined and with_local)), (change, with_local, n, least)
+        for m in sorted({n, least}):
+            before = forms()
+            L.vscan_test_window(WS, m)
+            assert L.vscan_encoder_reduce(ctypes.byref(d), FAKE, FAKE, loc, loc, FAKE, FAKE, FAKE, FAKE, FAKE, WS, m,
+                                          None) == 0
+            ran = [b - a for a, b in zip(before, forms())]
+            assert ran == [parted * (m > least), joined * with_local * (m > least), 0], (change, m, ran)
+            ok += 1
+        assert L.vscan_encoder_reduce(ctypes.byref(d), FAKE, FAKE, loc, loc, FAKE, FAKE, FAKE, FAKE, FAKE, WS,
+                                      least - 1, None) == vb.VSCAN_ERR_WORKSPACE
+        bad += 1
+        rc, n = size(L.vscan_encoder_fused_workspace_size, d, with_local)
+        assert rc == 0
+        sizes = [n]
+        L.vscan_test_window(WS, n)
+        if n > least:  # projected rows are fp32, scored triple by triple: parts, but no joined launch
+            sizes.append(next(m for m in range(256, n + 1, 256) if L.vscan_encoder_reduce_fused(
+                ctypes.byref(d), FAKE, FAKE, FAKE, loc, loc, loc, FAKE, FAKE, FAKE, FAKE, FAKE, WS, m, None) == 0))
+        for m in sizes:
+            L.vscan_test_window(WS, m)
+            assert L.vscan_encoder_reduce_fused(ctypes.byref(d), FAKE, FAKE, FAKE, loc, loc, loc, FAKE, FAKE, FAKE,
+                                                FAKE, FAKE, WS, m, None) == 0
+            ok += 1
+
+# a ragged batch of long spans: chunks
+s2 = wl.LlmShape(dtype=wl.BF16, batch=3, prefix=4, vis_len=3000, text=20, n_query=1, q_heads=8, kv_heads=4,
+                 head_dim=128, hidden=64, keep=100)
+for shape in (s2, dataclasses.replace(s2, in_place=1), dataclasses.replace(s2, softmax_domain=1)):
+    d, before = vb.llm_desc(shape), forms()
+    rc, n = size(L.vscan_llm_workspace_size, d)
+    outs = [None if shape.in_place else FAKE] * 3
+    meta = (ctypes.c_int32 * 12)(*[v for b in range(3) for v in (3024 - 900 * b, 4 - b, 3000 - 900 * b, 100 - 40 * b)])
+    L.vscan_test_window(WS, n)
+    assert rc == 0 and L.vscan_llm_prune_ragged(ctypes.byref(d), ctypes.addressof(meta), FAKE, FAKE, FAKE, FAKE, FAKE,
+                                                FAKE, *outs, FAKE, WS, n, None) == 0
+    padded(d, meta, outs[0], 0, n)
+    assert forms()[2] == before[2] + 2
+    ok += 2
 
 # descriptors that must be refused: nothing may reach a launcher
 calls0 = ctypes.c_int(0); regions = ctypes.c_int(0); viol = ctypes.c_int(0)
