@@ -45,7 +45,9 @@ enum { VSCAN_F32 = 0, VSCAN_BF16 = 1 };
 
 /* Which attention row scores the encoder tokens (Sec. 4.1 "Global Scan"):
  * the [CLS] query row (Eq. 1), or, for encoders without [CLS], the mean
- * attention each token receives from all visual query rows. */
+ * attention each token receives from all visual query rows.  (There fp32 rows
+ * are multiplied in three parts of eight bits: an element below 2^-110 keeps
+ * fewer than 24, which matters only against elements of 2^100 and more.) */
 enum { VSCAN_SCORE_CLS_ROW = 0, VSCAN_SCORE_MEAN_RECEIVED = 1 };
 
 /* Softmax key domain.  VISUAL_ONLY follows Eq. 1 / Eq. 5 as written (K_V holds

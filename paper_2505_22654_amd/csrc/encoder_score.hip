@@ -314,10 +314,11 @@ __device__ __forceinline__ void join_half_waves(float m, float l, float &M, floa
     if (m_o > -INFINITY) L += l_o * __builtin_amdgcn_exp2f(m_o - M);
 }
 
+// Both passes for wider bf16 rows (fp32 and bf16 rows of up to 160 bytes have the pipelined form below).
 // Pass 1: lse2[i] = log2 sum_j 2^(sl2 * q_i . k_j) over the key domain.
-template <typename T, int NC>
-__global__ __launch_bounds__(256, 2) void mean_lse_kernel(const T *__restrict__ q,
-                                                          const T *__restrict__ k,
+template <int NC>
+__global__ __launch_bounds__(256, 2) void mean_lse_kernel(const bf16_t *__restrict__ q,
+                                                          const bf16_t *__restrict__ k,
                                                           float *__restrict__ lse, int n_heads_total,
                                                           int S, int dh, int row_first, int N,
                                                           int key_first, int n_keys, float sl2) {
@@ -329,7 +330,7 @@ __global__ __launch_bounds__(256, 2) void mean_lse_kernel(const T *__restrict__ 
     const int item = xcd_contiguous_item(total);
     if (item >= total) return;
     const int bh = item / nblk, rb = item - bh * nblk;
-    const int row_bytes = dh * (int)sizeof(T);
+    const int row_bytes = dh * (int)sizeof(bf16_t);
     const unsigned char *qbase =
         reinterpret_cast<const unsigned char *>(q) + ((int64_t)bh * S + row_first) * row_bytes;
     const unsigned char *kbase =
@@ -362,7 +363,7 @@ __global__ __launch_bounds__(256, 2) void mean_lse_kernel(const T *__restrict__ 
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const uint4 a = *reinterpret_cast<const uint4 *>(arow + 32 * c);
-                mma32_chunk<T>(acc, a, qfrag[c]);
+                mma32_chunk<bf16_t>(acc, a, qfrag[c]);
             }
             // acc[r] = q_row(lane%32) . k_(key0 + acc_row(r)); mask the ragged tail
             const int key0 = t * kMeanTile + sub * 32;
@@ -405,9 +406,9 @@ __device__ __forceinline__ float resident_row_sum(float (&v)[16]) {
 }
 
 // Pass 2: head_scores[j] = sum_i 2^(sl2 * q_i . k_j - lse2[i]) for patch keys j.
-template <typename T, int NC>
-__global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict__ q,
-                                                             const T *__restrict__ k,
+template <int NC>
+__global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const bf16_t *__restrict__ q,
+                                                             const bf16_t *__restrict__ k,
                                                              const float *__restrict__ lse,
                                                              float *__restrict__ head_scores,
                                                              int n_heads_total, int S, int dh,
@@ -421,7 +422,7 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict
     const int item = xcd_contiguous_item(total);
     if (item >= total) return;
     const int bh = item / nblk, kb = item - bh * nblk;
-    const int row_bytes = dh * (int)sizeof(T);
+    const int row_bytes = dh * (int)sizeof(bf16_t);
     // queries and keys are both the patch rows here
     const unsigned char *qbase =
         reinterpret_cast<const unsigned char *>(q) + ((int64_t)bh * S + row_first) * row_bytes;
@@ -465,7 +466,7 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const uint4 a = *reinterpret_cast<const uint4 *>(arow + 32 * c);
-                mma32_chunk<T>(acc, kfrag[c], a);
+                mma32_chunk<bf16_t>(acc, kfrag[c], a);
             }
             // acc[r] = k_(key0 + acc_row(r)) . q_(row0 + lane%32): a lane's logits belong to one query
             // row, whose log-sum-exp is one LDS read; rows past N carry +inf -> 0
@@ -508,7 +509,8 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict
 // lane % 32 and sixteen streamed rows), in pass 2 its rows (a lane owns streamed row lane % 32 and sums
 // for its sixteen resident rows; the lanes are added once, at the end).  Subtracting the reference is
 // the multiply-add that scales the logit.  (Pass 2 had the log-sum-exp as one more 32-byte chunk of the
-// contraction before, a sixth more matrix instructions: 16384 tokens, 16 heads of 80, 911 -> 851 us.)  Rows past the end carry -inf and contribute 2^-inf = 0.
+// contraction before, a sixth more matrix instructions: 16384 tokens, 16 heads of 80, 850 -> 800 us.)  Rows past
+// the end carry -inf and contribute 2^-inf = 0.
 //
 // With `parts` > 1 the streamed rows are cut into runs of whole stages with a workgroup each
 // (mean_parts): pass 1 leaves a reference m and l = sum_j 2^(sl2 * q_i . k_j - m) per row and part, which
@@ -554,13 +556,14 @@ __device__ __forceinline__ float merged_lse(const float2 (&p)[kMeanMaxParts / 2]
     return m + log2_sum(group_sum<2>(l));
 }
 
-// fp32 on the bf16 matrix instructions: an fp32 value is the sum of three bf16 values (each the rounding of
-// what the previous ones left over: 24 significant bits, the same exponents), a product of two fp32 values
-// the sum of nine products of bf16 values, which are exact.  Six are formed.  The three left out (mid x lo,
-// lo x mid, lo x lo) come to at most 2^-24 of the product (mid up to 2^-8 of the value, lo up to 2^-17; below 2^-26
-// for 97 % of mantissas), which is what rounding an fp32 product may cost.  The small products are added first, so
-// that only the last, hi x hi, are rounded at the size of the result: 5 roundings for rows of 80 instead of the 40
-// of fp32 instructions.  Error of the scores against 64 bits (2-norm; 324 to 1023 tokens, three seeds of four
+// fp32 on the bf16 matrix instructions (the method of Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial
+// intelligence datatype for higher-precision computations", 2019): an fp32 value is the sum of three bf16 values
+// (each the rounding of what the previous ones left over: 24 significant bits, the same exponents), a product of
+// two fp32 values the sum of nine products of bf16 values, which are exact.  Six are formed.  The three left out
+// (mid x lo, lo x mid, lo x lo) come to at most 2^-24 of the product (mid up to 2^-8 of the value, lo up to 2^-17;
+// below 2^-26 for 97 % of mantissas), which is what rounding an fp32 product may cost.  The small products are added
+// first, so that only the last, hi x hi, are rounded at the size of the result: 5 roundings for rows of 80 instead of
+// the 40 of fp32 instructions.  Error of the scores against 64 bits (2-norm; 324 to 1023 tokens, three seeds of four
 // shapes): given rows 2.8e-7 on average and 5.6e-7 at worst with fp32 instructions, 0.9e-7 and 1.6e-7 so;
 // projected rows 7.0e-7 and 12.8e-7, 2.6e-7 and 4.8e-7; rows of values that leave out the most 1.9 to 4.2e-7, 0.7
 // to 3.3e-7.  Below 2^-110 (7.7e-34) the low planes run out of exponents; what a value loses there, less than
@@ -590,8 +593,8 @@ struct MeanForm<float> {
 };
 
 // eight consecutive elements -> their planes.  From 3.396e38 on, rounding would make hi infinite and the other
-// planes NaN: hi stops at the largest finite bf16 value and the others take the rest, exactly.  (The two
-// comparisons an element cost a call 0 to 0.5 % up to heads of 80 and 2 % at 128: 1600 tokens, 8 heads, 132 -> 134.6 us.)
+// planes NaN: hi stops at the largest finite bf16 value and the others take the rest, exactly.  (The clamp costs a
+// call 0 to 0.5 % up to heads of 80 and 2 % at 128: 1600 tokens, 8 heads, 132 -> 134.6 us.)
 __device__ __forceinline__ void split_planes(const uint4 &a, const uint4 &b, uint4 *out) {
     typedef float f32x2_t __attribute__((ext_vector_type(2)));
     typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -617,8 +620,6 @@ __device__ __forceinline__ void split_planes(const uint4 &a, const uint4 &b, uin
     }
 }
 
-// (PARTED, pass 2: the statistics come in parts.  A branch on `parts` where they are fetched would wait,
-// where its sides join, for every load in flight.)
 // f(0), ..., f(N - 1) with constants
 template <int... I, typename F>
 __device__ __forceinline__ void for_constants(std::integer_sequence<int, I...>, F f) {
@@ -626,7 +627,7 @@ __device__ __forceinline__ void for_constants(std::integer_sequence<int, I...>, 
 }
 
 // LDS of the kernel below: two stages of kRows streamed rows, in dynamic LDS where they pass 64 KB.
-template <typename T, int NC, int PASS>
+template <typename T, int NC>
 struct MeanLds {
     static constexpr int kPlanes = MeanForm<T>::kPlanes;
     static constexpr int kRows = kPlanes * NC * 32 * 2 * 128 > 144 * 1024 ? 64 : 128;
@@ -635,6 +636,8 @@ struct MeanLds {
     static constexpr bool kDynamic = kBytes > 62 * 1024;
 };
 
+// PARTED, pass 2: the statistics come in parts.  A branch on `parts` where they are fetched would wait,
+// where its sides join, for every load in flight.
 template <typename T, int NC, int HALVES, int PASS, bool PARTED>
 __global__ __launch_bounds__(256, MeanForm<T>::kWorkgroupsPerCu) void mean_pipe_kernel(
     MeanPair first, MeanPair second, int pairs, int n_heads, int S, int dh, int res_first, int n_res,
@@ -647,7 +650,7 @@ __global__ __launch_bounds__(256, MeanForm<T>::kWorkgroupsPerCu) void mean_pipe_
     // is then one contiguous block in memory and in LDS alike: it is fetched with direct loads.
     // Otherwise: padded rows (an odd number of 16-byte pieces, conflict-free) staged through registers.
     constexpr bool DIRECT = !SPLIT && (NC & 1) != 0;
-    using Lds = MeanLds<T, NC, PASS>;
+    using Lds = MeanLds<T, NC>;
     constexpr int ROWS = Lds::kRows, TILES = ROWS / 32, STRIDE = Lds::kStride;
     constexpr int PPR = NC * 2;                        // 16-byte pieces per plane of a streamed row
     constexpr int PER = (ROWS * PPR + 255) / 256;      // pieces per thread and stage
@@ -1046,7 +1049,7 @@ hipError_t launch_score_cls(const ScoreArgs &a, hipStream_t s) {
     return a.is_bf16 ? launch_score_cls_t<bf16_t>(a, s) : launch_score_cls_t<float>(a, s);
 }
 
-template <typename T, int NC>
+template <int NC>
 static hipError_t launch_score_mean_nc(const ScoreArgs &a, hipStream_t s, int pass) {
     const int row_first = a.has_cls;
     const int key_first = a.domain_all ? 0 : a.has_cls;
@@ -1056,12 +1059,12 @@ static hipError_t launch_score_mean_nc(const ScoreArgs &a, hipStream_t s, int pa
     const int grid = ((total + 7) / 8) * 8;
     const float sl2 = a.scale * 1.4426950408889634f;
     if (pass == 1)
-        hipLaunchKernelGGL((mean_lse_kernel<T, NC>), dim3(grid), dim3(256), 0, s, (const T *)a.q,
-                           (const T *)a.k, a.lse, a.BC * a.H, a.S, a.dh, row_first, a.N, key_first,
+        hipLaunchKernelGGL((mean_lse_kernel<NC>), dim3(grid), dim3(256), 0, s, (const bf16_t *)a.q,
+                           (const bf16_t *)a.k, a.lse, a.BC * a.H, a.S, a.dh, row_first, a.N, key_first,
                            n_keys, sl2);
     else
-        hipLaunchKernelGGL((mean_colsum_kernel<T, NC>), dim3(grid), dim3(256), 0, s,
-                           (const T *)a.q, (const T *)a.k, a.lse, a.head_scores, a.BC * a.H, a.S,
+        hipLaunchKernelGGL((mean_colsum_kernel<NC>), dim3(grid), dim3(256), 0, s,
+                           (const bf16_t *)a.q, (const bf16_t *)a.k, a.lse, a.head_scores, a.BC * a.H, a.S,
                            a.dh, row_first, a.N, sl2);
     return hipGetLastError();
 }
@@ -1080,7 +1083,7 @@ static hipError_t launch_mean_pipe(const ScoreArgs &a, hipStream_t s, int pass) 
     using Bytes = const unsigned char *;
     constexpr auto pass1 = mean_pipe_kernel<T, NC, HALVES, 1, false>, pass2 = mean_pipe_kernel<T, NC, HALVES, 2, false>,
                    pass2_parted = mean_pipe_kernel<T, NC, HALVES, 2, true>;
-    using Lds = MeanLds<T, NC, 1>;
+    using Lds = MeanLds<T, NC>;
     constexpr int lds = Lds::kDynamic ? Lds::kBytes : 0;
     if constexpr (Lds::kDynamic) {
         static std::atomic<uint64_t> allowed[3];
@@ -1114,9 +1117,9 @@ static hipError_t launch_score_mean(const ScoreArgs &a, hipStream_t s, int pass)
     if (nc <= 2) return launch_mean_pipe<bf16_t, 2, 2>(a, s, pass);
     if (nc <= 4) return launch_mean_pipe<bf16_t, 4, 2>(a, s, pass);
     if (nc <= 5) return launch_mean_pipe<bf16_t, 5, 2>(a, s, pass);
-    if (nc <= 8) return launch_score_mean_nc<bf16_t, 8>(a, s, pass);
-    if (nc <= 12) return launch_score_mean_nc<bf16_t, 12>(a, s, pass);
-    if (nc <= 16) return launch_score_mean_nc<bf16_t, 16>(a, s, pass);
+    if (nc <= 8) return launch_score_mean_nc<8>(a, s, pass);
+    if (nc <= 12) return launch_score_mean_nc<12>(a, s, pass);
+    if (nc <= 16) return launch_score_mean_nc<16>(a, s, pass);
     return hipErrorInvalidValue;
 }
 

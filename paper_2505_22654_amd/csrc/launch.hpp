@@ -55,7 +55,12 @@ inline bool mean_pair_launch(int is_bf16, int dh) { return !is_bf16 || dh <= 80;
 // A call in one part and in the number chosen, us (bf16, 16 heads of 80 unless said): 324 tokens 42, 37 (3
 // parts); 576 and a second pair 60, 45 (2, joined); 1023: 66, 50 (4); 1296, 8 heads of 64: 71, 49 (4); 2000:
 // 98, 77 (2); 7200, 12 heads of 64: 399, 340; 10000: 811, 724.  fp32: 324 tokens 65, 48; 1023: 133, 80;
-// 10000: 3064, 2777.  Near the line: 2745 tokens 125, 114 (4), in fp32 314, 308; 2 x 3120, 64 wide 190, 181.
+// 10000: 3064, 2777.  Near the line: 2745 tokens 125, 114 (4), in fp32 314, 308; 2 x 3120, 64 wide 190, 181;
+// 3 x 714 and a second pair in fp32, 128 wide 276, 264 (2).
+// Left in one part, and what two would take: 3 x 848 in fp32 138, 149; 2 x 850 in fp32, 128 wide 150, 166; 3234 from
+// hidden states, 64 wide 318, 336; 3 x 3640, 64 wide 312, 313; 5776 and a second pair 507, 510; 7200 457, 457; 8000
+// 515, 509; 4096 179, 171; 3 x 522 and a second pair, 64 wide 66, 58.  Of 105 calls, 256 to 9000 tokens, none took
+// more than 1 % longer with the number chosen than in one part.
 constexpr int kMeanMaxParts = 4;
 constexpr int kMeanStageRows = 128;
 constexpr double kMeanStart = 0.8;  // stages

@@ -744,7 +744,8 @@ hipError_t launch_encoder_select(const EncSelectArgs &a, hipStream_t s) {
     //   8 x 8 windows, 16 rows 39.9, 30.8; 20 x 20 33.1, 27.8; 4080, 4 x 4 46.5, 41.3.  Two to a wave: 2880, 6 x 3 34.2,
     //   35.4.  Shorter segments: 1980, 10 x 8 34.4, 29.3, but 1521, 8 x 8 27.0, 26.3 and 20 x 20 24.1, 25.1.
     //   one window a wave, or none: 2745, 4 x 4 windows, 16 rows 31.8, 34.2; 100352 values 37.9, 38.3; 122880
-    //   47.5, 48.6; 2000, 64 rows (128000) 35.1, 32.4; 2745, 64 rows (mean attention in parts has a row per head and part) 39.1, 35.7.
+    //   47.5, 48.6; 2000, 64 rows (128000) 35.1, 32.4; 2745, 64 rows (mean attention in parts has a row per head
+    //   and part) 39.1, 35.7.
     //   larger windows: 3136, 2 x 2 (784 tokens each) 40, 65; 2256, 8 x 1 (288) 36.3, 37.8; 2592, 3 x 3 (288), 82944
     //   values 41.7, 38.4; 2592, 4 x 2 (324), 82944 values 38.9, 40.3.
     //   more segments fill the chip by themselves: 2745, 20 x 20, 8 of them 41.5, 38.8; 16 52.0, 52.5; 24 60.5, 62.5; 64,

@@ -92,3 +92,17 @@ def test_scores_against_64_bits(dh, heads, gh, gw, hidden, most):
         error = _two_norm(out, ref)
         print("error", error, flush=True)
         assert error < most
+
+
+@pytest.mark.parametrize("power", [60, 100])
+def test_far_apart_exponents(power):
+    """Small values against large ones: the planes of 2^-100 are still whole."""
+    shape = _enc(wl.F32, batch=1, grid_h=18, grid_w=18, heads=8, head_dim=64, feat_dim=16, win_rows=1, win_cols=1,
+                 keep_global=7, keep_local=0, has_cls=0, score_mode=1)
+    print("case", power, flush=True)
+    for small, large in (("q", "k"), ("k", "q")):
+        inp = wl.encoder_inputs(shape, 8800, 0.25)
+        inp[small], inp[large] = inp[small] * np.float32(2.0 ** -power), inp[large] * np.float32(2.0 ** power)
+        error = _two_norm(_run_encoder(shape, inp), vo.encoder_reduce(shape, inp["q"], inp["k"], inp["x"]))
+        print(small, "error", error, flush=True)
+        assert error < 2.5e-7  # as for drawn rows
