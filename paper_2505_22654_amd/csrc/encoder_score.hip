@@ -22,18 +22,21 @@ namespace vscan {
 // bound by reading K once.  A key row is split into 16-byte pieces over adjacent
 // lanes, so a wave reads whole rows contiguously.
 // ---------------------------------------------------------------------------
-constexpr int kClsThreads = 512, kClsLoads = 10;  // loads in flight per thread
+// Two forms (THREADS threads with UNR loads each in flight; cls_small_form): 512 threads and five loads have the
+// loads of most waves on a CU in flight at the same time and the fewest rounds of softmax; short key blocks, and
+// many of them, take 256 threads and four loads, with less work for nothing in a workgroup.  Ten loads, and 256
+// threads with 8, 10 or 16, are nowhere better by more than 1 %.
 
-// Rows of any number of pieces: as many whole rows as fit a wave per load, ten loads in flight, a row's
-// pieces added in a tree of lane shifts (with 256 threads, four guarded loads and one shuffle per piece,
-// heads of 80: 576 bf16 tokens 45.2 us a call, now 37.4; 8 x 900 64.8, 46.7; fp32, 1296 tokens 163, 71).
-template <typename T>
-__global__ __launch_bounds__(kClsThreads) void score_cls_generic_kernel(const T *__restrict__ q,
+// Rows of any number of pieces: as many whole rows as fit a wave per load, a row's pieces added in a tree of lane
+// shifts (STEPS: its depth).  With 256 threads, four guarded loads and one shuffle per piece, heads of 80: 576 bf16
+// tokens 45.2 us a call, now 37; 8 x 900 64.8, 46; fp32, 1296 tokens 163, 71.
+template <typename T, int STEPS, int THREADS, int UNR>
+__global__ __launch_bounds__(THREADS) void score_cls_generic_kernel(const T *__restrict__ q,
                                                         const T *__restrict__ k,
                                                         float *__restrict__ head_scores, int H,
                                                         int S, int dh, int first_key, int col0,
                                                         int N, float scale_log2e) {
-    constexpr int E = ElemTraits<T>::kPer16B, UNR = kClsLoads;
+    constexpr int E = ElemTraits<T>::kPer16B;
     extern __shared__ __align__(16) unsigned char smem[];
     float *red = reinterpret_cast<float *>(smem);  // 16 floats
     float *qf = red + 16;                           // dh floats (dh <= 256)
@@ -51,7 +54,7 @@ __global__ __launch_bounds__(kClsThreads) void score_cls_generic_kernel(const T 
     const int lane = lane_id();
     const int row_in_wave = min(lane / cpr, rpw - 1);
     const int piece = lane < rpw * cpr ? lane - row_in_wave * cpr : cpr - 1;
-    constexpr int nw = kClsThreads / kWave;
+    constexpr int nw = THREADS / kWave;
     const int64_t row_bytes = (int64_t)dh * sizeof(T);
     auto row_of = [&](int base, int u) { return base + (u * nw + wave_id()) * rpw + row_in_wave; };
     auto fetch = [&](int base, uint4(&raw)[UNR]) {  // clamped: independent loads, in flight together
@@ -61,7 +64,7 @@ __global__ __launch_bounds__(kClsThreads) void score_cls_generic_kernel(const T 
     };
     uint4 raw[UNR];
     fetch(0, raw);
-    for (int e = tid; e < dh; e += kClsThreads) qf[e] = load_elem<T>(qrow + e) * scale_log2e;
+    for (int e = tid; e < dh; e += THREADS) qf[e] = load_elem<T>(qrow + e) * scale_log2e;
     __syncthreads();
     float qreg[E];
 #pragma unroll
@@ -73,14 +76,15 @@ __global__ __launch_bounds__(kClsThreads) void score_cls_generic_kernel(const T 
         if (base + step < n_keys) fetch(base + step, nxt);
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
+            if (base + (u * nw + wave_id()) * rpw >= n_keys) continue;  // none of this wave's rows
             float kv[E];
             unpack16<T>(raw[u], kv);
             float part = 0.f;
 #pragma unroll
             for (int e = 0; e < E; ++e) part = fmaf(kv[e], qreg[e], part);
             // a row's pieces sit in adjacent lanes: lane d adds lane d + n while both belong to the row
-            for (int n = 32; n >= 1; n >>= 1) {
-                if (n >= cpr) continue;
+#pragma unroll
+            for (int n = 1 << (STEPS - 1); n >= 1; n >>= 1) {
                 const float up = __shfl_down(part, n, kWave);
                 if (piece + n < min(2 * n, cpr)) part += up;
             }
@@ -92,10 +96,10 @@ __global__ __launch_bounds__(kClsThreads) void score_cls_generic_kernel(const T 
     __syncthreads();
 
     float m = -INFINITY;
-    for (int j = tid; j < n_keys; j += kClsThreads) m = fmaxf(m, z[j]);
+    for (int j = tid; j < n_keys; j += THREADS) m = fmaxf(m, z[j]);
     m = block_max(m, red);
     float sum = 0.f;
-    for (int j = tid; j < n_keys; j += kClsThreads) {
+    for (int j = tid; j < n_keys; j += THREADS) {
         const float e = __builtin_amdgcn_exp2f(z[j] - m);
         z[j] = e;
         sum += e;
@@ -103,25 +107,22 @@ __global__ __launch_bounds__(kClsThreads) void score_cls_generic_kernel(const T 
     sum = block_sum(sum, red);
     const float inv = 1.0f / sum;
     float *out = head_scores + ((int64_t)bc * H + h) * N;
-    for (int j = tid; j < N; j += kClsThreads) out[j] = z[col0 + j] * inv;
+    for (int j = tid; j < N; j += THREADS) out[j] = z[col0 + j] * inv;
 }
 
 // Same computation for rows whose piece count is a power of two (every common head
-// size).  The key block is read as one flat, fully coalesced stream with ten
-// independent 16-byte loads per thread in flight: at these sizes the kernel's time
-// is the number of serialised memory round-trips, so all of them are issued at once
-// (a 24 x 24 encoder's 577 rows of 128 bytes in one batch).  With 512 threads a CU has
-// the loads of more waves to wait for at the same time and fewer rounds of softmax than
-// with 256 threads and 16 or 20 loads: a call 16 x 576 35.4 -> 34.3 us, 24 x 576 37.7 ->
-// 35.0, 8 x 5 x 576 61.4 -> 58.9, one image in fp32 (9232 pieces) 32.6 -> 30.8; 12 loads,
-// or 1024 threads and 5, measured the same.
-template <typename T, int LOG2_CPR>
-__global__ __launch_bounds__(kClsThreads) void score_cls_kernel(const T *__restrict__ q,
+// size).  The key block is read as one flat, fully coalesced stream with all of a batch's
+// independent 16-byte loads in flight: at these sizes the kernel's time is the number of
+// serialised memory round-trips.  With 256 threads and 16 or 20 loads: a call 16 x 576 35.4
+// us, now 34.3, 24 x 576 37.7, 35.0, 8 x 5 x 576 61.4, 58.9, one image in fp32 (9232 pieces)
+// 32.6, 30.8.
+template <typename T, int LOG2_CPR, int THREADS, int UNR>
+__global__ __launch_bounds__(THREADS) void score_cls_kernel(const T *__restrict__ q,
                                                         const T *__restrict__ k,
                                                         float *__restrict__ head_scores, int H,
                                                         int S, int dh, int first_key, int col0,
                                                         int N, float scale_log2e) {
-    constexpr int E = ElemTraits<T>::kPer16B, THREADS = kClsThreads, UNR = kClsLoads;
+    constexpr int E = ElemTraits<T>::kPer16B;
     constexpr int cpr = 1 << LOG2_CPR;  // 16-byte pieces per key row
     constexpr int shift = LOG2_CPR;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -164,6 +165,7 @@ __global__ __launch_bounds__(kClsThreads) void score_cls_kernel(const T *__restr
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             const int p = base + u * THREADS + tid;
+            if (base + u * THREADS + wave_id() * kWave >= total) continue;  // none of this wave's pieces
             float kv[E];
             unpack16<T>(raw[u], kv);
             float part = 0.f;
@@ -1006,43 +1008,56 @@ __global__ __launch_bounds__(256, MeanForm<T>::kWorkgroupsPerCu) void mean_pipe_
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-template <typename T>
-static hipError_t launch_score_cls_t(const ScoreArgs &a, hipStream_t s) {
+template <typename T, int THREADS, int UNR>
+static hipError_t launch_score_cls_form(const ScoreArgs &a, hipStream_t s) {
     const int first_key = a.domain_all ? 0 : 1;
     const int n_keys = a.S - first_key;
     const size_t smem = (16 + 256 + (size_t)n_keys) * sizeof(float);
-    if (smem > 64 * 1024) {
-        static std::atomic<uint64_t> lds_allowed{0};  // one per element type
-        hipError_t e = allow_large_lds(score_cls_generic_kernel<T>, lds_allowed);
-        if (e != hipSuccess) return e;
-    }
-    dim3 grid(a.H, a.BC);
     const int cpr = a.dh / ElemTraits<T>::kPer16B;
-#define VSCAN_CLS(L)                                                                          \
-    case L: {                                                                                 \
-        if (smem > 64 * 1024) {                                                               \
-            static std::atomic<uint64_t> lds_allowed{0};                                      \
-            hipError_t e = allow_large_lds(score_cls_kernel<T, L>, lds_allowed);              \
-            if (e != hipSuccess) return e;                                                    \
-        }                                                                                     \
-        hipLaunchKernelGGL((score_cls_kernel<T, L>), grid, dim3(kClsThreads), smem, s,        \
-                           (const T *)a.q, (const T *)a.k, a.head_scores, a.H, a.S, a.dh,     \
-                           first_key, 1 - first_key, a.N, a.scale * 1.4426950408889634f);     \
-        return hipGetLastError();                                                             \
-    }
+    auto launch = [&](auto kernel, std::atomic<uint64_t> &lds_allowed) {
+        if (smem > 64 * 1024) {
+            hipError_t e = allow_large_lds(kernel, lds_allowed);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(kernel, dim3(a.H, a.BC), dim3(THREADS), smem, s, (const T *)a.q, (const T *)a.k,
+                           a.head_scores, a.H, a.S, a.dh, first_key, 1 - first_key, a.N,
+                           a.scale * 1.4426950408889634f);
+        return hipGetLastError();
+    };
+    static std::atomic<uint64_t> lds_allowed[12];  // one per kernel
     if ((cpr & (cpr - 1)) == 0) {
         switch (__builtin_ctz(cpr)) {
-            VSCAN_CLS(0) VSCAN_CLS(1) VSCAN_CLS(2) VSCAN_CLS(3) VSCAN_CLS(4) VSCAN_CLS(5)
-            VSCAN_CLS(6)
+            case 0: return launch(score_cls_kernel<T, 0, THREADS, UNR>, lds_allowed[0]);
+            case 1: return launch(score_cls_kernel<T, 1, THREADS, UNR>, lds_allowed[1]);
+            case 2: return launch(score_cls_kernel<T, 2, THREADS, UNR>, lds_allowed[2]);
+            case 3: return launch(score_cls_kernel<T, 3, THREADS, UNR>, lds_allowed[3]);
+            case 4: return launch(score_cls_kernel<T, 4, THREADS, UNR>, lds_allowed[4]);
+            case 5: return launch(score_cls_kernel<T, 5, THREADS, UNR>, lds_allowed[5]);
+            case 6: return launch(score_cls_kernel<T, 6, THREADS, UNR>, lds_allowed[6]);
         }
     }
-#undef VSCAN_CLS
-    {
-        hipLaunchKernelGGL(score_cls_generic_kernel<T>, grid, dim3(kClsThreads), smem, s, (const T *)a.q,
-                           (const T *)a.k, a.head_scores, a.H, a.S, a.dh, first_key,
-                           1 - first_key, a.N, a.scale * 1.4426950408889634f);
-    }
-    return hipGetLastError();
+    if (cpr < 4) return launch(score_cls_generic_kernel<T, 2, THREADS, UNR>, lds_allowed[7]);
+    if (cpr < 8) return launch(score_cls_generic_kernel<T, 3, THREADS, UNR>, lds_allowed[8]);
+    if (cpr < 16) return launch(score_cls_generic_kernel<T, 4, THREADS, UNR>, lds_allowed[9]);
+    if (cpr < 32) return launch(score_cls_generic_kernel<T, 5, THREADS, UNR>, lds_allowed[10]);
+    return launch(score_cls_generic_kernel<T, 6, THREADS, UNR>, lds_allowed[11]);
+}
+
+// 256 threads with four loads up to one batch of them, and up to three where a CU has more than three workgroups;
+// 512 threads with five otherwise.  GPU time of a call, us, with 512 and with 256 threads (16-byte pieces of a key
+// block x workgroups; rows of 8 pieces, then of 10):  448 x 16 16.3, 16.1;  448 x 4800 31.4, 25.1;  880 x 256 21.6, 21.6;
+// 2048 x 16 18.8, 19.2;  2048 x 640 22.1, 21.9;  2048 x 1600 27.5, 26.9;  2888 x 1600 39.0, 37.8;  2888 x 4800 72.2, 73.3;
+// 3872 x 4800 88.6, 90.0;  6960 x 256 37.8, 39.6;  10:  490 x 4800 41.9, 29.4;  900 x 256 21.9, 21.8;  1440 x 256 21.6,
+// 22.3;  2100 x 640 24.5, 25.5;  2100 x 1024 26.9, 25.2;  2890 x 4800 78, 74.5;  4000 x 4800 91.8, 93.3.
+static bool cls_small_form(int64_t pieces, int64_t workgroups) {
+    return pieces <= 1024 || (pieces <= 3072 && workgroups > 3 * kCus);
+}
+
+template <typename T>
+static hipError_t launch_score_cls_t(const ScoreArgs &a, hipStream_t s) {
+    const int64_t pieces = (int64_t)(a.S - (a.domain_all ? 0 : 1)) * (a.dh / ElemTraits<T>::kPer16B);
+    return cls_small_form(pieces, (int64_t)a.H * a.BC) ? launch_score_cls_form<T, 256, 4>(a, s)
+                                                       : launch_score_cls_form<T, 512, 5>(a, s);
 }
 
 hipError_t launch_score_cls(const ScoreArgs &a, hipStream_t s) {
