@@ -269,44 +269,6 @@ __device__ __forceinline__ float log2_sum(float l) {
     return y + 1.4426950408889634f * fmaf(l, __builtin_amdgcn_exp2f(-y), -1.0f);
 }
 
-// Sixteen logits of a lane's row into its running sum.  Lazy reference: exponentials are taken against a
-// per-lane reference m_run that is an actual logit of the row (so the sum is >= 1 and small terms may
-// underflow harmlessly) and is only raised when the partial sum threatens to overflow.  That removes the
-// per-element running max; the rescue path is rare.
-__device__ __forceinline__ void add_to_row_sum(const f32x16_t &acc, float sl2, float &m_run, float &l_run,
-                                               bool &have_ref) {
-    auto largest = [&] {
-        float mx = -INFINITY;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[r]);
-        return mx * sl2;
-    };
-    auto sum = [&](float m) {
-        float add = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) add += __builtin_amdgcn_exp2f(fmaf(acc[r], sl2, -m));
-        return add;
-    };
-    if (!have_ref) {
-        const float mx = largest();
-        if (mx > -INFINITY) {
-            m_run = mx;
-            have_ref = true;
-        }
-    }
-    if (have_ref) {
-        float add = sum(m_run);
-        if (add < 0x1p100f) {
-            l_run += add;
-        } else {  // a logit far above the reference: re-base on this tile's maximum
-            const float m_new = fmaxf(m_run, largest());
-            add = sum(m_new);
-            l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_new) + add;
-            m_run = m_new;
-        }
-    }
-}
-
 // The two half-waves hold disjoint streamed rows of the same resident row: reference and sum over both.
 __device__ __forceinline__ void join_half_waves(float m, float l, float &M, float &L) {
     const float m_o = __shfl_xor(m, 32, kWave), l_o = __shfl_xor(l, 32, kWave);
@@ -374,7 +336,40 @@ __global__ __launch_bounds__(256, 2) void mean_lse_kernel(const bf16_t *__restri
                 for (int r = 0; r < 16; ++r)
                     if (key0 + acc_row(r) >= n_keys) acc[r] = -INFINITY;
             }
-            add_to_row_sum(acc, sl2, m_run, l_run, have_ref);
+            // Lazy reference: exponentials are taken against a per-lane reference m_run that
+            // is an actual logit of the row (so the sum is >= 1 and small terms may underflow
+            // harmlessly) and is only raised when the partial sum threatens to overflow.  That
+            // removes the per-element running max; the rescue path is rare.  (As a function of its
+            // own this part costs calls of 800 to 3300 tokens 1.5 to 3 %.)
+            if (!have_ref) {
+                float mx = -INFINITY;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[r]);
+                if (mx > -INFINITY) {
+                    m_run = mx * sl2;
+                    have_ref = true;
+                }
+            }
+            if (have_ref) {
+                float add = 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    add += __builtin_amdgcn_exp2f(fmaf(acc[r], sl2, -m_run));
+                if (add < 0x1p100f) {
+                    l_run += add;
+                } else {  // a logit far above the reference: re-base on this tile's maximum
+                    float mx = -INFINITY;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[r]);
+                    const float m_new = fmaxf(m_run, mx * sl2);
+                    add = 0.f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        add += __builtin_amdgcn_exp2f(fmaf(acc[r], sl2, -m_new));
+                    l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_new) + add;
+                    m_run = m_new;
+                }
+            }
         }
         if (t + 1 < ntiles) st.store(lds[(t + 1) & 1]);
         __syncthreads();
@@ -382,29 +377,6 @@ __global__ __launch_bounds__(256, 2) void mean_lse_kernel(const bf16_t *__restri
     float M, L;
     join_half_waves(m_run, l_run, M, L);
     if (g == 0 && qrow < N) lse[(int64_t)bh * N + qrow] = M + log2_sum(L);
-}
-
-// Sum over the 32 streamed rows that the lanes of a half-wave hold, for each of the sixteen resident rows
-// of a 32x32 accumulator: lane l < 16 of half g gets the sum of resident row acc_row(l).  Every step
-// adds pairs of lanes and leaves each lane with half of the rows (31 exchanges instead of 80).
-template <int ROWS>  // lanes n < ROWS apart have yet to be added, ROWS rows are left to this one
-__device__ __forceinline__ float resident_row_sum(float (&v)[16]) {
-    if constexpr (ROWS == 16) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) v[r] += __shfl_xor(v[r], 16, kWave);
-    }
-    if constexpr (ROWS > 1) {
-        constexpr int n = ROWS / 2;
-        const bool upper = (lane_id() & n) != 0;
-#pragma unroll
-        for (int r = 0; r < n; ++r) {
-            const float mine = upper ? v[r + n] : v[r], other = upper ? v[r] : v[r + n];
-            v[r] = mine + __shfl_xor(other, n, kWave);
-        }
-        return resident_row_sum<n>(v);
-    } else {
-        return v[0];
-    }
 }
 
 // Pass 2: head_scores[j] = sum_i 2^(sl2 * q_i . k_j - lse2[i]) for patch keys j.
@@ -440,9 +412,7 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const bf16_t *__res
         kfrag[c] = load16_guard(kbase, (int64_t)key * row_bytes + 32 * c + 16 * g,
                                 key < N && 32 * c + 16 * g < row_bytes);
 
-    float colsum[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) colsum[r] = 0.f;
+    float colsum = 0.f;
     Stage st;
     const int ntiles = (N + kMeanTile - 1) / kMeanTile;
     const int tid = threadIdx.x;
@@ -454,6 +424,7 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const bf16_t *__res
     __syncthreads();
     for (int t = 0; t < ntiles; ++t) {
         const unsigned char *cur = lds[t & 1];
+        const float *lcur = lse_s[t & 1];
         if (t + 1 < ntiles) {
             st.load(qbase, (t + 1) * kMeanTile, N, row_bytes);
             const int r = (t + 1) * kMeanTile + tid;
@@ -468,14 +439,19 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const bf16_t *__res
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const uint4 a = *reinterpret_cast<const uint4 *>(arow + 32 * c);
-                mma32_chunk<bf16_t>(acc, kfrag[c], a);
+                mma32_chunk<bf16_t>(acc, a, kfrag[c]);
             }
-            // acc[r] = k_(key0 + acc_row(r)) . q_(row0 + lane%32): a lane's logits belong to one query
-            // row, whose log-sum-exp is one LDS read; rows past N carry +inf -> 0
-            const float lse_i = lse_s[t & 1][sub * 32 + (lane & 31)];
+            // acc[r] = q_(row0 + acc_row(r)) . k_key ; rows past N carry lse = +inf -> 0.  (A lane per query
+            // row, as in the form below, saves no matrix instruction here and adds sums over the lanes at the
+            // end: 3306 tokens, 4 heads of 96, 119 -> 121 us a call, 884 of 16 49.4 -> 50.2.)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                colsum[r] += __builtin_amdgcn_exp2f(fmaf(acc[r], sl2, -lse_i));
+            for (int rg = 0; rg < 4; ++rg) {
+                const float4 l4 = *reinterpret_cast<const float4 *>(lcur + sub * 32 + 8 * rg + 4 * g);
+                colsum += __builtin_amdgcn_exp2f(fmaf(acc[4 * rg + 0], sl2, -l4.x));
+                colsum += __builtin_amdgcn_exp2f(fmaf(acc[4 * rg + 1], sl2, -l4.y));
+                colsum += __builtin_amdgcn_exp2f(fmaf(acc[4 * rg + 2], sl2, -l4.z));
+                colsum += __builtin_amdgcn_exp2f(fmaf(acc[4 * rg + 3], sl2, -l4.w));
+            }
         }
         if (t + 1 < ntiles) {
             st.store(lds[(t + 1) & 1]);
@@ -483,9 +459,8 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const bf16_t *__res
         }
         __syncthreads();
     }
-    const float sum = resident_row_sum<16>(colsum);
-    const int l = lane & 31, out_key = kb * kMeanBlock + w * 32 + 8 * (l >> 2) + 4 * g + (l & 3);
-    if (l < 16 && out_key < N) head_scores[(int64_t)bh * N + out_key] = sum;
+    colsum += __shfl_xor(colsum, 32, kWave);
+    if (g == 0 && key < N) head_scores[(int64_t)bh * N + key] = colsum;
 }
 
 // ---------------------------------------------------------------------------
@@ -619,6 +594,29 @@ __device__ __forceinline__ void split_planes(const uint4 &a, const uint4 &b, uin
             v[2 * i + 1] -= bf16_hi(w[i]);
         }
         out[p] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+}
+
+// Sum over the 32 streamed rows that the lanes of a half-wave hold, for each of the sixteen resident rows
+// of a 32x32 accumulator: lane l < 16 of half g gets the sum of resident row acc_row(l).  Every step
+// adds pairs of lanes and leaves each lane with half of the rows (31 exchanges instead of 80).
+template <int ROWS>  // lanes n < ROWS apart have yet to be added, ROWS rows are left to this one
+__device__ __forceinline__ float resident_row_sum(float (&v)[16]) {
+    if constexpr (ROWS == 16) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] += __shfl_xor(v[r], 16, kWave);
+    }
+    if constexpr (ROWS > 1) {
+        constexpr int n = ROWS / 2;
+        const bool upper = (lane_id() & n) != 0;
+#pragma unroll
+        for (int r = 0; r < n; ++r) {
+            const float mine = upper ? v[r + n] : v[r], other = upper ? v[r] : v[r + n];
+            v[r] = mine + __shfl_xor(other, n, kWave);
+        }
+        return resident_row_sum<n>(v);
+    } else {
+        return v[0];
     }
 }
 
