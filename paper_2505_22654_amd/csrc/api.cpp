@@ -104,7 +104,7 @@ int plan_encoder(const vscan_encoder_desc *d, int with_local, EncoderPlan *p) {
 // is scored in one part, pair by pair.
 struct MeanParts {
     int parts = 1;
-    bool used = false;
+    bool pipelined = false, used = false;
     size_t off_lse[2] = {}, off_scores[2] = {}, end = 0;
 };
 
@@ -114,10 +114,11 @@ MeanParts plan_mean_parts(const vscan_encoder_desc *d, const EncoderPlan &p, int
                           bool with_local, bool together, size_t base) {
     MeanParts m;
     m.end = base;
-    if (d->score_mode != VSCAN_SCORE_MEAN_RECEIVED || !mean_pair_launch(scored_as_bf16, d->head_dim))
-        return m;
+    if (d->score_mode != VSCAN_SCORE_MEAN_RECEIVED) return m;
     const int sets = with_local ? 2 : 1, pairs = together ? sets : 1;
     const int64_t heads = (int64_t)p.BC * d->heads;
+    m.pipelined = mean_pipelined(scored_as_bf16, d->head_dim, heads, p.N, pairs == 2);
+    if (!m.pipelined) return m;
     m.parts = mean_parts(scored_as_bf16, d->head_dim, heads * pairs, p.N);
     const int block = mean_block_rows(scored_as_bf16, d->head_dim);
     m.used = mean_cost(heads * pairs, p.N, block, m.parts) < 0.95 * pairs * mean_cost(heads, p.N, block, 1);
@@ -486,6 +487,7 @@ static int encoder_reduce_impl(const vscan_encoder_desc *d, const void *q, const
     sa.scale = resolve_scale(d->scale, d->head_dim);
     const float norm = mean ? 1.0f / ((float)d->heads * (float)p.N) : 1.0f / (float)d->heads;
     const MeanParts mp = plan_mean_parts(d, p, sa.is_bf16, with_local, true, p.bytes);
+    sa.pipelined = mp.pipelined;
     if (mp.used && workspace_bytes >= mp.end) {
         sa.parts = mp.parts;
         sa.lse = reinterpret_cast<float *>(ws + mp.off_lse[0]);
@@ -501,7 +503,7 @@ static int encoder_reduce_impl(const vscan_encoder_desc *d, const void *q, const
         return enqueue_encoder_tail(d, p, with_local, d->heads * mp.parts, norm, x, kept_idx, merged,
                                     assign_out, scores_out, ws, s, mp.off_scores[0], mp.off_scores[1]);
     }
-    if (mean && with_local && mean_pair_launch(sa.is_bf16, sa.dh)) {
+    if (mean && with_local && mp.pipelined) {
         // Pass 1 of both pairs in one launch.  The second pair's log-sum-exps wait where the first
         // pair's scores go afterwards, so its second pass runs first.
         sa.q2 = q_local;
@@ -591,6 +593,7 @@ static int encoder_reduce_fused_impl(const vscan_encoder_desc *d, const void *hi
             mp.off_scores[1] = p.e.off_head_local;
         }
         sa.parts = mp.parts;
+        sa.pipelined = mp.pipelined;
         sa.lse = reinterpret_cast<float *>(ws + mp.off_lse[0]);
         sa.BC = p.e.BC;
         sa.H = d->heads;

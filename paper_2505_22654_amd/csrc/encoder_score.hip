@@ -278,11 +278,11 @@ __device__ __forceinline__ void join_half_waves(float m, float l, float &M, floa
     if (m_o > -INFINITY) L += l_o * __builtin_amdgcn_exp2f(m_o - M);
 }
 
-// Both passes for wider bf16 rows (fp32 and bf16 rows of up to 160 bytes have the pipelined form below).
+// The plain form of both passes (mean_pipelined).
 // Pass 1: lse2[i] = log2 sum_j 2^(sl2 * q_i . k_j) over the key domain.
-template <int NC>
-__global__ __launch_bounds__(256, 2) void mean_lse_kernel(const bf16_t *__restrict__ q,
-                                                          const bf16_t *__restrict__ k,
+template <typename T, int NC>
+__global__ __launch_bounds__(256, 2) void mean_lse_kernel(const T *__restrict__ q,
+                                                          const T *__restrict__ k,
                                                           float *__restrict__ lse, int n_heads_total,
                                                           int S, int dh, int row_first, int N,
                                                           int key_first, int n_keys, float sl2) {
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(256, 2) void mean_lse_kernel(const bf16_t *__restri
     const int item = xcd_contiguous_item(total);
     if (item >= total) return;
     const int bh = item / nblk, rb = item - bh * nblk;
-    const int row_bytes = dh * (int)sizeof(bf16_t);
+    const int row_bytes = dh * (int)sizeof(T);
     const unsigned char *qbase =
         reinterpret_cast<const unsigned char *>(q) + ((int64_t)bh * S + row_first) * row_bytes;
     const unsigned char *kbase =
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(256, 2) void mean_lse_kernel(const bf16_t *__restri
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const uint4 a = *reinterpret_cast<const uint4 *>(arow + 32 * c);
-                mma32_chunk<bf16_t>(acc, a, qfrag[c]);
+                mma32_chunk<T>(acc, a, qfrag[c]);
             }
             // acc[r] = q_row(lane%32) . k_(key0 + acc_row(r)); mask the ragged tail
             const int key0 = t * kMeanTile + sub * 32;
@@ -380,9 +380,9 @@ __global__ __launch_bounds__(256, 2) void mean_lse_kernel(const bf16_t *__restri
 }
 
 // Pass 2: head_scores[j] = sum_i 2^(sl2 * q_i . k_j - lse2[i]) for patch keys j.
-template <int NC>
-__global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const bf16_t *__restrict__ q,
-                                                             const bf16_t *__restrict__ k,
+template <typename T, int NC>
+__global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const T *__restrict__ q,
+                                                             const T *__restrict__ k,
                                                              const float *__restrict__ lse,
                                                              float *__restrict__ head_scores,
                                                              int n_heads_total, int S, int dh,
@@ -396,7 +396,7 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const bf16_t *__res
     const int item = xcd_contiguous_item(total);
     if (item >= total) return;
     const int bh = item / nblk, kb = item - bh * nblk;
-    const int row_bytes = dh * (int)sizeof(bf16_t);
+    const int row_bytes = dh * (int)sizeof(T);
     // queries and keys are both the patch rows here
     const unsigned char *qbase =
         reinterpret_cast<const unsigned char *>(q) + ((int64_t)bh * S + row_first) * row_bytes;
@@ -439,7 +439,7 @@ __global__ __launch_bounds__(256, 2) void mean_colsum_kernel(const bf16_t *__res
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const uint4 a = *reinterpret_cast<const uint4 *>(arow + 32 * c);
-                mma32_chunk<bf16_t>(acc, a, kfrag[c]);
+                mma32_chunk<T>(acc, a, kfrag[c]);
             }
             // acc[r] = q_(row0 + acc_row(r)) . k_key ; rows past N carry lse = +inf -> 0.  (A lane per query
             // row, as in the form below, saves no matrix instruction here and adds sums over the lanes at the
@@ -1062,7 +1062,7 @@ hipError_t launch_score_cls(const ScoreArgs &a, hipStream_t s) {
     return a.is_bf16 ? launch_score_cls_t<bf16_t>(a, s) : launch_score_cls_t<float>(a, s);
 }
 
-template <int NC>
+template <typename T, int NC>
 static hipError_t launch_score_mean_nc(const ScoreArgs &a, hipStream_t s, int pass) {
     const int row_first = a.has_cls;
     const int key_first = a.domain_all ? 0 : a.has_cls;
@@ -1072,17 +1072,17 @@ static hipError_t launch_score_mean_nc(const ScoreArgs &a, hipStream_t s, int pa
     const int grid = ((total + 7) / 8) * 8;
     const float sl2 = a.scale * 1.4426950408889634f;
     if (pass == 1)
-        hipLaunchKernelGGL((mean_lse_kernel<NC>), dim3(grid), dim3(256), 0, s, (const bf16_t *)a.q,
-                           (const bf16_t *)a.k, a.lse, a.BC * a.H, a.S, a.dh, row_first, a.N, key_first,
+        hipLaunchKernelGGL((mean_lse_kernel<T, NC>), dim3(grid), dim3(256), 0, s, (const T *)a.q,
+                           (const T *)a.k, a.lse, a.BC * a.H, a.S, a.dh, row_first, a.N, key_first,
                            n_keys, sl2);
     else
-        hipLaunchKernelGGL((mean_colsum_kernel<NC>), dim3(grid), dim3(256), 0, s,
-                           (const bf16_t *)a.q, (const bf16_t *)a.k, a.lse, a.head_scores, a.BC * a.H, a.S,
+        hipLaunchKernelGGL((mean_colsum_kernel<T, NC>), dim3(grid), dim3(256), 0, s,
+                           (const T *)a.q, (const T *)a.k, a.lse, a.head_scores, a.BC * a.H, a.S,
                            a.dh, row_first, a.N, sl2);
     return hipGetLastError();
 }
 
-// The forms that take pairs and parts (mean_pair_launch).
+// The pipelined form, which takes pairs and parts.
 template <typename T, int NC, int HALVES>
 static hipError_t launch_mean_pipe(const ScoreArgs &a, hipStream_t s, int pass) {
     const int row_first = a.has_cls;
@@ -1118,22 +1118,32 @@ static hipError_t launch_mean_pipe(const ScoreArgs &a, hipStream_t s, int pass) 
     return hipGetLastError();
 }
 
+// The plain kernels, by the 32-byte chunks of a row.
+template <typename T>
+static hipError_t launch_score_mean_plain(const ScoreArgs &a, hipStream_t s, int pass) {
+    const int nc = (a.dh * (int)sizeof(T) + 31) / 32;
+    if (nc <= 2) return launch_score_mean_nc<T, 2>(a, s, pass);
+    if (nc <= 4) return launch_score_mean_nc<T, 4>(a, s, pass);
+    if (nc <= 5) return launch_score_mean_nc<T, 5>(a, s, pass);
+    if (nc <= 8) return launch_score_mean_nc<T, 8>(a, s, pass);
+    if (nc <= 12) return launch_score_mean_nc<T, 12>(a, s, pass);
+    if (nc <= 16) return launch_score_mean_nc<T, 16>(a, s, pass);
+    return hipErrorInvalidValue;  // rows wider than 512 bytes are rejected by the ABI layer
+}
+
 static hipError_t launch_score_mean(const ScoreArgs &a, hipStream_t s, int pass) {
-    const int nc = (a.dh * 2 + 31) / 32;  // chunks of sixteen elements
+    if (!a.pipelined)
+        return a.is_bf16 ? launch_score_mean_plain<bf16_t>(a, s, pass) : launch_score_mean_plain<float>(a, s, pass);
+    const int nc = (a.dh + 15) / 16;  // chunks of sixteen elements
     if (!a.is_bf16) {
         if (nc <= 2) return launch_mean_pipe<float, 2, 2>(a, s, pass);
         if (nc <= 4) return launch_mean_pipe<float, 4, 2>(a, s, pass);
         if (nc <= 5) return launch_mean_pipe<float, 5, 2>(a, s, pass);
-        if (nc <= 8) return launch_mean_pipe<float, 8, 1>(a, s, pass);
-        return hipErrorInvalidValue;  // rows wider than 512 bytes are rejected by the ABI layer
+        return launch_mean_pipe<float, 8, 1>(a, s, pass);
     }
     if (nc <= 2) return launch_mean_pipe<bf16_t, 2, 2>(a, s, pass);
     if (nc <= 4) return launch_mean_pipe<bf16_t, 4, 2>(a, s, pass);
-    if (nc <= 5) return launch_mean_pipe<bf16_t, 5, 2>(a, s, pass);
-    if (nc <= 8) return launch_score_mean_nc<8>(a, s, pass);
-    if (nc <= 12) return launch_score_mean_nc<12>(a, s, pass);
-    if (nc <= 16) return launch_score_mean_nc<16>(a, s, pass);
-    return hipErrorInvalidValue;
+    return launch_mean_pipe<bf16_t, 5, 2>(a, s, pass);
 }
 
 hipError_t launch_score_mean_lse(const ScoreArgs &a, hipStream_t s) { return launch_score_mean(a, s, 1); }

@@ -37,16 +37,40 @@ struct ScoreArgs {
     int BC, H, S, dh, N;
     int has_cls, domain_all, is_bf16;
     float scale;
-    // a second pair to take along (mean_pair_launch), or NULL: pass 1 always may, pass 2 where
+    bool pipelined = false;  // mean_pipelined
+    // a second pair for the pipelined form to take along, or NULL: pass 1 always may, pass 2 where
     // head_scores2 is given
     const void *q2 = nullptr, *k2 = nullptr;
     float *lse2 = nullptr;
     int parts = 1;        // mean_parts
     float *head_scores2 = nullptr;
 };
-// whether mean attention takes two pairs in one launch, and streamed rows in parts: fp32, and bf16 rows of
-// up to 160 bytes
-inline bool mean_pair_launch(int is_bf16, int dh) { return !is_bf16 || dh <= 80; }
+// Which of its two forms mean attention takes (per call: both passes the same).  The pipelined form has 256
+// resident rows to a workgroup (128 for fp32 rows of more than 80), takes streamed rows in parts and, with Q and K
+// given (`pair`: a second pair comes along), both pairs in a launch; fp32 goes as bf16 planes there.  The plain one
+// has 128 rows and two workgroups a CU: better where the last 256 rows of a head would be mostly padding.  GPU time
+// of a call, us, plain and pipelined (N x heads, one pair unless said):
+//   bf16, 64 wide: 64 x 16 19.9, 22.0; 64 x 2048 30, 49; 256 x 64 26.8, 28.3; 256 x 1024 54, 63; 289 x 16 31.0, 31.3;
+//   289 x 160 35.6, 45.7; 380 x 64 33.9, 36.3; 380 x 512 59, 70; but 420 x 4 34.4, 30.1; 506 x 64 38.5, 38.0; 506 x 256 54.6,
+//   56.9; 650 x 16 46, 42; 650 x 512 132, 131; two pairs 64 x 16 24.9, 22.2; 289 x 16 44, 34; 64 x 256 27.0, 29.5
+//   (48 x 180, where the host's launches count, 32.7, 29).
+//   fp32, 80 wide: 64 x 16 26, 29; 121 x 2048 139, 179; 132 x 16 37, 35.5; 256 x 1024 231, 169; 289 x 64 60, 47; 289 x 160
+//   89, 96; 289 x 256 121, 102; 600 x 160 263, 153; two pairs 64 x 16 38, 31; 121 x 256 59, 65.
+//   fp32, 16 wide (padded to 32): 256 x 64 27, 29; 380 x 256 53, 61; 600 x 16 43, 40; 900 x 160 138, 142; 900 x 16 57, 46;
+//   40 wide (to 64): 169 x 64 30, 34; 441 x 64 48, 47; 441 x 160 87, 93; 600 x 256 172, 177; 600 x 160 143, 124; 900 x 256 373,
+//   325; 96 wide (to 128): 132 x 64 40, 37; 132 x 512 94, 111; 289 x 512 219, 228; 600 x 512 621, 609; 128 wide: 100 x 256
+//   43, 38; 100 x 2048 170, 180; 64 x 16 28, 28.3; 132 x 1024 202, 204; 256 x 1024 299, 269.
+inline bool mean_pipelined(int is_bf16, int dh, int64_t heads, int N, bool pair) {
+    if (is_bf16 && dh > 80) return false;
+    if (pair && heads <= (is_bf16 ? 192 : 64)) return true;  // two launches instead of four
+    if (is_bf16) return N > 384 || (N > 256 && heads < 64);
+    if (dh <= 16) return N >= 600 && heads <= 64;
+    if (dh <= 96 && N <= 128) return false;
+    if (dh <= 32 || (dh > 40 && dh <= 80)) return N <= 256 || N > 400 || heads <= 128 || heads >= 256;
+    if (dh <= 40) return N > 800 || (N > 400 && heads <= 64);
+    if (dh <= 96) return N >= 400 || heads <= 64;
+    return N >= 200 || heads <= (N >= 100 ? 256 : 0);
+}
 
 // Into how many parts the streamed rows of mean attention are cut.  A workgroup owns 256 (128) resident
 // rows of a head and takes as long as its stages of streamed rows and about 0.8 more (its own rows, the
@@ -70,9 +94,8 @@ inline double mean_cost(int64_t heads, int N, int block_rows, int parts) {
     const int stages = (N + kMeanStageRows - 1) / kMeanStageRows;
     return (double)((items * parts + 255) / 256) * ((stages + parts - 1) / parts + kMeanStart);
 }
-inline int mean_parts(int is_bf16, int dh, int64_t heads, int N) {
+inline int mean_parts(int is_bf16, int dh, int64_t heads, int N) {  // pipelined form
     int best = 1;
-    if (!mean_pair_launch(is_bf16, dh)) return best;
     const int stages = (N + kMeanStageRows - 1) / kMeanStageRows, rows = mean_block_rows(is_bf16, dh);
     for (int p = 2; p <= kMeanMaxParts && p <= stages; ++p)
         if (mean_cost(heads, N, rows, p) < 0.95 * mean_cost(heads, N, rows, best)) best = p;

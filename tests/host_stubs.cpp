@@ -85,7 +85,7 @@ static void check_mean(const char *who, const ScoreArgs &a, bool both) {
     expect(who, "more parts than stages or than the kernels add",
            a.parts >= 1 && a.parts <= kMeanMaxParts && a.parts <= stages);
     expect(who, "parts or two pairs in a form of one",
-           mean_pair_launch(a.is_bf16, a.dh) || (a.parts == 1 && !both));
+           a.pipelined || (a.parts == 1 && !both));
     if (both) expect(who, "second pair without rows", a.q2 && a.k2);
 }
 hipError_t launch_score_mean_lse(const ScoreArgs &a, hipStream_t) {

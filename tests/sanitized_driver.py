@@ -170,7 +170,8 @@ m1 = wl.EncoderShape(dtype=wl.BF16, batch=1, n_segments=1, grid_h=31, grid_w=33,
 for change, alone, paired, joined in (
         (dict(), 1, 1, 1), (dict(dtype=wl.F32), 1, 1, 1), (dict(head_dim=128), 0, 0, 0),
         (dict(dtype=wl.F32, head_dim=128, grid_h=17), 1, 1, 1),
-        (dict(batch=5, grid_h=18, grid_w=18, heads=30, head_dim=16), 1, 0, 1),
+        (dict(batch=5, grid_h=18, grid_w=18, heads=30, head_dim=16), 0, 0, 1),
+        (dict(grid_h=12, grid_w=12), 0, 1, 1),  # the pipelined form only with a second pair
         (dict(batch=2, heads=16, grid_h=45, grid_w=61), 1, 0, 1), (dict(grid_h=8, grid_w=16, batch=256), 0, 0, 0)):
     shape = dataclasses.replace(m1, **change)
     d, tokens, kept = vb.encoder_desc(shape), shape.batch * shape.n_tokens, shape.batch * shape.keep

@@ -1,4 +1,4 @@
-"""Mean attention of fp32 rows, whose values are multiplied as bf16 planes: elements at the top of the range, and
+"""Mean attention of fp32 rows, whose values the pipelined form multiplies as bf16 planes: elements at the top of the range, and
 the error of the scores against 64 bits."""
 import numpy as np
 import pytest
@@ -15,7 +15,8 @@ TOP = np.finfo(np.float32).max
 
 
 # (head size, grid): one chunk more than the rows fill, stages of 128 and of 64 rows, one and more parts
-@pytest.mark.parametrize("dh,gh,gw", [(64, 8, 16), (72, 13, 21), (80, 31, 33), (128, 17, 17), (8, 11, 12)])
+@pytest.mark.parametrize("dh,gh,gw", [(64, 12, 11), (72, 13, 21), (80, 31, 33), (128, 17, 17), (8, 24, 26),
+                                      (64, 8, 16), (8, 11, 12)])  # (these two: the plain form)
 def test_largest_finite_values(dh, gh, gw):
     """Keys and queries with elements at the top of the range whose products are nought, far below every other
     logit, or below the range: the oracle's scores, and no NaN."""
