@@ -22,10 +22,9 @@ namespace vscan {
 // bound by reading K once.  A key row is split into 16-byte pieces over adjacent
 // lanes, so a wave reads whole rows contiguously.
 // ---------------------------------------------------------------------------
-// Two forms (THREADS threads with UNR loads each in flight; cls_small_form): 512 threads and five loads have the
-// loads of most waves on a CU in flight at the same time and the fewest rounds of softmax; short key blocks, and
-// many of them, take 256 threads and four loads, with less work for nothing in a workgroup.  Ten loads, and 256
-// threads with 8, 10 or 16, are nowhere better by more than 1 %.
+// Three forms (THREADS threads with UNR loads each in flight; launch_score_cls_t): 512 threads have the loads of most
+// waves on a CU in flight at the same time and the fewest rounds of softmax; short key blocks, and many of them,
+// take 256 threads, with less work for nothing in a workgroup.
 
 // Rows of any number of pieces: as many whole rows as fit a wave per load, a row's pieces added in a tree of lane
 // shifts (STEPS: its depth).  With 256 threads, four guarded loads and one shuffle per piece, heads of 80: 576 bf16
@@ -165,7 +164,8 @@ __global__ __launch_bounds__(THREADS) void score_cls_kernel(const T *__restrict_
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             const int p = base + u * THREADS + tid;
-            if (base + u * THREADS + wave_id() * kWave >= total) continue;  // none of this wave's pieces
+            // none of this wave's pieces (ten loads are one batch, mostly full: there the test itself costs 1 %)
+            if (UNR < 10 && base + u * THREADS + wave_id() * kWave >= total) continue;
             float kv[E];
             unpack16<T>(raw[u], kv);
             float part = 0.f;
@@ -1042,20 +1042,21 @@ static hipError_t launch_score_cls_form(const ScoreArgs &a, hipStream_t s) {
 }
 
 // 256 threads with four loads up to one batch of them, and up to three where a CU has more than three workgroups;
-// 512 threads with five otherwise.  GPU time of a call, us, with 512 and with 256 threads (16-byte pieces of a key
-// block x workgroups; rows of 8 pieces, then of 10):  448 x 16 16.3, 16.1;  448 x 4800 31.4, 25.1;  880 x 256 21.6, 21.6;
+// 512 threads with ten where that is one batch and five would be two, for workgroups with a CU to themselves (a
+// call 16 x 576, on keys that are in no cache, 36.6 us, with five 36.9; warm, 4608 x 256 30.4, 30.3); 512 threads with
+// five otherwise.  GPU time of a call, us, with 512 x 5 and with 256 threads (16-byte pieces of a key block x
+// workgroups; rows of 8 pieces, then of 10):  448 x 16 16.3, 16.1;  448 x 4800 31.4, 25.1;  880 x 256 21.6, 21.6;
 // 2048 x 16 18.8, 19.2;  2048 x 640 22.1, 21.9;  2048 x 1600 27.5, 26.9;  2888 x 1600 39.0, 37.8;  2888 x 4800 72.2, 73.3;
 // 3872 x 4800 88.6, 90.0;  6960 x 256 37.8, 39.6;  10:  490 x 4800 41.9, 29.4;  900 x 256 21.9, 21.8;  1440 x 256 21.6,
-// 22.3;  2100 x 640 24.5, 25.5;  2100 x 1024 26.9, 25.2;  2890 x 4800 78, 74.5;  4000 x 4800 91.8, 93.3.
-static bool cls_small_form(int64_t pieces, int64_t workgroups) {
-    return pieces <= 1024 || (pieces <= 3072 && workgroups > 3 * kCus);
-}
-
+// 22.3;  2100 x 640 24.5, 25.5;  2100 x 1024 26.9, 25.2;  2890 x 4800 78, 74.5;  4000 x 4800 91.8, 93.3.  With 512 x 10 for
+// all of these 448 x 4800 takes 41.9, 2888 x 640 29.4 (five: 28.8), 10: 2100 x 1600 53.
 template <typename T>
 static hipError_t launch_score_cls_t(const ScoreArgs &a, hipStream_t s) {
     const int64_t pieces = (int64_t)(a.S - (a.domain_all ? 0 : 1)) * (a.dh / ElemTraits<T>::kPer16B);
-    return cls_small_form(pieces, (int64_t)a.H * a.BC) ? launch_score_cls_form<T, 256, 4>(a, s)
-                                                       : launch_score_cls_form<T, 512, 5>(a, s);
+    const int64_t workgroups = (int64_t)a.H * a.BC;
+    if (pieces <= 1024 || (pieces <= 3072 && workgroups > 3 * kCus)) return launch_score_cls_form<T, 256, 4>(a, s);
+    if (pieces > 2560 && pieces <= 5120 && workgroups <= kCus) return launch_score_cls_form<T, 512, 10>(a, s);
+    return launch_score_cls_form<T, 512, 5>(a, s);
 }
 
 hipError_t launch_score_cls(const ScoreArgs &a, hipStream_t s) {

@@ -1,5 +1,5 @@
 """[CLS] scoring at the edges of its batches of loads (256 threads with four pieces of sixteen bytes each, 512 with
-five), for rows of a power of two of pieces and rows of any other number, few segments and many."""
+five or ten), for rows of a power of two of pieces and rows of any other number, few segments and many."""
 import pytest
 
 from paper_2505_22654_amd import workloads as wl
