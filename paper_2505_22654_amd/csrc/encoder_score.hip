@@ -1049,7 +1049,9 @@ static hipError_t launch_score_cls_form(const ScoreArgs &a, hipStream_t s) {
 // 2048 x 16 18.8, 19.2;  2048 x 640 22.1, 21.9;  2048 x 1600 27.5, 26.9;  2888 x 1600 39.0, 37.8;  2888 x 4800 72.2, 73.3;
 // 3872 x 4800 88.6, 90.0;  6960 x 256 37.8, 39.6;  10:  490 x 4800 41.9, 29.4;  900 x 256 21.9, 21.8;  1440 x 256 21.6,
 // 22.3;  2100 x 640 24.5, 25.5;  2100 x 1024 26.9, 25.2;  2890 x 4800 78, 74.5;  4000 x 4800 91.8, 93.3.  With 512 x 10 for
-// all of these 448 x 4800 takes 41.9, 2888 x 640 29.4 (five: 28.8), 10: 2100 x 1600 53.
+// all of these 448 x 4800 takes 41.9, 2888 x 640 29.4 (five: 28.8), 10: 2100 x 1600 53.  Past one workgroup a CU, on
+// keys that are in no cache, with five and with ten: 4608 x 320 25.4, 26.1;  x 640 30.2, 30.8 (in a call 8 x 5 x 576
+// of wide features 58.9, 58.5);  x 1600 51.8, 53.4;  10: 4800 x 320 27.0, 32.0.
 template <typename T>
 static hipError_t launch_score_cls_t(const ScoreArgs &a, hipStream_t s) {
     const int64_t pieces = (int64_t)(a.S - (a.domain_all ? 0 : 1)) * (a.dh / ElemTraits<T>::kPer16B);
